@@ -288,13 +288,15 @@ relay_status relay_prepack_conv2d_weights(const relay_conv2d_desc* d, const void
 constexpr int kHaloBase = 100;
 constexpr int kStreamBase = 200;
 constexpr int kDwPwBase = 300;   // ... of the fused depthwise + 1x1 kernel (its own entry point)
+constexpr int kSmallBase = 400;  // ... of the kernel whose waves split the reduction of a small tile
 
 relay_status relay_set_conv_tile(int32_t tile) {
   const int most = relay::igemm_dma_tile_count() > relay::igemm_tile_count() ? relay::igemm_dma_tile_count()
                                                                              : relay::igemm_tile_count();
   const bool halo = (tile >= kHaloBase && tile < kHaloBase + relay::conv_halo_variant_count()) ||
                     (tile >= kStreamBase && tile < kStreamBase + relay::conv_stream_variant_count()) ||
-                    (tile >= kDwPwBase && tile < kDwPwBase + relay::dwpw_variant_count());
+                    (tile >= kDwPwBase && tile < kDwPwBase + relay::dwpw_variant_count()) ||
+                    (tile >= kSmallBase && tile < kSmallBase + relay::conv_small_variant_count());
   if (tile >= most && !halo) return fail(RELAY_ERR_UNSUPPORTED, "no tile %d", tile);
   g_force_tile = tile < -1 ? -2 : tile;
   return RELAY_OK;
@@ -313,6 +315,13 @@ static int halo_choice(const relay::ConvArgs& a, bool is_i8) {
   if (g_force_tile >= kStreamBase) return -1;
   if (g_force_tile >= kHaloBase) return relay::conv_halo_supported(a, is_i8, g_force_tile - kHaloBase) ? g_force_tile - kHaloBase : -1;
   return g_force_tile == -1 ? relay::conv_halo_pick(a, is_i8) : -1;
+}
+
+// which variant of the small-tile kernel runs this layer, or -1.  A caller that forces a split of the reduction
+// over workgroups, or another kernel's tile, gets that instead.
+static int small_choice(const relay::ConvArgs& a, bool is_i8) {
+  if (g_force_tile >= kSmallBase) return relay::conv_small_supported(a, is_i8, g_force_tile - kSmallBase) ? g_force_tile - kSmallBase : -1;
+  return g_force_tile == -1 && g_force_split == 0 ? relay::conv_small_pick(a, is_i8) : -1;
 }
 
 static int plan_split(const relay::ConvArgs& a, bool is_i8, size_t* counter_bytes, size_t* total_bytes) {
@@ -343,6 +352,7 @@ static relay_status use_workspace(relay::ConvArgs& a, bool is_i8, void* workspac
   if (!aligned(workspace, 256)) return fail(RELAY_ERR_ALIGN, "workspace must be 256-byte aligned");
   if (workspace_bytes < need)
     return fail(RELAY_ERR_WORKSPACE, "workspace has %zu bytes, relay_workspace_bytes asks for %zu", workspace_bytes, need);
+  if (small_choice(a, is_i8) >= 0) return RELAY_OK;  // the waves of one workgroup split the reduction instead
   a.split = split;
   a.ws_cnt = static_cast<unsigned*>(workspace);
   a.ws_part = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + cb);
@@ -350,6 +360,8 @@ static relay_status use_workspace(relay::ConvArgs& a, bool is_i8, void* workspac
 }
 
 static hipError_t launch_igemm(const relay::ConvArgs& a, bool is_i8, hipStream_t s) {
+  const int mv = small_choice(a, is_i8);
+  if (mv >= 0) return relay::launch_conv_small(a, is_i8, mv, s);
   const int sv = stream_choice(a, is_i8);
   if (sv >= 0) return relay::launch_conv_stream(a, is_i8, sv, s);
   const int hv = halo_choice(a, is_i8);
@@ -368,7 +380,9 @@ relay_status relay_conv2d_kernel_name(const relay_conv2d_desc* d, char* buf, siz
   if ((st = check_igemm_support(d)) != RELAY_OK) return st;
   relay::ConvArgs a = make_args(d, ho, wo);
   const bool i8 = d->dtype == RELAY_I8;
-  if (stream_choice(a, i8) >= 0)
+  if (small_choice(a, i8) >= 0)
+    relay::conv_small_kernel_name(a, i8, small_choice(a, i8), buf, len);
+  else if (stream_choice(a, i8) >= 0)
     relay::conv_stream_kernel_name(a, i8, stream_choice(a, i8), buf, len);
   else if (halo_choice(a, i8) >= 0)
     relay::conv_halo_kernel_name(a, i8, halo_choice(a, i8), buf, len);
@@ -437,7 +451,7 @@ relay_status relay_fused_conv2d_bias_bn_relu_static(const relay_conv2d_desc* d, 
                 (unsigned)RELAY_STATIC_SCRATCH_BYTES);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   a.split = 1;
-  if (split > 1) {
+  if (split > 1 && small_choice(a, false) < 0) {
     void* base = nullptr;
     if ((st = scratch_address(&base)) != RELAY_OK) return st;
     a.split = split;
@@ -1002,7 +1016,7 @@ relay_status relay_dwconv_pwconv_kernel_name(const relay_conv2d_desc* dw, int32_
   relay::DwPwArgs a;
   const relay_status st = dwpw_args(dw, k, 0, &a);
   if (st != RELAY_OK) return st;
-  const int variant = g_force_tile >= kDwPwBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
+  const int variant = g_force_tile >= kDwPwBase && g_force_tile < kSmallBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
   if (variant < 0 || !relay::dwpw_supported(a, variant))
     return fail(RELAY_ERR_UNSUPPORTED, "no fused depthwise + 1x1 kernel variant takes this shape (variant %d)", variant);
   relay::dwpw_kernel_name(variant, buf, len);
@@ -1029,7 +1043,7 @@ relay_status relay_fused_dwconv_pwconv(const relay_conv2d_desc* dw, const void* 
   a.x = x; a.dw_w = dw_w_rsc; a.dw_bias = dw_bias; a.dw_scale = dw_scale; a.dw_shift = dw_shift;
   a.pw.w = pw_w_packed; a.pw.y = y; a.pw.bias = pw_bias; a.pw.scale = pw_scale; a.pw.shift = pw_shift;
   finish_args(a.pw);
-  const int variant = g_force_tile >= kDwPwBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
+  const int variant = g_force_tile >= kDwPwBase && g_force_tile < kSmallBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
   if (variant < 0 || !relay::dwpw_supported(a, variant))
     return fail(RELAY_ERR_UNSUPPORTED, "no fused depthwise + 1x1 kernel variant takes this shape (variant %d)", variant);
   return device_status(relay::launch_dwpw(a, variant, static_cast<hipStream_t>(hip_stream)), "depthwise + 1x1 launch");

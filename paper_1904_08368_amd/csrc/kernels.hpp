@@ -131,6 +131,12 @@ int conv_halo_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the
 int conv_halo_variant_count();
 hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
+// The kernel for layers of few output tiles: the waves of a workgroup split the reduction (conv_small.hip).
+bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);
+int conv_small_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the layer to the other kernels
+int conv_small_variant_count();
+hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
+void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
 // The persistent 3x3 / stride 1 / pad 1 kernel whose workgroups stream tile after tile (conv_stream.hip).
 bool conv_stream_supported(const ConvArgs& a, bool is_i8, int variant);
 int conv_stream_pick(const ConvArgs& a, bool is_i8);  // variant, or -1
