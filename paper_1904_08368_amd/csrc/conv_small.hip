@@ -368,16 +368,17 @@ bool conv_small_supported(const ConvArgs& a, bool is_i8, int v) {
 //           64 x 64 tile: 512 -> 512 at 7 x 7, batch 8: 14.0 us against 7.5 here; 256 -> 256 at 14 x 14, batch 8: 8.4
 //           against 7.0, batch 16: 8.8 against 12.6
 // A layer of more than 256 such tiles goes to the tall tiles of the staged kernels, which this one does not reach.
-int conv_small_pick(const ConvArgs& a, bool is_i8) {
+int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup) {
   if (!conv_small_supported(a, is_i8, 0)) return -1;
   const long tiles64 = (long)((a.M + 63) / 64) * ((a.K + 63) / 64);
   if (tiles64 > 256 || conv_halo_pick(a, is_i8) >= 0) return -1;
   const int row = a.Kred * (is_i8 ? 1 : 2);  // reduction bytes of a tile row
   // fp16: splitting a reduction groups its sums anew.  The convs that other entry points run as part of a larger
   // launch with a promise of the same bits keep the staged kernels' order: a 1x1 conv (behind a depthwise conv),
-  // a conv with a max pool behind it, and a short strided conv (merged with the 1x1 shortcut beside it; 0.2 to
-  // 1.4 us of such a layer at batch 1).
-  if (!is_i8 && (a.R * a.S == 1 || igemm_dma_pool_supported(a, false) || (a.sh > 1 && row <= 1152))) return -1;
+  // a conv with a max pool behind it, and a short strided conv whose window is centred on a 1x1 shortcut conv's
+  // (merged with it; 0.2 to 1.4 us of such a layer at batch 1).
+  const bool centred = a.sh > 1 && (a.R & 1) && (a.S & 1) && a.ph == a.R / 2 && a.pw == a.S / 2;
+  if (!is_i8 && !regroup && (a.R * a.S == 1 || igemm_dma_pool_supported(a, false) || (centred && row <= 1152))) return -1;
   const int per_tap = a.C * (is_i8 ? 1 : 2);
   const int chunk = per_tap % 256 == 0 ? 256 : per_tap % 128 == 0 ? 128 : 64;
   float best = 0.98f * (2.7f + (chunk == 256 ? 0.32f : 0.26f) * (float)(row / chunk));

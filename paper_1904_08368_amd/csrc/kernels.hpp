@@ -133,7 +133,9 @@ hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int variant, hipStrea
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
 // The kernel for layers of few output tiles: the waves of a workgroup split the reduction (conv_small.hip).
 bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);
-int conv_small_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the layer to the other kernels
+// The variant, or -1: leave the layer to the other kernels.  regroup: nothing else promises the bits of this call, so
+// its fp16 sums may be grouped by wave whatever the layer's shape.
+int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup = false);
 int conv_small_variant_count();
 hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
@@ -156,6 +158,7 @@ int dwpw_pick(const DwPwArgs& a);   // variant expected to beat the two separate
 int dwpw_any(const DwPwArgs& a);    // dwpw_pick, else any variant that takes the shape, or -1
 hipError_t launch_dwpw(const DwPwArgs& a, int variant, hipStream_t st);
 void dwpw_kernel_name(int variant, char* buf, size_t len);
+bool dense_splits_units(int m, int k);  // fp16: launch_dense is the faster kernel for this many rows
 hipError_t launch_dense(int m, int n, int k, bool is_f16, const void* x, const void* w, const float* bias,
                         int act, void* y, hipStream_t st);
 hipError_t launch_pack_filters(const void* w_oihw, void* w_packed, int K, int Csrc, int C, int R, int S,

@@ -1,0 +1,46 @@
+"""GPU parity of the dense kernels at the edges of their rules: few and many rows, units
+that are no multiple of 8, reductions on both sides of the split."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+
+pytestmark = pytest.mark.gpu
+# Both sides round to fp16: one unit in the last place where the fp32 sums fall on the other side of a boundary.
+TOL_F16 = 2.0 ** -10 + 1e-5
+
+
+@pytest.fixture(scope="module")
+def G():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 1000, 512), (1, 18, 512), (4, 10, 2048), (5, 10, 2048), (1, 7, 3136), (15, 33, 96),
+                                   (16, 64, 64), (17, 1000, 1024), (3, 40, 72), (70, 24, 32)])
+@pytest.mark.parametrize("act", [0, 1])
+def test_dense_matches_the_oracle(G, m, n, k, act):
+    from paper_1904_08368_amd import binding as B
+    g = np.random.default_rng(9100 + m + n + k)
+    x = g.standard_normal((m, k)).astype(np.float16)
+    w = (g.standard_normal((n, k)) / np.sqrt(k)).astype(np.float16)
+    b = g.standard_normal(n).astype(np.float32)
+    y = torch.full((m, n), float("nan"), dtype=torch.float16, device=G.DEV)
+    B.relay_fused_dense_bias_act(m, n, k, B.RELAY_F16, G.up(x), G.up(w), G.up(b), act, y)
+    torch.cuda.synchronize()
+    want = O.fused_dense(x, w, bias=b, relu_flag=bool(act), out_dtype="f16")
+    assert O.max_rel_err(y.cpu().numpy(), want) <= TOL_F16
+
+
+def test_dense_takes_outputs_of_element_alignment(G):
+    from paper_1904_08368_amd import binding as B
+    g = np.random.default_rng(9200)
+    x, w = g.standard_normal((3, 64)).astype(np.float16), (g.standard_normal((16, 64)) / 8).astype(np.float16)
+    buf = torch.full((3 * 16 + 1,), float("nan"), dtype=torch.float16, device=G.DEV)
+    B.relay_fused_dense_bias_act(3, 16, 64, B.RELAY_F16, G.up(x), G.up(w), None, 0, buf[1:])
+    torch.cuda.synchronize()
+    want = O.fused_dense(x, w, bias=None, relu_flag=False, out_dtype="f16")
+    assert O.max_rel_err(buf[1:].cpu().numpy().reshape(3, 16), want) <= TOL_F16
