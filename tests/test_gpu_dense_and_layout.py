@@ -1,5 +1,6 @@
-"""GPU parity of the dense kernels at the edges of their rules: few and many rows, units
-that are no multiple of 8, reductions on both sides of the split."""
+"""GPU parity of the dense kernels and the layout conversion at the edges of their rules: few and many rows, units
+that are no multiple of 8, reductions on both sides of the split; pixel counts around a vector and channel counts
+around a block."""
 import numpy as np
 import pytest
 import torch
@@ -44,3 +45,18 @@ def test_dense_takes_outputs_of_element_alignment(G):
     torch.cuda.synchronize()
     want = O.fused_dense(x, w, bias=None, relu_flag=False, out_dtype="f16")
     assert O.max_rel_err(buf[1:].cpu().numpy().reshape(3, 16), want) <= TOL_F16
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.int8])
+@pytest.mark.parametrize("n,c,h,w,pad", [(1, 1, 1, 1, 15), (2, 3, 1, 7, 5), (2, 5, 2, 4, 11), (3, 37, 3, 3, 43), (1, 64, 5, 13, 0),
+                                         (2, 70, 8, 8, 10), (1, 129, 7, 11, 31), (2, 16, 1, 3, 0), (1, 9, 6, 5, 4)])
+def test_layout_conversion_at_vector_edges(G, dtype, n, c, h, w, pad):
+    """(the last shape has a padded channel count that takes the element-wise kernel)"""
+    from paper_1904_08368_amd import binding as B
+    x = np.random.default_rng(9300 + c).integers(-127, 128, (n, c, h, w)).astype(dtype)
+    cp = c + pad
+    y = torch.full((n, h, w, cp), 7, dtype=torch.float16 if dtype is np.float16 else torch.int8, device=G.DEV)
+    B.relay_nchw_to_nhwc(B.RELAY_F16 if dtype is np.float16 else B.RELAY_I8, n, c, h, w, cp, G.up(x), y)
+    torch.cuda.synchronize()
+    got = y.cpu().numpy()
+    assert np.array_equal(got[..., :c], x.transpose(0, 2, 3, 1)) and not got[..., c:].any()
