@@ -1,6 +1,6 @@
-"""GPU parity of the dense kernels and the layout conversion at the edges of their rules: few and many rows, units
+"""GPU parity of the dense kernels and the two layout-side kernels at the edges of their rules: few and many rows, units
 that are no multiple of 8, reductions on both sides of the split; pixel counts around a vector and channel counts
-around a block."""
+around a block; average pools of fewer and more positions than a workgroup has threads for."""
 import numpy as np
 import pytest
 import torch
@@ -60,3 +60,14 @@ def test_layout_conversion_at_vector_edges(G, dtype, n, c, h, w, pad):
     torch.cuda.synchronize()
     got = y.cpu().numpy()
     assert np.array_equal(got[..., :c], x.transpose(0, 2, 3, 1)) and not got[..., c:].any()
+
+
+@pytest.mark.parametrize("n,c,hw", [(1, 8, 1), (2, 24, 31), (1, 72, 33), (3, 512, 49), (1, 64, 500)])
+def test_average_pool_matches_the_mean(G, n, c, hw):
+    from paper_1904_08368_amd import binding as B
+    x = np.random.default_rng(9400 + c).standard_normal((n, hw, c)).astype(np.float16)
+    y = torch.full((n, c), float("nan"), dtype=torch.float16, device=G.DEV)
+    B.relay_global_avgpool(B.RELAY_F16, n, c, hw, G.up(x), y)
+    torch.cuda.synchronize()
+    want = x.astype(np.float64).mean(axis=1).astype(np.float16)
+    assert O.max_rel_err(y.cpu().numpy(), want) <= TOL_F16
