@@ -177,6 +177,22 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv3x3_halo_kernel
   }
 #pragma unroll
   for (int s = 1; s < NSW - 1; ++s) issue_filters(s);
+  // ---- the filters this XCD is going to read, towards its L2 (see touch_filters): with n_major the channel tiles of
+  //      its run of tiles, else all of them.  (These loads are younger than those the first step waits for, and
+  //      older than all others.)  Only in short launches (measured up to 912 tiles x chunks): in longer ones the first
+  //      use of the filters is a small part of the time and the extra wait costs as much (VGG-16 0.7 %).
+  const int nb = tiles_m * tiles_n, xcd_idx = blockIdx.x >> 3;
+  if (nb * g.ncc <= 1024 && xcd_idx < 64) {
+    const int per = nb >> 3, wgs = min(per + 1, 64);  // (two workgroups on each of the XCD's 32 CUs)
+    unsigned first = 0, bytes = (unsigned)(a.K * a.Kp * ES);
+    if (a.n_major) {
+      const int t0 = tile - xcd_idx, c0 = (int)fast_div((uint32_t)t0, g.fd_tiles_m) * BN;
+      const int c1 = ((int)fast_div((uint32_t)min(t0 + per, nb - 1), g.fd_tiles_m) + 1) * BN;
+      first = (unsigned)(c0 * a.Kp * ES);
+      bytes = (unsigned)((min(c1, a.K) - c0) * a.Kp * ES);
+    }
+    touch_filters<4>(rs_w, dump_base, first, bytes, xcd_idx * NW + wave, wgs * NW, lane);
+  }
 
   // the i-th load of the issue slot behind step (cc, t): filters of step (cc, t) + NSW - 1, then
   // blocks t * HB ... of the halo of chunk cc + 1
