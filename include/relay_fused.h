@@ -277,7 +277,8 @@ relay_status relay_fused_conv2d_first_layer(const relay_conv2d_desc* d, const vo
  * _RELU.  pw_w_packed: the 1x1 filters [k][c] packed by relay_prepack_conv2d_weights for a 1x1 / stride 1 /
  * F16 / NHWC descriptor of c input channels.  x [n,h,w,c], y [n,ho,wo,k] device, 16-byte aligned,
  * caller-owned, distinct.  Per-channel arrays fp32 device ([c] for dw_*, [k] for pw_*) or NULL with the
- * flag clear.  relay_set_conv_tile(300 + v) forces kernel variant v for the calling thread.
+ * flag clear.  relay_set_conv_tile(300 + v) forces variant v of the kernel that walks the channels in chunks,
+ * 500 + v of the one for few pixels, for the calling thread.
  * Errors: as relay_fused_dwconv_bias_relu, plus RELAY_ERR_UNSUPPORTED (padding, c % 32, residual flag, no
  * variant for the stride) and _SHAPE (k); nothing is launched on an error. */
 relay_status relay_fused_dwconv_pwconv(const relay_conv2d_desc* dw, const void* x, const void* dw_w_rsc,
@@ -289,10 +290,15 @@ relay_status relay_fused_dwconv_pwconv(const relay_conv2d_desc* dw, const void* 
 /* Whether the single launch above is expected to be faster than relay_fused_dwconv_bias_relu followed by
  * the 1x1 relay_fused_conv2d_bias_bn_relu (paper Section 4.1: fusion is a choice the compiler makes per
  * group of operators; Section 5.2 measures what it buys): *pays = 1 on the layers that stream from
- * memory (many pixels, at most 256 channels), 0 on the deep layers, where the single launch would have to
- * recompute the depthwise tile once per tile of output channels.  From measurements on MI355X; host-only,
+ * memory (many pixels, at most 256 channels), 0 on the deep layers, where a kernel that walks the channels in
+ * chunks would have to recompute the depthwise tile once per tile of output channels.  From measurements on MI355X; host-only,
  * nothing is launched.  dw, k as for relay_fused_dwconv_pwconv; same errors for shapes it does not take. */
 relay_status relay_dwconv_pwconv_fusion_pays(const relay_conv2d_desc* dw, int32_t k, int32_t* pays);
+/* The same question for the other kernel behind relay_fused_dwconv_pwconv, the one for layers of few pixels (paper Section
+ * 4.1, as above): *few = 1 where that kernel runs the layer, which is where it was measured faster than two
+ * launches and than the kernel the query above is about: 64 channels or more, and one round of its
+ * workgroups fits the chip.  One launch pays where either query says 1.  Host-only; same errors. */
+relay_status relay_dwconv_pwconv_few_pixels(const relay_conv2d_desc* dw, int32_t k, int32_t* few);
 /* Profiling aid (paper Section 4.1 "Lowering": the lowered code is specific to the shape): the name, as a
  * kernel trace prints it, of the variant relay_fused_dwconv_pwconv runs for this shape. */
 relay_status relay_dwconv_pwconv_kernel_name(const relay_conv2d_desc* dw, int32_t k, char* buf, size_t len);

@@ -61,6 +61,7 @@ SIGNATURES = {
     "relay_first_layer_packed_weight_bytes": [_DP, C.POINTER(C.c_size_t)],
     "relay_prepack_first_layer_weights": [_DP, _P, _P, _P],
     "relay_dwconv_pwconv_fusion_pays": [_DP, C.c_int32, C.POINTER(C.c_int32)],
+    "relay_dwconv_pwconv_few_pixels": [_DP, C.c_int32, C.POINTER(C.c_int32)],
     "relay_fused_dwconv_pwconv": [_DP, _P, _P, _P, _P, _P, C.c_int32, C.c_uint32, _P, _P, _P, _P, _P, _P],
     "relay_fused_dense_bias_act": [_I, _I, _I, _I, _P, _P, _P, _I, _P, _P],
     "relay_maxpool2d": [_I, _I, _I, _I, _I, _I, _I, _I, _P, _P, _P],
@@ -231,6 +232,12 @@ def relay_dwconv_pwconv_fusion_pays(dw: ConvDesc, k: int) -> bool:
     pays = C.c_int32(0)
     _check(lib().relay_dwconv_pwconv_fusion_pays(C.byref(dw), k, C.byref(pays)))
     return bool(pays.value)
+
+
+def relay_dwconv_pwconv_few_pixels(dw: ConvDesc, k: int) -> bool:
+    few = C.c_int32(0)
+    _check(lib().relay_dwconv_pwconv_few_pixels(C.byref(dw), k, C.byref(few)))
+    return bool(few.value)
 
 
 def relay_fused_dwconv_pwconv(dw: ConvDesc, x, dw_w_rsc, dw_bias, dw_scale, dw_shift, k: int, pw_flags: int, pw_w_packed,

@@ -289,6 +289,7 @@ constexpr int kHaloBase = 100;
 constexpr int kStreamBase = 200;
 constexpr int kDwPwBase = 300;   // ... of the fused depthwise + 1x1 kernel (its own entry point)
 constexpr int kSmallBase = 400;  // ... of the kernel whose waves split the reduction of a small tile
+constexpr int kDwPwDirectBase = 500;  // ... of the fused depthwise + 1x1 kernel for layers of few pixels
 
 relay_status relay_set_conv_tile(int32_t tile) {
   const int most = relay::igemm_dma_tile_count() > relay::igemm_tile_count() ? relay::igemm_dma_tile_count()
@@ -296,7 +297,8 @@ relay_status relay_set_conv_tile(int32_t tile) {
   const bool halo = (tile >= kHaloBase && tile < kHaloBase + relay::conv_halo_variant_count()) ||
                     (tile >= kStreamBase && tile < kStreamBase + relay::conv_stream_variant_count()) ||
                     (tile >= kDwPwBase && tile < kDwPwBase + relay::dwpw_variant_count()) ||
-                    (tile >= kSmallBase && tile < kSmallBase + relay::conv_small_variant_count());
+                    (tile >= kSmallBase && tile < kSmallBase + relay::conv_small_variant_count()) ||
+                    (tile >= kDwPwDirectBase && tile < kDwPwDirectBase + relay::dwpw_direct_variant_count());
   if (tile >= most && !halo) return fail(RELAY_ERR_UNSUPPORTED, "no tile %d", tile);
   g_force_tile = tile < -1 ? -2 : tile;
   return RELAY_OK;
@@ -320,6 +322,7 @@ static int halo_choice(const relay::ConvArgs& a, bool is_i8) {
 // which variant of the small-tile kernel runs this layer, or -1.  A caller that forces a split of the reduction
 // over workgroups, or another kernel's tile, gets that instead.
 static int small_choice(const relay::ConvArgs& a, bool is_i8) {
+  if (g_force_tile >= kDwPwDirectBase) return -1;
   if (g_force_tile >= kSmallBase) return relay::conv_small_supported(a, is_i8, g_force_tile - kSmallBase) ? g_force_tile - kSmallBase : -1;
   return g_force_tile == -1 && g_force_split == 0 ? relay::conv_small_pick(a, is_i8) : -1;
 }
@@ -1002,6 +1005,13 @@ static relay_status dwpw_args(const relay_conv2d_desc* dw, int32_t k, uint32_t p
   return RELAY_OK;
 }
 
+// which variant of the kernel for layers of few pixels runs this block, or -1
+static int dwpw_direct_choice(const relay::DwPwArgs& a) {
+  if (g_force_tile >= kDwPwDirectBase) return relay::dwpw_direct_supported(a, g_force_tile - kDwPwDirectBase) ? g_force_tile - kDwPwDirectBase : -1;
+  if (g_force_tile >= kDwPwBase && g_force_tile < kSmallBase) return -1;
+  return relay::dwpw_direct_pick(a);
+}
+
 relay_status relay_dwconv_pwconv_fusion_pays(const relay_conv2d_desc* dw, int32_t k, int32_t* pays) {
   if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
   relay::DwPwArgs a;
@@ -1011,11 +1021,25 @@ relay_status relay_dwconv_pwconv_fusion_pays(const relay_conv2d_desc* dw, int32_
   return RELAY_OK;
 }
 
+relay_status relay_dwconv_pwconv_few_pixels(const relay_conv2d_desc* dw, int32_t k, int32_t* few) {
+  if (!few) return fail(RELAY_ERR_NULL, "few is NULL");
+  relay::DwPwArgs a;
+  const relay_status st = dwpw_args(dw, k, 0, &a);
+  if (st != RELAY_OK) return st;
+  *few = relay::dwpw_direct_pick(a) >= 0 ? 1 : 0;
+  return RELAY_OK;
+}
+
 relay_status relay_dwconv_pwconv_kernel_name(const relay_conv2d_desc* dw, int32_t k, char* buf, size_t len) {
   if (!buf || len == 0) return fail(RELAY_ERR_NULL, "name buffer is NULL or empty");
   relay::DwPwArgs a;
   const relay_status st = dwpw_args(dw, k, 0, &a);
   if (st != RELAY_OK) return st;
+  const int direct = dwpw_direct_choice(a);
+  if (direct >= 0) {
+    relay::dwpw_direct_kernel_name(a, direct, buf, len);
+    return RELAY_OK;
+  }
   const int variant = g_force_tile >= kDwPwBase && g_force_tile < kSmallBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
   if (variant < 0 || !relay::dwpw_supported(a, variant))
     return fail(RELAY_ERR_UNSUPPORTED, "no fused depthwise + 1x1 kernel variant takes this shape (variant %d)", variant);
@@ -1043,6 +1067,9 @@ relay_status relay_fused_dwconv_pwconv(const relay_conv2d_desc* dw, const void* 
   a.x = x; a.dw_w = dw_w_rsc; a.dw_bias = dw_bias; a.dw_scale = dw_scale; a.dw_shift = dw_shift;
   a.pw.w = pw_w_packed; a.pw.y = y; a.pw.bias = pw_bias; a.pw.scale = pw_scale; a.pw.shift = pw_shift;
   finish_args(a.pw);
+  const int direct = dwpw_direct_choice(a);
+  if (direct >= 0)
+    return device_status(relay::launch_dwpw_direct(a, direct, static_cast<hipStream_t>(hip_stream)), "depthwise + 1x1 launch");
   const int variant = g_force_tile >= kDwPwBase && g_force_tile < kSmallBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
   if (variant < 0 || !relay::dwpw_supported(a, variant))
     return fail(RELAY_ERR_UNSUPPORTED, "no fused depthwise + 1x1 kernel variant takes this shape (variant %d)", variant);

@@ -13,6 +13,14 @@ __device__ __forceinline__ void fma_mix_hi(float& acc, unsigned x, unsigned w) {
   asm("v_fma_mix_f32 %0, %1, %2, %0 op_sel:[1,1,0] op_sel_hi:[1,1,0]" : "+v"(acc) : "v"(x), "v"(w));
 }
 
+// acc = x.lo*w.lo: the first tap (the same value as the multiply-add onto +0)
+__device__ __forceinline__ void mul_mix_lo(float& acc, unsigned x, unsigned w) {
+  asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[0,0,0] op_sel_hi:[1,1,0]" : "=v"(acc) : "v"(x), "v"(w));
+}
+__device__ __forceinline__ void mul_mix_hi(float& acc, unsigned x, unsigned w) {
+  asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,1,0] op_sel_hi:[1,1,0]" : "=v"(acc) : "v"(x), "v"(w));
+}
+
 // The fused tail of eight depthwise results: scale and shift in fp32, two results narrowed by one packed
 // conversion, the lower bound (0 for relu, -infinity for none) applied to the narrowed pair by one packed
 // maximum.  Rounding is monotone and keeps the sign, so this equals the bound applied before the

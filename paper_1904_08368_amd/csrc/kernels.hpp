@@ -158,6 +158,12 @@ int dwpw_pick(const DwPwArgs& a);   // variant expected to beat the two separate
 int dwpw_any(const DwPwArgs& a);    // dwpw_pick, else any variant that takes the shape, or -1
 hipError_t launch_dwpw(const DwPwArgs& a, int variant, hipStream_t st);
 void dwpw_kernel_name(int variant, char* buf, size_t len);
+// ... and for layers of few pixels, without chunks (dwpw_direct.hip).
+int dwpw_direct_variant_count();
+bool dwpw_direct_supported(const DwPwArgs& a, int variant);
+int dwpw_direct_pick(const DwPwArgs& a);   // variant expected to beat the two separate launches and the chunked kernel, or -1
+hipError_t launch_dwpw_direct(const DwPwArgs& a, int variant, hipStream_t st);
+void dwpw_direct_kernel_name(const DwPwArgs& a, int variant, char* buf, size_t len);
 bool dense_splits_units(int m, int k);  // fp16: launch_dense is the faster kernel for this many rows
 hipError_t launch_dense(int m, int n, int k, bool is_f16, const void* x, const void* w, const float* bias,
                         int act, void* y, hipStream_t st);

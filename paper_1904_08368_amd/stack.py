@@ -196,7 +196,8 @@ class FusedNet:
                 B.relay_prepack_dwconv_weights(d, wsrc, wp)
                 pw = self._pointwise_behind(ops, i, group_of, absorbed) if self.fuse_dwpw and op.r == 3 and op.pad == 1 \
                     and cin_p % 32 == 0 and src.is_contiguous() else None
-                if pw is not None and (self.fuse_dwpw == "always" or B.relay_dwconv_pwconv_fusion_pays(d, ops[pw].cout)):
+                if pw is not None and (self.fuse_dwpw == "always" or B.relay_dwconv_pwconv_few_pixels(d, ops[pw].cout) or
+                                       B.relay_dwconv_pwconv_fusion_pays(d, ops[pw].cout)):
                     q, pp = ops[pw], params[pw]
                     pflags = B.flags_of(pp.get("bias"), pp.get("scale"), None, q.relu)
                     pd = B.conv_desc(batch, cin_p, ho, wo, q.cout, 1, 1, 1, 0, self.dtype, B.RELAY_NHWC, pflags)

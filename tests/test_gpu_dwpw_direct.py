@@ -1,0 +1,43 @@
+"""The one-launch depthwise + 1x1 kernel for layers of few pixels, against the oracle's two fused operators and bit for bit
+against the two separate launches: every variant at the edges of its tiles, and the rule that chooses them."""
+import pytest
+import torch
+
+from tests.test_gpu_dwpw import _case
+
+pytestmark = pytest.mark.gpu
+
+# (most channels, ring stages of 32 channels) of every variant, in the library's order
+VARIANTS = ((256, 8), (256, 8), (256, 8), (1024, 32), (512, 16), (512, 16), (512, 8), (512, 6), (512, 4))
+
+
+@pytest.fixture(scope="module")
+def G():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("variant", range(len(VARIANTS)))
+def test_every_variant_at_the_edges(G, variant, stride):
+    """Images narrower and wider than a rectangle, odd and even, a single pixel, channel tiles that end within a wave's
+    32 channels, the fewest channels and the most, one image and several."""
+    most = VARIANTS[variant][0]
+    for i, (n, c, h, w, k) in enumerate([(1, 32, 1, 1, 8), (2, 64, 5, 3, 40), (1, most, 7, 7, 264), (3, 64, 9, 33, 72), (1, 128, 2, 70, 136),
+                                         (1, most // 2, 14, 15, 64)]):
+        _case(G, 9000 + 100 * variant + 10 * stride + i, n, c, h, w, k, stride, variant=200 + variant, plain_tail=i % 2 == 1)
+
+
+# the first and last sizes at which the rule takes a tile (the number of workgroups that fit the chip at once)
+@pytest.mark.parametrize("n,c,h,w,k,stride,name", [
+    (1, 64, 32, 32, 64, 1, "16, 2, 4, 8, 8"), (8, 64, 28, 28, 64, 1, "32, 4, 4, 8, 8"), (2, 512, 14, 14, 512, 1, "16, 2, 8, 16, 16"), (1, 1024, 7, 7, 1024, 1, "16, 1, 8, 32, 32"),
+    (1, 512, 14, 14, 256, 1, "16, 1, 8, 32, 32"), (4, 512, 14, 14, 512, 1, "32, 2, 8, 16, 16"), (32, 512, 14, 14, 512, 1, "64, 8, 8, 4, 16"),
+    (37, 512, 14, 14, 512, 1, None), (3, 1024, 7, 7, 1024, 1, None), (1, 32, 16, 16, 64, 1, None)])
+def test_rule(G, n, c, h, w, k, stride, name):
+    from paper_1904_08368_amd import binding as B
+    d = B.conv_desc(n, c, h, w, c, 3, 3, stride, 1, B.RELAY_F16, B.RELAY_NHWC, 0)
+    got = B.relay_dwconv_pwconv_kernel_name(d, k)
+    assert (f"dwpw_fused_direct_kernel<{stride}, {name}>" == got) if name else ("direct" not in got)
+    assert B.relay_dwconv_pwconv_few_pixels(d, k) == (name is not None)
