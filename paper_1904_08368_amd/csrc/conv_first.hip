@@ -35,10 +35,13 @@ __device__ __forceinline__ float dot2(unsigned x, unsigned w, float acc) {
   return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, x), __builtin_bit_cast(half2v, w), acc, false);
 }
 
+// PASS: output channels per pass.  SPLIT: a workgroup takes one pass only, of PASS channels from blockIdx.y * PASS on.
+template <int PASS, bool SPLIT>
 __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
   extern __shared__ uint4 lds[];
-  float* cmul = reinterpret_cast<float*>(lds);                              // [K]
-  float* cadd = cmul + a.K;                                                 // [K]
+  const int k0 = SPLIT ? (int)blockIdx.y * PASS : 0, kn = SPLIT ? PASS : a.K;   // this workgroup's output channels
+  float* cmul = reinterpret_cast<float*>(lds);                              // [kn]
+  float* cadd = cmul + kn;                                                  // [kn]
   // the packed filters, read through the scalar cache: the table is written before the launch and never by it
   typedef const unsigned __attribute__((address_space(4)))* const_words;
   const const_words wt = (const_words)(unsigned long)a.w;
@@ -80,8 +83,8 @@ __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
       xl[c * 3 + r] = l;
     }
   // ---- the constants of the tail into LDS (behind the image loads above, so that both memory latencies pass together)
-  for (int k = tid; k < a.K; k += blockDim.x) {
-    const float sc = a.scale ? a.scale[k] : 1.f, sf = a.shift ? a.shift[k] : 0.f, bb = a.bias ? a.bias[k] : 0.f;
+  for (int k = tid; k < kn; k += blockDim.x) {
+    const float sc = a.scale ? a.scale[k0 + k] : 1.f, sf = a.shift ? a.shift[k0 + k] : 0.f, bb = a.bias ? a.bias[k0 + k] : 0.f;
     cmul[k] = sc;
     cadd[k] = bb * sc + sf;   // (acc + b) * sc + sf
   }
@@ -100,20 +103,20 @@ __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
 
   const float lo_bound = (a.flags & F_RELU) ? 0.f : -__builtin_inff();
   if (!live) return;
-  _Float16* y = static_cast<_Float16*>(a.y) + (size_t)t * kPix * a.K;   // (thread t owns pixels t * kPix ... of the NHWC output)
-  for (int kb = 0; kb < a.K; kb += kPass) {
-    float acc[kPix][kPass];
+  _Float16* y = static_cast<_Float16*>(a.y) + (size_t)t * kPix * a.K + k0;   // (thread t owns pixels t * kPix ... of the NHWC output)
+  for (int kb = 0; kb < kn; kb += PASS) {
+    float acc[kPix][PASS];
 #pragma unroll
     for (int i = 0; i < kPix; ++i)
 #pragma unroll
-      for (int k = 0; k < kPass; ++k) acc[i][k] = 0.f;
+      for (int k = 0; k < PASS; ++k) acc[i][k] = 0.f;
 #pragma unroll
-    for (int k4 = 0; k4 < kPass / 4; ++k4) {
+    for (int k4 = 0; k4 < PASS / 4; ++k4) {
       unsigned wk[kPairs][4];   // (uniform: scalar registers)
 #pragma unroll
       for (int pair = 0; pair < kPairs; ++pair)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) wk[pair][e] = wt[((kb >> 2) + k4) * (kPairs * 4) + pair * 4 + e];
+        for (int e = 0; e < 4; ++e) wk[pair][e] = wt[(((k0 + kb) >> 2) + k4) * (kPairs * 4) + pair * 4 + e];
 #pragma unroll
       for (int pair = 0; pair < kPairs; ++pair)
 #pragma unroll
@@ -123,9 +126,9 @@ __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
           for (int e = 0; e < 4; ++e) acc[i][4 * k4 + e] = dot2(xv, wk[pair][e], acc[i][4 * k4 + e]);
         }
     }
-    float mul[kPass], add[kPass];
+    float mul[PASS], add[PASS];
 #pragma unroll
-    for (int k4 = 0; k4 < kPass / 4; ++k4) {
+    for (int k4 = 0; k4 < PASS / 4; ++k4) {
       const float4 m4 = *reinterpret_cast<const float4*>(cmul + kb + 4 * k4);
       const float4 a4 = *reinterpret_cast<const float4*>(cadd + kb + 4 * k4);
       mul[4 * k4] = m4.x; mul[4 * k4 + 1] = m4.y; mul[4 * k4 + 2] = m4.z; mul[4 * k4 + 3] = m4.w;
@@ -134,7 +137,7 @@ __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
 #pragma unroll
     for (int i = 0; i < kPix; ++i)
 #pragma unroll
-      for (int h = 0; h < kPass / 8; ++h) {
+      for (int h = 0; h < PASS / 8; ++h) {
         float a8[8], m8[8], s8[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -187,8 +190,18 @@ hipError_t launch_conv_first(const ConvArgs& a, hipStream_t st) {
   b.fd_howo = make_fastdiv((uint32_t)(a.Wo / kPix));   // thread index -> output row n * Ho + p
   b.fd_wo = make_fastdiv((uint32_t)a.Ho);              // output row -> image
   const long threads = (long)a.N * a.Ho * (a.Wo / kPix);
-  const size_t lds_bytes = (size_t)a.K * 8;
-  hipLaunchKernelGGL(conv_first_kernel, dim3((unsigned)((threads + 127) / 128)), dim3(128), lds_bytes, st, b);
+  // Few pixels: a workgroup per pass of output channels (the threads that share pixels load them again).  A wave's passes
+  // follow each other behind the scalar loads of their filters, with no other wave on its SIMD to cover those: 32
+  // channels at 224 x 224, graph-timed with one, two, 8 and 16 images 5.8 -> 3.9, 5.8 -> 4.6, 7.7 -> 6.7 and 10.0 -> 9.4 us (64
+  // channels 8.8 -> 4.7 with one).  With 32 images (15.4 against 16.7) the chip is full without.
+  const dim3 grid((unsigned)((threads + 127) / 128));
+  const long waves = (threads + 63) / 64;
+  if (waves * (a.K / 16) <= 256)
+    hipLaunchKernelGGL((conv_first_kernel<kPass / 2, true>), dim3(grid.x, a.K / (kPass / 2)), dim3(128), kPass / 2 * 8, st, b);
+  else if (waves <= 1600 && a.K > kPass)
+    hipLaunchKernelGGL((conv_first_kernel<kPass, true>), dim3(grid.x, a.K / kPass), dim3(128), kPass * 8, st, b);
+  else
+    hipLaunchKernelGGL((conv_first_kernel<kPass, false>), grid, dim3(128), (size_t)a.K * 8, st, b);
   return hipGetLastError();
 }
 

@@ -121,7 +121,7 @@ def main() -> int:
     B.relay_prepack_first_layer_weights(d, (tensor((32, 3, 3, 3), False) * 0.1).to(torch.float16), wpk)
     y = torch.empty((32, 112, 112, 32), dtype=torch.float16, device=dev)
     sc, sf = torch.ones(32, device=dev), torch.zeros(32, device=dev)
-    run("first_f16_c3_224", "conv_first_kernel", lambda d=d, x=x, wpk=wpk, sc=sc, sf=sf, y=y: B.relay_fused_conv2d_first_layer(d, x, wpk, None, sc, sf, y),
+    run("first_f16_c3_224", "conv_first_kernel<16, false>", lambda d=d, x=x, wpk=wpk, sc=sc, sf=sf, y=y: B.relay_fused_conv2d_first_layer(d, x, wpk, None, sc, sf, y),
         2.0 * 32 * 112 * 112 * 32 * 27 / 1e9, (32 * 224 * 224 * 3 + 32 * 112 * 112 * 32 + 32 * 27) * 2 / 1e6)
 
     # ---- depthwise 3x3 (MobileNet-v1, batch 32): the LDS-staged stride-1 kernel and the register-patch kernel
