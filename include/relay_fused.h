@@ -474,6 +474,32 @@ relay_status relay_realize_conv(int32_t k, int64_t per_k, const float* w, const 
                                 int32_t* bias_q, relay_realized_conv* out, void* workspace, size_t workspace_bytes,
                                 void* hip_stream);
 
+/* One member of relay_conv2d_pair below: the operands of one conv2d primitive function (paper Section 4.1). */
+typedef struct relay_conv2d_call {
+  const relay_conv2d_desc* d;
+  const void* x;
+  const void* w_packed;
+  const void* bias;
+  const float* bn_scale;
+  const float* bn_shift;
+  const void* residual;
+  int32_t residual_lshift;   /* I8 */
+  int32_t out_rshift;        /* I8 */
+  void* y;
+} relay_conv2d_call;
+/* Two conv2d primitive functions that do not read each other's output as ONE launch (paper Section 5.2: what each saved
+ * launch is worth): the workgroups of both share the grid.  Meant for a residual block's first conv and the shortcut
+ * conv beside it.  Each member is a call of relay_fused_conv2d_bias_bn_relu (F16: bias fp32) or relay_qconv2d_requant (I8: bias
+ * int32, bn_scale and bn_shift NULL) without a workspace, and is checked as by that call; both have one dtype.
+ * Where no kernel takes the two together they run as two launches, one after the other.  Results: I8 bit for bit those
+ * of the separate calls; F16 the same up to the grouping of a reduction's fp32 sums.
+ * Errors: as the calls above, plus RELAY_ERR_DTYPE (two dtypes) and _UNSUPPORTED (a member's output is the other's output or
+ * operand); nothing is launched on an error. */
+relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2d_call* second, void* hip_stream);
+/* Whether relay_conv2d_pair runs two convs of these shapes as one launch (paper Section 4.1, a choice per group of operators);
+ * host-only, nothing is launched.  Errors: as relay_workspace_bytes, _DTYPE (two dtypes). */
+relay_status relay_conv2d_pair_fusable(const relay_conv2d_desc* first, const relay_conv2d_desc* second, int32_t* fusable);
+
 /* For callers that cannot allocate device memory (code under HIP-graph capture, serving loops and
  * harnesses that forbid hipMalloc): relay_fused_conv2d_bias_bn_relu for F16 NHWC / NHWC4_PADDED
  * descriptors with the reduction-split scratch (see relay_workspace_bytes) taken from a static

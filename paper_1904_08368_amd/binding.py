@@ -34,6 +34,12 @@ class ConvDesc(C.Structure):
                                          "pad_h", "pad_w", "dtype", "layout")] + [("flags", C.c_uint32)]
 
 
+class ConvCall(C.Structure):
+    """One member of relay_conv2d_pair."""
+    _fields_ = [("d", C.POINTER(ConvDesc))] + [(n, C.c_void_p) for n in ("x", "w_packed", "bias", "bn_scale", "bn_shift", "residual")] + \
+        [("residual_lshift", C.c_int32), ("out_rshift", C.c_int32), ("y", C.c_void_p)]
+
+
 _lib = None
 
 # name -> argtypes; every symbol the header declares
@@ -46,6 +52,8 @@ SIGNATURES = {
     "relay_prepack_conv2d_weights": [_DP, _P, _I, _P, _SZ, _P],
     "relay_fused_conv2d_bias_bn_relu": [_DP, _P, _P, _P, _P, _P, _P, _P, _P, _SZ, _P],
     "relay_fused_conv2d_bias_bn_relu_static": [_DP, _P, _P, _P, _P, _P, _P, _P, _P],
+    "relay_conv2d_pair": [C.POINTER(ConvCall), C.POINTER(ConvCall), _P],
+    "relay_conv2d_pair_fusable": [_DP, _DP, C.POINTER(_I)],
     "relay_qconv2d_requant": [_DP, _P, _P, _P, _P, _I, _I, _P, _P, _SZ, _P],
     "relay_qconv2d_requant_scaled": [_DP, _P, _P, _P, _P, _I, _P, _P, _P, _P, _SZ, _P],
     "relay_quantize_multiplier": [C.c_double, C.POINTER(_I), C.POINTER(_I)],
@@ -185,6 +193,28 @@ def relay_qconv2d_requant(d: ConvDesc, x, w_packed, bias, residual, residual_lsh
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().relay_qconv2d_requant(C.byref(d), _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(residual),
                                        residual_lshift, out_rshift, _ptr(y), _ptr(workspace), ws_bytes, _stream()))
+
+
+def relay_conv2d_pair_fusable(first: ConvDesc, second: ConvDesc) -> bool:
+    ok = C.c_int32(0)
+    _check(lib().relay_conv2d_pair_fusable(C.byref(first), C.byref(second), C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_conv2d_pair(first, second) -> None:
+    """first, second: the argument tuples of two relay_fused_conv2d_bias_bn_relu (or two relay_qconv2d_requant) calls; a
+    workspace among them is not used."""
+    def member(args):
+        d = args[0]
+        if d.dtype == RELAY_I8:
+            _, x, w, bias, res, lshift, rshift, y = args[:8]
+            scale = shift = None
+        else:
+            _, x, w, bias, scale, shift, res, y = args[:8]
+            lshift = rshift = 0
+        return ConvCall(C.pointer(d), _ptr(x), _ptr(w), _ptr(bias), _ptr(scale), _ptr(shift), _ptr(res), lshift, rshift, _ptr(y))
+    a, b = member(first), member(second)
+    _check(lib().relay_conv2d_pair(C.byref(a), C.byref(b), _stream()))
 
 
 def relay_conv2d_maxpool_fusable(d: ConvDesc) -> bool:

@@ -362,7 +362,14 @@ static relay_status use_workspace(relay::ConvArgs& a, bool is_i8, void* workspac
   return RELAY_OK;
 }
 
+// where a conv's arguments go instead of into a launch, while its caller collects the members of a shared one
+static thread_local relay::ConvArgs* g_collect = nullptr;
+
 static hipError_t launch_igemm(const relay::ConvArgs& a, bool is_i8, hipStream_t s) {
+  if (g_collect) {
+    *g_collect = a;
+    return hipSuccess;
+  }
   const int mv = small_choice(a, is_i8);
   if (mv >= 0) return relay::launch_conv_small(a, is_i8, mv, s);
   const int sv = stream_choice(a, is_i8);
@@ -853,6 +860,79 @@ static relay_status qconv_common(const relay_conv2d_desc* d, const int8_t* x, co
   finish_args(a);
   if ((st = use_workspace(a, true, workspace, workspace_bytes)) != RELAY_OK) return st;
   return device_status(launch_igemm(a, true, static_cast<hipStream_t>(hip_stream)), "qconv2d launch");
+}
+
+// ---- two independent convs in one launch ----------------------------------------------------------------------
+
+// Which kernel runs the two: variant `small` of the small-tile kernel (the first conv's own choice), or tile `dma` of the
+// staged kernel (the choice of both); neither: two launches.  A conv that another kernel runs, or whose reduction is split
+// over workgroups, stays by itself.
+struct PairPlan {
+  int small = -1, dma = -1;
+};
+static PairPlan pair_plan(const relay::ConvArgs& a, const relay::ConvArgs& b, bool i8) {
+  PairPlan p;
+  if (g_force_tile != -1 || g_force_split != 0 || a.xs_w != a.C || b.xs_w != b.C) return p;
+  if (stream_choice(a, i8) >= 0 || stream_choice(b, i8) >= 0 || halo_choice(a, i8) >= 0 || halo_choice(b, i8) >= 0) return p;
+  const int v = small_choice(a, i8);
+  if (v >= 0) {
+    if (relay::conv_small_pair_supported(a, b, i8, v)) p.small = v;
+    return p;
+  }
+  size_t cb, total;
+  if (plan_split(a, i8, &cb, &total) > 1 || plan_split(b, i8, &cb, &total) > 1) return p;
+  p.dma = relay::igemm_dma_pair_tile(a, b, i8);
+  return p;
+}
+
+relay_status relay_conv2d_pair_fusable(const relay_conv2d_desc* first, const relay_conv2d_desc* second, int32_t* fusable) {
+  if (!fusable) return fail(RELAY_ERR_NULL, "fusable is NULL");
+  const relay_conv2d_desc* ds[2] = {first, second};
+  relay::ConvArgs m[2];
+  bool mfma = true;
+  for (int i = 0; i < 2; ++i) {
+    int ho, wo;
+    const relay_status st = check_geometry(ds[i], &ho, &wo);
+    if (st != RELAY_OK) return st;
+    mfma = mfma && (ds[i]->dtype == RELAY_F16 || ds[i]->dtype == RELAY_I8) && check_igemm_support(ds[i]) == RELAY_OK;
+    m[i] = make_args(ds[i], ho, wo);
+    finish_args(m[i]);
+  }
+  if (first->dtype != second->dtype) return fail(RELAY_ERR_DTYPE, "the two convs have different dtypes");
+  const PairPlan p = mfma ? pair_plan(m[0], m[1], first->dtype == RELAY_I8) : PairPlan();
+  *fusable = p.small >= 0 || p.dma >= 0 ? 1 : 0;
+  return RELAY_OK;
+}
+
+relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2d_call* second, void* hip_stream) {
+  if (!first || !second) return fail(RELAY_ERR_NULL, "a member is NULL");
+  const relay_conv2d_call* c[2] = {first, second};
+  if (!first->d || !second->d) return fail(RELAY_ERR_NULL, "descriptor is NULL");
+  if (first->d->dtype != second->d->dtype) return fail(RELAY_ERR_DTYPE, "the two convs have different dtypes");
+  const bool i8 = first->d->dtype == RELAY_I8;
+  if (!i8 && first->d->dtype != RELAY_F16) return fail(RELAY_ERR_DTYPE, "the paired conv2d takes F16 or I8");
+  if (first->y == second->y || first->y == second->x || second->y == first->x || (first->residual && first->residual == second->y) ||
+      (second->residual && second->residual == first->y))
+    return fail(RELAY_ERR_UNSUPPORTED, "one conv's output is the other's output or operand");
+  relay::ConvArgs m[2];
+  for (int i = 0; i < 2; ++i) {
+    if (i8 && (c[i]->bn_scale || c[i]->bn_shift)) return fail(RELAY_ERR_UNSUPPORTED, "the quantized epilogue has no float scale/shift");
+    g_collect = &m[i];
+    const relay_status st =
+        i8 ? relay_qconv2d_requant(c[i]->d, static_cast<const int8_t*>(c[i]->x), static_cast<const int8_t*>(c[i]->w_packed),
+                                   static_cast<const int32_t*>(c[i]->bias), static_cast<const int8_t*>(c[i]->residual), c[i]->residual_lshift,
+                                   c[i]->out_rshift, static_cast<int8_t*>(c[i]->y), nullptr, 0, hip_stream)
+           : relay_fused_conv2d_bias_bn_relu(c[i]->d, c[i]->x, c[i]->w_packed, static_cast<const float*>(c[i]->bias), c[i]->bn_scale, c[i]->bn_shift,
+                                             c[i]->residual, c[i]->y, nullptr, 0, hip_stream);
+    g_collect = nullptr;
+    if (st != RELAY_OK) return st;
+  }
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  const PairPlan p = pair_plan(m[0], m[1], i8);
+  if (p.small >= 0) return device_status(relay::launch_conv_small_pair(m[0], m[1], i8, p.small, s), "paired conv2d launch");
+  if (p.dma >= 0) return device_status(relay::launch_conv_igemm_dma_pair(m[0], m[1], i8, p.dma, s), "paired conv2d launch");
+  const relay_status st = device_status(launch_igemm(m[0], i8, s), "conv2d launch");
+  return st != RELAY_OK ? st : device_status(launch_igemm(m[1], i8, s), "conv2d launch");
 }
 
 // ---- conv2d + 3x3 / stride 2 / pad 1 max pool in one launch -------------------------------------

@@ -56,12 +56,9 @@ using acc_t_scalar = typename std::conditional<IS_I8, int, float>::type;
 // branches they cost it about 1 % each (registers held across the main loop, code size).
 // POOL: the tile is the 15 x 17 patch of conv outputs under a 7 x 8 block of 3x3/s2/p1 max-pool
 // outputs (255 of 256 rows); the finished patch goes to LDS and only the pooled block is stored.
-template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP, int SK, bool STOCH, bool EXT,
-          bool POOL = false>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
-                             // two workgroups per CU where their LDS rings fit side by side
-                             (NS * KP * (WAVES_M * TM + WAVES_N * TN) * 32 * 64 <= 80 * 1024 ? 2 : 1))
-    void igemm_dma_kernel(const ConvArgs a) {
+// bid: the workgroup's number among those of this conv
+template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP, int SK, bool STOCH, bool EXT, bool POOL>
+__device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid) {
   constexpr int NW = WAVES_M * WAVES_N * SK;
   static_assert(SK == 1 || (SK == 2 && KP == 2 && TM % 2 == 0), "k-split pairs take one 64-byte plane each");
   constexpr int VE = IS_I8 ? 16 : 8;
@@ -114,7 +111,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
   const int tiles_m = POOL ? a.N * a.pool_tiles_img : (a.M + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
   // with a split reduction consecutive workgroups (same XCD) share a tile
   const int nsplit = (EXT && a.split > 1) ? a.split : 1;
-  const int wg = xcd_remap(blockIdx.x, tiles_m * tiles_n * nsplit);
+  const int wg = xcd_remap(bid, tiles_m * tiles_n * nsplit);
   const int tile = wg / nsplit, ks = wg - tile * nsplit;
   const int tile_q = (int)fast_div((uint32_t)tile, a.n_major ? a.fd_tiles_m : a.fd_tiles_n);
   const int tile_n = a.n_major ? tile_q : tile - tile_q * tiles_n;
@@ -702,6 +699,28 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
   }
 }
 
+template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP, int SK, bool STOCH, bool EXT,
+          bool POOL = false>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
+                             // two workgroups per CU where their LDS rings fit side by side
+                             (NS * KP * (WAVES_M * TM + WAVES_N * TN) * 32 * 64 <= 80 * 1024 ? 2 : 1))
+    void igemm_dma_kernel(const ConvArgs a) {
+  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, STOCH, EXT, POOL>(a, (int)blockIdx.x);
+}
+
+// Two convs that do not read each other's output, in one launch: the first `tiles` workgroups run the first, the others the
+// second (see igemm_small_pair_kernel).
+struct DmaPair {
+  ConvArgs a[2];
+  int tiles;
+};
+template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (NS * KP * (WAVES_M * TM + WAVES_N * TN) * 32 * 64 <= 80 * 1024 ? 2 : 1))
+    void igemm_dma_pair_kernel(const DmaPair p) {
+  const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
+  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, 1, false, false, false>(p.a[second], (int)blockIdx.x - (second ? p.tiles : 0));
+}
+
 struct DmaTile {
   int waves_m, waves_n, tm, tn, ns, kp, sk;
   constexpr int bm() const { return waves_m * tm * 32; }
@@ -752,6 +771,37 @@ hipError_t launch_one(const ConvArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, false, false>), dim3(tiles),
                        dim3(64 * WAVES_M * WAVES_N * SK), 0, st, b);
   return hipGetLastError();
+}
+
+template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP>
+hipError_t launch_pair_one(const ConvArgs& a, const ConvArgs& b, hipStream_t st) {
+  constexpr int BM = WAVES_M * TM * 32, BN = WAVES_N * TN * 32;
+  DmaPair p;
+  p.a[0] = a;
+  p.a[1] = b;
+  int tiles[2];
+  for (int i = 0; i < 2; ++i) {
+    const int tiles_m = (p.a[i].M + BM - 1) / BM, tiles_n = (p.a[i].K + BN - 1) / BN;
+    tiles[i] = tiles_m * tiles_n;
+    p.a[i].split = 1;
+    p.a[i].fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
+    p.a[i].fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
+  }
+  p.tiles = tiles[0];
+  hipLaunchKernelGGL((igemm_dma_pair_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP>), dim3(tiles[0] + tiles[1]), dim3(64 * WAVES_M * WAVES_N), 0, st, p);
+  return hipGetLastError();
+}
+
+// the tiles the short strided convs take
+template <bool IS_I8>
+hipError_t launch_pair_typed(const ConvArgs& a, const ConvArgs& b, int tile, hipStream_t st) {
+  switch (tile) {
+    case 4: return launch_pair_one<IS_I8, 2, 2, 2, 1, 4, 1>(a, b, st);
+    case 5: return launch_pair_one<IS_I8, 2, 2, 1, 1, 4, 1>(a, b, st);
+    case 9: return launch_pair_one<IS_I8, 2, 2, 2, 1, 3, 2>(a, b, st);
+    case 10: return launch_pair_one<IS_I8, 2, 2, 1, 1, 3, 2>(a, b, st);
+    default: return launch_pair_one<IS_I8, 2, 2, 1, 1, 3, 4>(a, b, st);
+  }
 }
 
 template <bool IS_I8, bool STOCH>
@@ -821,6 +871,24 @@ bool igemm_dma_supported(const ConvArgs& a, bool is_i8) {
   // tile rows are decoded as small offsets from the tile's first pixel (float reciprocal, < 2^22)
   return (a.C % ck) == 0 && a.R * a.S <= 32 && (size_t)a.N * a.xs_n * es <= lim &&
          (size_t)a.K * a.Kp * es <= lim && a.Wo < (1 << 20) && a.Ho < (1 << 20);
+}
+
+// Two convs share a launch where both take the same of these tiles by themselves (the sums are then grouped as in their own
+// launches), and the one whose ring leaves room for a single workgroup per CU only where that is one round.  ResNet-18's
+// first convs and shortcuts of a stage at batch 32, together against one after the other: 784 tiles of 128 x 64 14.8 us
+// against 11.7 + 5.5, 392 12.4 against 10.5 + 5.2; int8 at batch 16 9.9 against 7.8 + 4.4, 64 x 64 tiles 8.2 against 6.3 + 3.7.
+int igemm_dma_pair_tile(const ConvArgs& a, const ConvArgs& b, bool is_i8) {
+  if (!igemm_dma_supported(a, is_i8) || !igemm_dma_supported(b, is_i8) || a.nseg || b.nseg || a.pool || b.pool ||
+      a.round_mode == ROUND_STOCHASTIC || b.round_mode == ROUND_STOCHASTIC)
+    return -1;
+  const int t = pick_tile(a, is_i8);
+  if (t != pick_tile(b, is_i8)) return -1;
+  if (t == 15) return tiles_of(a, kTiles[t]) + tiles_of(b, kTiles[t]) <= 256 ? t : -1;
+  return t == 4 || t == 5 || t == 9 || t == 10 ? t : -1;
+}
+
+hipError_t launch_conv_igemm_dma_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int tile, hipStream_t st) {
+  return is_i8 ? launch_pair_typed<true>(a, b, tile, st) : launch_pair_typed<false>(a, b, tile, st);
 }
 
 bool igemm_dma_pool_supported(const ConvArgs& a, bool is_i8) {

@@ -61,9 +61,9 @@ struct SmallGeom {
   FastDiv fd_per_tap, fd_s;      // division by per_tap and by S
 };
 
-// EXT: the instantiation that stores output channel segments.
+// EXT: the instantiation that stores output channel segments.  bid: the workgroup's number among the tiles of this conv.
 template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT>
-__global__ __launch_bounds__(64 * W) void igemm_small_kernel(const ConvArgs a, const SmallGeom g) {
+__device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g, const int bid) {
   constexpr int VE = IS_I8 ? 16 : 8;
   constexpr int ES = IS_I8 ? 1 : 2;
   constexpr int CU = U * BKV * VE;  // channels per unit: U steps of 64 bytes
@@ -95,8 +95,8 @@ __global__ __launch_bounds__(64 * W) void igemm_small_kernel(const ConvArgs a, c
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // (xcd_remap with the host's divisions)
-  const int xcd = blockIdx.x & 7;
-  const int tile = xcd * g.xcd_per + min(xcd, g.xcd_rem) + (int)(blockIdx.x >> 3);
+  const int xcd = bid & 7;
+  const int tile = xcd * g.xcd_per + min(xcd, g.xcd_rem) + (bid >> 3);
   const int tile_q = (int)div_by((uint32_t)tile, a.n_major ? a.fd_tiles_m : a.fd_tiles_n);
   const int tile_n = a.n_major ? tile_q : tile - tile_q * g.tiles_n;
   const int tile_m = a.n_major ? tile - tile_q * g.tiles_m : tile_q;
@@ -282,6 +282,24 @@ __global__ __launch_bounds__(64 * W) void igemm_small_kernel(const ConvArgs a, c
   }
 }
 
+template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT>
+__global__ __launch_bounds__(64 * W) void igemm_small_kernel(const ConvArgs a, const SmallGeom g) {
+  small_tile<IS_I8, TM, TN, W, U, NS, EXT>(a, g, (int)blockIdx.x);
+}
+
+// Two convs that do not read each other's output, in one launch: the first `tiles` workgroups run the first, the others the
+// second.  (The argument block is addressed by a uniform index: the same scalar loads as with one conv.)
+struct SmallPair {
+  ConvArgs a[2];
+  SmallGeom g[2];
+  int tiles;
+};
+template <bool IS_I8, int TM, int TN, int W, int U, int NS>
+__global__ __launch_bounds__(64 * W) void igemm_small_pair_kernel(const SmallPair p) {
+  const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
+  small_tile<IS_I8, TM, TN, W, U, NS, false>(p.a[second], p.g[second], (int)blockIdx.x - (second ? p.tiles : 0));
+}
+
 struct SmallTile {
   int tm, tn, w;
 };
@@ -305,7 +323,7 @@ int small_unit(const ConvArgs& a, bool is_i8, int v) {
 }
 
 template <bool IS_I8, int TM, int TN, int W, int U>
-hipError_t launch_small_one(const ConvArgs& a, hipStream_t st) {
+SmallGeom small_geom(const ConvArgs& a, ConvArgs& b) {
   SmallGeom g;
   g.tiles_m = (a.M + TM * 16 - 1) / (TM * 16);
   g.tiles_n = (a.K + TN * 16 - 1) / (TN * 16);
@@ -317,10 +335,27 @@ hipError_t launch_small_one(const ConvArgs& a, hipStream_t st) {
   g.per_wave = (g.units + W - 1) / W;
   g.fd_per_tap = make_fastdiv((uint32_t)g.per_tap);
   g.fd_s = make_fastdiv((uint32_t)a.S);
-  ConvArgs b = a;
+  b = a;
   b.fd_tiles_m = make_fastdiv((uint32_t)g.tiles_m);
   b.fd_tiles_n = make_fastdiv((uint32_t)g.tiles_n);
+  return g;
+}
+
+// second: NULL, or the conv that shares the launch
+template <bool IS_I8, int TM, int TN, int W, int U>
+hipError_t launch_small_one(const ConvArgs& a, const ConvArgs* second, hipStream_t st) {
   constexpr int NS = stages(U, TM, TN, W);
+  if (second) {
+    SmallPair p;
+    p.g[0] = small_geom<IS_I8, TM, TN, W, U>(a, p.a[0]);
+    p.g[1] = small_geom<IS_I8, TM, TN, W, U>(*second, p.a[1]);
+    p.tiles = p.g[0].tiles_m * p.g[0].tiles_n;
+    hipLaunchKernelGGL((igemm_small_pair_kernel<IS_I8, TM, TN, W, U, NS>), dim3(p.tiles + p.g[1].tiles_m * p.g[1].tiles_n), dim3(64 * W), 0, st, p);
+    return hipGetLastError();
+  }
+  ConvArgs b;
+  const SmallGeom g = small_geom<IS_I8, TM, TN, W, U>(a, b);
+  const int tiles = g.tiles_m * g.tiles_n;
   if (a.nseg)
     hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, true>), dim3(tiles), dim3(64 * W), 0, st, b, g);
   else
@@ -329,20 +364,20 @@ hipError_t launch_small_one(const ConvArgs& a, hipStream_t st) {
 }
 
 template <bool IS_I8, int TM, int TN, int W>
-hipError_t launch_small_units(const ConvArgs& a, int u, hipStream_t st) {
+hipError_t launch_small_units(const ConvArgs& a, const ConvArgs* second, int u, hipStream_t st) {
   if constexpr (unit_fits(4, TM, TN, W))
-    if (u == 4) return launch_small_one<IS_I8, TM, TN, W, 4>(a, st);
+    if (u == 4) return launch_small_one<IS_I8, TM, TN, W, 4>(a, second, st);
   if constexpr (unit_fits(2, TM, TN, W))
-    if (u == 2) return launch_small_one<IS_I8, TM, TN, W, 2>(a, st);
-  return launch_small_one<IS_I8, TM, TN, W, 1>(a, st);
+    if (u == 2) return launch_small_one<IS_I8, TM, TN, W, 2>(a, second, st);
+  return launch_small_one<IS_I8, TM, TN, W, 1>(a, second, st);
 }
 
 template <bool IS_I8>
-hipError_t launch_small_typed(const ConvArgs& a, int v, hipStream_t st) {
+hipError_t launch_small_typed(const ConvArgs& a, const ConvArgs* second, int v, hipStream_t st) {
   const int u = small_unit(a, IS_I8, v);
   switch (v) {
 #define RELAY_SMALL_CASE(i, tm, tn, w) \
-  case i: return launch_small_units<IS_I8, tm, tn, w>(a, u, st);
+  case i: return launch_small_units<IS_I8, tm, tn, w>(a, second, u, st);
     RELAY_SMALL_TILES(RELAY_SMALL_CASE)
     default: return hipErrorInvalidValue;
   }
@@ -406,7 +441,26 @@ void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, siz
 }
 
 hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int v, hipStream_t st) {
-  return is_i8 ? launch_small_typed<true>(a, v, st) : launch_small_typed<false>(a, v, st);
+  return is_i8 ? launch_small_typed<true>(a, nullptr, v, st) : launch_small_typed<false>(a, nullptr, v, st);
+}
+
+// Two convs share a launch where their tiles fit the chip at once, as many to a CU as its LDS takes.  ResNet-18's first convs
+// and shortcuts of a stage, graph-timed together against one after the other: at batch 1, 416 tiles, two to a CU 5.3 us
+// against 3.4 + 3.5, int8 4.9 against 3.6 + 3.0; at batch 7 368 tiles, one to a CU 11.2 against 7.1 + 3.9, int8 at batch 16 400 tiles,
+// one to a CU 10.6 against 6.4 + 4.0.
+bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int v) {
+  if (!conv_small_supported(a, is_i8, v) || !conv_small_supported(b, is_i8, v) || a.nseg || b.nseg) return false;
+  const int u = small_unit(a, is_i8, v);
+  if (small_unit(b, is_i8, v) != u) return false;
+  const SmallTile& t = kSmall[v];
+  const long lds = (long)t.w * stages(u, t.tm, t.tn, t.w) * (t.tm + t.tn) * u * 1024 + 2 * t.tn * 16 * 4;
+  long tiles = 0;
+  for (const ConvArgs* c : {&a, &b}) tiles += (long)((c->M + t.tm * 16 - 1) / (t.tm * 16)) * ((c->K + t.tn * 16 - 1) / (t.tn * 16));
+  return tiles <= 256 * (160 * 1024 / lds);
+}
+
+hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int v, hipStream_t st) {
+  return is_i8 ? launch_small_typed<true>(a, &b, v, st) : launch_small_typed<false>(a, &b, v, st);
 }
 
 }  // namespace relay

@@ -124,6 +124,9 @@ void fill_pool_args(ConvArgs& a);
 hipError_t launch_conv_igemm_dma_pool(const ConvArgs& a, bool is_i8, hipStream_t st);
 void igemm_dma_pool_kernel_name(bool is_i8, char* buf, size_t len);
 int igemm_dma_tile_count();
+// two independent convs as one launch: the tile both take by themselves, or -1
+int igemm_dma_pair_tile(const ConvArgs& a, const ConvArgs& b, bool is_i8);
+hipError_t launch_conv_igemm_dma_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int tile, hipStream_t st);
 void igemm_dma_kernel_name(const ConvArgs& a, bool is_i8, int tile, char* buf, size_t len);
 // The 3x3 / stride 1 / pad 1 kernel that stages the activations once per channel chunk (conv_halo.hip).
 bool conv_halo_supported(const ConvArgs& a, bool is_i8, int variant);
@@ -138,6 +141,8 @@ bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);
 int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup = false);
 int conv_small_variant_count();
 hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
+bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant);
+hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, hipStream_t st);
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
 // The persistent 3x3 / stride 1 / pad 1 kernel whose workgroups stream tile after tile (conv_stream.hip).
 bool conv_stream_supported(const ConvArgs& a, bool is_i8, int variant);
