@@ -969,7 +969,7 @@ relay_status relay_conv2d_maxpool_kernel_name(const relay_conv2d_desc* d, char* 
   relay::ConvArgs a;
   const relay_status st = check_pool_fusable(d, &ho, &wo, &a);
   if (st != RELAY_OK) return st;
-  relay::igemm_dma_pool_kernel_name(d->dtype == RELAY_I8, buf, len);
+  relay::igemm_dma_pool_kernel_name(a, d->dtype == RELAY_I8, buf, len);
   return RELAY_OK;
 }
 

@@ -79,16 +79,27 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
   static_assert(LPC <= TM * TN * KSW || (SK == 1 && !(TM + TN <= 4 && KP >= 4)), "the carried-MFMA schedule issues loads behind MFMAs only");
   constexpr int EP = WTN / 4 + 1;  // epilogue staging pitch (16-byte slots) of one pixel row, padded
   constexpr int XCH = SK == 2 ? (TM / 2) * TN * 4 * 64 : 0;  // slots a wave hands to its k-split partner
-  static_assert(NW * (32 * EP + XCH) <= NS * STAGE, "epilogue staging reuses the ring");
+  static_assert((POOL && NS == 1) || NW * (32 * EP + XCH) <= NS * STAGE, "epilogue staging reuses the ring");
   typedef typename Mma<IS_I8>::acc_t acc_t;
 
   constexpr int PDY = 15, PDX = 17;                 // conv patch of a pooled 7 x 8 block
   // the finished patch in LDS, [conv pixel][channel] in the output type; 8 bytes of padding per row
   // spread the accumulator layout's writes (32 lanes, 32 consecutive rows, one 4-channel group) over the banks
   constexpr int PPITCH = POOL ? BN * ES + 8 : 0;
+  // STEM (a pooled tile with NS == 1): the row-packed first layer at stride 2.  Its 255 conv outputs read 35 x 39 input
+  // pixels between them, 11 KB, of which the ring form fetches 64 bytes per output and filter row, 115 KB in pieces
+  // that straddle cache lines.  So the patch and all filter rows are loaded once and the operands come out of the
+  // patch: row (2 dy + r), 16-byte steps (fp16) or 8-byte steps (int8) along dx, conflict-free as they lie.
+  constexpr bool STEM = POOL && NS == 1;
+  constexpr int SR = 7;                               // most filter rows
+  constexpr int SPH = 2 * (PDY - 1) + SR;             // patch rows
+  constexpr int SPV = IS_I8 ? 13 : 20;                // 16-byte vectors of a patch row (int8: from 4 columns left of the block, a whole vector)
+  constexpr int SXB = (SPH * SPV + 63) / 64, SXL = (SXB + NW - 1) / NW;   // 1 KiB load blocks of the patch, ... per wave
+  constexpr int SWB = SR * (BN / 16), SWL = (SWB + NW - 1) / NW;          // ... of the filters
+  constexpr int RING = STEM ? ((SXB * 64 + SR * BN * BKV) * 16 > BM * PPITCH ? SXB * 64 + SR * BN * BKV : (BM * PPITCH + 15) / 16) : NS * STAGE;
   static_assert(!POOL || (BM >= PDY * PDX && SK == 1 && !EXT && !STOCH && WAVES_N == 1), "pooled tiles hold one 15 x 17 patch");
-  static_assert(BM * PPITCH <= NS * STAGE * 16, "the patch reuses the ring");
-  __shared__ uint4 ring[NS * STAGE];
+  static_assert(BM * PPITCH <= RING * 16, "the patch reuses the ring");
+  __shared__ uint4 ring[RING];
   __shared__ float pool_cst[POOL ? 2 * BN : 1];  // pooled tiles: the epilogue constants of the tile's channels
 
   // The arguments of the prologue are asked for here, so that their scalar loads leave as one batch with
@@ -137,7 +148,7 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
   int x_off[XL];        // byte offset of tap (0,0), channel 0 of the row's k-vector
   unsigned x_taps[XL];  // bit t set: tap t of this row lies inside the image
 #pragma unroll
-  for (int j = 0; j < XL; ++j) {
+  for (int j = 0; j < (STEM ? 0 : XL); ++j) {
     const int row = (wave * XL + j) * 16 + srow;
     const int kvl = sphys ^ lds_swizzle(row);
     int dp, q, dn, p, n;
@@ -170,7 +181,7 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
   }
   unsigned w_off[WL];
 #pragma unroll
-  for (int j = 0; j < WL; ++j) {
+  for (int j = 0; j < (STEM ? 0 : WL); ++j) {
     const int row = (wave * WL + j) * 16 + srow;
     const int kvl = sphys ^ lds_swizzle(row);
     const int ch = n0 + row;
@@ -266,6 +277,24 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
   RawLaneParams rawp;
   fetch_lane_params<IS_I8>(a, ech, rawp);
 
+  if constexpr (STEM) {
+    const int row0 = 2 * (2 * 7 * pool_i - 1), col0 = (2 * (2 * 8 * pool_j - 1) - (IS_I8 ? 2 : 0)) * 4 * ES;   // (bytes; a multiple of 16)
+#pragma unroll
+    for (int j = 0; j < SXL; ++j) {
+      const int blk = wave + j * NW, v = blk * 64 + lane;
+      const int pr = v / SPV, pb = col0 + (v - pr * SPV) * 16;
+      const bool ok = pr < SPH && (unsigned)(row0 + pr) < (unsigned)a.H && (unsigned)pb < (unsigned)(a.xs_h * ES);
+      if (blk < SXB)   // (uniform)
+        lds_dma16(rs_x, ring_base + (unsigned)blk * 1024u, ok ? (unsigned)((pool_n * a.xs_n + (row0 + pr) * a.xs_h) * ES + pb) : kOob);
+    }
+#pragma unroll
+    for (int j = 0; j < SWL; ++j) {
+      const int blk = wave + j * NW, r = blk / (BN / 16), row = (blk % (BN / 16)) * 16 + srow, ch = n0 + row;
+      if (blk < SWB && r < a.R)   // (uniform)
+        lds_dma16(rs_w, ring_base + (unsigned)(SXB + blk) * 1024u,
+                  ch < a.K ? (unsigned)((ch * a.Kp + r * a.C + (sphys ^ lds_swizzle(row)) * VE) * ES) : kOob);
+    }
+  }
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s) {
     if (!RUNOUT || is_live) {  // (uniform) a reduction shorter than the ring issues nothing for the chunks it does not have
@@ -383,7 +412,51 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
   };
   using std::integral_constant;
   const int klen = max(nchunks - kbeg, 0);
-  if constexpr (RUNOUT) {
+  if constexpr (STEM) {
+    wait_loads<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const char* xs[TM];   // this lane's pixel of each block, at filter row 0
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+      const int row = wm * WTM + tm * 32 + lrow, dy = min(row / PDX, PDY - 1), dx = row - (row / PDX) * PDX;   // (row 255 is no output)
+      xs[tm] = reinterpret_cast<const char*>(ring) + (2 * dy * SPV) * 16 + (IS_I8 ? dx * 8 + 8 : dx * 16) + lhalf * 16;
+    }
+    const uint4* ws = ring + SXB * 64;
+    uint4 wf[2][2][TN], xf[2][2][TM];
+    auto fetch = [&](int r, int b) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) wf[b][k][tn] = ws[r * (BN * BKV) + lds_slot(wn * WTN + tn * 32 + lrow, 2 * k + lhalf)];
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+          const char* at = xs[tm] + r * (SPV * 16) + k * 32;
+          if constexpr (IS_I8) {   // (8-byte aligned)
+            const uint2 lo = *reinterpret_cast<const uint2*>(at), hi = *reinterpret_cast<const uint2*>(at + 8);
+            xf[b][k][tm] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+          } else {
+            xf[b][k][tm] = *reinterpret_cast<const uint4*>(at);
+          }
+        }
+      }
+    };
+    auto multiply = [&](int b) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+          for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = Mma<IS_I8>::mma(wf[b][k][tn], xf[b][k][tm], acc[tn][tm]);
+    };
+    fetch(0, 0);
+    for (int r = 0; r < a.R; r += 2) {
+      if (r + 1 < a.R) fetch(r + 1, 1);
+      multiply(0);
+      if (r + 2 < a.R) fetch(r + 2, 0);
+      if (r + 1 < a.R) multiply(1);
+    }
+  } else if constexpr (RUNOUT) {
     // all but the last NS-1 chunks: one more chunk is issued per chunk consumed, NS-2 stay in flight
     for (int kc = NS - 1; kc < klen; ++kc) chunk(std::true_type{}, integral_constant<int, (NS - 2) * LPC>{});
     // the last NS-1 (or fewer) chunks: nothing is issued any more, the loads in flight run out
@@ -908,6 +981,25 @@ void fill_pool_args(ConvArgs& a) {
 // 256 x 64 tiles of four 64 x 64 waves with a two-stage ring: 41 KB of LDS, three workgroups per CU.
 // A workgroup's life is mostly latency (first loads, epilogue, pooling), so the third resident
 // workgroup buys more than a third ring stage (measured on the 7x7 first layer of ResNet-18).
+namespace {
+// The row-packed view of an NHWC4 image, one chunk per filter row, at stride 2: the form that stages the input patch once.
+// 7x7 / 2, 64 channels, 224 x 224: fp16 batch 32 26.0 -> 22.4 us, batch 1 6.9 -> 6.1; int8 batch 16 16.0 -> 13.8, batch 1 7.4 -> 6.1
+// (the reduction with its loads 7.5 K -> 4.5 K cycles of a workgroup; the two-stage ring with more stages was slower, its
+// loads are bound by the addresser, not by latency).  The pooling behind it (4.5 K cycles) is the larger part now.
+bool pool_stem(const ConvArgs& a, bool is_i8) {
+  return a.xs_w == 4 && a.C == BKV * (is_i8 ? 16 : 8) && a.S == 1 && a.sh == 2 && a.sw == 2 && a.R <= 7 && a.ph == 0 && a.pw == 0;
+}
+
+template <bool IS_I8>
+hipError_t launch_pool_one(const ConvArgs& a, int tiles, hipStream_t st) {
+  if (pool_stem(a, IS_I8))
+    hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, 4, 1, 2, 2, 1, 1, 1, false, false, true>), dim3(tiles), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, 4, 1, 2, 2, 2, 1, 1, false, false, true>), dim3(tiles), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_conv_igemm_dma_pool(const ConvArgs& a, bool is_i8, hipStream_t st) {
   constexpr int BN = 64;
   const int tiles_m = a.N * a.pool_tiles_img, tiles_n = (a.K + BN - 1) / BN;
@@ -915,17 +1007,11 @@ hipError_t launch_conv_igemm_dma_pool(const ConvArgs& a, bool is_i8, hipStream_t
   b.fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
   b.fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
   b.split = 1;
-  if (is_i8)
-    hipLaunchKernelGGL((igemm_dma_kernel<true, 4, 1, 2, 2, 2, 1, 1, false, false, true>), dim3(tiles_m * tiles_n), dim3(256), 0,
-                       st, b);
-  else
-    hipLaunchKernelGGL((igemm_dma_kernel<false, 4, 1, 2, 2, 2, 1, 1, false, false, true>), dim3(tiles_m * tiles_n), dim3(256), 0,
-                       st, b);
-  return hipGetLastError();
+  return is_i8 ? launch_pool_one<true>(b, tiles_m * tiles_n, st) : launch_pool_one<false>(b, tiles_m * tiles_n, st);
 }
 
-void igemm_dma_pool_kernel_name(bool is_i8, char* buf, size_t len) {
-  snprintf(buf, len, "igemm_dma_kernel<%s, 4, 1, 2, 2, 2, 1, 1, false, false, true>", is_i8 ? "true" : "false");
+void igemm_dma_pool_kernel_name(const ConvArgs& a, bool is_i8, char* buf, size_t len) {
+  snprintf(buf, len, "igemm_dma_kernel<%s, 4, 1, 2, 2, %d, 1, 1, false, false, true>", is_i8 ? "true" : "false", pool_stem(a, is_i8) ? 1 : 2);
 }
 
 int igemm_dma_tile_count() { return kNumTiles; }

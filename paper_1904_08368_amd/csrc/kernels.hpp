@@ -122,7 +122,7 @@ int igemm_dma_plan_split(const ConvArgs& a, bool is_i8, int tile, int want, size
 bool igemm_dma_pool_supported(const ConvArgs& a, bool is_i8);
 void fill_pool_args(ConvArgs& a);
 hipError_t launch_conv_igemm_dma_pool(const ConvArgs& a, bool is_i8, hipStream_t st);
-void igemm_dma_pool_kernel_name(bool is_i8, char* buf, size_t len);
+void igemm_dma_pool_kernel_name(const ConvArgs& a, bool is_i8, char* buf, size_t len);
 int igemm_dma_tile_count();
 // two independent convs as one launch: the tile both take by themselves, or -1
 int igemm_dma_pair_tile(const ConvArgs& a, const ConvArgs& b, bool is_i8);
