@@ -1170,7 +1170,7 @@ relay_status relay_fused_dense_bias_act(int32_t m, int32_t n, int32_t k, int32_t
   if (!aligned(x, 16) || !aligned(w, 16) || !aligned(y, dtype == RELAY_F16 ? 2 : 4))
     return fail(RELAY_ERR_ALIGN, "x and w must be 16-byte aligned");
   if (y == x || y == w) return fail(RELAY_ERR_UNSUPPORTED, "output must not alias an input");
-  if (dtype == RELAY_F16 && k % 32 == 0 && !relay::dense_splits_units(m, k)) {
+  if (dtype == RELAY_F16 && k % 32 == 0 && !relay::dense_splits_units(m, n, k)) {
     // dense is a 1x1 convolution over m one-pixel images; its weight rows are packed filter rows of pitch k, so the
     // MFMA kernels take them as they are.  Few rows: the kernel whose waves split the reduction (1024 -> 1000 at
     // m = 1, 11 and 32: 4.0, 11.4 and 5.4 us with a wave per output unit or 64 x 64 tiles, 3.0, 3.1 and 3.1 with it).

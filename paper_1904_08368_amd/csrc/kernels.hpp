@@ -169,7 +169,7 @@ bool dwpw_direct_supported(const DwPwArgs& a, int variant);
 int dwpw_direct_pick(const DwPwArgs& a);   // variant expected to beat the two separate launches and the chunked kernel, or -1
 hipError_t launch_dwpw_direct(const DwPwArgs& a, int variant, hipStream_t st);
 void dwpw_direct_kernel_name(const DwPwArgs& a, int variant, char* buf, size_t len);
-bool dense_splits_units(int m, int k);  // fp16: launch_dense is the faster kernel for this many rows
+bool dense_splits_units(int m, int n, int k);  // fp16: launch_dense is the faster kernel for these extents
 hipError_t launch_dense(int m, int n, int k, bool is_f16, const void* x, const void* w, const float* bias,
                         int act, void* y, hipStream_t st);
 hipError_t launch_pack_filters(const void* w_oihw, void* w_packed, int K, int Csrc, int C, int R, int S,

@@ -36,6 +36,28 @@ def test_dense_matches_the_oracle(G, m, n, k, act):
     assert O.max_rel_err(y.cpu().numpy(), want) <= TOL_F16
 
 
+# one row or more, units and reductions on both sides of the rule that gives a workgroup to an output unit; reductions the
+# small-tile kernel does not take
+@pytest.mark.parametrize("m,n,k", [(2, 1024, 2048), (2, 1032, 2048), (3, 24, 2048), (3, 24, 8192), (4, 40, 2056), (4, 2056, 2056), (1, 20, 40),
+                                   (9, 20, 40), (33, 12, 72)])
+def test_dense_on_both_sides_of_its_rules(G, m, n, k):
+    test_dense_matches_the_oracle(G, m, n, k, 1)
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 9, 36), (1, 30, 1028), (2, 9, 36), (8, 5, 260), (9, 30, 1028), (33, 12, 516)])
+def test_dense_fp32_matches_the_oracle(G, m, n, k):
+    from paper_1904_08368_amd import binding as B
+    g = np.random.default_rng(9150 + m + n + k)
+    x, w = g.standard_normal((m, k)).astype(np.float32), (g.standard_normal((n, k)) / np.sqrt(k)).astype(np.float32)
+    b = g.standard_normal(n).astype(np.float32)
+    y = torch.full((m, n), float("nan"), dtype=torch.float32, device=G.DEV)
+    B.relay_fused_dense_bias_act(m, n, k, B.RELAY_F32, G.up(x), G.up(w), G.up(b), 1, y)
+    torch.cuda.synchronize()
+    want = np.maximum(x.astype(np.float64) @ w.astype(np.float64).T + b, 0)
+    # at most 20 rounded sums in a row per lane, 6 across the lanes: under 26 half-units of the largest partial sum (below 4)
+    assert np.abs(y.cpu().numpy() - want).max() <= 26 * 2.0 ** -24 * 4
+
+
 def test_dense_takes_outputs_of_element_alignment(G):
     from paper_1904_08368_amd import binding as B
     g = np.random.default_rng(9200)
