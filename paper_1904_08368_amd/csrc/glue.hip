@@ -246,12 +246,13 @@ __global__ __launch_bounds__(256) void maxpool_fixed_kernel(const V* x, V* y, co
   }
 }
 
-// global average pool, NHWC fp16 -> [N][C] fp16, fp32 sum.  One workgroup per image and 8 channel vectors (128 bytes of
-// a pixel); 32 thread groups share the positions, their sums meet by lane exchanges and once in LDS.  Bound by
+// global average pool, NHWC fp16 -> [N][C] fp16, fp32 sum.  One workgroup per image and CVB channel vectors; 256 / CVB
+// thread groups share the positions, their sums meet by lane exchanges and once in LDS.  Bound by
 // latency: 49 positions of 512 channels took 3.6 us at batch 1 and 4.0 at batch 32 with one workgroup per image whose
-// four thread groups read 13 positions each in turn, 2.4 and 2.6 this way.
+// four thread groups read 13 positions each in turn, 2.4 and 2.6 with CVB = 8.
+template <int CVB>
 __global__ __launch_bounds__(256) void avgpool_f16_kernel(const half8* x, half8* y, int N, int CV, int HW, int groups) {
-  constexpr int CVB = 8, PARTS = 32;
+  constexpr int PARTS = 256 / CVB;
   __shared__ float part[3][CVB][8];
   const int n = blockIdx.x / groups, g = blockIdx.x - n * groups;
   const int cvl = threadIdx.x & (CVB - 1), pi = threadIdx.x / CVB, wave = threadIdx.x >> 6;
@@ -432,9 +433,21 @@ hipError_t launch_maxpool(bool is_i8, int N, int C, int H, int W, int R, int str
 
 hipError_t launch_avgpool_f16(int N, int C, int HW, const void* x, void* y, hipStream_t st) {
   const int cv = C / 8;
-  const int groups = (cv + 7) / 8;
-  hipLaunchKernelGGL(avgpool_f16_kernel, dim3((unsigned)(N * groups)), dim3(256), 0, st, (const half8*)x, (half8*)y, N, cv, HW,
-                     groups);
+  // 8 channel vectors (128 bytes of a pixel) a workgroup; more where that leaves thread groups without a position (2048
+  // channels, batch 32: 4 positions 3.0 us with 8, 2.1 with 64, 25 positions 3.3 with 8, 2.7 with 16); fewer where there are fewer
+  // and the positions go round more than once (8 channels, 3136 positions: 13.6 us with 8, 3.1 with 1).
+  int cvb = 8;
+  while (cvb < 64 && 256 / cvb > HW) cvb *= 2;
+  while (cvb > 1 && cvb / 2 >= cv && 256 / cvb < HW) cvb /= 2;
+  const int groups = (cv + cvb - 1) / cvb;
+  const dim3 grid((unsigned)(N * groups)), block(256);
+  switch (cvb) {
+#define RELAY_AVGPOOL_CASE(b) \
+  case b: hipLaunchKernelGGL((avgpool_f16_kernel<b>), grid, block, 0, st, (const half8*)x, (half8*)y, N, cv, HW, groups); break;
+    RELAY_AVGPOOL_CASE(1) RELAY_AVGPOOL_CASE(2) RELAY_AVGPOOL_CASE(4) RELAY_AVGPOOL_CASE(8)
+    RELAY_AVGPOOL_CASE(16) RELAY_AVGPOOL_CASE(32) RELAY_AVGPOOL_CASE(64)
+#undef RELAY_AVGPOOL_CASE
+  }
   return hipGetLastError();
 }
 

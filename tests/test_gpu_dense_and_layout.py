@@ -93,3 +93,9 @@ def test_average_pool_matches_the_mean(G, n, c, hw):
     torch.cuda.synchronize()
     want = x.astype(np.float64).mean(axis=1).astype(np.float16)
     assert O.max_rel_err(y.cpu().numpy(), want) <= TOL_F16
+
+
+@pytest.mark.parametrize("n,c,hw", [(2, 520, 3), (1, 264, 9), (2, 136, 25), (3, 64, 32), (2, 24, 100), (1, 16, 200), (3, 8, 300), (2, 8, 5)])
+def test_average_pool_with_every_number_of_channel_vectors(G, n, c, hw):
+    """64, 32, 16, 8, 4, 2 and 1 channel vectors a workgroup, and fewer vectors than that."""
+    test_average_pool_matches_the_mean(G, n, c, hw)
