@@ -95,9 +95,9 @@ __global__ __launch_bounds__(64) void nchw_to_nhwc_vec_kernel(const T* x, T* y, 
 }
 
 // [N][C<=4][H][W] -> [N][H+2ph][Wp][4], zeros in the border, in the slack columns and in the channels past C: one thread
-// per PX neighbouring output pixels (Wp is a multiple of 8), 16 bytes stored at a time.  Memory-bound in principle; with a
-// thread per pixel the two software divisions and a store of half the width cost more than the traffic:
-// 3 x 224 x 224, batch 32 (9.6 MB in, 13.7 MB out) 7.3 -> 6.1 us.
+// per PX neighbouring output pixels (Wp is a multiple of 8).  Memory-bound in principle; the two software divisions per
+// pixel cost more than the traffic: fp16, 3 x 224 x 224, batch 32 (9.6 MB in, 13.7 MB out) 7.3 -> 6.2 us with the host's constants,
+// 6.05 with two pixels and 16 bytes stored per thread.
 template <typename T, int PX>
 __global__ __launch_bounds__(256) void pack_input_nhwc4_kernel(const T* x, T* y, int C, int H, int W, int ph, int pw, int Hp, int Wp,
                                                                unsigned total, FastDiv fd_w, FastDiv fd_h) {
@@ -453,13 +453,20 @@ hipError_t launch_avgpool_f16(int N, int C, int HW, const void* x, void* y, hipS
 
 hipError_t launch_pack_input_nhwc4(int esize, int N, int C, int H, int W, int ph, int pw, int Wp, const void* x,
                                    void* y, hipStream_t st) {
-  const int Hp = H + 2 * ph, px = esize == 1 ? 4 : 2;
+  const int Hp = H + 2 * ph;
+  // Two pixels per thread pay on large fp16 images only (4 channels, 1.7 M pixels 7.5 -> 6.7 us; 8640 pixels 2.06 against 2.10);
+  // int8, whose stores are half as wide, is faster with one at all sizes but the largest of one channel (3 channels, 26 K pixels 2.03 us
+  // against 2.36 with two and 2.25 with four, 1.7 M pixels 5.1 against 5.7 and 5.3).
+  const int px = esize == 2 && (long)N * Hp * Wp >= 200 * 1000 ? 2 : 1;
   const unsigned total = (unsigned)((long)N * Hp * (Wp / px));
   const FastDiv fd_w = make_fastdiv((uint32_t)(Wp / px)), fd_h = make_fastdiv((uint32_t)Hp);
   const dim3 grid(blocks_for(total)), block(256);
   if (esize == 1)
-    hipLaunchKernelGGL((pack_input_nhwc4_kernel<int8_t, 4>), grid, block, 0, st, (const int8_t*)x, (int8_t*)y, C, H, W, ph, pw, Hp, Wp, total,
+    hipLaunchKernelGGL((pack_input_nhwc4_kernel<int8_t, 1>), grid, block, 0, st, (const int8_t*)x, (int8_t*)y, C, H, W, ph, pw, Hp, Wp, total,
                        fd_w, fd_h);
+  else if (px == 1)
+    hipLaunchKernelGGL((pack_input_nhwc4_kernel<uint16_t, 1>), grid, block, 0, st, (const uint16_t*)x, (uint16_t*)y, C, H, W, ph, pw, Hp, Wp,
+                       total, fd_w, fd_h);
   else
     hipLaunchKernelGGL((pack_input_nhwc4_kernel<uint16_t, 2>), grid, block, 0, st, (const uint16_t*)x, (uint16_t*)y, C, H, W, ph, pw, Hp, Wp,
                        total, fd_w, fd_h);

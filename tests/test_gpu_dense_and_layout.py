@@ -99,3 +99,21 @@ def test_average_pool_matches_the_mean(G, n, c, hw):
 def test_average_pool_with_every_number_of_channel_vectors(G, n, c, hw):
     """64, 32, 16, 8, 4, 2 and 1 channel vectors a workgroup, and fewer vectors than that."""
     test_average_pool_matches_the_mean(G, n, c, hw)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.int8])
+@pytest.mark.parametrize("n,c,h,w,r", [(1, 3, 5, 7, 7), (2, 4, 9, 16, 3), (3, 1, 1, 9, 1), (2, 2, 13, 2, 3), (4, 3, 226, 221, 7), (5, 4, 200, 202, 5)])
+def test_padded_copy_of_the_image(G, dtype, n, c, h, w, r):
+    """One and (fp16, the last two) two pixels per thread; every side of the image on and off a whole group of pixels."""
+    from paper_1904_08368_amd import binding as B
+    p = r // 2
+    dt = B.RELAY_F16 if dtype is np.float16 else B.RELAY_I8
+    x = np.random.default_rng(9500 + h).integers(-127, 128, (n, c, h, w)).astype(dtype)
+    d = B.conv_desc(n, c, h, w, 8, r, r, 1, p, dt, B.RELAY_NHWC4_PADDED, 0)
+    hp, wp = B.relay_nhwc4_padded_shape(d)
+    y = torch.full((n, hp, wp, 4), 7, dtype=torch.float16 if dtype is np.float16 else torch.int8, device=G.DEV)
+    B.relay_pack_input_nhwc4(d, G.up(x), y)
+    torch.cuda.synchronize()
+    want = np.zeros((n, hp, wp, 4), dtype)
+    want[:, p:p + h, p:p + w, :c] = x.transpose(0, 2, 3, 1)
+    assert np.array_equal(y.cpu().numpy(), want)
