@@ -84,6 +84,12 @@ def test_layout_conversion_at_vector_edges(G, dtype, n, c, h, w, pad):
     assert np.array_equal(got[..., :c], x.transpose(0, 2, 3, 1)) and not got[..., c:].any()
 
 
+@pytest.mark.parametrize("n,c,h,w,pad", [(3, 37, 47, 43, 11), (40, 129, 7, 11, 31), (1600, 16, 2, 4, 0), (1, 1, 113, 117, 15), (2100, 70, 1, 5, 10)])
+def test_int8_layout_conversion_in_pieces(G, n, c, h, w, pad):
+    """The sizes from which int8 takes whole vectors, with ragged pixel counts, channels and channel blocks."""
+    test_layout_conversion_at_vector_edges(G, np.int8, n, c, h, w, pad)
+
+
 @pytest.mark.parametrize("n,c,hw", [(1, 8, 1), (2, 24, 31), (1, 72, 33), (3, 512, 49), (1, 64, 500)])
 def test_average_pool_matches_the_mean(G, n, c, hw):
     from paper_1904_08368_amd import binding as B
