@@ -491,8 +491,8 @@ typedef struct relay_conv2d_call {
  * launch is worth): the workgroups of both share the grid.  Meant for a residual block's first conv and the shortcut
  * conv beside it.  Each member is a call of relay_fused_conv2d_bias_bn_relu (F16: bias fp32) or relay_qconv2d_requant (I8: bias
  * int32, bn_scale and bn_shift NULL) without a workspace, and is checked as by that call; both have one dtype.
- * Where no kernel takes the two together they run as two launches, one after the other.  Results: I8 bit for bit those
- * of the separate calls; F16 the same up to the grouping of a reduction's fp32 sums.
+ * Where no kernel takes the two together they run as two launches, one after the other.  Results: bit for bit those
+ * of the separate calls.
  * Errors: as the calls above, plus RELAY_ERR_DTYPE (two dtypes) and _UNSUPPORTED (a member's output is the other's output or
  * operand); nothing is launched on an error. */
 relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2d_call* second, void* hip_stream);

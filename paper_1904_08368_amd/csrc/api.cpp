@@ -866,7 +866,7 @@ static relay_status qconv_common(const relay_conv2d_desc* d, const int8_t* x, co
 
 // Which kernel runs the two: variant `small` of the small-tile kernel (the first conv's own choice), or tile `dma` of the
 // staged kernel (the choice of both); neither: two launches.  A conv that another kernel runs, or whose reduction is split
-// over workgroups, stays by itself.
+// over workgroups, stays by itself: the results are those of the separate launches bit for bit.
 struct PairPlan {
   int small = -1, dma = -1;
 };
@@ -874,11 +874,12 @@ static PairPlan pair_plan(const relay::ConvArgs& a, const relay::ConvArgs& b, bo
   PairPlan p;
   if (g_force_tile != -1 || g_force_split != 0 || a.xs_w != a.C || b.xs_w != b.C) return p;
   if (stream_choice(a, i8) >= 0 || stream_choice(b, i8) >= 0 || halo_choice(a, i8) >= 0 || halo_choice(b, i8) >= 0) return p;
-  const int v = small_choice(a, i8);
+  const int v = small_choice(a, i8), vb = small_choice(b, i8);
   if (v >= 0) {
-    if (relay::conv_small_pair_supported(a, b, i8, v)) p.small = v;
+    if (relay::conv_small_pair_supported(a, b, i8, v, vb)) p.small = v;
     return p;
   }
+  if (!i8 && vb >= 0) return p;  // (fp16: the staged kernel would group the second conv's sums differently)
   size_t cb, total;
   if (plan_split(a, i8, &cb, &total) > 1 || plan_split(b, i8, &cb, &total) > 1) return p;
   p.dma = relay::igemm_dma_pair_tile(a, b, i8);

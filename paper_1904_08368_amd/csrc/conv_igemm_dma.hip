@@ -950,6 +950,7 @@ bool igemm_dma_supported(const ConvArgs& a, bool is_i8) {
 // launches), and the one whose ring leaves room for a single workgroup per CU only where that is one round.  ResNet-18's
 // first convs and shortcuts of a stage at batch 32, together against one after the other: 784 tiles of 128 x 64 14.8 us
 // against 11.7 + 5.5, 392 12.4 against 10.5 + 5.2; int8 at batch 16 9.9 against 7.8 + 4.4, 64 x 64 tiles 8.2 against 6.3 + 3.7.
+// fp16 at batch 1: 32 tiles of 128 -> 256 7.0 against 8.5 for both, 256 -> 512 9.8 against 11.5.
 int igemm_dma_pair_tile(const ConvArgs& a, const ConvArgs& b, bool is_i8) {
   if (!igemm_dma_supported(a, is_i8) || !igemm_dma_supported(b, is_i8) || a.nseg || b.nseg || a.pool || b.pool ||
       a.round_mode == ROUND_STOCHASTIC || b.round_mode == ROUND_STOCHASTIC)

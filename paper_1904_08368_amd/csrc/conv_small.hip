@@ -410,10 +410,11 @@ int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup) {
   const int row = a.Kred * (is_i8 ? 1 : 2);  // reduction bytes of a tile row
   // fp16: splitting a reduction groups its sums anew.  The convs that other entry points run as part of a larger
   // launch with a promise of the same bits keep the staged kernels' order: a 1x1 conv (behind a depthwise conv),
-  // a conv with a max pool behind it, and a short strided conv whose window is centred on a 1x1 shortcut conv's
-  // (merged with it; 0.2 to 1.4 us of such a layer at batch 1).
-  const bool centred = a.sh > 1 && (a.R & 1) && (a.S & 1) && a.ph == a.R / 2 && a.pw == a.S / 2;
-  if (!is_i8 && !regroup && (a.R * a.S == 1 || igemm_dma_pool_supported(a, false) || (centred && row <= 1152))) return -1;
+  // a conv with a max pool behind it, and a strided conv whose window is centred on a 1x1 shortcut conv's (merged with it:
+  // such a launch is always the staged kernel's).  At batch 1 that costs 128 -> 256 at 28 x 28 / 2 5.8 us instead
+  // of 3.5 and 256 -> 512 at 14 x 14 / 2 8.4 instead of 4.0.
+  const bool centred = (a.sh > 1 || a.sw > 1) && (a.R & 1) && (a.S & 1) && a.ph == a.R / 2 && a.pw == a.S / 2;
+  if (!is_i8 && !regroup && (a.R * a.S == 1 || centred || igemm_dma_pool_supported(a, false))) return -1;
   const int per_tap = a.C * (is_i8 ? 1 : 2);
   const int chunk = per_tap % 256 == 0 ? 256 : per_tap % 128 == 0 ? 128 : 64;
   float best = 0.98f * (2.7f + (chunk == 256 ? 0.32f : 0.26f) * (float)(row / chunk));
@@ -445,11 +446,13 @@ hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int v, hipStream_t s
 }
 
 // Two convs share a launch where their tiles fit the chip at once, as many to a CU as its LDS takes.  ResNet-18's first convs
-// and shortcuts of a stage, graph-timed together against one after the other: at batch 1, 416 tiles, two to a CU 5.3 us
-// against 3.4 + 3.5, int8 4.9 against 3.6 + 3.0; at batch 7 368 tiles, one to a CU 11.2 against 7.1 + 3.9, int8 at batch 16 400 tiles,
-// one to a CU 10.6 against 6.4 + 4.0.
-bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int v) {
+// and shortcuts of a stage in int8, graph-timed together against one after the other: at batch 1, 416 tiles of 128 -> 256, two to a
+// CU, 4.8 us against 5.7, 256 -> 512 4.4 against 5.8; at batch 16 400 tiles, one to a CU, 10.6 against 10.4.
+// fp16: only with the groups of sums of the second conv's own launch (own: the variant it takes by itself, or -1), so
+// that both results are those of the separate launches bit for bit; the first conv runs its own variant.
+bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int v, int own) {
   if (!conv_small_supported(a, is_i8, v) || !conv_small_supported(b, is_i8, v) || a.nseg || b.nseg) return false;
+  if (!is_i8 && (own < 0 || kSmall[own].w != kSmall[v].w || small_unit(b, false, own) != small_unit(b, false, v))) return false;
   const int u = small_unit(a, is_i8, v);
   if (small_unit(b, is_i8, v) != u) return false;
   const SmallTile& t = kSmall[v];

@@ -141,7 +141,7 @@ bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);
 int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup = false);
 int conv_small_variant_count();
 hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
-bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant);
+bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, int own_of_b);
 hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, hipStream_t st);
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
 // The persistent 3x3 / stride 1 / pad 1 kernel whose workgroups stream tile after tile (conv_stream.hip).

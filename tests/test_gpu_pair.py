@@ -6,11 +6,15 @@ import torch
 import oracle as O
 from workloads import inputs
 
-# (n, c, h, w, k of the two, r of the two, stride): the small-tile kernel, the staged kernel's five tiles and pairs that stay two launches
-SHAPES = [(1, 128, 28, 28, (256, 256), (3, 1), 2), (1, 256, 14, 14, (512, 40), (3, 1), 2), (1, 64, 15, 13, (72, 136), (3, 1), 1),
-          (2, 64, 57, 55, (128, 128), (3, 1), 2), (32, 64, 56, 56, (128, 128), (3, 1), 2), (16, 128, 28, 28, (256, 256), (3, 1), 2),
-          (1, 32, 5, 3, (8, 24), (1, 3), 1), (3, 192, 28, 28, (256, 64), (3, 1), 2)]
-
+# n, c, h, w, k of the two, r of the two, stride; whether they share a launch in fp16 and in int8 (there at least 64 channels).  The staged
+# kernel's five tiles (4, 5, 9, 10, 15 of its list), the small-tile kernel, and pairs that stay two launches.
+SHAPES = [(1, 128, 28, 28, (256, 256), (3, 1), 2, True, True), (1, 256, 14, 14, (512, 40), (3, 1), 2, True, True),
+          (1, 64, 15, 13, (72, 136), (3, 1), 1, False, True), (2, 64, 57, 55, (128, 128), (3, 1), 2, True, True),
+          (32, 64, 56, 56, (128, 128), (3, 1), 2, True, True), (16, 128, 28, 28, (256, 256), (3, 1), 2, False, True),
+          (1, 32, 5, 3, (8, 24), (1, 3), 1, False, True), (3, 192, 28, 28, (256, 64), (3, 1), 2, True, True),
+          (1, 128, 28, 28, (64, 64), (1, 1), 1, True, True), (2, 256, 28, 28, (256, 256), (1, 1), 1, True, True),
+          (1, 64, 15, 13, (72, 136), (3, 3), 1, True, True), (1, 128, 14, 14, (128, 64), (3, 3), 1, True, True),
+          (2, 96, 9, 11, (40, 40), (1, 1), 1, True, False)]
 
 def _member(B, G, g, i8, n, c, h, w, k, r, st, relu, res):
     pad = r // 2
@@ -30,6 +34,16 @@ def _member(B, G, g, i8, n, c, h, w, k, r, st, relu, res):
     return d, wt, wp, p, y, dict(stride=(st, st), pad=(pad, pad), **p)
 
 
+def _oracle_points(g, x, wt, got, oargs, i8):
+    """The oracle's values at 200 sampled outputs and the corners, and where they are."""
+    pts = [tuple(int(g.integers(e)) for e in got.shape) for _ in range(200)] + [(0, 0, 0, 0), tuple(e - 1 for e in got.shape)]
+    acc = O.conv2d_points(x, wt, pts, oargs["stride"], oargs["pad"], integer=i8)
+    ks = [t[1] for t in pts]
+    if i8:
+        return pts, O.requant_points(np.asarray(acc) + oargs["bias"].astype(np.int64)[ks], out_rshift=oargs["out_rshift"], relu_flag=oargs["relu_flag"])
+    return pts, O.cast_f16(O.float_epilogue_points(acc, ks, scale=oargs["scale"], shift=oargs["shift"], relu_flag=oargs["relu_flag"]))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("i8", [False, True])
 @pytest.mark.parametrize("shape", SHAPES)
@@ -38,7 +52,7 @@ def test_pair_matches_oracle_and_separate_launches(shape, i8):
         pytest.skip("no GPU")
     from paper_1904_08368_amd import binding as B
     from tests import gpu_util as G
-    n, c, h, w, ks, rs, st = shape
+    n, c, h, w, ks, rs, st, *shared = shape
     if i8:
         c = max(c, 64)
     g = np.random.default_rng(inputs.BASE_SEED + 97000 + c + n)
@@ -51,6 +65,7 @@ def test_pair_matches_oracle_and_separate_launches(shape, i8):
                      (d, xd, wp, None, G.up(p["scale"]), G.up(p["shift"]), None, y))
         refs.append((wt, oargs))
         ys.append(y)
+    assert B.relay_conv2d_pair_fusable(calls[0][0], calls[1][0]) == shared[i8]
     B.relay_conv2d_pair(*calls)
     torch.cuda.synchronize()
     got = [G.from_nhwc(y, k) for y, k in zip(ys, ks)]
@@ -60,19 +75,24 @@ def test_pair_matches_oracle_and_separate_launches(shape, i8):
         (B.relay_qconv2d_requant if i8 else B.relay_fused_conv2d_bias_bn_relu)(*cl)
     torch.cuda.synchronize()
     for a, y, k, (wt, oargs) in zip(got, ys, ks, refs):
+        assert np.array_equal(a.view(np.uint8), G.from_nhwc(y, k).view(np.uint8))
+        pts, want = _oracle_points(g, x, wt, a, oargs, i8)
+        at = np.array([a[t] for t in pts])
         if i8:
-            assert np.array_equal(a, G.from_nhwc(y, k))
-        else:
-            assert O.max_rel_err(a, G.from_nhwc(y, k)) <= 2e-3     # the same fp16 result up to the grouping of fp32 sums: one rounding apart
-        if n <= 3:
-            assert np.array_equal(a, O.qconv2d_requant(x, wt, **oargs)) if i8 else O.max_rel_err(a, O.fused_conv2d(x, wt, out_dtype="f16", **oargs)) <= 1e-2
+            assert np.array_equal(at, want)
+        else:   # (one fp16 unit in the last place, or 1e-5 of the result's scale in the fp32 sums)
+            rms = float(np.sqrt(np.mean(a.astype(np.float64) ** 2)))
+            err = np.abs(at.astype(np.float64) - want.astype(np.float64)) / np.maximum(np.abs(want.astype(np.float64)), rms)
+            assert err.max() <= 2.0 ** -10 + 1e-5
 
 
 def test_pair_checks_and_rule_on_the_host():
     import ctypes as C
     from paper_1904_08368_amd import binding as B
     d = lambda n, c, hw, k, r, st=2, dt=B.RELAY_F16: B.conv_desc(n, c, hw, hw, k, r, r, st, r // 2, dt, B.RELAY_NHWC, 0)
-    assert B.relay_conv2d_pair_fusable(d(1, 128, 28, 256, 3), d(1, 128, 28, 256, 1))          # 416 small tiles, two to a CU
+    assert B.relay_conv2d_pair_fusable(d(1, 128, 28, 256, 3), d(1, 128, 28, 256, 1))          # 32 staged 64 x 64 tiles
+    assert not B.relay_conv2d_pair_fusable(d(1, 128, 28, 256, 3, 1), d(1, 128, 28, 256, 1, 1))  # fp16: small tiles would sum the second differently
+    assert B.relay_conv2d_pair_fusable(d(1, 128, 28, 256, 3, dt=B.RELAY_I8), d(1, 128, 28, 256, 1, dt=B.RELAY_I8))  # small tiles, two to a CU
     assert not B.relay_conv2d_pair_fusable(d(16, 256, 14, 512, 3, dt=B.RELAY_I8), d(16, 256, 14, 512, 1, dt=B.RELAY_I8))  # one to a CU: two rounds
     assert B.relay_conv2d_pair_fusable(d(32, 64, 56, 128, 3), d(32, 64, 56, 128, 1))          # the staged kernel's 128 x 64 tile
     assert not B.relay_conv2d_pair_fusable(d(32, 128, 28, 128, 3, 1), d(32, 128, 28, 128, 1, 1))   # the 3x3 kernel runs the first
