@@ -1093,6 +1093,13 @@ static int dwpw_direct_choice(const relay::DwPwArgs& a) {
   return relay::dwpw_direct_pick(a);
 }
 
+// which variant of the chunked kernel runs a block that the other leaves, or -1: also where the calling thread asks for
+// a variant of the other kernel that does not take the shape
+static int dwpw_chunked_choice(const relay::DwPwArgs& a) {
+  if (g_force_tile >= kDwPwDirectBase) return -1;
+  return g_force_tile >= kDwPwBase && g_force_tile < kSmallBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
+}
+
 relay_status relay_dwconv_pwconv_fusion_pays(const relay_conv2d_desc* dw, int32_t k, int32_t* pays) {
   if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
   relay::DwPwArgs a;
@@ -1121,7 +1128,7 @@ relay_status relay_dwconv_pwconv_kernel_name(const relay_conv2d_desc* dw, int32_
     relay::dwpw_direct_kernel_name(a, direct, buf, len);
     return RELAY_OK;
   }
-  const int variant = g_force_tile >= kDwPwBase && g_force_tile < kSmallBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
+  const int variant = dwpw_chunked_choice(a);
   if (variant < 0 || !relay::dwpw_supported(a, variant))
     return fail(RELAY_ERR_UNSUPPORTED, "no fused depthwise + 1x1 kernel variant takes this shape (variant %d)", variant);
   relay::dwpw_kernel_name(variant, buf, len);
@@ -1151,7 +1158,7 @@ relay_status relay_fused_dwconv_pwconv(const relay_conv2d_desc* dw, const void* 
   const int direct = dwpw_direct_choice(a);
   if (direct >= 0)
     return device_status(relay::launch_dwpw_direct(a, direct, static_cast<hipStream_t>(hip_stream)), "depthwise + 1x1 launch");
-  const int variant = g_force_tile >= kDwPwBase && g_force_tile < kSmallBase ? g_force_tile - kDwPwBase : relay::dwpw_any(a);
+  const int variant = dwpw_chunked_choice(a);
   if (variant < 0 || !relay::dwpw_supported(a, variant))
     return fail(RELAY_ERR_UNSUPPORTED, "no fused depthwise + 1x1 kernel variant takes this shape (variant %d)", variant);
   return device_status(relay::launch_dwpw(a, variant, static_cast<hipStream_t>(hip_stream)), "depthwise + 1x1 launch");

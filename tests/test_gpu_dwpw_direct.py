@@ -1,11 +1,11 @@
 """The one-launch depthwise + 1x1 kernel for layers of few pixels, against the oracle's two fused operators and bit for bit
 against the two separate launches: every variant at the edges of its tiles, and the rule that chooses them."""
+import ctypes as C
+
 import pytest
 import torch
 
 from tests.test_gpu_dwpw import _case
-
-pytestmark = pytest.mark.gpu
 
 # (most channels, ring stages of 32 channels) of every variant, in the library's order
 VARIANTS = ((256, 8), (256, 8), (256, 8), (1024, 32), (512, 16), (512, 16), (512, 8), (512, 6), (512, 4))
@@ -19,6 +19,7 @@ def G():
     return gpu_util
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("stride", [1, 2])
 @pytest.mark.parametrize("variant", range(len(VARIANTS)))
 def test_every_variant_at_the_edges(G, variant, stride):
@@ -30,7 +31,27 @@ def test_every_variant_at_the_edges(G, variant, stride):
         _case(G, 9000 + 100 * variant + 10 * stride + i, n, c, h, w, k, stride, variant=200 + variant, plain_tail=i % 2 == 1)
 
 
+def test_a_forced_variant_that_does_not_take_the_shape_is_an_error():
+    """(host only: every check runs before the first launch)"""
+    from paper_1904_08368_amd import binding as B
+    d = B.conv_desc(1, 384, 14, 14, 384, 3, 3, 1, 1, B.RELAY_F16, B.RELAY_NHWC, 0)     # no power of two of channels
+    assert "direct" not in B.relay_dwconv_pwconv_kernel_name(d, 512)
+    mem = [(1 << 30) + i * 4096 for i in range(4)]
+    for tile in (500, 508, 300):
+        B.relay_set_conv_tile(tile)
+        try:
+            if tile == 300:
+                d = B.conv_desc(1, 384, 14, 14, 384, 3, 3, 2, 1, B.RELAY_F16, B.RELAY_NHWC, 0)     # a variant for stride 1
+            with pytest.raises(B.RelayError) as e:
+                B.relay_dwconv_pwconv_kernel_name(d, 512)
+            assert e.value.status == 4
+            assert B.lib().relay_fused_dwconv_pwconv(C.byref(d), mem[0], mem[1], None, None, None, 512, 0, mem[2], None, None, None, mem[3], None) == 4
+        finally:
+            B.relay_set_conv_tile(-1)
+
+
 # the first and last sizes at which the rule takes a tile (the number of workgroups that fit the chip at once)
+@pytest.mark.gpu
 @pytest.mark.parametrize("n,c,h,w,k,stride,name", [
     (1, 64, 32, 32, 64, 1, "16, 2, 4, 8, 8"), (8, 64, 28, 28, 64, 1, "32, 4, 4, 8, 8"), (2, 512, 14, 14, 512, 1, "16, 2, 8, 16, 16"), (1, 1024, 7, 7, 1024, 1, "16, 1, 8, 32, 32"),
     (1, 512, 14, 14, 256, 1, "16, 1, 8, 32, 32"), (4, 512, 14, 14, 512, 1, "32, 2, 8, 16, 16"), (32, 512, 14, 14, 512, 1, "64, 8, 8, 4, 16"),
