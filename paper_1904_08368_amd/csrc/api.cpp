@@ -912,9 +912,13 @@ relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2
   if (first->d->dtype != second->d->dtype) return fail(RELAY_ERR_DTYPE, "the two convs have different dtypes");
   const bool i8 = first->d->dtype == RELAY_I8;
   if (!i8 && first->d->dtype != RELAY_F16) return fail(RELAY_ERR_DTYPE, "the paired conv2d takes F16 or I8");
-  if (first->y == second->y || first->y == second->x || second->y == first->x || (first->residual && first->residual == second->y) ||
-      (second->residual && second->residual == first->y))
-    return fail(RELAY_ERR_UNSUPPORTED, "one conv's output is the other's output or operand");
+  for (int i = 0; i < 2; ++i) {
+    const void* y = c[i]->y;
+    const relay_conv2d_call& o = *c[1 - i];
+    const void* others[] = {o.y, o.x, o.w_packed, o.bias, o.bn_scale, o.bn_shift, o.residual};
+    for (const void* p : others)
+      if (y && y == p) return fail(RELAY_ERR_UNSUPPORTED, "one conv's output is the other's output or operand");
+  }
   relay::ConvArgs m[2];
   for (int i = 0; i < 2; ++i) {
     if (i8 && (c[i]->bn_scale || c[i]->bn_shift)) return fail(RELAY_ERR_UNSUPPORTED, "the quantized epilogue has no float scale/shift");

@@ -101,11 +101,16 @@ def test_pair_checks_and_rule_on_the_host():
     assert e.value.status == 3
     F = 1 << 30
     dd = d(1, 64, 8, 64, 3)
-    call = lambda y, x=F, res=None: B.ConvCall(C.pointer(dd), x, F + 4096, None, None, None, res, 0, 0, y)
+    call = lambda y, x=F, res=None, **kw: B.ConvCall(*{**dict(d=C.pointer(dd), x=x, w=F + 4096, b=None, sc=None, sf=None, res=res, l=0, r=0, y=y), **kw}.values())
     run = lambda a, b: B.lib().relay_conv2d_pair(C.byref(a), C.byref(b), None)
     assert run(call(F + 8192), call(F + 8192)) == 4                   # one output
     assert run(call(F + 8192), call(F + 16384, x=F + 8192)) == 4      # the second reads the first's output
     assert run(call(F + 8192, res=F + 16384), call(F + 16384)) == 4
+    for kw in (dict(w=F + 8192), dict(b=F + 8192), dict(sc=F + 8192), dict(sf=F + 8192)):     # filters and constants, either way round
+        assert run(call(F + 8192), call(F + 16384, **kw)) == 4
+        assert b"one conv's output" in B.lib().relay_last_error()
+        assert run(call(F + 16384, **kw), call(F + 8192)) == 4
+        assert b"one conv's output" in B.lib().relay_last_error()
     assert run(call(F + 8200), call(F + 16384)) == 5                  # a member's own checks
     assert run(call(None), call(F + 16384)) == 1
     assert B.lib().relay_conv2d_pair(None, C.byref(call(F)), None) == 1
