@@ -21,7 +21,6 @@ __device__ __forceinline__ void lds_dma16(intx4 rsrc, unsigned lds_base, unsigne
                "s"(rsrc)
                : "memory", "m0");
 }
-#pragma clang diagnostic pop
 
 // Touches 64 memory lines of 128 bytes, one per lane, so that they are on their way to this XCD's L2: the four bytes
 // each lane fetches land in a 256-byte dump block of LDS and are never read.
