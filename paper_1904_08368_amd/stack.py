@@ -276,23 +276,23 @@ class FusedNet:
             if self.side_calls:
                 self.side = torch.cuda.Stream(device=self.dev)
         # two neighbouring calls that run as one launch: a block's first conv and the shortcut conv beside it
-        self.pair_first = set() if self.side_calls else self._independent_pairs()
+        self.pairs = {} if self.side_calls else self._independent_pairs()
         torch.cuda.synchronize(self.dev)
         self.graph = None
 
     def _independent_pairs(self):
-        """Indices i of calls that share a launch with call i + 1: plain convs over the same tensor, neither reading what the
+        """{i: (call i, call i + 1)} of calls that share a launch: plain convs over the same tensor, neither reading what the
         other writes, where the library takes the two together."""
-        first = set()
+        pairs = {}
         for i in range(len(self.calls) - 1):
             (f0, a0), (f1, a1) = self.calls[i], self.calls[i + 1]
-            if i - 1 in first or f0 is not f1 or f0 not in (B.relay_fused_conv2d_bias_bn_relu, B.relay_qconv2d_requant):
+            if i - 1 in pairs or f0 is not f1 or f0 not in (B.relay_fused_conv2d_bias_bn_relu, B.relay_qconv2d_requant):
                 continue
             y0, y1 = a0[7], a1[7]
             reads = [t for t in a0[1:7] + a1[1:7] if torch.is_tensor(t)]
             if a0[1] is a1[1] and not any(t is y0 or t is y1 for t in reads) and B.relay_conv2d_pair_fusable(a0[0], a1[0]):
-                first.add(i)
-        return first
+                pairs[i] = (self.calls[i], self.calls[i + 1])
+        return pairs
 
     def _pointwise_behind(self, ops, i, group_of, absorbed):
         """Index of the plain 1x1 / stride 1 conv that is the only reader of depthwise conv i's output, or None."""
@@ -470,11 +470,17 @@ class FusedNet:
         recorded BEFORE that first conv is enqueued, so the side stream waits only for the
         producer of the block input."""
         if not self.side_calls:
-            for i, (fn, args) in enumerate(self.calls):
-                if i in self.pair_first:
-                    B.relay_conv2d_pair(args, self.calls[i + 1][1])
-                elif i - 1 not in self.pair_first:
+            i = 0
+            while i < len(self.calls):
+                # (a pair only while both entries are those it was made of: `calls` may be edited, entries wrapped or cut off)
+                pair = self.pairs.get(i)
+                if pair and len(self.calls) > i + 1 and self.calls[i] is pair[0] and self.calls[i + 1] is pair[1]:
+                    B.relay_conv2d_pair(pair[0][1], pair[1][1])
+                    i += 2
+                else:
+                    fn, args = self.calls[i]
                     fn(*args)
+                    i += 1
             return
         main = torch.cuda.current_stream()
         pending = fork = None

@@ -1,0 +1,41 @@
+"""FusedNet.run over its list of calls: neighbouring convs in one launch, and a list that its owner has edited."""
+import pytest
+
+from paper_1904_08368_amd import binding as B
+from paper_1904_08368_amd.stack import FusedNet
+
+
+@pytest.fixture
+def net(monkeypatch):
+    """A network of four calls, of which the second and third share a launch, and what its runs called."""
+    done = []
+    net = FusedNet.__new__(FusedNet)
+    net.side_calls = set()
+    net.calls = [(lambda *a, i=i: done.append(i), ("args", i)) for i in range(4)]
+    net.pairs = {1: (net.calls[1], net.calls[2])}
+    monkeypatch.setattr(B, "relay_conv2d_pair", lambda a, b: done.append((a[1], b[1])))
+    return net, done
+
+
+def test_a_pair_is_one_call(net):
+    net, done = net
+    net.run()
+    assert done == [0, (1, 2), 3]
+
+
+def test_a_wrapped_entry_is_called(net):
+    net, done = net
+    net.calls[2] = (lambda *a: done.append("wrapped"), net.calls[2][1])
+    net.run()
+    assert done == [0, 1, "wrapped", 3]
+
+
+def test_a_shortened_list_and_one_with_an_entry_more(net):
+    net, done = net
+    net.calls = net.calls[:2]
+    net.run()
+    assert done == [0, 1]
+    done.clear()
+    net.calls.insert(0, (lambda *a: done.append("new"), ()))
+    net.run()
+    assert done == ["new", 0, 1]
