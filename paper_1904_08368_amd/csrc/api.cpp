@@ -1199,7 +1199,7 @@ relay_status relay_fused_dense_bias_act(int32_t m, int32_t n, int32_t k, int32_t
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int v = relay::conv_small_pick(a, false, true);
     if (v >= 0 && (n % 8 || aligned(y, 16)))  // (a row of y is stored in 16-byte pieces where n allows)
-      return device_status(relay::launch_conv_small(a, false, v, s), "dense launch");
+      return device_status(relay::launch_conv_small(a, false, v, s, true), "dense launch");
     if (m >= 16 && k % 64 == 0 && relay::igemm_dma_supported(a, false))
       return device_status(relay::launch_conv_igemm_dma(a, false, -1, s), "dense launch");
   }

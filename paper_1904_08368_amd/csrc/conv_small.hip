@@ -61,8 +61,9 @@ struct SmallGeom {
   FastDiv fd_per_tap, fd_s;      // division by per_tap and by S
 };
 
-// EXT: the instantiation that stores output channel segments.  bid: the workgroup's number among the tiles of this conv.
-template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT>
+// EXT: the instantiation that stores output channel segments.  NA: accumulators per block of a tile, used in turn (see small_runs).
+// bid: the workgroup's number among the tiles of this conv.
+template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT, int NA>
 __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g, const int bid) {
   constexpr int VE = IS_I8 ? 16 : 8;
   constexpr int ES = IS_I8 ? 1 : 2;
@@ -175,16 +176,19 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
       request_pixels(st);
     }
 
-  acc_t acc[TN][TM];
+  acc_t acc[NA][TN][TM];   // step u of a unit adds to accumulator (phase * U + u) % NA of its block
 #pragma unroll
-  for (int tn = 0; tn < TN; ++tn)
+  for (int i = 0; i < NA; ++i)
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
+    for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) acc[tn][tm][v] = 0;
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][tn][tm][v] = 0;
   // MFMA operand of lane l: row l % 16, k-vector l / 16 of a block's 64-byte step
   const int slot = lds_slot(lane & 15, lane >> 4);
-  auto mma_unit = [&](int st) {
+  using std::integral_constant;
+  auto mma_unit = [&](int st, auto phase) {
     const uint4* at = my + st * (LPU * 64) + slot;
     uint4 f[TN + TM][U];
 #pragma unroll
@@ -196,7 +200,10 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = Mma16<IS_I8>::mma(f[tn][u], f[TN + tm][u], acc[tn][tm]);
+        for (int tm = 0; tm < TM; ++tm) {
+          acc_t& c = acc[(decltype(phase)::value * U + u) % NA][tn][tm];
+          c = Mma16<IS_I8>::mma(f[tn][u], f[TN + tm][u], c);
+        }
   };
 
   auto constants = [&]() {  // of the tile's channels, to LDS
@@ -214,22 +221,62 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
   };
   // NS units are in flight.  The ring is the wave's own: no barrier, only its own loads are waited for.
   int st = 0;
-  for (; left > NS; --left) {
+  auto step = [&](auto phase) {  // one unit multiplied, another requested in its place
     wait_loads<(NS - 1) * LPU>();
-    mma_unit(st);
+    mma_unit(st, phase);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     request_filters(st);
     request_pixels(st);
     st = st + 1 == NS ? 0 : st + 1;
+    --left;
+  };
+  constexpr int TURN = NA > U ? NA / U : 1;  // units that go round the accumulators
+  static_assert(NA % U == 0 || U % NA == 0, "a turn is a whole number of units");
+  while (left > NS + TURN - 1) {
+    step(integral_constant<int, 0>{});
+    if constexpr (TURN > 1) step(integral_constant<int, 1>{});
+    if constexpr (TURN > 2) {
+      step(integral_constant<int, 2>{});
+      step(integral_constant<int, 3>{});
+    }
   }
-  for (; left > 0; --left) {
-    if (NS > 3 && left > 3) wait_loads<(NS > 3 ? 3 : 0) * LPU>();
-    else if (NS > 2 && left == 3) wait_loads<(NS > 2 ? 2 : 0) * LPU>();
-    else if (left == 2) wait_loads<LPU>();
-    else wait_loads<0>();
-    mma_unit(st);
-    st = st + 1 == NS ? 0 : st + 1;
+  if constexpr (TURN > 1)
+    if (left > NS) step(integral_constant<int, 0>{});
+  if constexpr (TURN > 2) {
+    if (left > NS) step(integral_constant<int, 1>{});
+    if (left > NS) step(integral_constant<int, 2>{});
   }
+  // the last NS (or fewer) units: the loads in flight run out
+  if constexpr (TURN == 1) {
+    for (; left > 0; --left) {
+      if (NS > 3 && left > 3) wait_loads<(NS > 3 ? 3 : 0) * LPU>();
+      else if (NS > 2 && left == 3) wait_loads<(NS > 2 ? 2 : 0) * LPU>();
+      else if (left == 2) wait_loads<LPU>();
+      else wait_loads<0>();
+      mma_unit(st, integral_constant<int, 0>{});
+      st = st + 1 == NS ? 0 : st + 1;
+    }
+  } else {
+    auto last = [&](auto l) {
+      if (left >= decltype(l)::value) {
+        wait_loads<(decltype(l)::value - 1) * LPU>();
+        mma_unit(st, l);
+        st = st + 1 == NS ? 0 : st + 1;
+      }
+    };
+    if constexpr (NS > 3) last(integral_constant<int, 4>{});
+    if constexpr (NS > 2) last(integral_constant<int, 3>{});
+    last(integral_constant<int, 2>{});
+    last(integral_constant<int, 1>{});
+  }
+#pragma unroll
+  for (int n = NA / 2; n > 0; n /= 2)
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) acc[i][tn][tm] += acc[i + n][tn][tm];
   constants();
 
   // ---- partial tiles to LDS.  Lane l of a block holds channels 4 (l / 16) .. + 3 of pixel l % 16.
@@ -238,7 +285,7 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
       my[(tm * TN + tn) * 64 + lane] =
-          make_uint4(as_u32(acc[tn][tm][0]), as_u32(acc[tn][tm][1]), as_u32(acc[tn][tm][2]), as_u32(acc[tn][tm][3]));
+          make_uint4(as_u32(acc[0][tn][tm][0]), as_u32(acc[0][tn][tm][1]), as_u32(acc[0][tn][tm][2]), as_u32(acc[0][tn][tm][3]));
   __syncthreads();
   const bool vec_ok = (a.K & 7) == 0;
   typedef typename std::conditional<IS_I8, int, float>::type sum_t;
@@ -282,9 +329,9 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
   }
 }
 
-template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT>
+template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT, int NA>
 __global__ __launch_bounds__(64 * W) void igemm_small_kernel(const ConvArgs a, const SmallGeom g) {
-  small_tile<IS_I8, TM, TN, W, U, NS, EXT>(a, g, (int)blockIdx.x);
+  small_tile<IS_I8, TM, TN, W, U, NS, EXT, NA>(a, g, (int)blockIdx.x);
 }
 
 // Two convs that do not read each other's output, in one launch: the first `tiles` workgroups run the first, the others the
@@ -297,7 +344,7 @@ struct SmallPair {
 template <bool IS_I8, int TM, int TN, int W, int U, int NS>
 __global__ __launch_bounds__(64 * W) void igemm_small_pair_kernel(const SmallPair p) {
   const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
-  small_tile<IS_I8, TM, TN, W, U, NS, false>(p.a[second], p.g[second], (int)blockIdx.x - (second ? p.tiles : 0));
+  small_tile<IS_I8, TM, TN, W, U, NS, false, 1>(p.a[second], p.g[second], (int)blockIdx.x - (second ? p.tiles : 0));
 }
 
 struct SmallTile {
@@ -312,6 +359,31 @@ constexpr int kNumSmall = sizeof(kSmall) / sizeof(kSmall[0]);
 constexpr bool unit_fits(int u, int tm, int tn, int w) { return 2 * (tm + tn) * u * w <= 156; }   // two stages in LDS
 constexpr int stages(int u, int tm, int tn, int w) {
   return (tm + tn) * u * w * 4 <= 64 ? 4 : (tm + tn) * u * w * 3 <= 80 ? 3 : 2;
+}
+
+// blocks of a tile that can have more than one accumulator (the 32 x 64 tile takes no layers from kernels of more runs)
+constexpr int kMostBlocks = 4;
+
+// Bytes of a reduction chunk of the staged kernels: the most that divide the channels of a tap.
+int staged_chunk(const ConvArgs& a, bool is_i8) {
+  const int per_tap = a.C * (is_i8 ? 1 : 2);
+  return per_tap % 256 == 0 ? 256 : per_tap % 128 == 0 ? 128 : 64;
+}
+
+// Accumulators per block of a tile, fp16: in how many runs a wave sums.  A run's rounding error grows with its length and a matrix
+// instruction rounds about four times, so four waves with one accumulator each are less exact than the kernels they
+// took the layer from where those sum in more runs: a reduction split over 5 to 16 workgroups (at most 32 tiles of 64 x 64, a
+// run for every 6 staged chunks), and a dense layer (lane by lane, in 64).  Rms error of the fp32 sums against 64 bits in 1e-7, the
+// other kernel / one accumulator / as chosen here: 512 channels 3 x 3 1.80 / 2.19 / 1.60, 1024 1.97 / 3.15 / 1.77, 192 channels 5 x 5 1.48 /
+// 2.21 / 1.30; dense, k = 1024 0.89 / 1.10 / 0.86, 4096 1.43 / 2.12 / 1.10, 9216 2.14 / 3.04 / 1.66.  Not split and not dense, one is
+// more exact than the kernel before (256 channels 3 x 3 2.36 / 1.55).
+// Two cost nothing measurable on a 16-pixel tile; four 0.3 to 0.6 us of a layer of 6 to 8.
+int small_runs(const ConvArgs& a, bool is_i8, int v, bool dense) {
+  if (is_i8 || kSmall[v].tm * kSmall[v].tn > kMostBlocks) return 1;
+  if (dense) return a.M >= 16 && a.Kred % 64 == 0 ? 1 : a.Kred <= 2048 ? 2 : 4;   // (of 16 rows and whole chunks: from the staged kernel)
+  const int chunks = a.Kred * 2 / staged_chunk(a, false);
+  const long tiles64 = (long)((a.M + 63) / 64) * ((a.K + 63) / 64);
+  return tiles64 > 32 || chunks < 30 ? 1 : chunks < 48 ? 2 : 4;
 }
 
 // steps per unit: the most that divide the channels of a tap
@@ -341,9 +413,22 @@ SmallGeom small_geom(const ConvArgs& a, ConvArgs& b) {
   return g;
 }
 
+template <bool IS_I8, int TM, int TN, int W, int U, int NA>
+hipError_t launch_small_alone(const ConvArgs& a, hipStream_t st) {
+  constexpr int NS = stages(U, TM, TN, W);
+  ConvArgs b;
+  const SmallGeom g = small_geom<IS_I8, TM, TN, W, U>(a, b);
+  const int tiles = g.tiles_m * g.tiles_n;
+  if (a.nseg)
+    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, true, NA>), dim3(tiles), dim3(64 * W), 0, st, b, g);
+  else
+    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, false, NA>), dim3(tiles), dim3(64 * W), 0, st, b, g);
+  return hipGetLastError();
+}
+
 // second: NULL, or the conv that shares the launch
 template <bool IS_I8, int TM, int TN, int W, int U>
-hipError_t launch_small_one(const ConvArgs& a, const ConvArgs* second, hipStream_t st) {
+hipError_t launch_small_one(const ConvArgs& a, const ConvArgs* second, int runs, hipStream_t st) {
   constexpr int NS = stages(U, TM, TN, W);
   if (second) {
     SmallPair p;
@@ -353,31 +438,28 @@ hipError_t launch_small_one(const ConvArgs& a, const ConvArgs* second, hipStream
     hipLaunchKernelGGL((igemm_small_pair_kernel<IS_I8, TM, TN, W, U, NS>), dim3(p.tiles + p.g[1].tiles_m * p.g[1].tiles_n), dim3(64 * W), 0, st, p);
     return hipGetLastError();
   }
-  ConvArgs b;
-  const SmallGeom g = small_geom<IS_I8, TM, TN, W, U>(a, b);
-  const int tiles = g.tiles_m * g.tiles_n;
-  if (a.nseg)
-    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, true>), dim3(tiles), dim3(64 * W), 0, st, b, g);
-  else
-    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, false>), dim3(tiles), dim3(64 * W), 0, st, b, g);
-  return hipGetLastError();
+  if constexpr (!IS_I8 && TM * TN <= kMostBlocks) {
+    if (runs == 4) return launch_small_alone<IS_I8, TM, TN, W, U, 4>(a, st);
+    if (runs == 2) return launch_small_alone<IS_I8, TM, TN, W, U, 2>(a, st);
+  }
+  return launch_small_alone<IS_I8, TM, TN, W, U, 1>(a, st);
 }
 
 template <bool IS_I8, int TM, int TN, int W>
-hipError_t launch_small_units(const ConvArgs& a, const ConvArgs* second, int u, hipStream_t st) {
+hipError_t launch_small_units(const ConvArgs& a, const ConvArgs* second, int u, int runs, hipStream_t st) {
   if constexpr (unit_fits(4, TM, TN, W))
-    if (u == 4) return launch_small_one<IS_I8, TM, TN, W, 4>(a, second, st);
+    if (u == 4) return launch_small_one<IS_I8, TM, TN, W, 4>(a, second, runs, st);
   if constexpr (unit_fits(2, TM, TN, W))
-    if (u == 2) return launch_small_one<IS_I8, TM, TN, W, 2>(a, second, st);
-  return launch_small_one<IS_I8, TM, TN, W, 1>(a, second, st);
+    if (u == 2) return launch_small_one<IS_I8, TM, TN, W, 2>(a, second, runs, st);
+  return launch_small_one<IS_I8, TM, TN, W, 1>(a, second, runs, st);
 }
 
 template <bool IS_I8>
-hipError_t launch_small_typed(const ConvArgs& a, const ConvArgs* second, int v, hipStream_t st) {
+hipError_t launch_small_typed(const ConvArgs& a, const ConvArgs* second, int v, int runs, hipStream_t st) {
   const int u = small_unit(a, IS_I8, v);
   switch (v) {
 #define RELAY_SMALL_CASE(i, tm, tn, w) \
-  case i: return launch_small_units<IS_I8, tm, tn, w>(a, second, u, st);
+  case i: return launch_small_units<IS_I8, tm, tn, w>(a, second, u, runs, st);
     RELAY_SMALL_TILES(RELAY_SMALL_CASE)
     default: return hipErrorInvalidValue;
   }
@@ -415,12 +497,12 @@ int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup) {
   // of 3.5 and 256 -> 512 at 14 x 14 / 2 8.4 instead of 4.0.
   const bool centred = (a.sh > 1 || a.sw > 1) && (a.R & 1) && (a.S & 1) && a.ph == a.R / 2 && a.pw == a.S / 2;
   if (!is_i8 && !regroup && (a.R * a.S == 1 || centred || igemm_dma_pool_supported(a, false))) return -1;
-  const int per_tap = a.C * (is_i8 ? 1 : 2);
-  const int chunk = per_tap % 256 == 0 ? 256 : per_tap % 128 == 0 ? 128 : 64;
+  const int chunk = staged_chunk(a, is_i8);
   float best = 0.98f * (2.7f + (chunk == 256 ? 0.32f : 0.26f) * (float)(row / chunk));
   int pick = -1;
   for (int v = 0; v < kNumSmall; ++v) {
     const SmallTile& t = kSmall[v];
+    if (regroup && a.M <= 16 && t.tm > 1) continue;   // (rows that no pixel fills)
     if ((t.w == 2) != (row <= 512) && t.tm + t.tn <= 3) continue;  // two waves where there is little to split (2.7 against 2.8 us)
     const long tiles = (long)((a.M + t.tm * 16 - 1) / (t.tm * 16)) * ((a.K + t.tn * 16 - 1) / (t.tn * 16));
     const int rounds = (int)((tiles + 255) / 256);
@@ -437,12 +519,13 @@ int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup) {
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {
   const SmallTile& t = kSmall[v];
   const int u = small_unit(a, is_i8, v);
-  snprintf(buf, len, "igemm_small_kernel<%s, %d, %d, %d, %d, %d, %s>", is_i8 ? "true" : "false", t.tm, t.tn, t.w, u,
-           stages(u, t.tm, t.tn, t.w), a.nseg ? "true" : "false");
+  snprintf(buf, len, "igemm_small_kernel<%s, %d, %d, %d, %d, %d, %s, %d>", is_i8 ? "true" : "false", t.tm, t.tn, t.w, u,
+           stages(u, t.tm, t.tn, t.w), a.nseg ? "true" : "false", small_runs(a, is_i8, v, false));
 }
 
-hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int v, hipStream_t st) {
-  return is_i8 ? launch_small_typed<true>(a, nullptr, v, st) : launch_small_typed<false>(a, nullptr, v, st);
+hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int v, hipStream_t st, bool dense) {
+  const int runs = small_runs(a, is_i8, v, dense);
+  return is_i8 ? launch_small_typed<true>(a, nullptr, v, runs, st) : launch_small_typed<false>(a, nullptr, v, runs, st);
 }
 
 // Two convs share a launch where their tiles fit the chip at once, as many to a CU as its LDS takes.  ResNet-18's first convs
@@ -452,7 +535,9 @@ hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int v, hipStream_t s
 // that both results are those of the separate launches bit for bit; the first conv runs its own variant.
 bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int v, int own) {
   if (!conv_small_supported(a, is_i8, v) || !conv_small_supported(b, is_i8, v) || a.nseg || b.nseg) return false;
-  if (!is_i8 && (own < 0 || kSmall[own].w != kSmall[v].w || small_unit(b, false, own) != small_unit(b, false, v))) return false;
+  if (!is_i8 && (own < 0 || kSmall[own].w != kSmall[v].w || small_unit(b, false, own) != small_unit(b, false, v) ||
+                 small_runs(a, false, v, false) > 1 || small_runs(b, false, own, false) > 1))   // (the paired kernel has one accumulator)
+    return false;
   const int u = small_unit(a, is_i8, v);
   if (small_unit(b, is_i8, v) != u) return false;
   const SmallTile& t = kSmall[v];
@@ -463,7 +548,7 @@ bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8,
 }
 
 hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int v, hipStream_t st) {
-  return is_i8 ? launch_small_typed<true>(a, &b, v, st) : launch_small_typed<false>(a, &b, v, st);
+  return is_i8 ? launch_small_typed<true>(a, &b, v, 1, st) : launch_small_typed<false>(a, &b, v, 1, st);
 }
 
 }  // namespace relay

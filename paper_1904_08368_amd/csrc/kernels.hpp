@@ -140,7 +140,7 @@ bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);
 // its fp16 sums may be grouped by wave whatever the layer's shape.
 int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup = false);
 int conv_small_variant_count();
-hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
+hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStream_t st, bool dense = false);
 bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, int own_of_b);
 hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, hipStream_t st);
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);

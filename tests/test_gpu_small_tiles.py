@@ -87,3 +87,63 @@ def test_the_library_takes_small_tiles_at_batch_1_only(G):
     for c, hw in ((64, 56), (128, 28), (256, 14), (512, 7)):
         assert "igemm_small_kernel" in B.relay_conv2d_kernel_name(d(1, c, hw, c, 3))
         assert "igemm_small_kernel" not in B.relay_conv2d_kernel_name(d(32, c, hw, c, 3))
+
+
+# The rounding error of the fp32 sums themselves: every pixel alike, so that one shift per channel takes the exact result off
+# at all of them, and what is left, scaled into fp16's range, is the error of the sum.
+SCALE = 2.0 ** 14
+
+
+def _sum_errors(exact, run):
+    """rms over the channels of (sum - exact result) against the rms of the results; run(shift) -> [.., channels] fp16."""
+    shift = (-exact * SCALE).astype(np.float32)
+    y = run(shift).astype(np.float64).reshape(-1, exact.size)
+    err = (y - (exact * SCALE + shift.astype(np.float64))) / SCALE
+    return float(np.sqrt((err ** 2).mean() / (exact ** 2).mean()))
+
+
+# (channels of all four numbers of steps per unit, reductions of 800 to 25600)
+@pytest.mark.parametrize("c,r", [(512, 3), (1024, 3), (128, 5), (1024, 5), (192, 5), (96, 5), (32, 5)])
+def test_sums_are_as_exact_as_in_the_kernels_this_one_takes_layers_from(G, c, r):
+    """Against the staged kernel, its reduction split over workgroups where the library would."""
+    from paper_1904_08368_amd import binding as B
+    g = np.random.default_rng(8300 + c + r)
+    k = 512
+    v, wt = g.standard_normal(c).astype(np.float16), (g.standard_normal((k, c, r, r)) * np.sqrt(2.0 / (c * r * r))).astype(np.float16)
+    x = np.ascontiguousarray(np.broadcast_to(v[None, :, None, None], (1, c, r + 2, r + 2)))
+    exact = np.einsum("kcrs,c->k", wt.astype(np.float64), v.astype(np.float64))
+    d = B.conv_desc(1, c, r + 2, r + 2, k, r, r, 1, 0, B.RELAY_F16, B.RELAY_NHWC, B.HAS_BN)
+    assert "igemm_small_kernel" in B.relay_conv2d_kernel_name(d)
+    errs = [_sum_errors(exact, lambda sf: G.run_conv_f16(x, wt, 1, 0, scale=np.full(k, SCALE, np.float32), shift=sf, tile=t, split=0).transpose(0, 2, 3, 1))
+            for t in (-1, -2)]
+    # (an rms over 512 channels of one random filter is known to about 3 %)
+    assert errs[0] <= 1.05 * errs[1], errs
+
+
+@pytest.mark.parametrize("m", [1, 8])
+@pytest.mark.parametrize("k", [1024, 4096, 9216, 3168])
+def test_dense_sums_are_as_exact_as_lane_by_lane(G, m, k):
+    """Against 64 lanes that each add up every 64th group of 8 products in fp32, and their sums in pairs."""
+    from paper_1904_08368_amd import binding as B
+    g = np.random.default_rng(8400 + k)
+    n = 512
+    v, w = (g.standard_normal(k) * 128).astype(np.float16), (g.standard_normal((n, k)) * 128 * np.sqrt(2.0 / k)).astype(np.float16)
+    prod = w.astype(np.float64) * v.astype(np.float64)
+    exact = prod.sum(1) / SCALE
+
+    def run(shift):
+        y = torch.full((m, n), float("nan"), dtype=torch.float16, device=G.DEV)
+        B.relay_fused_dense_bias_act(m, n, k, B.RELAY_F16, G.up(np.repeat(v[None], m, 0)), G.up(w), G.up(shift), 0, y)
+        torch.cuda.synchronize()
+        return y.cpu().numpy()
+
+    prod = np.concatenate([prod, np.zeros((n, -k % 512))], axis=1).reshape(n, -1, 64, 8)
+    lanes = np.zeros((n, 64), np.float32)
+    for i in range(prod.shape[1]):
+        for e in range(8):
+            lanes = (lanes + prod[:, i, :, e]).astype(np.float32)
+    while lanes.shape[1] > 1:
+        lanes = lanes[:, : lanes.shape[1] // 2] + lanes[:, lanes.shape[1] // 2:]
+    by_lane = float(np.sqrt(((lanes[:, 0] / SCALE - exact) ** 2).mean() / (exact ** 2).mean()))
+    err = _sum_errors(exact, run)
+    assert err <= 1.05 * by_lane, (err, by_lane)
