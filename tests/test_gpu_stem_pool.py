@@ -25,10 +25,7 @@ def test_stem_pool(case, i8):
     pd = (r - 1) // 2
     g = np.random.default_rng(inputs.BASE_SEED + 98000 + r * 10 + c)
     d = B.conv_desc(n, c, h, w, k, r, r, 2, pd, B.RELAY_I8 if i8 else B.RELAY_F16, B.RELAY_NHWC4_PADDED, 0)
-    if not B.relay_conv2d_maxpool_fusable(d):   # (an even filter changes the output size)
-        d = None
-        h, w = h + 2, w + 2
-        d = B.conv_desc(n, c, h, w, k, r, r, 2, pd, B.RELAY_I8 if i8 else B.RELAY_F16, B.RELAY_NHWC4_PADDED, 0)
+    assert B.relay_conv2d_maxpool_fusable(d)
     assert (", 1, 1, 1, false" in B.relay_conv2d_maxpool_kernel_name(d)) == (r <= 7)
     if i8:
         x = g.integers(-127, 128, (n, c, h, w)).astype(np.int8)
@@ -37,6 +34,8 @@ def test_stem_pool(case, i8):
         want = O.maxpool2d(O.qconv2d_requant(x, wt, stride=(2, 2), pad=(pd, pd), bias=b, out_rshift=9, relu_flag=False), 3, 2, 1).astype(np.int8)
         got = G.run_qconv_pool(x, wt, 2, pd, bias=b, rshift=9)
         assert np.array_equal(got, want)
+        if k % 16 == 0:   # (what the int8 pool by itself takes)
+            assert np.array_equal(got, G.run_qconv_pool(x, wt, 2, pd, bias=b, rshift=9, fused=False))
     else:
         op = nets.conv("c", "x", "y", c, k, r, 2, pd, bias=True, bn=True, relu=False)
         p = inputs.layer_params(op, 33, k + r, "f16")
@@ -44,5 +43,4 @@ def test_stem_pool(case, i8):
         got = G.run_conv_pool_f16(x, p["w"], 2, pd, bias=p["bias"], scale=p["scale"], shift=p["shift"])
         two = G.run_conv_pool_f16(x, p["w"], 2, pd, bias=p["bias"], scale=p["scale"], shift=p["shift"], fused=False)
         assert O.max_rel_err(got, _oracle_f16(x, p, 2, pd, False)) <= TOL_F16
-        if k > 16 and n * h * w >= 2048:   # (a smaller conv alone may regroup its sums)
-            assert O.max_rel_err(got, two) <= 2e-3
+        assert np.array_equal(got.view(np.uint16), two.view(np.uint16))
