@@ -40,7 +40,8 @@ class FusedNet:
         # launch where the library takes the shape; the conv's own output tensor then does not exist
         self.fuse_pool = fuse_pool and fused
         # fuse_dwpw: a depthwise conv whose only reader is a plain 1x1 conv runs with it as one launch where
-        # the library expects that to be faster; the depthwise output tensor then does not exist
+        # the library expects that to be faster (by layer and batch: nearly everywhere at batch 1, the first
+        # blocks and the 512-channel ones at batch 32); the depthwise output tensor then does not exist
         # ("always": wherever the library has a kernel for the shape, profitable or not)
         self.fuse_dwpw = fuse_dwpw if (fused and mode == "f16" and not fold_scale) else False
         # fused=False launches every elementwise operator behind a contraction as a kernel of its
@@ -469,6 +470,10 @@ class FusedNet:
         first conv: both read the block input, neither reads the other.  The fork event is
         recorded BEFORE that first conv is enqueued, so the side stream waits only for the
         producer of the block input."""
+        if not self.side_calls and not self.pairs:
+            for fn, args in self.calls:
+                fn(*args)
+            return
         if not self.side_calls:
             i = 0
             while i < len(self.calls):

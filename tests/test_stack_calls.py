@@ -23,6 +23,13 @@ def test_a_pair_is_one_call(net):
     assert done == [0, (1, 2), 3]
 
 
+def test_without_pairs_every_entry_is_called(net):
+    net, done = net
+    net.pairs = {}
+    net.run()
+    assert done == [0, 1, 2, 3]
+
+
 def test_a_wrapped_entry_is_called(net):
     net, done = net
     net.calls[2] = (lambda *a: done.append("wrapped"), net.calls[2][1])
