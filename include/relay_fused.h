@@ -77,7 +77,8 @@ relay_status relay_conv2d_out_shape(const relay_conv2d_desc* d, int32_t* ho, int
 /* Lowered operators work on inputs and outputs that are allocated beforehand (paper Section 3.3,
  * "Backends"); the same holds for scratch memory, which the caller sizes with this query and owns.
  * Bytes of device scratch the conv entry points (relay_fused_conv2d_bias_bn_relu, relay_qconv2d_requant*)
- * can use for this descriptor (d, bytes: host pointers); 0 for most layers.  A layer with few output tiles and a long reduction
+ * can use for this descriptor (d, bytes: host pointers); 0 for most layers.  (A layer of few tiles that the
+ * small-tile kernel runs needs none of it; the size stays what the split kernel would take, and is checked.)  A layer with few output tiles and a long reduction
  * (the deep layers at small batch) is split along the reduction over several workgroups per tile, which
  * leave partial sums and a per-tile arrival count in the workspace; the last to arrive adds the partials
  * in a fixed order (results do not depend on timing; int8 stays bit-exact) and runs the fused tail.
@@ -525,10 +526,12 @@ relay_status relay_nchw_to_nhwc(int32_t dtype, int32_t n, int32_t c, int32_t h, 
 /* Tuning aid (the library's stand-in for the schedule search of paper Section 4.1, "Lowering":
  * which schedule a fused operator gets is a choice made per shape and platform): force the
  * implicit-GEMM workgroup tile of later fp16 / int8 conv calls made BY THE CALLING THREAD
- * (0 .. count-1, largest first; 100 + v: variant v of the 3x3 stride-1 kernel; -1 = choose by
- * layer shape, the default; -2 = by layer shape without the 3x3 stride-1 kernel).  The setting is
+ * (0 .. count-1, largest first; 100 + v: variant v of the 3x3 stride-1 kernel, 200 + v of its persistent form,
+ * 400 + v of the kernel for few output tiles; 300 + v and 500 + v: see relay_fused_dwconv_pwconv; -1 = choose by
+ * layer shape, the default; -2 = by layer shape without the 3x3 stride-1 kernels and the one for few tiles).  The setting is
  * thread-local: other threads' calls are unaffected and nothing is shared between threads.
- * Results do not depend on the tile (int8: bit for bit). */
+ * A conv call that the variant does not take runs on the tile its shape chooses.
+ * Results do not depend on the tile (int8: bit for bit; F16: up to the grouping of a reduction's fp32 sums). */
 relay_status relay_set_conv_tile(int32_t tile);
 /* Tuning aid (paper Section 4.1, "Lowering", as above), thread-local like relay_set_conv_tile: workgroups per output tile of the calling
  * thread's later conv calls that are given a workspace (0 = choose by layer shape, the default;

@@ -133,7 +133,7 @@ def _ptr(t) -> Optional[int]:
 def _stream() -> Optional[int]:
     """Handle of torch's current stream on the current device (the default stream: None).  Asked of torch's runtime
     directly: building the Python stream object around the handle took 2.9 us of the 6.5 us of a call that launches one
-    kernel (a residual block of three eager launches 21.8 us, now 14.0)."""
+    kernel (a residual block of three eager launches 21.8 us, now 14.5 to 14.9)."""
     import torch
     if not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream or None

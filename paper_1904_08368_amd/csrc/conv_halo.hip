@@ -411,7 +411,7 @@ bool conv_halo_supported(const ConvArgs& a, bool is_i8, int v) {
 // stack 0.8 % faster), slower at 7 x 7 (a quarter of the flat positions are not pixels) and outside
 // the range of tile counts where both kernels get two workgroups per CU.
 int conv_halo_pick(const ConvArgs& a, bool is_i8) {
-  const bool thin = !is_i8 && a.C == 64 && a.K <= 64;   // (wide images too: 112 x 112 at batch 32 57.4 against 62.8 us, 224 x 224 216.8 against 226.5)
+  const bool thin = !is_i8 && a.C == 64 && a.K <= 64;   // (images up to 62 wide, the widest whose flat halo make_geom takes)
   // fp16, 512 and more channels at 7 x 7 and below: the 64 x 64 tile with 256-byte chunks (a third of the global->LDS
   // traffic of the implicit GEMM's 64 x 64 tile; 512 -> 512 at batch 32: 14.9 against 16.4 us)
   if (!is_i8 && a.C >= 512 && a.W <= 7 && chunk_planes(a, is_i8, 1) == 4 && conv_halo_supported(a, is_i8, 1)) {
