@@ -931,6 +931,22 @@ int pick_tile(const ConvArgs& a, bool is_i8) {
   return kp2 ? 10 : 5;
 }
 
+// What the tile pick_tile takes is estimated to cost a 3 x 3 layer, a + b n + c n k + e x k microseconds with k the chunks of the
+// reduction, x the tiles per CU and n the tiles of the CU that has most (fitted as the 3 x 3 kernel's estimates are); fp16, int8.
+struct DmaCost {
+  int tile;
+  float f[4], q[4];
+};
+constexpr DmaCost kCost[] = {
+    {0, {7.26f, 1.97f, 0.261f, 0.304f}, {3.71f, 5.50f, 0.348f, 0.188f}},
+    {4, {3.49f, 0.36f, 0.043f, 0.213f}, {4.89f, 0.00f, 0.056f, 0.187f}},
+    {5, {5.82f, 0.00f, 0.076f, 0.000f}, {4.10f, 0.00f, 0.121f, 0.000f}},
+    {9, {2.63f, 0.83f, 0.124f, 0.246f}, {3.43f, 0.34f, 0.137f, 0.246f}},
+    {10, {3.95f, 0.00f, 0.160f, 0.000f}, {4.26f, 0.00f, 0.133f, 0.015f}},
+    {14, {0.00f, 0.67f, 0.363f, 0.146f}, {0.00f, 0.67f, 0.363f, 0.146f}},   // (int8 only)
+    {15, {3.27f, 0.00f, 0.287f, 0.057f}, {3.69f, 0.00f, 0.280f, 0.036f}},
+};
+
 int resolve_tile(const ConvArgs& a, bool is_i8, int tile) {
   return tile_fits(a, is_i8, tile) ? tile : pick_tile(a, is_i8);
 }
@@ -1013,6 +1029,23 @@ hipError_t launch_conv_igemm_dma_pool(const ConvArgs& a, bool is_i8, hipStream_t
 
 void igemm_dma_pool_kernel_name(const ConvArgs& a, bool is_i8, char* buf, size_t len) {
   snprintf(buf, len, "igemm_dma_kernel<%s, 4, 1, 2, 2, %d, 1, 1, false, false, true>", is_i8 ? "true" : "false", pool_stem(a, is_i8) ? 1 : 2);
+}
+
+// int8 with the 256 x 128 tile's 384 tiles or more
+bool igemm_dma_wide(const ConvArgs& a) { return a.K > 64 && tiles_of(a, kTiles[0]) >= 384; }
+
+float igemm_dma_estimate(const ConvArgs& a, bool is_i8) {
+  const int tile = pick_tile(a, is_i8);
+  const DmaTile& t = kTiles[tile];
+  const long tiles = tiles_of(a, t);
+  const float n = (float)((tiles + 255) / 256), x = (float)tiles * (1.f / 256.f);
+  const float k = (float)(a.Kred / (t.kp * BKV * (is_i8 ? 16 : 8)));
+  for (const DmaCost& c : kCost)
+    if (c.tile == tile) {
+      const float(&p)[4] = is_i8 ? c.q : c.f;
+      return p[0] + n * (p[1] + p[2] * k) + p[3] * x * k;
+    }
+  return 0.f;   // (a tile no 3 x 3 layer of 64 channels takes: nothing is faster)
 }
 
 int igemm_dma_tile_count() { return kNumTiles; }

@@ -19,6 +19,7 @@
 // draws for its tile (about 125 KB/us).  Graph-timed at batch 1, staged kernels -> this one: fp16 64 -> 64 at
 // 56 x 56 5.1 -> 3.8 us, 128 at 28 x 28 5.9 -> 3.7, 256 at 14 x 14 8.2 -> 3.9, 512 at 7 x 7 9.5 -> 4.7; int8 5.0 -> 3.5,
 // 5.3 -> 3.5, 5.8 -> 3.3, 9.0 -> 3.9.
+#include <cmath>
 #include <cstdio>
 #include <type_traits>
 
@@ -485,10 +486,8 @@ bool conv_small_supported(const ConvArgs& a, bool is_i8, int v) {
 //           64 x 64 tile: 512 -> 512 at 7 x 7, batch 8: 14.0 us against 7.5 here; 256 -> 256 at 14 x 14, batch 8: 8.4
 //           against 7.0, batch 16: 8.8 against 12.6
 // A layer of more than 256 such tiles goes to the tall tiles of the staged kernels, which this one does not reach.
-int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup) {
-  if (!conv_small_supported(a, is_i8, 0)) return -1;
-  const long tiles64 = (long)((a.M + 63) / 64) * ((a.K + 63) / 64);
-  if (tiles64 > 256 || conv_halo_pick(a, is_i8) >= 0) return -1;
+namespace {
+int small_best(const ConvArgs& a, bool is_i8, bool regroup, float* us_out) {
   const int row = a.Kred * (is_i8 ? 1 : 2);  // reduction bytes of a tile row
   // fp16: splitting a reduction groups its sums anew.  The convs that other entry points run as part of a larger
   // launch with a promise of the same bits keep the staged kernels' order: a 1x1 conv (behind a depthwise conv),
@@ -513,7 +512,24 @@ int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup) {
       pick = v;
     }
   }
+  *us_out = best;
   return pick;
+}
+
+bool small_considered(const ConvArgs& a, bool is_i8) {
+  return conv_small_supported(a, is_i8, 0) && (long)((a.M + 63) / 64) * ((a.K + 63) / 64) <= 256;
+}
+}  // namespace
+
+int conv_small_pick(const ConvArgs& a, bool is_i8, bool regroup) {
+  float us;
+  if (!small_considered(a, is_i8) || conv_halo_pick(a, is_i8) >= 0) return -1;
+  return small_best(a, is_i8, regroup, &us);
+}
+
+float conv_small_estimate(const ConvArgs& a, bool is_i8) {
+  float us;
+  return small_considered(a, is_i8) && small_best(a, is_i8, false, &us) >= 0 ? us : INFINITY;
 }
 
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {

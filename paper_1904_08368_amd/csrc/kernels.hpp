@@ -130,6 +130,10 @@ hipError_t launch_conv_igemm_dma_pair(const ConvArgs& a, const ConvArgs& b, bool
 void igemm_dma_kernel_name(const ConvArgs& a, bool is_i8, int tile, char* buf, size_t len);
 // The 3x3 / stride 1 / pad 1 kernel that stages the activations once per channel chunk (conv_halo.hip).
 bool conv_halo_supported(const ConvArgs& a, bool is_i8, int variant);
+// microseconds a 3 x 3 layer is estimated to take there (infinite where the small-tile kernel does not take it)
+float igemm_dma_estimate(const ConvArgs& a, bool is_i8);
+float conv_small_estimate(const ConvArgs& a, bool is_i8);
+bool igemm_dma_wide(const ConvArgs& a);
 int conv_halo_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the layer to the implicit-GEMM kernel
 int conv_halo_variant_count();
 hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);

@@ -63,15 +63,16 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
 // every line of the filters that XCD is going to read, right behind their own first loads: with filters from HBM
 // 512 -> 512 at 7 x 7, batch 32 takes 16.5 us instead of 19.9, 256 -> 256 at 14 x 14 14.8 instead of 17.7.
 // first, bytes: the XCD's range of the packed filters; wid: this wave's place among the `waves` that take part; at
-// most MAX touches (8 KiB each).
+// most MAX touches (8 KiB each); returns how many this wave issued.
 template <int MAX>
-__device__ __forceinline__ void touch_filters(intx4 rs_w, unsigned dump_base, unsigned first, unsigned bytes, int wid, int waves, int lane) {
+__device__ __forceinline__ int touch_filters(intx4 rs_w, unsigned dump_base, unsigned first, unsigned bytes, int wid, int waves, int lane) {
 #pragma unroll
   for (int j = 0; j < MAX; ++j) {
     const unsigned at = (unsigned)(wid + j * waves) * 8192u;
-    if (at >= bytes) break;  // (uniform)
+    if (at >= bytes) return j;  // (uniform)
     l2_touch(rs_w, dump_base, first + at + (unsigned)lane * 128u);
   }
+  return MAX;
 }
 
 }  // namespace relay

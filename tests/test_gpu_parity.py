@@ -347,6 +347,23 @@ def test_int8_halo_kernel_bit_exact(G, shape, variant):
         assert np.array_equal(got, ref)
 
 
+# variant -> shapes at the edges of its tiles: 64-byte chunks on wide images; 16 x 16 outputs (whole, one short, one over, a
+# single pixel; one chunk and several); four waves that split the k-steps (one chunk and several)
+WIDE = [(2, 96, 9, 100, 72), (1, 64, 33, 63, 64), (3, 128, 1, 1, 40), (1, 256, 30, 30, 136)]
+SQUARE = [(1, 64, 16, 16, 64), (2, 64, 15, 33, 72), (1, 64, 17, 31, 37), (2, 128, 16, 48, 64), (1, 96, 1, 1, 40), (1, 64, 40, 100, 64)]
+QUARTERS = [(1, 128, 7, 7, 64), (2, 512, 7, 9, 72), (1, 256, 5, 20, 136), (3, 384, 1, 1, 24)]
+
+
+@pytest.mark.parametrize("variant,shape", [(4, s) for s in WIDE] + [(5, s) for s in SQUARE] + [(6, s) for s in QUARTERS])
+def test_fp16_halo_kernel_wide_square_and_split_tiles(G, variant, shape):
+    test_fp16_halo_kernel(G, shape, variant)
+
+
+@pytest.mark.parametrize("shape", [(2, 256, 7, 7, 64), (1, 512, 5, 20, 136), (1, 768, 1, 1, 24)])
+def test_int8_split_tile_bit_exact(G, shape):
+    test_int8_halo_kernel_bit_exact(G, shape, 6)
+
+
 # -------------------------------------------------------------------------- maximum sizes
 def _pattern(shape, dtype):
     """A cheap deterministic tensor (no generator can fill 2 GB in seconds): small signed values that
