@@ -311,12 +311,12 @@ static int stream_choice(const relay::ConvArgs& a, bool is_i8) {
   return g_force_tile == -1 ? relay::conv_stream_pick(a, is_i8) : -1;
 }
 
-// which halo variant runs this layer, or -1
+// which halo variant runs this layer, or -1.  (As below, a forced split of the reduction is the implicit GEMM's.)
 static int halo_choice(const relay::ConvArgs& a, bool is_i8) {
   if (stream_choice(a, is_i8) >= 0) return -1;
   if (g_force_tile >= kStreamBase) return -1;
   if (g_force_tile >= kHaloBase) return relay::conv_halo_supported(a, is_i8, g_force_tile - kHaloBase) ? g_force_tile - kHaloBase : -1;
-  return g_force_tile == -1 ? relay::conv_halo_pick(a, is_i8) : -1;
+  return g_force_tile == -1 && g_force_split == 0 ? relay::conv_halo_pick(a, is_i8) : -1;
 }
 
 // which variant of the small-tile kernel runs this layer, or -1.  A caller that forces a split of the reduction
