@@ -781,6 +781,166 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
   igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, STOCH, EXT, POOL>(a, (int)blockIdx.x);
 }
 
+// The tile for fp16 layers of few pixels whose sums other launches promise to the bit (strided convs centred on a shortcut's,
+// 1x1 convs): every output is still one accumulator fed in the order of the tiles above, but a workgroup owns 32 x 32
+// outputs, so that four times as many CUs take part, and its waves have one job each: four load (16 rows of one operand), the
+// fifth multiplies.  The fifth reads chunk kc from LDS while it multiplies chunk kc - 1, so a chunk takes the longest of its
+// loads (KP KB per wave), its LDS reads and its MFMAs (64 KP clocks) instead of their sum behind a barrier.
+template <int KP>
+__device__ __forceinline__ void igemm_dma_narrow_tile(const ConvArgs& a, const int bid) {
+  constexpr int VE = 8, ES = 2, CK = KP * BKV * VE, BM = 32, BN = 32, NS = KP == 4 ? 4 : (KP == 2 ? 6 : 8);
+  constexpr int PLANE = (BM + BN) * BKV, STAGE = KP * PLANE, KSTEPS = KP * 2;
+  constexpr int EP = BN / 4 + 1;
+  __shared__ uint4 ring[NS * STAGE + 32 * EP];
+  asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.res), "s"(a.y));
+  asm volatile("" ::"s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw), "s"(a.ph),
+               "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.xs_n), "s"(a.xs_h), "s"(a.xs_w), "s"(a.rcp_wo), "s"(a.rcp_ho),
+               "s"(a.tap_spread), "s"(a.param_vec), "s"(a.n_major), "s"(a.M), "s"(a.Kred), "s"(a.Kp), "s"(a.flags));
+  asm volatile("" ::"s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul),
+               "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul), "s"(a.fd_tiles_n.shift));
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
+  const int tile = xcd_remap(bid, tiles_m * tiles_n);
+  const int tile_q = (int)fast_div((uint32_t)tile, a.n_major ? a.fd_tiles_m : a.fd_tiles_n);
+  const int tile_n = a.n_major ? tile_q : tile - tile_q * tiles_n;
+  const int tile_m = a.n_major ? tile - tile_q * tiles_m : tile_q;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int nchunks = a.Kred / CK;
+
+  if (wave < 4) {  // (uniform) a loader: rows 16 (wave % 2) ... of the activations (waves 0, 1) or of the filters
+    const int srow = lane >> 2, row = (wave & 1) * 16 + srow, kvl = (lane & 3) ^ lds_swizzle(row);
+    const bool filters = wave >= 2;
+    unsigned off, taps;
+    intx4 rs = filters ? make_rsrc(a.w, (unsigned)((size_t)a.K * a.Kp * ES)) : make_rsrc(a.x, (unsigned)((size_t)a.N * a.xs_n * ES));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rs[i] = __builtin_amdgcn_readfirstlane(rs[i]);   // (in scalar registers, as the loads want it)
+    if (filters) {
+      off = (unsigned)(((n0 + row) * a.Kp + kvl * VE) * ES);
+      taps = n0 + row < a.K ? ~0u : 0u;
+    } else {
+      const int n_0 = (int)fast_div((uint32_t)m0, a.fd_howo), rem_0 = m0 - n_0 * (a.Ho * a.Wo);
+      const int p_0 = (int)fast_div((uint32_t)rem_0, a.fd_wo), q_0 = rem_0 - p_0 * a.Wo;
+      int dp, q, dn, p;
+      small_divmod(q_0 + row, a.Wo, a.rcp_wo, dp, q);
+      small_divmod(p_0 + dp, a.Ho, a.rcp_ho, dn, p);
+      const int ih0 = p * a.sh - a.ph, iw0 = q * a.sw - a.pw;
+      const int rlo = max(0, -ih0), rhi = min(a.R, a.H - ih0), clo = max(0, -iw0), chi = min(a.S, a.W - iw0);
+      const unsigned colbits = (unsigned)((1ull << max(chi, 0)) - 1ull) & ~(unsigned)((1ull << clo) - 1ull);
+      const unsigned rows = a.tap_spread & (unsigned)((1ull << (max(rhi, 0) * a.S)) - 1ull) & ~(unsigned)((1ull << (rlo * a.S)) - 1ull);
+      taps = m0 + row < a.M && rhi > rlo && chi > clo ? colbits * rows : 0u;   // (the column run at every valid row)
+      off = (unsigned)(((n_0 + dn) * a.xs_n + ih0 * a.xs_h + iw0 * a.xs_w + kvl * VE) * ES);
+    }
+    const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) uint4*)(&ring[0]) + (unsigned)wave * 1024u;
+    int tap = 0, r = 0, s = 0, c = 0, stage = 0;
+    auto issue = [&](int kc) {  // chunk kc (past the end: zeros nobody reads, so that the wait counts stay constants)
+      const unsigned delta = (unsigned)((filters ? kc * CK : r * a.xs_h + s * a.xs_w + c) * ES);
+      const bool live = kc < nchunks && ((taps >> (filters ? 0 : tap)) & 1u);
+#pragma unroll
+      for (int pl = 0; pl < KP; ++pl)
+        lds_dma16(rs, base + (unsigned)(stage * STAGE + pl * PLANE) * 16u, live ? off + delta + (unsigned)(pl * 64) : kOob);
+      stage = stage + 1 == NS ? 0 : stage + 1;
+      c += CK;
+      if (c == a.C) {
+        c = 0;
+        ++tap;
+        if (++s == a.S) {
+          s = 0;
+          ++r;
+        }
+      }
+    };
+    for (int kc = 0; kc < NS - 1; ++kc) issue(kc);
+    for (int kc = 0; kc < nchunks; ++kc) {
+      wait_loads<(NS - 2) * KP>();   // chunk kc has landed
+      __builtin_amdgcn_s_barrier();  // the multiplying wave has read chunk kc - 1, whose stage is filled next
+      issue(kc + NS - 1);
+    }
+    wait_loads<0>();   // (LDS is given back only when nothing writes to it any more)
+    return;
+  }
+
+  // ---- the multiplying wave.  Its constants and residuals come while the first chunks do.
+  constexpr int CG = BN / 8, PPI = 64 / CG, ITS = 32 / PPI;
+  const int ech = n0 + (lane % CG) * 8, epix = lane / CG;
+  const bool vec_ok = (a.K & 7) == 0, pre_res = (a.flags & F_RES) && vec_ok;
+  RawLaneParams rawp;
+  fetch_lane_params<false>(a, ech, rawp);
+  uint4 resv[ITS];
+  if (pre_res) {
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const int m = m0 + it * PPI + epix;
+      resv[it] = m < a.M && ech < a.K ? load_residual8<false>(a, m, ech) : make_uint4(0u, 0u, 0u, 0u);
+    }
+  }
+  typedef typename Mma<false>::acc_t acc_t;
+  acc_t acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0;
+  const int lrow = lane & 31, lhalf = lane >> 5;
+  const int slot = lds_slot(lrow, lhalf);   // (the other k-vectors of a plane: ^ 2)
+  uint4 wf[2][KSTEPS], xf[2][KSTEPS];
+  int stage = 0;
+  auto read = [&](int set) {
+    const uint4* st = ring + stage * STAGE;
+#pragma unroll
+    for (int k = 0; k < KSTEPS; ++k) {
+      xf[set][k] = st[(k >> 1) * PLANE + (slot ^ (2 * (k & 1)))];
+      wf[set][k] = st[(k >> 1) * PLANE + BM * BKV + (slot ^ (2 * (k & 1)))];
+    }
+    stage = stage + 1 == NS ? 0 : stage + 1;
+  };
+  auto multiply = [&](int set) {
+#pragma unroll
+    for (int k = 0; k < KSTEPS; ++k) acc = Mma<false>::mma(wf[set][k], xf[set][k], acc);
+    asm volatile("" : "+v"(acc));   // (not sunk below the next barrier)
+  };
+  auto meet = [&]() {  // everything read so far has arrived, the next chunk has landed
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  meet();
+  read(0);
+  int kc = 1;
+  for (; kc + 1 < nchunks; kc += 2) {
+    meet();
+    read(1);
+    multiply(0);
+    meet();
+    read(0);
+    multiply(1);
+  }
+  if (kc < nchunks) {
+    meet();
+    read(1);
+    multiply(0);
+    multiply(1);
+  } else {
+    multiply(0);
+  }
+  LaneParams lp;
+  finish_lane_params<false>(rawp, lp);
+  uint4* stg = ring + NS * STAGE;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    stg[lrow * EP + 2 * g + lhalf] = make_uint4(as_u32(acc[4 * g]), as_u32(acc[4 * g + 1]), as_u32(acc[4 * g + 2]), as_u32(acc[4 * g + 3]));
+  const OutLoc ol{nullptr, 0, 0, 0};
+#pragma unroll
+  for (int it = 0; it < ITS; ++it) {
+    const int pix = it * PPI + epix, m = m0 + pix;
+    const uint4 lo = stg[pix * EP + (lane % CG) * 2], hi = stg[pix * EP + (lane % CG) * 2 + 1];
+    const unsigned raw[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    if (m < a.M && ech < a.K) finish_store8<false, false>(a, raw, m, ech, lp, ol, vec_ok, pre_res, resv[it]);
+  }
+}
+
+template <int KP>
+__global__ __launch_bounds__(320) void igemm_dma_kernel_narrow(const ConvArgs a) {
+  igemm_dma_narrow_tile<KP>(a, (int)blockIdx.x);
+}
+
 // Two convs that do not read each other's output, in one launch: the first `tiles` workgroups run the first, the others the
 // second (see igemm_small_pair_kernel).
 struct DmaPair {
@@ -792,6 +952,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (NS * KP * (WAVES_M * TM + 
     void igemm_dma_pair_kernel(const DmaPair p) {
   const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
   igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, 1, false, false, false>(p.a[second], (int)blockIdx.x - (second ? p.tiles : 0));
+}
+
+template <int KP>
+__global__ __launch_bounds__(320) void igemm_dma_pair_kernel_narrow(const DmaPair p) {
+  const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
+  igemm_dma_narrow_tile<KP>(p.a[second], (int)blockIdx.x - (second ? p.tiles : 0));
 }
 
 struct DmaTile {
@@ -844,6 +1010,32 @@ hipError_t launch_one(const ConvArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, false, false>), dim3(tiles),
                        dim3(64 * WAVES_M * WAVES_N * SK), 0, st, b);
   return hipGetLastError();
+}
+
+// second: NULL, or the conv that shares the launch
+template <int KP>
+hipError_t launch_narrow_one(const ConvArgs& a, const ConvArgs* second, hipStream_t st) {
+  DmaPair p;
+  p.a[0] = a;
+  if (second) p.a[1] = *second;
+  int tiles[2] = {0, 0};
+  for (int i = 0; i < (second ? 2 : 1); ++i) {
+    const int tiles_m = (p.a[i].M + 31) / 32, tiles_n = (p.a[i].K + 31) / 32;
+    tiles[i] = tiles_m * tiles_n;
+    p.a[i].fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
+    p.a[i].fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
+  }
+  p.tiles = tiles[0];
+  if (second) hipLaunchKernelGGL(igemm_dma_pair_kernel_narrow<KP>, dim3(tiles[0] + tiles[1]), dim3(320), 0, st, p);
+  else hipLaunchKernelGGL(igemm_dma_kernel_narrow<KP>, dim3(tiles[0]), dim3(320), 0, st, p.a[0]);
+  return hipGetLastError();
+}
+
+int narrow_planes(const ConvArgs& a) { return a.C % 128 == 0 ? 4 : a.C % 64 == 0 ? 2 : 1; }
+
+hipError_t launch_narrow(const ConvArgs& a, const ConvArgs* second, hipStream_t st) {
+  const int kp = narrow_planes(a);
+  return kp == 4 ? launch_narrow_one<4>(a, second, st) : kp == 2 ? launch_narrow_one<2>(a, second, st) : launch_narrow_one<1>(a, second, st);
 }
 
 template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP>
@@ -905,8 +1097,13 @@ long tiles_of(const ConvArgs& a, const DmaTile& t) {
   return (long)((a.M + t.bm() - 1) / t.bm()) * ((a.K + t.bn() - 1) / t.bn());
 }
 
+constexpr int kNarrow = kNumTiles;   // the number of the 32 x 32 tile behind those of the list
+
+bool narrow_fits(const ConvArgs& a, bool is_i8) { return !is_i8 && !a.nseg && !a.pool && a.split <= 1 && a.Kred >= BKV * 8; }
+
 // can tile t run this layer?  (its chunk must divide the channel count)
 bool tile_fits(const ConvArgs& a, bool is_i8, int t) {
+  if (t == kNarrow) return narrow_fits(a, is_i8);
   return t >= 0 && t < kNumTiles && a.C % (kTiles[t].kp * BKV * (is_i8 ? 16 : 8)) == 0;
 }
 
@@ -947,8 +1144,19 @@ constexpr DmaCost kCost[] = {
     {15, {3.27f, 0.00f, 0.287f, 0.057f}, {3.69f, 0.00f, 0.280f, 0.036f}},
 };
 
+// The 32 x 32 tile where each CU gets at most one and the reduction is long enough for its loaders to run ahead (graph-timed, the
+// 64 x 64 tile / this one, stride 2: 256 -> 512 at 14 x 14 8.36 / 5.68 us, its 1x1 shortcut 3.62 / 3.21, 128 -> 256 at 28 x 28 5.77 /
+// 4.36, 64 -> 128 at 56 x 56 5.06 / 4.13, its shortcut of a single chunk 3.10 / 3.16; 1x1 1024 -> 1024 at 7 x 7 5.41 / 4.16; two
+// tiles to a CU 5.8 / 6.9).
+long narrow_tiles(const ConvArgs& a) { return (long)((a.M + 31) / 32) * ((a.K + 31) / 32); }
+bool narrow_better(const ConvArgs& a, bool is_i8) {
+  if (!narrow_fits(a, is_i8) || narrow_tiles(a) > 256) return false;
+  return a.C % 128 == 0 || (a.C % 64 == 0 && a.Kred / 64 >= 8);
+}
+
 int resolve_tile(const ConvArgs& a, bool is_i8, int tile) {
-  return tile_fits(a, is_i8, tile) ? tile : pick_tile(a, is_i8);
+  if (tile_fits(a, is_i8, tile)) return tile;
+  return narrow_better(a, is_i8) ? kNarrow : pick_tile(a, is_i8);
 }
 
 }  // namespace
@@ -978,6 +1186,8 @@ int igemm_dma_pair_tile(const ConvArgs& a, const ConvArgs& b, bool is_i8) {
 }
 
 hipError_t launch_conv_igemm_dma_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int tile, hipStream_t st) {
+  // (same sums, whatever the tile; ResNet-18's first convs and shortcuts of a stage, 64 x 64 tiles / 32 x 32: see narrow_better)
+  if (narrow_better(a, is_i8) && narrow_fits(b, is_i8) && narrow_tiles(b) <= 256 && narrow_planes(a) == narrow_planes(b)) return launch_narrow(a, &b, st);
   return is_i8 ? launch_pair_typed<true>(a, b, tile, st) : launch_pair_typed<false>(a, b, tile, st);
 }
 
@@ -1048,11 +1258,12 @@ float igemm_dma_estimate(const ConvArgs& a, bool is_i8) {
   return 0.f;   // (a tile no 3 x 3 layer of 64 channels takes: nothing is faster)
 }
 
-int igemm_dma_tile_count() { return kNumTiles; }
+int igemm_dma_tile_count() { return kNumTiles + 1; }
 
 int igemm_dma_plan_split(const ConvArgs& a, bool is_i8, int tile, int want, size_t* counter_bytes,
                          size_t* total_bytes) {
-  const DmaTile& t = kTiles[resolve_tile(a, is_i8, tile)];
+  // (the 32 x 32 tile is for layers that are not split: what the other tiles would do stays the answer)
+  const DmaTile& t = kTiles[tile != kNarrow && tile_fits(a, is_i8, tile) ? tile : pick_tile(a, is_i8)];
   const int tiles = (int)tiles_of(a, t);
   const int chunks = a.Kred / (t.kp * BKV * (is_i8 ? 16 : 8));
   int split = want;
@@ -1080,7 +1291,12 @@ int igemm_dma_plan_split(const ConvArgs& a, bool is_i8, int tile, int want, size
 }
 
 void igemm_dma_kernel_name(const ConvArgs& a, bool is_i8, int tile, char* buf, size_t len) {
-  const DmaTile& t = kTiles[resolve_tile(a, is_i8, tile)];
+  tile = resolve_tile(a, is_i8, tile);
+  if (tile == kNarrow) {
+    snprintf(buf, len, "igemm_dma_kernel_narrow<%d>", narrow_planes(a));
+    return;
+  }
+  const DmaTile& t = kTiles[tile];
   const bool stoch = is_i8 && a.round_mode == ROUND_STOCHASTIC;
   snprintf(buf, len, "igemm_dma_kernel<%s, %d, %d, %d, %d, %d, %d, %d, %s, %s, false>", is_i8 ? "true" : "false", t.waves_m,
            t.waves_n, t.tm, t.tn, t.ns, t.kp, t.sk, stoch ? "true" : "false",
@@ -1089,6 +1305,7 @@ void igemm_dma_kernel_name(const ConvArgs& a, bool is_i8, int tile, char* buf, s
 
 hipError_t launch_conv_igemm_dma(const ConvArgs& a, bool is_i8, int tile, hipStream_t st) {
   tile = resolve_tile(a, is_i8, tile);
+  if (tile == kNarrow) return launch_narrow(a, nullptr, st);
   if (!is_i8) return launch_typed<false, false>(a, tile, st);
   return a.round_mode == ROUND_STOCHASTIC ? launch_typed<true, true>(a, tile, st) : launch_typed<true, false>(a, tile, st);
 }

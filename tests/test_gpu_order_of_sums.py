@@ -53,3 +53,26 @@ def test_shortcuts_on_a_side_stream_give_the_same_bits(batch):
     assert outs[0].keys() == outs[1].keys()
     for name in outs[0]:
         assert np.array_equal(outs[0][name].view(np.uint16), outs[1][name].view(np.uint16)), name
+
+
+# 32 x 32 tiles: whole and ragged pixels and channels, one chunk and many, all three chunk lengths, a residual
+NARROW = [(1, 128, 13, 9, 64, 3, 2, False), (1, 256, 14, 14, 40, 3, 2, True), (2, 64, 15, 17, 100, 3, 2, False), (1, 384, 7, 7, 33, 1, 1, True),
+          (1, 128, 1, 1, 8, 1, 1, False), (3, 96, 9, 10, 72, 3, 1, True), (1, 32, 5, 5, 24, 5, 2, False)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", NARROW)
+def test_narrow_tile_gives_the_bits_of_the_other_tiles(shape):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_util as G
+    n, c, h, w, k, r, st, res = shape
+    g = np.random.default_rng(inputs.BASE_SEED + 98000 + c + k)
+    x = g.standard_normal((n, c, h, w)).astype(np.float16)
+    wt = (g.standard_normal((k, c, r, r)) * np.sqrt(2.0 / (c * r * r))).astype(np.float16)
+    ho, wo = ((e + 2 * (r // 2) - r) // st + 1 for e in (h, w))
+    p = dict(scale=(1 + 0.1 * g.standard_normal(k)).astype(np.float32), shift=(0.1 * g.standard_normal(k)).astype(np.float32), relu=True,
+             residual=g.standard_normal((n, k, ho, wo)).astype(np.float16) if res else None)
+    narrow = G.run_conv_f16(x, wt, st, r // 2, tile=18, **p)
+    other = G.run_conv_f16(x, wt, st, r // 2, tile=5, **p)
+    assert np.array_equal(narrow.view(np.uint16), other.view(np.uint16))
