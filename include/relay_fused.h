@@ -350,6 +350,23 @@ relay_status relay_qconv2d_requant_maxpool(const relay_conv2d_desc* d, const int
                                            const int32_t* bias, int32_t out_rshift, int8_t* y_pooled,
                                            void* hip_stream);
 
+/* A first-layer convolution primitive function read from the NCHW image as it arrives, with the 3x3 / stride 2 / pad 1 max
+ * pool behind it if y_pooled is given: relay_pack_input_nhwc4, relay_fused_conv2d_bias_bn_relu (or relay_qconv2d_requant) and
+ * relay_maxpool2d as ONE launch that keeps the padded copy in LDS (the layout alteration of paper Section 5.3 folded into
+ * the fused function of Section 4.1).  Results are those of the separate calls (F16: up to the grouping of the fp32 sums).
+ *   d         the conv over the PADDED image (RELAY_NHWC4_PADDED, F16 or I8, c <= 4), without HAS_RESIDUAL; I8 without
+ *             HAS_BN and with an even stride; a pooled F16 conv with RELU; w_packed as for that conv
+ *   x_nchw    the image [n, c, h, w], aligned to two elements
+ *   y         the conv outputs NHWC, or NULL if only the pooled ones are wanted
+ *   y_pooled  [n, (ho - 1) / 2 + 1, (wo - 1) / 2 + 1, k] NHWC, or NULL: no pool.  F16 16-byte, I8 8-byte aligned
+ * relay_image_conv2d_supported writes 1 if these calls take the descriptor (with a pool if `pooled`), else 0; the calls
+ * themselves then return an error and launch nothing. */
+relay_status relay_image_conv2d_supported(const relay_conv2d_desc* d, int32_t pooled, int32_t* supported);
+relay_status relay_fused_image_conv2d(const relay_conv2d_desc* d, const void* x_nchw, const void* w_packed, const float* bias,
+                                      const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream);
+relay_status relay_qimage_conv2d(const relay_conv2d_desc* d, const int8_t* x_nchw, const int8_t* w_packed, const int32_t* bias,
+                                 int32_t out_rshift, int8_t* y, int8_t* y_pooled, void* hip_stream);
+
 /* One UNFUSED elementwise operator on an fp16 NHWC tensor [n_pixels, c] (c % 8 == 0): what runs
  * behind a convolution when operator fusion is switched off.  The paper measures fusion against
  * such a pipeline (Section 5.2); this entry point exists for that comparison and for checking

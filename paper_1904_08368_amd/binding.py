@@ -88,6 +88,9 @@ SIGNATURES = {
     "relay_fold_scale_axis": [_I, _I, _I, _I, _I, _P, _P, _P, _P],
     "relay_fold_bias": [_I, _P, _P, _P, _P, _P],
     "relay_conv2d_maxpool_fusable": [_DP, C.POINTER(_I)],
+    "relay_image_conv2d_supported": [_DP, _I, C.POINTER(_I)],
+    "relay_fused_image_conv2d": [_DP, _P, _P, _P, _P, _P, _P, _P, _P],
+    "relay_qimage_conv2d": [_DP, _P, _P, _P, _I, _P, _P, _P],
     "relay_conv2d_maxpool_kernel_name": [_DP, C.c_char_p, _SZ],
     "relay_fused_conv2d_bn_relu_maxpool": [_DP, _P, _P, _P, _P, _P, _P, _P],
     "relay_qconv2d_requant_maxpool": [_DP, _P, _P, _P, _I, _P, _P],
@@ -231,6 +234,22 @@ def relay_fused_conv2d_bn_relu_maxpool(d: ConvDesc, x, w_packed, bias, bn_scale,
 def relay_qconv2d_requant_maxpool(d: ConvDesc, x, w_packed, bias, out_rshift: int, y_pooled) -> None:
     _check(lib().relay_qconv2d_requant_maxpool(C.byref(d), _ptr(x), _ptr(w_packed), _ptr(bias), out_rshift,
                                                _ptr(y_pooled), _stream()))
+
+
+def relay_image_conv2d_supported(d: ConvDesc, pooled: bool) -> bool:
+    ok = C.c_int32(0)
+    _check(lib().relay_image_conv2d_supported(C.byref(d), 1 if pooled else 0, C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_fused_image_conv2d(d: ConvDesc, x_nchw, w_packed, bias, bn_scale, bn_shift, y, y_pooled) -> None:
+    _check(lib().relay_fused_image_conv2d(C.byref(d), _ptr(x_nchw), _ptr(w_packed), _ptr(bias), _ptr(bn_scale), _ptr(bn_shift),
+                                          _ptr(y), _ptr(y_pooled), _stream()))
+
+
+def relay_qimage_conv2d(d: ConvDesc, x_nchw, w_packed, bias, out_rshift: int, y, y_pooled) -> None:
+    _check(lib().relay_qimage_conv2d(C.byref(d), _ptr(x_nchw), _ptr(w_packed), _ptr(bias), out_rshift, _ptr(y), _ptr(y_pooled),
+                                     _stream()))
 
 
 def relay_prepack_dwconv_weights(d: ConvDesc, w_crs, w_rsc) -> None:

@@ -1022,6 +1022,83 @@ relay_status relay_qconv2d_requant_maxpool(const relay_conv2d_desc* d, const int
                        "pooled qconv2d launch");
 }
 
+// ---- a first-layer conv on the NCHW image, with or without the max pool behind it, in one launch --------------
+
+static relay_status image_conv_args(const relay_conv2d_desc* d, bool pool, relay::StemArgs* out) {
+  int ho, wo;
+  relay_status st = check_geometry(d, &ho, &wo);
+  if (st != RELAY_OK) return st;
+  if (d->dtype != RELAY_F16 && d->dtype != RELAY_I8) return fail(RELAY_ERR_DTYPE, "the image conv2d takes F16 or I8");
+  if (d->layout != RELAY_NHWC4_PADDED)
+    return fail(RELAY_ERR_UNSUPPORTED, "the image conv2d is described as the conv over the padded image (layout RELAY_NHWC4_PADDED)");
+  if (d->flags & RELAY_HAS_RESIDUAL) return fail(RELAY_ERR_UNSUPPORTED, "the image conv2d has no residual operand");
+  const bool i8 = d->dtype == RELAY_I8;
+  if (i8 && (d->flags & RELAY_HAS_BN)) return fail(RELAY_ERR_UNSUPPORTED, "the quantized epilogue has no float scale/shift");
+  if ((st = check_igemm_support(d)) != RELAY_OK) return st;
+  relay::StemArgs g;
+  memset(&g, 0, sizeof(g));
+  g.a = make_args(d, ho, wo);   // (the packed filters are those of the padded image's conv)
+  g.a.C = d->c; g.a.S = d->s; g.a.H = d->h; g.a.W = d->w; g.a.ph = d->pad_h; g.a.pw = d->pad_w;
+  g.Hp = (ho - 1) / 2 + 1;
+  g.Wp = (wo - 1) / 2 + 1;
+  // (a float maximum that may meet a NaN follows rules of its own; behind a relu there is none)
+  if (pool && !i8 && !(d->flags & RELAY_RELU)) return fail(RELAY_ERR_UNSUPPORTED, "the pooled image conv2d needs a relu");
+  if (!relay::conv_stem_supported(g, i8, pool))
+    return fail(RELAY_ERR_UNSUPPORTED, "the image conv2d takes k %% 8 == 0 and windows of at most 8 columns (c=%d k=%d r=%d s=%d stride=%d)", d->c,
+                d->k, d->r, d->s, d->stride_w);
+  *out = g;
+  return RELAY_OK;
+}
+
+relay_status relay_image_conv2d_supported(const relay_conv2d_desc* d, int32_t pooled, int32_t* supported) {
+  if (!supported) return fail(RELAY_ERR_NULL, "supported is NULL");
+  relay::StemArgs g;
+  *supported = image_conv_args(d, pooled != 0, &g) == RELAY_OK ? 1 : 0;
+  return RELAY_OK;
+}
+
+static relay_status check_image_operands(const relay_conv2d_desc* d, const void* x, const void* w, const void* y, const void* yp) {
+  const int es = esize_of(d->dtype), out = es == 2 ? 16 : 8;
+  if (!x || !w || (!y && !yp)) return fail(RELAY_ERR_NULL, "x_nchw, w_packed and y or y_pooled are required");
+  if (x == y || x == yp || y == yp) return fail(RELAY_ERR_UNSUPPORTED, "an output must not alias the input or the other output");
+  if (!aligned(x, 2 * es) || !aligned(w, 16) || (y && !aligned(y, out)) || (yp && !aligned(yp, out)))
+    return fail(RELAY_ERR_ALIGN, "x_nchw must be aligned to two elements, w_packed to 16 bytes, outputs to 8 channels");
+  return RELAY_OK;
+}
+
+relay_status relay_fused_image_conv2d(const relay_conv2d_desc* d, const void* x_nchw, const void* w_packed, const float* bias,
+                                      const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream) {
+  relay::StemArgs g;
+  relay_status st = image_conv_args(d, y_pooled != nullptr, &g);
+  if (st != RELAY_OK) return st;
+  if (d->dtype != RELAY_F16) return fail(RELAY_ERR_DTYPE, "the float image conv2d takes F16");
+  if ((st = check_image_operands(d, x_nchw, w_packed, y, y_pooled)) != RELAY_OK) return st;
+  if ((st = check_optional(bias, d->flags & RELAY_HAS_BIAS, "bias")) != RELAY_OK) return st;
+  if ((st = check_optional(bn_scale, d->flags & RELAY_HAS_BN, "bn_scale")) != RELAY_OK) return st;
+  if ((st = check_optional(bn_shift, d->flags & RELAY_HAS_BN, "bn_shift")) != RELAY_OK) return st;
+  g.a.x = x_nchw; g.a.w = w_packed; g.a.y = y; g.a.bias = bias; g.a.scale = bn_scale; g.a.shift = bn_shift;
+  g.y_pooled = y_pooled;
+  return device_status(relay::launch_conv_stem(g, false, y_pooled != nullptr, static_cast<hipStream_t>(hip_stream)), "image conv2d launch");
+}
+
+relay_status relay_qimage_conv2d(const relay_conv2d_desc* d, const int8_t* x_nchw, const int8_t* w_packed, const int32_t* bias,
+                                 int32_t out_rshift, int8_t* y, int8_t* y_pooled, void* hip_stream) {
+  relay::StemArgs g;
+  relay_status st = image_conv_args(d, y_pooled != nullptr, &g);
+  if (st != RELAY_OK) return st;
+  if (d->dtype != RELAY_I8) return fail(RELAY_ERR_DTYPE, "the quantized image conv2d takes I8");
+  if ((st = check_image_operands(d, x_nchw, w_packed, y, y_pooled)) != RELAY_OK) return st;
+  if ((st = check_optional(bias, d->flags & RELAY_HAS_BIAS, "bias")) != RELAY_OK) return st;
+  if (out_rshift < 0 || out_rshift > 31) return fail(RELAY_ERR_UNSUPPORTED, "out_rshift=%d outside 0..31", out_rshift);
+  if (bias && !aligned(bias, 4)) return fail(RELAY_ERR_ALIGN, "bias must be 4-byte aligned");
+  g.a.x = x_nchw; g.a.w = w_packed; g.a.y = y; g.a.qbias = bias;
+  g.y_pooled = y_pooled;
+  g.a.rshift = out_rshift;
+  g.a.round_mode = RELAY_ROUND_NEAREST;
+  g.a.round_add = out_rshift == 0 ? 0 : 1 << (out_rshift - 1);
+  return device_status(relay::launch_conv_stem(g, true, y_pooled != nullptr, static_cast<hipStream_t>(hip_stream)), "quantized image conv2d launch");
+}
+
 static relay_status check_dw(const relay_conv2d_desc* d, int* ho, int* wo) {
   relay_status st = check_geometry(d, ho, wo);
   if (st != RELAY_OK) return st;

@@ -148,6 +148,19 @@ hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStre
 bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, int own_of_b);
 hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, hipStream_t st);
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
+// A first-layer conv on the NCHW image (conv_stem.hip): `a` describes the conv over the image itself (x: the image, H and W its
+// extents, C its channels, Kp the packed filters' pitch; y: the conv outputs or NULL); the rest is set by the launcher.
+struct StemArgs {
+  ConvArgs a;
+  void* y_pooled;
+  int Hp, Wp;                         // extents of the pooled outputs
+  int tiles, tiles_img, tiles_row;
+  int pitch, patch_bytes, cst_at;     // pixels of a patch row, bytes of the patch, where the constants stand in LDS
+  int pairs, per_row, items;          // loads of the patch: pixel pairs or pixels, per row, in all
+  FastDiv fd_img, fd_row, fd_items;
+};
+bool conv_stem_supported(const StemArgs& g, bool is_i8, bool pool);
+hipError_t launch_conv_stem(const StemArgs& g, bool is_i8, bool pool, hipStream_t st);
 // The persistent 3x3 / stride 1 / pad 1 kernel whose workgroups stream tile after tile (conv_stream.hip).
 bool conv_stream_supported(const ConvArgs& a, bool is_i8, int variant);
 int conv_stream_pick(const ConvArgs& a, bool is_i8);  // variant, or -1

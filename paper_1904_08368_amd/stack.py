@@ -278,8 +278,40 @@ class FusedNet:
                 self.side = torch.cuda.Stream(device=self.dev)
         # two neighbouring calls that run as one launch: a block's first conv and the shortcut conv beside it
         self.pairs = {} if self.side_calls else self._independent_pairs()
+        # the first calls as one launch on the image itself: its padded copy (not written then), the conv and the pool behind it
+        self.stem = self._image_stem()
         torch.cuda.synchronize(self.dev)
         self.graph = None
+
+    stem = None
+
+    def _image_stem(self):
+        """(calls, function, arguments) of the launch that stands for the first two or three calls -- the padded copy of the image,
+        the conv on it, its 3x3 / stride 2 / pad 1 max pool -- where the library takes them together, else None."""
+        if len(self.calls) < 2 or self.calls[0][0] is not B.relay_pack_input_nhwc4:
+            return None
+        (_, a0), (f1, a1) = self.calls[:2]
+        x, packed, d = a0[1], a0[2], a1[0]
+        if len(a1) < 2 or a1[1] is not packed:
+            return None
+        pooled_only = f1 in (B.relay_fused_conv2d_bn_relu_maxpool, B.relay_qconv2d_requant_maxpool)
+        if f1 is B.relay_fused_conv2d_bias_bn_relu and len(a1) == 9 and a1[6] is None and a1[8] is None:   # (no residual, no workspace)
+            fn, args, y = B.relay_fused_image_conv2d, (d, x) + tuple(a1[2:6]), a1[7]
+        elif f1 is B.relay_qconv2d_requant and a1[4] is None and a1[8] is None:
+            fn, args, y = B.relay_qimage_conv2d, (d, x, a1[2], a1[3], a1[6]), a1[7]
+        elif f1 is B.relay_fused_conv2d_bn_relu_maxpool:
+            fn, args, y = B.relay_fused_image_conv2d, (d, x) + tuple(a1[2:6]), None
+        elif f1 is B.relay_qconv2d_requant_maxpool:
+            fn, args, y = B.relay_qimage_conv2d, (d, x, a1[2], a1[3], a1[4]), None
+        else:
+            return None
+        if pooled_only:
+            return (self.calls[:2], fn, args + (None, a1[-1])) if B.relay_image_conv2d_supported(d, True) else None
+        if len(self.calls) > 2 and self.calls[2][0] is B.relay_maxpool2d:
+            a2 = self.calls[2][1]
+            if a2[5:8] == (3, 2, 1) and a2[8] is y and B.relay_image_conv2d_supported(d, True):
+                return self.calls[:3], fn, args + (y, a2[9])
+        return (self.calls[:2], fn, args + (y, None)) if B.relay_image_conv2d_supported(d, False) else None
 
     def _independent_pairs(self):
         """{i: (call i, call i + 1)} of calls that share a launch: plain convs over the same tensor, neither reading what the
@@ -470,12 +502,17 @@ class FusedNet:
         first conv: both read the block input, neither reads the other.  The fork event is
         recorded BEFORE that first conv is enqueued, so the side stream waits only for the
         producer of the block input."""
-        if not self.side_calls and not self.pairs:
+        if not self.side_calls and not self.pairs and not self.stem:
             for fn, args in self.calls:
                 fn(*args)
             return
+        done = 0
+        if self.stem and len(self.calls) >= len(self.stem[0]) and all(a is b for a, b in zip(self.stem[0], self.calls)) and \
+                not any(i <= len(self.stem[0]) for i in self.side_calls):
+            self.stem[1](*self.stem[2])
+            done = len(self.stem[0])
         if not self.side_calls:
-            i = 0
+            i = done
             while i < len(self.calls):
                 # (a pair only while both entries are those it was made of: `calls` may be edited, entries wrapped or cut off)
                 pair = self.pairs.get(i)
@@ -489,7 +526,7 @@ class FusedNet:
             return
         main = torch.cuda.current_stream()
         pending = fork = None
-        for i, (fn, args) in enumerate(self.calls):
+        for i, (fn, args) in enumerate(self.calls[done:], done):
             if i + 1 in self.side_calls:      # the next call runs beside this one
                 fork = torch.cuda.Event()
                 fork.record(main)

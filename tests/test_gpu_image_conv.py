@@ -1,0 +1,98 @@
+"""The first-layer conv on the NCHW image, with and without the max pool behind it, against the separate calls: the padded copy,
+the conv over it, the pool."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from workloads import inputs
+
+# n, c, h, w, k, window, stride, pad, pooled: large and small tiles, 64 and 32 channels and ragged ones, images that end inside a tile, odd
+# widths (single pixels) and even ones (pairs), one and two k-steps per filter row, a pooled map whose last windows stick out
+SHAPES = [(1, 3, 224, 224, 64, 7, 2, 3, True), (2, 3, 61, 45, 64, 7, 2, 3, True), (3, 3, 33, 70, 80, 7, 2, 3, True), (24, 3, 57, 64, 64, 7, 2, 3, True),
+          (1, 4, 84, 84, 32, 8, 4, 0, False), (40, 4, 84, 84, 32, 8, 4, 0, False), (1, 3, 17, 15, 64, 3, 1, 1, False), (3, 3, 130, 97, 64, 3, 1, 1, False),
+          (2, 3, 163, 206, 32, 3, 2, 1, False), (30, 3, 64, 50, 32, 3, 2, 1, False), (1, 1, 5, 4, 8, 5, 2, 2, False), (2, 2, 1, 2, 48, 7, 2, 3, True)]
+
+
+def _calls(G, B, i8, x, wt, p, d, ho, wo, pooled):
+    """The separate calls' conv output and pooled output (NHWC, on the device) and the operands."""
+    n, c, k = x.shape[0], x.shape[1], wt.shape[0]
+    dt, tdt = (B.RELAY_I8, torch.int8) if i8 else (B.RELAY_F16, torch.float16)
+    hp, wp = B.relay_nhwc4_padded_shape(d)
+    xd, packed = G.up(x), torch.empty((n, hp, wp, 4), dtype=tdt, device=G.DEV)
+    w = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device=G.DEV)
+    B.relay_prepack_conv2d_weights(d, G.up(wt), c, w)
+    y = torch.zeros((n, ho, wo, k), dtype=tdt, device=G.DEV)
+    yp = torch.zeros((n, (ho - 1) // 2 + 1, (wo - 1) // 2 + 1, k), dtype=tdt, device=G.DEV)
+    B.relay_pack_input_nhwc4(d, xd, packed)
+    if i8:
+        B.relay_qconv2d_requant(d, packed, w, p["b"], None, 0, p["s"], y, None)
+    else:
+        B.relay_fused_conv2d_bias_bn_relu(d, packed, w, p["b"], p["sc"], p["sf"], None, y, None)
+    if pooled:
+        B.relay_maxpool2d(dt, n, k, ho, wo, 3, 2, 1, y, yp)
+    return xd, w, y, yp
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("i8", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_image_conv_gives_the_results_of_the_separate_calls(shape, i8):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1904_08368_amd import binding as B
+    from tests import gpu_util as G
+    n, c, h, w, k, r, st, pad, pooled = shape
+    g = np.random.default_rng(inputs.BASE_SEED + 99000 + h + k)
+    if i8:
+        x, wt = (g.integers(-127, 128, e).astype(np.int8) for e in ((n, c, h, w), (k, c, r, r)))
+        p = dict(b=G.up(g.integers(-4000, 4000, k).astype(np.int32)), s=9)
+        flags = B.HAS_BIAS | B.RELU
+    else:
+        x = g.standard_normal((n, c, h, w)).astype(np.float16)
+        wt = (g.standard_normal((k, c, r, r)) * np.sqrt(2.0 / (c * r * r))).astype(np.float16)
+        p = {a: G.up((m + 0.1 * g.standard_normal(k)).astype(np.float32)) for a, m in (("b", 0), ("sc", 1), ("sf", 0))}
+        flags = B.HAS_BIAS | B.HAS_BN | B.RELU
+    d = B.conv_desc(n, c, h, w, k, r, r, st, pad, B.RELAY_I8 if i8 else B.RELAY_F16, B.RELAY_NHWC4_PADDED, flags)
+    assert B.relay_image_conv2d_supported(d, pooled) == (not i8 or st % 2 == 0)
+    if i8 and st % 2:
+        return
+    ho, wo = B.relay_conv2d_out_shape(d)
+    xd, wp, y0, yp0 = _calls(G, B, i8, x, wt, p, d, ho, wo, pooled)
+    for conv_too in ((True, False) if pooled else (True,)):
+        y, yp = torch.full_like(y0, 77), torch.full_like(yp0, 77)
+        outs = (y if conv_too else None, yp if pooled else None)
+        if i8:
+            B.relay_qimage_conv2d(d, xd, wp, p["b"], p["s"], *outs)
+        else:
+            B.relay_fused_image_conv2d(d, xd, wp, p["b"], p["sc"], p["sf"], *outs)
+        torch.cuda.synchronize()
+        for got, want, used in ((y, y0, conv_too), (yp, yp0, pooled)):
+            if not used:
+                assert bool((got == 77).all())
+            elif i8:
+                assert torch.equal(got, want)
+            else:   # the same fp32 sums up to their grouping (1e-6 of the outputs' size): a rounding to fp16 may go the other way, one ulp
+                assert O.max_rel_err(got.cpu().numpy(), want.cpu().numpy()) <= 1.1 * 2.0 ** -10
+
+
+def test_image_conv_argument_checks():
+    from paper_1904_08368_amd import binding as B
+    ok = dict(dtype=B.RELAY_F16, layout=B.RELAY_NHWC4_PADDED, flags=B.RELU)
+
+    def desc(n=1, c=3, h=32, w=32, k=64, r=7, st=2, pad=3, **kw):
+        e = dict(ok, **kw)
+        return B.conv_desc(n, c, h, w, k, r, r, st, pad, e["dtype"], e["layout"], e["flags"])
+    assert B.relay_image_conv2d_supported(desc(), True) and B.relay_image_conv2d_supported(desc(), False)
+    for bad in (desc(layout=B.RELAY_NHWC), desc(flags=B.RELU | B.HAS_RESIDUAL), desc(k=60), desc(r=11, pad=5), desc(dtype=B.RELAY_I8, st=1),
+                desc(dtype=B.RELAY_I8, flags=B.HAS_BN), desc(c=5)):
+        assert not B.relay_image_conv2d_supported(bad, False)
+    assert not B.relay_image_conv2d_supported(desc(flags=0), True)      # a float pool without relu
+
+    x, w, y = 0x7F0000000000, 0x7F0000100000, 0x7F0000200000     # (never dereferenced: every call is refused)
+    for args, status in (((None, w, y, None), 1), ((x, w, None, None), 1), ((x, w, x, None), 4), ((x, w, y, y), 4), ((x + 2, w, y, None), 5),
+                         ((x, w + 8, y, None), 5), ((x, w, y + 8, None), 5)):
+        got = B.lib().relay_fused_image_conv2d(C.byref(desc()), args[0], args[1], None, None, None, args[2], args[3], None)
+        assert got == status, (status, got, B.lib().relay_last_error())

@@ -46,3 +46,14 @@ def test_a_shortened_list_and_one_with_an_entry_more(net):
     net.calls.insert(0, (lambda *a: done.append("new"), ()))
     net.run()
     assert done == ["new", 0, 1]
+
+
+def test_the_first_calls_as_one_launch_unless_edited(net):
+    net, done = net
+    net.stem = (net.calls[:1], lambda *a: done.append(("stem",) + a), ("x",))
+    net.run()
+    assert done == [("stem", "x"), (1, 2), 3]
+    done.clear()
+    net.calls[0] = (lambda *a: done.append("edited"), ())
+    net.run()
+    assert done == ["edited", (1, 2), 3]
