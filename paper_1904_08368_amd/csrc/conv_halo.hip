@@ -62,7 +62,7 @@ constexpr int SQ = 16, SQP = SQ + 2;   // square tiles: 16 x 16 outputs, 18 x 18
 // SK: waves that share a tile of sums and split the k-steps of every step between them (their sums meet in LDS before the
 // epilogue, where each finishes 1 / SK of the tile).  A wave then owns an SK times larger tile for the same workgroup
 // tile, so each matrix instruction needs fewer operand reads -- what the small tiles are bound by.
-template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int KP, int HB = 1, bool SQUARE = false, int SK = 1>
+template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int KP, int HB = 1, bool SQUARE = false, int SK = 1, bool EXT = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_kernel(const ConvArgs a, const HaloGeom g) {
   constexpr int NW = WAVES_M * WAVES_N * SK;
   constexpr int VE = IS_I8 ? 16 : 8;
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   constexpr int PPI = 64 / CG;
   const int epix = lane / CG, ecg = lane % CG;
   const bool vec_ok = (a.K & 7) == 0;
-  const OutLoc ol{nullptr, 0, 0};  // this kernel stores plain tensors only
+  const OutLoc ol = EXT ? locate_output(a, ech) : OutLoc{nullptr, 0, 0, 0};
   // the output pixels of this lane (the output pixel of a flat position o is the table's entry for o + P + 1),
   // read together, and all its residual vectors: in flight together, behind the transpositions below
   constexpr int ITS = 32 / PPI;
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
       const unsigned raw[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
       const unsigned m = mpix[tm][it];
       if (m == ~0u || ech >= a.K) continue;  // not a pixel, or past Cout
-      finish_store8<IS_I8, false>(a, raw, (int)m, ech, lp, ol, vec_ok, pre_res, resv[tm][it]);
+      finish_store8<IS_I8, false, EXT>(a, raw, (int)m, ech, lp, ol, vec_ok, pre_res, resv[tm][it]);
     }
   }
 }
@@ -507,9 +507,9 @@ bool make_geom(const ConvArgs& a, bool is_i8, int v, HaloGeom& g, size_t& lds_by
   return lds_bytes <= 160 * 1024;
 }
 
-template <bool IS_I8, int WM, int WN, int TM, int TN, int KP, int HB = 1, bool SQUARE = false, int SK = 1>
-hipError_t launch_halo_one(const ConvArgs& a, const HaloGeom& g, size_t lds_bytes, hipStream_t st) {
-  auto kern = conv3x3_halo_kernel<IS_I8, WM, WN, TM, TN, KP, HB, SQUARE, SK>;
+template <bool EXT, bool IS_I8, int WM, int WN, int TM, int TN, int KP, int HB, bool SQUARE, int SK>
+hipError_t launch_halo_store(const ConvArgs& a, const HaloGeom& g, size_t lds_bytes, hipStream_t st) {
+  auto kern = conv3x3_halo_kernel<IS_I8, WM, WN, TM, TN, KP, HB, SQUARE, SK, EXT>;
   static std::atomic<bool> raised{false};  // dynamic LDS above the default limit has to be asked for once per kernel
   if (!raised.load(std::memory_order_acquire)) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -524,6 +524,13 @@ hipError_t launch_halo_one(const ConvArgs& a, const HaloGeom& g, size_t lds_byte
   gl.fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
   hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(64 * WM * WN * SK), lds_bytes, st, a, gl);
   return hipGetLastError();
+}
+
+// (output channel segments take an instantiation of their own, as in the implicit GEMM)
+template <bool IS_I8, int WM, int WN, int TM, int TN, int KP, int HB = 1, bool SQUARE = false, int SK = 1>
+hipError_t launch_halo_one(const ConvArgs& a, const HaloGeom& g, size_t lds_bytes, hipStream_t st) {
+  return a.nseg ? launch_halo_store<true, IS_I8, WM, WN, TM, TN, KP, HB, SQUARE, SK>(a, g, lds_bytes, st)
+                : launch_halo_store<false, IS_I8, WM, WN, TM, TN, KP, HB, SQUARE, SK>(a, g, lds_bytes, st);
 }
 
 template <bool IS_I8>
@@ -555,7 +562,11 @@ bool conv_halo_shape(const ConvArgs& a, bool is_i8) {
   const int es = is_i8 ? 1 : 2, ve = is_i8 ? 16 : 8;
   if (a.R != 3 || a.S != 3 || a.sh != 1 || a.sw != 1 || a.ph != 1 || a.pw != 1) return false;
   if (a.xs_w != a.C || a.xs_h != a.W * a.C || a.xs_n != a.H * a.W * a.C) return false;
-  if (a.C % (BKV * ve) != 0 || a.round_mode == ROUND_STOCHASTIC || a.nseg) return false;
+  if (a.C % (BKV * ve) != 0 || a.round_mode == ROUND_STOCHASTIC) return false;
+  // Output channel segments, as long as they share the window and hold whole vectors of 8 channels: the 128 -> 192 conv of an Inception
+  // block at 32 x 28 x 28 into 192 of 480 channels 21.3 us by the implicit GEMM, 16.9 here (20.0 against 24.1 behind the block's
+  // other launches, its operands no longer in L2).
+  if (a.nseg && (a.seg_centre || (a.K & 7) || (a.flags & F_RES))) return false;   // (segments of the whole window, in vectors of 8 channels)
   if ((size_t)a.N * a.xs_n * es > 0x7fffffffu || (size_t)a.K * a.Kp * es > 0x7fffffffu) return false;
   return true;
 }
@@ -658,7 +669,8 @@ int conv_halo_pick(const ConvArgs& a, bool is_i8) {
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {
   const HaloTile& t = kHalo[v];
   char tail[40] = "";   // the arguments that differ from their defaults, and those in front of them
-  if (t.sk > 1) snprintf(tail, sizeof(tail), ", %s, %d", t.square ? "true" : "false", t.sk);
+  if (a.nseg) snprintf(tail, sizeof(tail), ", %s, %d, true", t.square ? "true" : "false", t.sk);
+  else if (t.sk > 1) snprintf(tail, sizeof(tail), ", %s, %d", t.square ? "true" : "false", t.sk);
   else if (t.square) snprintf(tail, sizeof(tail), ", true");
   snprintf(buf, len, "conv3x3_halo_kernel<%s, %d, %d, %d, %d, %d, %d%s>", is_i8 ? "true" : "false", t.waves_m, t.waves_n, t.tm, t.tn,
            chunk_planes(a, is_i8, v), t.hb, tail);

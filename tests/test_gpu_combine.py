@@ -390,3 +390,42 @@ def test_int8_combined_convs_bit_exact(r):
     for wt, b, (m, sh), got in zip(ws, bs, ms, outs):
         ref = S.qconv2d_requant_scaled(x, wt, stride=(1, 1), pad=(pad, pad), bias=b, mult=m, rshift=sh, relu_flag=True)
         assert np.array_equal(got, ref)
+
+
+# the 3x3 kernel's variants: an image off its tiles, segment boundaries inside its 64-channel tiles, several chunks where it has
+# such forms; channels of the joined tensor that no member owns stay as they are
+@pytest.mark.parametrize("variant", [0, 1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("shape", [(2, 128, 17, 21), (1, 256, 5, 9)])
+def test_3x3_kernel_stores_segments(G, shape, variant):
+    n, c, h, w = shape
+    ops, params = _members(c, (8, 72, 40), 3, 4, bias=True)
+    x = inputs.activation(21, 5, (n, c, h, w), "f16")
+    plan = [(0, 16, 64), (1, 0, 72), (0, 24, 64)]
+    outs, bufs = _run_combined(G, x, ops, params, 1, 1, True, out_plan=plan, tile=100 + variant)
+    _check_members(x, ops, params, outs, 1, 1, True)
+    assert torch.all(bufs[0][..., :16] == -77.0)
+
+
+@pytest.mark.parametrize("variant", [0, 1, 6])
+def test_int8_3x3_kernel_stores_segments(G, variant):
+    from paper_1904_08368_amd import binding as B
+    g = np.random.default_rng(560)
+    n, c, h, w, k, first = 2, 256, 9, 11, 136, 40
+    x = g.integers(-127, 128, (n, c, h, w)).astype(np.int8)
+    wt = g.integers(-127, 128, (k, c, 3, 3)).astype(np.int8)
+    b = g.integers(-4000, 4000, k).astype(np.int32)
+    d = B.conv_desc(n, c, h, w, k, 3, 3, 1, 1, B.RELAY_I8, B.RELAY_NHWC, B.flags_of(True, None, None, True))
+    wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device=G.DEV)
+    B.relay_prepack_conv2d_weights(d, G.up(wt), c, wp)
+    y0 = torch.full((n, h, w, first + 8), -128, dtype=torch.int8, device=G.DEV)      # 8 channels before the segment
+    y1 = torch.full((n, h, w, k - first), -128, dtype=torch.int8, device=G.DEV)
+    B.relay_set_conv_tile(100 + variant)
+    try:
+        B.relay_qconv2d_combined(d, G.to_nhwc(x, c, B.RELAY_I8), c, wp, G.up(b), None, None, 13, [first, k - first], [y0[..., 8:], y1],
+                                 [first + 8, k - first])
+    finally:
+        B.relay_set_conv_tile(-1)
+    torch.cuda.synchronize()
+    ref = O.qconv2d_requant(x, wt, stride=(1, 1), pad=(1, 1), bias=b, out_rshift=13, relu_flag=True)
+    assert np.array_equal(np.concatenate([G.from_nhwc(y0, first + 8)[:, 8:], G.from_nhwc(y1, k - first)], axis=1), ref)
+    assert torch.all(y0[..., :8] == -128)
