@@ -350,6 +350,14 @@ relay_status relay_qconv2d_requant_maxpool(const relay_conv2d_desc* d, const int
                                            const int32_t* bias, int32_t out_rshift, int8_t* y_pooled,
                                            void* hip_stream);
 
+/* relay_fused_conv2d_bias_bn_relu with the 2x2 / stride 2 / pad 0 max pool behind it in the same launch (the fused functions
+ * of paper Section 4.1), both results written: those of the two separate calls bit for bit.  F16 NHWC, 3x3 / stride 1 / pad 1 with RELU, no residual, c % 32 == 0, k % 8 == 0,
+ * h and w even; y [n, h, w, k], y_pooled [n, h/2, w/2, k], 16-byte aligned.  relay_conv2d_pool2x2_pays writes 1 where the
+ * separate conv would take the kernel that this call runs (else the two launches may be the faster ones, or the call is refused). */
+relay_status relay_conv2d_pool2x2_pays(const relay_conv2d_desc* d, int32_t* pays);
+relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* x, const void* w_packed, const float* bias,
+                                        const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream);
+
 /* A first-layer convolution primitive function read from the NCHW image as it arrives, with the 3x3 / stride 2 / pad 1 max
  * pool behind it if y_pooled is given: relay_pack_input_nhwc4, relay_fused_conv2d_bias_bn_relu (or relay_qconv2d_requant) and
  * relay_maxpool2d as ONE launch that keeps the padded copy in LDS (the layout alteration of paper Section 5.3 folded into

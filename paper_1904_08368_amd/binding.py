@@ -88,6 +88,8 @@ SIGNATURES = {
     "relay_fold_scale_axis": [_I, _I, _I, _I, _I, _P, _P, _P, _P],
     "relay_fold_bias": [_I, _P, _P, _P, _P, _P],
     "relay_conv2d_maxpool_fusable": [_DP, C.POINTER(_I)],
+    "relay_conv2d_pool2x2_pays": [_DP, C.POINTER(_I)],
+    "relay_fused_conv2d_pool2x2": [_DP, _P, _P, _P, _P, _P, _P, _P, _P],
     "relay_image_conv2d_supported": [_DP, _I, C.POINTER(_I)],
     "relay_fused_image_conv2d": [_DP, _P, _P, _P, _P, _P, _P, _P, _P],
     "relay_qimage_conv2d": [_DP, _P, _P, _P, _I, _P, _P, _P],
@@ -234,6 +236,17 @@ def relay_fused_conv2d_bn_relu_maxpool(d: ConvDesc, x, w_packed, bias, bn_scale,
 def relay_qconv2d_requant_maxpool(d: ConvDesc, x, w_packed, bias, out_rshift: int, y_pooled) -> None:
     _check(lib().relay_qconv2d_requant_maxpool(C.byref(d), _ptr(x), _ptr(w_packed), _ptr(bias), out_rshift,
                                                _ptr(y_pooled), _stream()))
+
+
+def relay_conv2d_pool2x2_pays(d: ConvDesc) -> bool:
+    ok = C.c_int32(0)
+    _check(lib().relay_conv2d_pool2x2_pays(C.byref(d), C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_fused_conv2d_pool2x2(d: ConvDesc, x, w_packed, bias, bn_scale, bn_shift, y, y_pooled) -> None:
+    _check(lib().relay_fused_conv2d_pool2x2(C.byref(d), _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(bn_scale), _ptr(bn_shift),
+                                            _ptr(y), _ptr(y_pooled), _stream()))
 
 
 def relay_image_conv2d_supported(d: ConvDesc, pooled: bool) -> bool:

@@ -999,6 +999,44 @@ relay_status relay_fused_conv2d_bn_relu_maxpool(const relay_conv2d_desc* d, cons
                        "pooled conv2d fp16 launch");
 }
 
+static relay_status check_pool2x2(const relay_conv2d_desc* d, relay::ConvArgs* out) {
+  int ho, wo;
+  relay_status st = check_geometry(d, &ho, &wo);
+  if (st != RELAY_OK) return st;
+  if (d->dtype != RELAY_F16) return fail(RELAY_ERR_DTYPE, "the conv2d with a 2x2 pool takes F16");
+  if ((st = check_igemm_support(d)) != RELAY_OK) return st;
+  const relay::ConvArgs a = make_args(d, ho, wo);
+  if (!relay::conv_halo_pool2_supported(a))
+    return fail(RELAY_ERR_UNSUPPORTED, "the conv2d with a 2x2 pool takes 3x3 / stride 1 / pad 1 with relu and without a residual, c %% 32 == 0, "
+                "k %% 8 == 0, an even height and width (c=%d k=%d h=%d w=%d)", d->c, d->k, d->h, d->w);
+  *out = a;
+  return RELAY_OK;
+}
+
+relay_status relay_conv2d_pool2x2_pays(const relay_conv2d_desc* d, int32_t* pays) {
+  if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
+  relay::ConvArgs a;
+  *pays = check_pool2x2(d, &a) == RELAY_OK && small_choice(a, false) < 0 && halo_choice(a, false) == 5 ? 1 : 0;
+  return RELAY_OK;
+}
+
+relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* x, const void* w_packed, const float* bias,
+                                        const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream) {
+  relay::ConvArgs a;
+  relay_status st = check_pool2x2(d, &a);
+  if (st != RELAY_OK) return st;
+  if (!x || !w_packed || !y || !y_pooled) return fail(RELAY_ERR_NULL, "x, w_packed, y and y_pooled are required");
+  if ((st = check_optional(bias, d->flags & RELAY_HAS_BIAS, "bias")) != RELAY_OK) return st;
+  if ((st = check_optional(bn_scale, d->flags & RELAY_HAS_BN, "bn_scale")) != RELAY_OK) return st;
+  if ((st = check_optional(bn_shift, d->flags & RELAY_HAS_BN, "bn_shift")) != RELAY_OK) return st;
+  if (y == x || y_pooled == x || y == y_pooled) return fail(RELAY_ERR_UNSUPPORTED, "an output must not alias the input or the other output");
+  if (!aligned(x, 16) || !aligned(w_packed, 16) || !aligned(y, 16) || !aligned(y_pooled, 16))
+    return fail(RELAY_ERR_ALIGN, "fp16 tensors must be 16-byte aligned");
+  a.x = x; a.w = w_packed; a.y = y; a.bias = bias; a.scale = bn_scale; a.shift = bn_shift;
+  finish_args(a);
+  return device_status(relay::launch_conv_halo_pool2(a, y_pooled, static_cast<hipStream_t>(hip_stream)), "conv2d with a 2x2 pool launch");
+}
+
 relay_status relay_qconv2d_requant_maxpool(const relay_conv2d_desc* d, const int8_t* x, const int8_t* w_packed,
                                            const int32_t* bias, int32_t out_rshift, int8_t* y_pooled,
                                            void* hip_stream) {

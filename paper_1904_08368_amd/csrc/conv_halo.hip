@@ -44,6 +44,9 @@ struct HaloGeom {
   int tab_slot;       // 16-byte slot of LDS where the pixel table starts (behind the ring and the epilogue staging)
   FastDiv fd_f, fd_xblk, fd_row;    // division by F, by xblk and (square tiles) by the tiles of a row
   FastDiv fd_tiles_m, fd_tiles_n;   // ... by the tile counts of the launched variant
+  // the 2x2 / stride 2 maxima of the outputs [N][H/2][W/2][K], and division by W (square tiles with POOL)
+  void* y_pooled;
+  FastDiv fd_w;
 };
 
 constexpr int NSW = 3;         // filter ring stages (9 taps per chunk keep step % NSW compile-time)
@@ -62,7 +65,8 @@ constexpr int SQ = 16, SQP = SQ + 2;   // square tiles: 16 x 16 outputs, 18 x 18
 // SK: waves that share a tile of sums and split the k-steps of every step between them (their sums meet in LDS before the
 // epilogue, where each finishes 1 / SK of the tile).  A wave then owns an SK times larger tile for the same workgroup
 // tile, so each matrix instruction needs fewer operand reads -- what the small tiles are bound by.
-template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int KP, int HB = 1, bool SQUARE = false, int SK = 1, bool EXT = false>
+template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int KP, int HB = 1, bool SQUARE = false, int SK = 1, bool EXT = false,
+          bool POOL = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_kernel(const ConvArgs a, const HaloGeom g) {
   constexpr int NW = WAVES_M * WAVES_N * SK;
   constexpr int VE = IS_I8 ? 16 : 8;
@@ -426,14 +430,34 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
         stg[lrow * EP + tn * 8 + 2 * q4 + lhalf] = v;
       }
     // same wave wrote what it now reads: LDS operations of a wave execute in order
+    uint4 kept[POOL ? 4 : 1];
 #pragma unroll
     for (int it = 0; it < 32 / PPI; ++it) {
       const int pix = it * PPI + epix;
       const uint4 lo = stg[pix * EP + ecg * 2], hi = stg[pix * EP + ecg * 2 + 1];
       const unsigned raw[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
       const unsigned m = mpix[tm][it];
+      if constexpr (POOL) {
+        kept[it] = make_uint4(0u, 0u, 0u, 0u);
+        if (m != ~0u && ech < a.K) finish_store8<IS_I8, false>(a, raw, (int)m, ech, lp, ol, true, false, uint4{0u, 0u, 0u, 0u}, &kept[it]);
+        continue;
+      }
       if (m == ~0u || ech >= a.K) continue;  // not a pixel, or past Cout
       finish_store8<IS_I8, false, EXT>(a, raw, (int)m, ech, lp, ol, vec_ok, pre_res, resv[tm][it]);
+    }
+    if constexpr (POOL) {
+      // a block is two rows of 16 outputs: a lane has columns epix and epix + 8 of both, the lane CG further the column to the
+      // right.  (Even heights and widths: the four outputs of a maximum are all pixels or all not.)
+      static_assert(!POOL || (SQUARE && !IS_I8 && CG == 8 && SK == 1 && !EXT), "two rows of 16 fp16 outputs in four passes of 8 pixels");
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        uint4 v = max_half8(kept[h], kept[h + 2]);
+        v = max_half8(v, make_uint4(__shfl_xor(v.x, CG, 64), __shfl_xor(v.y, CG, 64), __shfl_xor(v.z, CG, 64), __shfl_xor(v.w, CG, 64)));
+        const unsigned m = mpix[tm][h];
+        if ((epix & 1) || m == ~0u || ech >= a.K) continue;
+        const unsigned x = m - fast_div(m, g.fd_w) * (unsigned)a.W;   // (row * W + x) -> (row / 2) * (W / 2) + x / 2
+        *reinterpret_cast<uint4*>(static_cast<_Float16*>(g.y_pooled) + (size_t)((m + x) >> 2) * a.K + ech) = v;
+      }
     }
   }
 }
@@ -507,9 +531,9 @@ bool make_geom(const ConvArgs& a, bool is_i8, int v, HaloGeom& g, size_t& lds_by
   return lds_bytes <= 160 * 1024;
 }
 
-template <bool EXT, bool IS_I8, int WM, int WN, int TM, int TN, int KP, int HB, bool SQUARE, int SK>
+template <bool EXT, bool IS_I8, int WM, int WN, int TM, int TN, int KP, int HB, bool SQUARE, int SK, bool POOL = false>
 hipError_t launch_halo_store(const ConvArgs& a, const HaloGeom& g, size_t lds_bytes, hipStream_t st) {
-  auto kern = conv3x3_halo_kernel<IS_I8, WM, WN, TM, TN, KP, HB, SQUARE, SK, EXT>;
+  auto kern = conv3x3_halo_kernel<IS_I8, WM, WN, TM, TN, KP, HB, SQUARE, SK, EXT, POOL>;
   static std::atomic<bool> raised{false};  // dynamic LDS above the default limit has to be asked for once per kernel
   if (!raised.load(std::memory_order_acquire)) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -674,6 +698,25 @@ void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size
   else if (t.square) snprintf(tail, sizeof(tail), ", true");
   snprintf(buf, len, "conv3x3_halo_kernel<%s, %d, %d, %d, %d, %d, %d%s>", is_i8 ? "true" : "false", t.waves_m, t.waves_n, t.tm, t.tn,
            chunk_planes(a, is_i8, v), t.hb, tail);
+}
+
+// 2x2 / stride 2 max pool behind the conv, on 16 x 16 tiles: fp16, whole vectors of channels, whole windows, and a relu (no NaN left
+// to order).  The pool's read of the conv outputs and its launch go: of 64 -> 64 at batch 32 of 224 x 224 155 + 42 us as two launches,
+// of 128 -> 128 at 112 x 112 120 + 21 us; 168 and 127 as one each.  (The card is at its power limit there: the whole network
+// gains 24 of 1170 us, the convs behind take 5 % longer than with the pools between them.)
+bool conv_halo_pool2_supported(const ConvArgs& a) {
+  return conv_halo_supported(a, false, 5) && !a.nseg && (a.flags & F_RELU) && !(a.flags & F_RES) && !((a.H | a.W) & 1) && !(a.K & 7) &&
+         (long)a.M * 2 <= 0x7fffffffL;
+}
+
+hipError_t launch_conv_halo_pool2(const ConvArgs& a, void* y_pooled, hipStream_t st) {
+  HaloGeom g;
+  size_t lds_bytes;
+  if (!conv_halo_pool2_supported(a) || !make_geom(a, false, 5, g, lds_bytes)) return hipErrorInvalidValue;
+  g.y_pooled = y_pooled;
+  g.fd_w = make_fastdiv((uint32_t)a.W);
+  return chunk_planes(a, false, 5) == 2 ? launch_halo_store<false, false, 4, 1, 2, 2, 2, 2, true, 1, true>(a, g, lds_bytes, st)
+                                        : launch_halo_store<false, false, 4, 1, 2, 2, 1, 2, true, 1, true>(a, g, lds_bytes, st);
 }
 
 hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int v, hipStream_t st) {

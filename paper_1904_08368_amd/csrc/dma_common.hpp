@@ -137,6 +137,14 @@ __device__ __forceinline__ void load_lane_params(const ConvArgs& a, int ech, Lan
   finish_lane_params<IS_I8>(rp, lp);
 }
 
+__device__ __forceinline__ uint4 max_half8(uint4 a, uint4 b) {
+  typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+  const auto m = [](unsigned u, unsigned v) {
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(half2v, u), __builtin_bit_cast(half2v, v)));
+  };
+  return make_uint4(m(a.x, b.x), m(a.y, b.y), m(a.z, b.z), m(a.w, b.w));
+}
+
 // EXT: the instantiation that knows about output segments (the plain one ignores ol).
 // Finish the 8 consecutive channels [ech, ech + 8) of output pixel m (its index in the NHWC output;
 // residual and random draws are addressed in the plain [M][K] tensor, the store goes where ol says)
@@ -160,7 +168,7 @@ __device__ __forceinline__ uint4 load_residual8(const ConvArgs& a, int m, int ec
 template <bool IS_I8, bool STOCH, bool EXT = false>
 __device__ __forceinline__ void finish_store8(const ConvArgs& a, const unsigned (&raw)[8], int m, int ech,
                                               const LaneParams& lp, const OutLoc& ol, bool vec_ok,
-                                              bool have_pre = false, uint4 pre = uint4{0u, 0u, 0u, 0u}) {
+                                              bool have_pre = false, uint4 pre = uint4{0u, 0u, 0u, 0u}, uint4* kept = nullptr) {
   const float(&emul)[8] = lp.mul;
   const float(&eadd)[8] = lp.add;
   const int(&ebias)[8] = lp.ibias;
@@ -204,6 +212,7 @@ __device__ __forceinline__ void finish_store8(const ConvArgs& a, const unsigned 
     _Float16* yp = static_cast<_Float16*>(a.y) + o;
     if constexpr (EXT)
       if (a.nseg) yp = static_cast<_Float16*>(ol.y) + ((size_t)m * ol.ldy + ol.cho);
+    if (kept) *kept = make_uint4(hw[0], hw[1], hw[2], hw[3]);
     if (vec_ok) {
       *reinterpret_cast<uint4*>(yp) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
     } else {

@@ -137,6 +137,9 @@ bool igemm_dma_wide(const ConvArgs& a);
 int conv_halo_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the layer to the implicit-GEMM kernel
 int conv_halo_variant_count();
 hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
+// ... with the 2x2 / stride 2 max pool behind it: y as without, and y_pooled
+bool conv_halo_pool2_supported(const ConvArgs& a);
+hipError_t launch_conv_halo_pool2(const ConvArgs& a, void* y_pooled, hipStream_t st);
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
 // The kernel for layers of few output tiles: the waves of a workgroup split the reduction (conv_small.hip).
 bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);

@@ -280,10 +280,24 @@ class FusedNet:
         self.pairs = {} if self.side_calls else self._independent_pairs()
         # the first calls as one launch on the image itself: its padded copy (not written then), the conv and the pool behind it
         self.stem = self._image_stem()
+        # further calls that one launch stands for, writing the same tensors
+        self.merged = self._convs_with_pools()
         torch.cuda.synchronize(self.dev)
         self.graph = None
 
     stem = None
+    merged: Dict[int, tuple] = {}
+
+    def _convs_with_pools(self):
+        """{i: (calls, function, arguments)} of a conv and the 2x2 max pool on its outputs where the library takes them together."""
+        merged = {}
+        for i in range(len(self.calls) - 1):
+            (f0, a0), (f1, a1) = self.calls[i], self.calls[i + 1]
+            # (no residual, no workspace; the pool reads what the conv wrote)
+            if f0 is B.relay_fused_conv2d_bias_bn_relu and len(a0) == 9 and a0[6] is None and a0[8] is None and \
+                    f1 is B.relay_maxpool2d and a1[5:8] == (2, 2, 0) and a1[8] is a0[7] and B.relay_conv2d_pool2x2_pays(a0[0]):
+                merged[i] = (self.calls[i:i + 2], B.relay_fused_conv2d_pool2x2, tuple(a0[:6]) + (a0[7], a1[9]))
+        return merged
 
     def _image_stem(self):
         """(calls, function, arguments) of the launch that stands for the first two or three calls -- the padded copy of the image,
@@ -502,7 +516,7 @@ class FusedNet:
         first conv: both read the block input, neither reads the other.  The fork event is
         recorded BEFORE that first conv is enqueued, so the side stream waits only for the
         producer of the block input."""
-        if not self.side_calls and not self.pairs and not self.stem:
+        if not self.side_calls and not self.pairs and not self.stem and not self.merged:
             for fn, args in self.calls:
                 fn(*args)
             return
@@ -514,9 +528,12 @@ class FusedNet:
         if not self.side_calls:
             i = done
             while i < len(self.calls):
-                # (a pair only while both entries are those it was made of: `calls` may be edited, entries wrapped or cut off)
-                pair = self.pairs.get(i)
-                if pair and len(self.calls) > i + 1 and self.calls[i] is pair[0] and self.calls[i + 1] is pair[1]:
+                # (calls share a launch only while all entries are those it was made for: `calls` may be edited, entries wrapped or cut off)
+                pair, merged = self.pairs.get(i), self.merged.get(i)
+                if merged and len(self.calls) >= i + len(merged[0]) and all(a is b for a, b in zip(merged[0], self.calls[i:])):
+                    merged[1](*merged[2])
+                    i += len(merged[0])
+                elif pair and len(self.calls) > i + 1 and self.calls[i] is pair[0] and self.calls[i + 1] is pair[1]:
                     B.relay_conv2d_pair(pair[0][1], pair[1][1])
                     i += 2
                 else:

@@ -57,3 +57,14 @@ def test_the_first_calls_as_one_launch_unless_edited(net):
     net.calls[0] = (lambda *a: done.append("edited"), ())
     net.run()
     assert done == ["edited", (1, 2), 3]
+
+
+def test_calls_with_a_launch_of_their_own_unless_edited(net):
+    net, done = net
+    net.pairs, net.merged = {}, {2: (net.calls[2:4], lambda *a: done.append(a), ("both",))}
+    net.run()
+    assert done == [0, 1, ("both",)]
+    done.clear()
+    net.calls[3] = (lambda *a: done.append("edited"), ())
+    net.run()
+    assert done == [0, 1, 2, "edited"]
