@@ -358,6 +358,14 @@ relay_status relay_conv2d_pool2x2_pays(const relay_conv2d_desc* d, int32_t* pays
 relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* x, const void* w_packed, const float* bias,
                                         const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream);
 
+/* relay_global_avgpool and relay_fused_dense_bias_act on its result as one launch (one fused function of paper Section 4.1), both
+ * results written: pooled [n, c] as by the first (up to the grouping of its fp32 sums), y [n, units] from those fp16 values.  F16;
+ * x [n, hw, c], w [units, c]; c % 8 == 0, c <= 2048; x, w and pooled 16-byte aligned.  relay_avgpool_dense_pays writes 1 where
+ * that is faster than the two launches. */
+relay_status relay_avgpool_dense_pays(int32_t dtype, int32_t n, int32_t c, int32_t hw, int32_t units, int32_t* pays);
+relay_status relay_fused_avgpool_dense(int32_t dtype, int32_t n, int32_t c, int32_t hw, int32_t units, const void* x, const void* w,
+                                       const float* bias, int32_t act, void* pooled, void* y, void* hip_stream);
+
 /* A first-layer convolution primitive function read from the NCHW image as it arrives, with the 3x3 / stride 2 / pad 1 max
  * pool behind it if y_pooled is given: relay_pack_input_nhwc4, relay_fused_conv2d_bias_bn_relu (or relay_qconv2d_requant) and
  * relay_maxpool2d as ONE launch that keeps the padded copy in LDS (the layout alteration of paper Section 5.3 folded into

@@ -88,6 +88,8 @@ SIGNATURES = {
     "relay_fold_scale_axis": [_I, _I, _I, _I, _I, _P, _P, _P, _P],
     "relay_fold_bias": [_I, _P, _P, _P, _P, _P],
     "relay_conv2d_maxpool_fusable": [_DP, C.POINTER(_I)],
+    "relay_avgpool_dense_pays": [_I, _I, _I, _I, _I, C.POINTER(_I)],
+    "relay_fused_avgpool_dense": [_I, _I, _I, _I, _I, _P, _P, _P, _I, _P, _P, _P],
     "relay_conv2d_pool2x2_pays": [_DP, C.POINTER(_I)],
     "relay_fused_conv2d_pool2x2": [_DP, _P, _P, _P, _P, _P, _P, _P, _P],
     "relay_image_conv2d_supported": [_DP, _I, C.POINTER(_I)],
@@ -236,6 +238,16 @@ def relay_fused_conv2d_bn_relu_maxpool(d: ConvDesc, x, w_packed, bias, bn_scale,
 def relay_qconv2d_requant_maxpool(d: ConvDesc, x, w_packed, bias, out_rshift: int, y_pooled) -> None:
     _check(lib().relay_qconv2d_requant_maxpool(C.byref(d), _ptr(x), _ptr(w_packed), _ptr(bias), out_rshift,
                                                _ptr(y_pooled), _stream()))
+
+
+def relay_avgpool_dense_pays(dtype: int, n: int, c: int, hw: int, units: int) -> bool:
+    ok = C.c_int32(0)
+    _check(lib().relay_avgpool_dense_pays(dtype, n, c, hw, units, C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_fused_avgpool_dense(dtype: int, n: int, c: int, hw: int, units: int, x, w, bias, act: int, pooled, y) -> None:
+    _check(lib().relay_fused_avgpool_dense(dtype, n, c, hw, units, _ptr(x), _ptr(w), _ptr(bias), act, _ptr(pooled), _ptr(y), _stream()))
 
 
 def relay_conv2d_pool2x2_pays(d: ConvDesc) -> bool:

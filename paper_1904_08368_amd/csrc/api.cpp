@@ -1322,6 +1322,34 @@ relay_status relay_fused_dense_bias_act(int32_t m, int32_t n, int32_t k, int32_t
                        "dense launch");
 }
 
+static relay_status check_avgpool_dense(int32_t dtype, int32_t n, int32_t c, int32_t hw, int32_t units) {
+  if (n <= 0 || c <= 0 || hw <= 0 || units <= 0) return fail(RELAY_ERR_SHAPE, "non-positive extent (n=%d c=%d hw=%d units=%d)", n, c, hw, units);
+  if (dtype != RELAY_F16) return fail(RELAY_ERR_DTYPE, "average pool with dense takes F16");
+  if (!relay::avgpool_dense_supported(n, c, hw, units)) return fail(RELAY_ERR_UNSUPPORTED, "average pool with dense takes c %% 8 == 0, c <= 2048 (c=%d)", c);
+  if ((long)n * hw > kMaxElems || (long)n * hw * c > kMaxElems || (long)units * c > kMaxElems || (long)n * units > kMaxElems)
+    return fail(RELAY_ERR_SHAPE, "tensor exceeds 2^31-1 elements");
+  return RELAY_OK;
+}
+
+relay_status relay_avgpool_dense_pays(int32_t dtype, int32_t n, int32_t c, int32_t hw, int32_t units, int32_t* pays) {
+  if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
+  *pays = check_avgpool_dense(dtype, n, c, hw, units) == RELAY_OK && relay::avgpool_dense_pays(n, c, hw, units) ? 1 : 0;
+  return RELAY_OK;
+}
+
+relay_status relay_fused_avgpool_dense(int32_t dtype, int32_t n, int32_t c, int32_t hw, int32_t units, const void* x, const void* w,
+                                       const float* bias, int32_t act, void* pooled, void* y, void* hip_stream) {
+  const relay_status st = check_avgpool_dense(dtype, n, c, hw, units);
+  if (st != RELAY_OK) return st;
+  if (act != 0 && act != 1) return fail(RELAY_ERR_UNSUPPORTED, "act=%d (0 none, 1 relu)", act);
+  if (!x || !w || !pooled || !y) return fail(RELAY_ERR_NULL, "x, w, pooled and y are required");
+  if (!aligned(x, 16) || !aligned(w, 16) || !aligned(pooled, 16) || !aligned(y, 2) || (bias && !aligned(bias, 4)))
+    return fail(RELAY_ERR_ALIGN, "x, w and pooled must be 16-byte aligned");
+  if (y == x || y == w || y == pooled || pooled == x || pooled == w) return fail(RELAY_ERR_UNSUPPORTED, "an output must not alias an input or the other output");
+  return device_status(relay::launch_avgpool_dense(n, c, hw, units, x, w, bias, act, pooled, y, static_cast<hipStream_t>(hip_stream)),
+                       "average pool with dense launch");
+}
+
 relay_status relay_elementwise_f16(int32_t op, int64_t n_pixels, int32_t c, const void* x, const float* p0,
                                    const float* p1, const void* other, void* y, void* hip_stream) {
   if (op < RELAY_EW_BIAS_ADD || op > RELAY_EW_RELU) return fail(RELAY_ERR_UNSUPPORTED, "op=%d is not a relay_elementwise_op", op);

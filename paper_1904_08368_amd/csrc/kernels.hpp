@@ -206,6 +206,11 @@ hipError_t launch_fold_scale_axis(bool is_f16, int K, int C, int RS, bool axis_i
 // out[k] = bias[k]*scale[k] + shift[k] (bias may be NULL: 0), fp64 arithmetic, fp32 result
 hipError_t launch_fold_bias(int K, const float* bias, const float* scale, const float* shift, float* out,
                             hipStream_t st);
+// global average pool + dense, fp16, one launch (head.hip)
+bool avgpool_dense_supported(int n, int c, int hw, int units);
+bool avgpool_dense_pays(int n, int c, int hw, int units);
+hipError_t launch_avgpool_dense(int n, int c, int hw, int units, const void* x, const void* w, const float* bias, int act, void* pooled,
+                                void* y, hipStream_t st);
 hipError_t launch_avgpool_f16(int N, int C, int HW, const void* x, void* y, hipStream_t st);
 hipError_t launch_nchw_to_nhwc(int esize, int N, int C, int H, int W, int Cpad, const void* x, void* y,
                                hipStream_t st);

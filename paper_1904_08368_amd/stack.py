@@ -281,15 +281,16 @@ class FusedNet:
         # the first calls as one launch on the image itself: its padded copy (not written then), the conv and the pool behind it
         self.stem = self._image_stem()
         # further calls that one launch stands for, writing the same tensors
-        self.merged = self._convs_with_pools()
+        self.merged = self._merged_calls()
         torch.cuda.synchronize(self.dev)
         self.graph = None
 
     stem = None
     merged: Dict[int, tuple] = {}
 
-    def _convs_with_pools(self):
-        """{i: (calls, function, arguments)} of a conv and the 2x2 max pool on its outputs where the library takes them together."""
+    def _merged_calls(self):
+        """{i: (calls, function, arguments)} of a conv and the 2x2 max pool on its outputs, and of the average pool and the dense
+        layer on its result, where the library takes them together and that pays."""
         merged = {}
         for i in range(len(self.calls) - 1):
             (f0, a0), (f1, a1) = self.calls[i], self.calls[i + 1]
@@ -297,6 +298,9 @@ class FusedNet:
             if f0 is B.relay_fused_conv2d_bias_bn_relu and len(a0) == 9 and a0[6] is None and a0[8] is None and \
                     f1 is B.relay_maxpool2d and a1[5:8] == (2, 2, 0) and a1[8] is a0[7] and B.relay_conv2d_pool2x2_pays(a0[0]):
                 merged[i] = (self.calls[i:i + 2], B.relay_fused_conv2d_pool2x2, tuple(a0[:6]) + (a0[7], a1[9]))
+            elif f0 is B.relay_global_avgpool and f1 is B.relay_fused_dense_bias_act and a1[4] is a0[5] and a1[2] == a0[2] and \
+                    a1[3] == a0[0] and B.relay_avgpool_dense_pays(*a0[:4], a1[1]):
+                merged[i] = (self.calls[i:i + 2], B.relay_fused_avgpool_dense, (*a0[:4], a1[1], a0[4], *a1[5:8], a0[5], a1[8]))
         return merged
 
     def _image_stem(self):
@@ -525,12 +529,14 @@ class FusedNet:
                 not any(i <= len(self.stem[0]) for i in self.side_calls):
             self.stem[1](*self.stem[2])
             done = len(self.stem[0])
+        # (calls share a launch only while all entries are those it was made for: `calls` may be edited, entries wrapped or cut off)
+        merged_at = lambda i: (m := self.merged.get(i)) and len(self.calls) >= i + len(m[0]) and \
+            all(a is b for a, b in zip(m[0], self.calls[i:])) and m
         if not self.side_calls:
             i = done
             while i < len(self.calls):
-                # (calls share a launch only while all entries are those it was made for: `calls` may be edited, entries wrapped or cut off)
-                pair, merged = self.pairs.get(i), self.merged.get(i)
-                if merged and len(self.calls) >= i + len(merged[0]) and all(a is b for a, b in zip(merged[0], self.calls[i:])):
+                pair, merged = self.pairs.get(i), merged_at(i)
+                if merged:
                     merged[1](*merged[2])
                     i += len(merged[0])
                 elif pair and len(self.calls) > i + 1 and self.calls[i] is pair[0] and self.calls[i + 1] is pair[1]:
@@ -543,7 +549,15 @@ class FusedNet:
             return
         main = torch.cuda.current_stream()
         pending = fork = None
-        for i, (fn, args) in enumerate(self.calls[done:], done):
+        for i, (fn, args) in enumerate(self.calls):
+            if i < done:
+                continue
+            merged = merged_at(i)
+            if merged:      # (only where no fork or join falls between its calls, or behind the last of them)
+                last = i + len(merged[0]) - 1
+                if not any(j in self.side_calls for j in range(i, last + 2)) and not any(j in self.join_before for j in range(i + 1, last + 1)):
+                    fn, args = merged[1:]
+                    done = last + 1
             if i + 1 in self.side_calls:      # the next call runs beside this one
                 fork = torch.cuda.Event()
                 fork.record(main)
