@@ -82,7 +82,7 @@ def main() -> int:
     conv_case("halo_f16_c128_28", 32, 128, 28, 128, 3, 1, 1, False, False)
     conv_case("halo_f16_c256_14", 32, 256, 14, 256, 3, 1, 1, False, True)
     conv_case("halo_f16_c64_56_tile_128x64", 32, 64, 56, 64, 3, 1, 1, False, True, tile=100)   # (the default there is the 256 x 64 tile)
-    conv_case("halo_f16_c256_56", 32, 256, 56, 256, 3, 1, 1, False, False)                      # (VGG-16's third stage: the 128 x 128 tile)
+    conv_case("halo_f16_c256_56", 32, 256, 56, 256, 3, 1, 1, False, False)                      # (VGG-16's third stage: the 256 x 128 tile)
     conv_case("halo_i8_c64_56", 16, 64, 56, 64, 3, 1, 1, True, True)
     conv_case("halo_i8_c128_28", 16, 128, 28, 128, 3, 1, 1, True, False)
     # ---- the implicit-GEMM kernel: 64 x 64 tile with 256-byte chunks (stage 4), the stride-2 layers, 1x1 layers
