@@ -568,7 +568,8 @@ relay_status relay_nchw_to_nhwc(int32_t dtype, int32_t n, int32_t c, int32_t h, 
 relay_status relay_set_conv_tile(int32_t tile);
 /* Tuning aid (paper Section 4.1, "Lowering", as above), thread-local like relay_set_conv_tile: workgroups per output tile of the calling
  * thread's later conv calls that are given a workspace (0 = choose by layer shape, the default;
- * 1 = never split; n <= 64, clamped to the number of reduction chunks).  relay_workspace_bytes
+ * 1 = never split; n <= 64, clamped to the number of reduction chunks).  A 3x3 / stride 1 layer with enough 128 x 64 tiles for
+ * all compute units stays whole at any setting (relay_workspace_bytes writes 0).  relay_workspace_bytes
  * called from the same thread follows the setting. */
 relay_status relay_set_conv_split(int32_t split);
 /* Tuning aid (paper Section 4.1, "Lowering", as above), thread-local: upper bound on the number of

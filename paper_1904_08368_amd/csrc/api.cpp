@@ -311,12 +311,15 @@ static int stream_choice(const relay::ConvArgs& a, bool is_i8) {
   return g_force_tile == -1 ? relay::conv_stream_pick(a, is_i8) : -1;
 }
 
-// which halo variant runs this layer, or -1.  (As below, a forced split of the reduction is the implicit GEMM's.)
+// does a forced split of the reduction send this layer to the implicit GEMM?
+static bool split_is_forced(const relay::ConvArgs& a, bool is_i8) { return g_force_split > 1 && !relay::conv_halo_keeps_whole(a, is_i8); }
+
+// which halo variant runs this layer, or -1
 static int halo_choice(const relay::ConvArgs& a, bool is_i8) {
   if (stream_choice(a, is_i8) >= 0) return -1;
   if (g_force_tile >= kStreamBase) return -1;
   if (g_force_tile >= kHaloBase) return relay::conv_halo_supported(a, is_i8, g_force_tile - kHaloBase) ? g_force_tile - kHaloBase : -1;
-  return g_force_tile == -1 && g_force_split == 0 ? relay::conv_halo_pick(a, is_i8) : -1;
+  return g_force_tile == -1 && !split_is_forced(a, is_i8) ? relay::conv_halo_pick(a, is_i8) : -1;
 }
 
 // which variant of the small-tile kernel runs this layer, or -1.  A caller that forces a split of the reduction
@@ -330,6 +333,7 @@ static int small_choice(const relay::ConvArgs& a, bool is_i8) {
 static int plan_split(const relay::ConvArgs& a, bool is_i8, size_t* counter_bytes, size_t* total_bytes) {
   *counter_bytes = *total_bytes = 0;
   if (stream_choice(a, is_i8) >= 0 || halo_choice(a, is_i8) >= 0 || !relay::igemm_dma_supported(a, is_i8)) return 1;
+  if (g_force_tile == -1 && g_force_split > 1 && !split_is_forced(a, is_i8)) return 1;
   return relay::igemm_dma_plan_split(a, is_i8, g_force_tile, g_force_split, counter_bytes, total_bytes);
 }
 

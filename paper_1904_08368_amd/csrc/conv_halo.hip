@@ -690,6 +690,24 @@ int conv_halo_pick(const ConvArgs& a, bool is_i8) {
   return pick;
 }
 
+// Layers that a caller's forced split of the reduction (n > 1) leaves whole.  Their 128 x 64 tiles give every CU one or fill the
+// 512 workgroup slots up to twice over (256 channels and more, 64 -> 64 in fp16: any number), so that there is nothing to gain
+// from partial sums and these would be large: 206 MB for 256 -> 256 at 56 x 56, batch 32 in two runs.  Outside this range a
+// forced split is the implicit GEMM's, also of a layer that conv_halo_pick would take (512 -> 512 at 14 x 14, batch 8).
+bool conv_halo_keeps_whole(const ConvArgs& a, bool is_i8) {
+  if (a.R != 3 || a.S != 3 || a.C < 64 || a.nseg || !conv_halo_shape(a, is_i8)) return false;
+  const long flat = (long)a.N * (a.H + 1) * (a.W + 1), tiles_n = (a.K + 63) / 64;
+  if (!is_i8 && a.C >= 512 && a.W <= 7 && chunk_planes(a, is_i8, 1) == 4 && halo_fits(a, is_i8, 1)) {
+    const long t64 = ((flat + 63) / 64) * tiles_n;
+    if (t64 >= 190 && t64 <= 512) return true;
+  }
+  const bool thin = !is_i8 && a.C == 64 && a.K <= 64;
+  if ((a.W > 56 && !thin) || !halo_fits(a, is_i8, 0)) return false;
+  const long t128 = ((flat + 127) / 128) * tiles_n;
+  if (!is_i8 && (a.C >= 256 || thin)) return t128 >= 190;
+  return t128 >= 190 && t128 <= (!is_i8 && a.C == 64 ? 1024 : 512);
+}
+
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {
   const HaloTile& t = kHalo[v];
   char tail[40] = "";   // the arguments that differ from their defaults, and those in front of them

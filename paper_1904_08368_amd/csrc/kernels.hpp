@@ -135,6 +135,7 @@ float igemm_dma_estimate(const ConvArgs& a, bool is_i8);
 float conv_small_estimate(const ConvArgs& a, bool is_i8);
 bool igemm_dma_wide(const ConvArgs& a);
 int conv_halo_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the layer to the implicit-GEMM kernel
+bool conv_halo_keeps_whole(const ConvArgs& a, bool is_i8);  // a forced split of the reduction leaves this layer whole
 int conv_halo_variant_count();
 hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);
 // ... with the 2x2 / stride 2 max pool behind it: y as without, and y_pooled
