@@ -332,8 +332,9 @@ relay_status relay_global_avgpool(int32_t dtype, int32_t n, int32_t c, int32_t h
  * as ONE launch: the conv output never reaches memory.  This carries the operator fusion of
  * paper Section 4.1 one operator past the elementwise tail (a window operator whose input tile
  * the workgroup already holds); the result equals relay_fused_conv2d_bias_bn_relu (or
- * relay_qconv2d_requant) followed by relay_maxpool2d(r=3, stride=2, pad=1) bit for bit, because
- * each conv output is finished and narrowed exactly as there before the maximum is taken.
+ * relay_qconv2d_requant) without a workspace followed by relay_maxpool2d(r=3, stride=2, pad=1) bit for bit, because
+ * each conv output is summed in the order of the kernel that the conv alone runs on (F16), finished and narrowed exactly as there
+ * before the maximum is taken.  (Under a forced tile, see relay_set_conv_tile, F16 up to the grouping of the sums.)
  *   d          the CONVOLUTION (F16 or I8; NHWC or NHWC4_PADDED; flags without HAS_RESIDUAL;
  *              I8 also without HAS_BN), with conv output ho % 14 == 0, wo % 16 == 0, k % 8 == 0
  *   y_pooled   [n, ho/2, wo/2, k] NHWC in d->dtype; F16 16-byte, I8 8-byte aligned

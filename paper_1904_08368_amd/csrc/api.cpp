@@ -959,7 +959,9 @@ static relay_status check_pool_fusable(const relay_conv2d_desc* d, int* ho, int*
     return fail(RELAY_ERR_UNSUPPORTED,
                 "the pooled conv2d needs a conv output of ho %% 14 == 0 and wo %% 16 == 0 and k %% 8 == 0 (ho=%d wo=%d k=%d)",
                 *ho, *wo, d->k);
+  const int halo = d->dtype == RELAY_F16 ? halo_choice(a, false) : -1;   // (int8 sums are exact in any order)
   relay::fill_pool_args(a);
+  if (halo >= 0) a.pool_block = relay::conv_halo_chunk(a, false, halo);
   *out = a;
   return RELAY_OK;
 }

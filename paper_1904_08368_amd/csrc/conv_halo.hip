@@ -651,6 +651,8 @@ constexpr HaloCost kCostI8[] = {
 //    an eager call about 0.2 us).
 //  * fp16, a layer the small-tile kernel would take: only variant 6, which sums in four runs as that kernel does.  The others sum
 //    in one, which is less exact.
+//  * fp16 with a max pool behind it in mind: not variant 6.  The pooled launch promises the bits of the two calls and follows the
+//    order of one run of sums, not the exchange of four.
 //  * 256 x 64 tiles with 64-byte chunks: only two to a CU, by their number and by their LDS (alone they wait at every barrier:
 //    12 x 20 x 18, 512 -> 512 38.6 us against 32.4 as 128 x 64).
 //  * 64 -> 64 channels in fp16, 128-position tiles for between one and about three rounds of the chip's 512 workgroup slots: the
@@ -671,12 +673,13 @@ int conv_halo_pick(const ConvArgs& a, bool is_i8) {
   const float staged = igemm_dma_estimate(a, is_i8), small = conv_small_estimate(a, is_i8);
   float best = 0.98f * (staged < small ? staged : small);
   int pick = -1;
+  const bool pooled = !is_i8 && igemm_dma_pool_supported(a, false);
   const int ve = is_i8 ? 16 : 8, rows = is_i8 ? (int)(sizeof(kCostI8) / sizeof(HaloCost)) : (int)(sizeof(kCostF16) / sizeof(HaloCost));
   for (int i = 0; i < rows; ++i) {
     const HaloCost& h = is_i8 ? kCostI8[i] : kCostF16[i];
     const HaloTile& t = kHalo[h.v];
     const int chunk = h.kp * BKV * ve;
-    if ((a.C == chunk) != h.one || a.C % chunk != 0 || (!is_i8 && small < staged && h.v != 6)) continue;
+    if ((a.C == chunk) != h.one || a.C % chunk != 0 || (!is_i8 && small < staged && h.v != 6) || (pooled && h.v == 6)) continue;
     const long tm = t.square ? (long)a.N * ((a.H + SQ - 1) / SQ) * ((a.W + SQ - 1) / SQ) : (flat + t.bm() - 1) / t.bm();
     const long tiles = tm * ((a.K + t.bn() - 1) / t.bn());
     if ((h.most && tiles > h.most) || ((h.v == 4 || h.v == 5) && tiles <= 256)) continue;
@@ -689,6 +692,8 @@ int conv_halo_pick(const ConvArgs& a, bool is_i8) {
   }
   return pick;
 }
+
+int conv_halo_chunk(const ConvArgs& a, bool is_i8, int v) { return chunk_planes(a, is_i8, v) * BKV * (is_i8 ? 16 : 8); }
 
 // Layers that a caller's forced split of the reduction (n > 1) leaves whole.  Their 128 x 64 tiles give every CU one or fill the
 // 512 workgroup slots up to twice over (256 channels and more, 64 -> 64 in fp16: any number), so that there is nothing to gain

@@ -222,6 +222,7 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
   }
   unsigned is_delta = (unsigned)((is_r * a.xs_h + is_s * a.xs_w + is_c) * ES), is_sbase = ring_base;
   bool is_live = is_kc < nchunks;
+  int is_cend = POOL ? a.pool_block : a.C;   // channel behind the block whose taps are being issued (pooled tiles: see pool_block)
   // Small wave tiles (the short reductions) never issue a load for a chunk past the end of the
   // reduction: their loop ends in NS-1 iterations that only let the loads in flight run out.  The
   // large ones keep one loop shape for every chunk and issue all-out-of-range loads there instead
@@ -239,19 +240,25 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
     } else {
       const int j = i - XL;
       // (kOob + the chunk position stays out of range)
-      const unsigned voff = (RUNOUT || is_live) ? w_off[j] + (unsigned)(is_kc * CK * ES + plane * 64) : kOob;
+      const unsigned at = POOL ? (unsigned)((is_tap * a.C + is_c) * ES) : (unsigned)(is_kc * CK * ES);
+      const unsigned voff = (RUNOUT || is_live) ? w_off[j] + at + (unsigned)(plane * 64) : kOob;
       lds_dma16(rs_w, pbase + (unsigned)(BM * BKV + (wave * WL + j) * 64) * 16u, voff);
     }
   };
   auto next_chunk = [&](int stage) {  // advance the issue position to the next chunk, landing in `stage`
     ++is_kc;
     is_c += CK;
-    if (is_c == a.C) {
-      is_c = 0;
+    if (is_c == is_cend) {
+      is_c = POOL ? is_cend - a.pool_block : 0;
       ++is_tap;
       if (++is_s == a.S) {
         is_s = 0;
         ++is_r;
+        if (POOL && is_r == a.R) {   // the next block of channels
+          is_tap = is_r = 0;
+          is_c = is_cend;
+          is_cend += a.pool_block;
+        }
       }
     }
     is_live = is_kc < nchunks;
@@ -1199,6 +1206,7 @@ bool igemm_dma_pool_supported(const ConvArgs& a, bool is_i8) {
 
 void fill_pool_args(ConvArgs& a) {
   a.pool = 1;
+  a.pool_block = a.C;
   a.pool_tiles_row = (a.Wo / 2) / 8;
   a.pool_tiles_img = ((a.Ho / 2) / 7) * a.pool_tiles_row;
   a.fd_pool_row = make_fastdiv((uint32_t)a.pool_tiles_row);

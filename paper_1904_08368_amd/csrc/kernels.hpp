@@ -59,6 +59,9 @@ struct ConvArgs {
   // tiles): a workgroup computes the 15 x 17 conv outputs under a 7 x 8 block of pooled outputs
   // and writes only those.  pool != 0: y is the pooled tensor [N][Ho/2][Wo/2][K].
   int pool;
+  // channels that one filter tap takes before the next one, block after block: the order in which the kernel of the conv alone adds
+  // up its sums (the 3x3 kernel's chunk, else C), so that both give the same bits
+  int pool_block;
   int pool_tiles_img, pool_tiles_row;   // 7 x 8 blocks per image and per row of blocks
   FastDiv fd_pool_img, fd_pool_row;
   // Reduction split over workgroups (direct-to-LDS implicit GEMM only): `split` workgroups share one
@@ -135,6 +138,7 @@ float igemm_dma_estimate(const ConvArgs& a, bool is_i8);
 float conv_small_estimate(const ConvArgs& a, bool is_i8);
 bool igemm_dma_wide(const ConvArgs& a);
 int conv_halo_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the layer to the implicit-GEMM kernel
+int conv_halo_chunk(const ConvArgs& a, bool is_i8, int variant);   // channels of a chunk of that variant
 bool conv_halo_keeps_whole(const ConvArgs& a, bool is_i8);  // a forced split of the reduction leaves this layer whole
 int conv_halo_variant_count();
 hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int variant, hipStream_t st);

@@ -56,6 +56,23 @@ def test_fp16_conv_maxpool_one_launch(G, case):
         assert int((got.view(np.uint16) != two.view(np.uint16)).sum()) == 0, nhwc4
 
 
+# 3x3 layers whose conv alone takes the 3x3 kernel's tiles (flat, square, wide) with channels in several chunks, one that would
+# take its exchange of four partial sums, and some that stay with the implicit GEMM
+@pytest.mark.parametrize("n,c,h,w,k,kernel", [
+    (3, 128, 112, 112, 72, "conv3x3_halo_kernel"), (4, 128, 112, 80, 72, "conv3x3_halo_kernel"), (3, 128, 56, 16, 72, "conv3x3_halo_kernel"),
+    (3, 96, 14, 112, 40, "conv3x3_halo_kernel"), (1, 256, 56, 64, 136, None), (3, 192, 112, 112, 72, "conv3x3_halo_kernel"),
+    (3, 256, 56, 16, 72, None), (1, 512, 28, 32, 64, None), (3, 96, 56, 96, 72, "igemm_dma_kernel"), (1, 128, 14, 16, 40, "igemm_dma_kernel_narrow")])
+def test_fp16_wide_layers_give_the_bits_of_the_two_calls(G, n, c, h, w, k, kernel):
+    from paper_1904_08368_amd import binding as B
+    d = B.conv_desc(n, c, h, w, k, 3, 3, 1, 1, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(None, True, None, True))
+    assert kernel is None or B.relay_conv2d_kernel_name(d).split("<")[0] == kernel
+    op = nets.conv("c", "x", "y", c, k, 3, 1, 1, bn=True, relu=True)
+    p = inputs.layer_params(op, 36, k + c, "f16")
+    x = inputs.activation(36, c + h, (n, c, h, w), "f16")
+    got, two = (G.run_conv_pool_f16(x, p["w"], 1, 1, scale=p["scale"], shift=p["shift"], relu=True, fused=f) for f in (True, False))
+    assert np.abs(two).max() > 0 and int((got.view(np.uint16) != two.view(np.uint16)).sum()) == 0
+
+
 I8_CASES = [
     (2, 64, 28, 32, 64, 3, 1, 1, True, True),
     (1, 64, 14, 16, 72, 3, 1, 1, False, False),   # no relu: negative maxima, the -127 clip
