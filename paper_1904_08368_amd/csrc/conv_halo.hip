@@ -645,56 +645,6 @@ constexpr HaloCost kCostI8[] = {
 };
 }  // namespace
 
-// The variant the heuristic takes, or -1 to leave the layer to the other kernels: the least of the estimates above,
-// where it is below those of the implicit GEMM and of the small-tile kernel.
-//  * Below 80 tiles of 64 x 64 the small-tile kernel is the better one always (the search is not even begun: it costs
-//    an eager call about 0.2 us).
-//  * fp16, a layer the small-tile kernel would take: only variant 6, which sums in four runs as that kernel does.  The others sum
-//    in one, which is less exact.
-//  * fp16 with a max pool behind it in mind: not variant 6.  The pooled launch promises the bits of the two calls and follows the
-//    order of one run of sums, not the exchange of four.
-//  * 256 x 64 tiles with 64-byte chunks: only two to a CU, by their number and by their LDS (alone they wait at every barrier:
-//    12 x 20 x 18, 512 -> 512 38.6 us against 32.4 as 128 x 64).
-//  * 64 -> 64 channels in fp16, 128-position tiles for between one and about three rounds of the chip's 512 workgroup slots: the
-//    256-position tile halves the rounds (56 x 56 at batch 32: 13.9 against 14.9 us).
-//  * int8 that gives the 256 x 128 tile of the implicit GEMM its 384 tiles stays there (512 -> 512 at 33 x 55, batch 18: 94
-//    against 110 us).
-// Fp16 at batch 32, graph-timed, before this kernel overlapped its operand reads with the matrix instructions and had the wider
-// tiles / now: 64 -> 64 at 224 x 224 208 (implicit GEMM) / 148 us, 64 -> 128 at 112 x 112 84 / 72, 128 -> 128 147 / 125, 128 -> 256 at
-// 56 x 56 81 / 67, 256 -> 256 127 / 120, 256 -> 512 at 28 x 28 66.6 / 60.4, 512 -> 512 126.5 / 109.6; 64 -> 64 at 56 x 56 14.5 / 13.9,
-// 128 -> 128 at 28 x 28 11.3 / 11.1, 512 -> 512 at 7 x 7 14.1 / 13.1.
-int conv_halo_pick(const ConvArgs& a, bool is_i8) {
-  if (a.R != 3 || a.S != 3 || a.C < 64) return -1;
-  const long flat = (long)a.N * (a.H + 1) * (a.W + 1), tiles_n = (a.K + 63) / 64;
-  if (((flat + 63) / 64) * tiles_n < 80 || !conv_halo_shape(a, is_i8)) return -1;
-  const long t128 = ((flat + 127) / 128) * tiles_n;
-  if (!is_i8 && a.C == 64 && a.K <= 64 && t128 > 512 && t128 <= 1700 && halo_fits(a, is_i8, 2)) return 2;
-  if (is_i8 && igemm_dma_wide(a)) return -1;
-  const float staged = igemm_dma_estimate(a, is_i8), small = conv_small_estimate(a, is_i8);
-  float best = 0.98f * (staged < small ? staged : small);
-  int pick = -1;
-  const bool pooled = !is_i8 && igemm_dma_pool_supported(a, false);
-  const int ve = is_i8 ? 16 : 8, rows = is_i8 ? (int)(sizeof(kCostI8) / sizeof(HaloCost)) : (int)(sizeof(kCostF16) / sizeof(HaloCost));
-  for (int i = 0; i < rows; ++i) {
-    const HaloCost& h = is_i8 ? kCostI8[i] : kCostF16[i];
-    const HaloTile& t = kHalo[h.v];
-    const int chunk = h.kp * BKV * ve;
-    if ((a.C == chunk) != h.one || a.C % chunk != 0 || (!is_i8 && small < staged && h.v != 6) || (pooled && h.v == 6)) continue;
-    const long tm = t.square ? (long)a.N * ((a.H + SQ - 1) / SQ) * ((a.W + SQ - 1) / SQ) : (flat + t.bm() - 1) / t.bm();
-    const long tiles = tm * ((a.K + t.bn() - 1) / t.bn());
-    if ((h.most && tiles > h.most) || ((h.v == 4 || h.v == 5) && tiles <= 256)) continue;
-    const float n = (float)((tiles + 255) / 256), x = (float)tiles * (1.f / 256.f), s = 9.f * (float)(a.C / chunk);
-    const float us = h.a + n * (h.b + h.c * s) + h.e * x * s;
-    if (us < best && chunk_planes(a, is_i8, h.v) == h.kp && halo_fits(a, is_i8, h.v, (h.v == 4 ? 80 : 160) * 1024)) {
-      best = us;
-      pick = h.v;
-    }
-  }
-  return pick;
-}
-
-int conv_halo_chunk(const ConvArgs& a, bool is_i8, int v) { return chunk_planes(a, is_i8, v) * BKV * (is_i8 ? 16 : 8); }
-
 // Layers that a caller's forced split of the reduction (n > 1) leaves whole.  Their 128 x 64 tiles give every CU one or fill the
 // 512 workgroup slots up to twice over (256 channels and more, 64 -> 64 in fp16: any number), so that there is nothing to gain
 // from partial sums and these would be large: 206 MB for 256 -> 256 at 56 x 56, batch 32 in two runs.  Outside this range a
@@ -712,6 +662,68 @@ bool conv_halo_keeps_whole(const ConvArgs& a, bool is_i8) {
   if (!is_i8 && (a.C >= 256 || thin)) return t128 >= 190;
   return t128 >= 190 && t128 <= (!is_i8 && a.C == 64 ? 1024 : 512);
 }
+
+// The variant the heuristic takes, or -1 to leave the layer to the other kernels: the least of the estimates above,
+// where it is below those of the implicit GEMM and of the small-tile kernel.
+//  * Below 80 tiles of 64 x 64 the small-tile kernel is the better one always (the search is not even begun: it costs
+//    an eager call about 0.2 us).
+//  * fp16, a layer the small-tile kernel would take: only variant 6, which sums in four runs as that kernel does.  The others sum
+//    in one, which is less exact.
+//  * fp16 with a max pool behind it in mind: not variant 6.  The pooled launch promises the bits of the two calls and follows the
+//    order of one run of sums, not the exchange of four.
+//  * 256 x 64 tiles with 64-byte chunks: only two to a CU, by their number and by their LDS (alone they wait at every barrier:
+//    12 x 20 x 18, 512 -> 512 38.6 us against 32.4 as 128 x 64).
+//  * 64 -> 64 channels in fp16, 128-position tiles for between one and about three rounds of the chip's 512 workgroup slots: the
+//    256-position tile halves the rounds (56 x 56 at batch 32: 13.9 against 14.9 us).
+//    Two of its workgroups have to fit a CU's LDS (images up to 86 wide): 34 x 23 x 121, 64 -> 56 13.9 us by the implicit GEMM, 17.0.
+//  * Layers that 128 x 64 tiles suit (conv_halo_keeps_whole) leave them only for a clear gain, since the estimates err by 10 %: for
+//    the implicit GEMM where it is estimated at 0.9 of their time (0.82 with its 64-byte chunks, whose estimates are low), for 16 x 16
+//    tiles at 0.95 (0.9).  Of 492 and 141 random layers that the plain minimum took away 42 % and 20 % became slower, by up to 24 %
+//    (int8 42 x 27 x 13, 576 -> 80 17.8 us, implicit GEMM 22.5); with the margins 0.4 % and 2 %.
+//  * int8, a single chunk, 64 x 64 tiles on images wider than 62, whose halos are three times the tile and more: only where all tiles
+//    fit the LDS of the chip at once (44 x 18 x 72, 128 -> 64 in 1026 tiles 10.9 us, implicit GEMM 9.2; 3 x 175 x 68, 128 -> 32 in 570
+//    7.0 and 8.1).
+//  * int8 that gives the 256 x 128 tile of the implicit GEMM its 384 tiles stays there (512 -> 512 at 33 x 55, batch 18: 94
+//    against 110 us).
+// Fp16 at batch 32, graph-timed, before this kernel overlapped its operand reads with the matrix instructions and had the wider
+// tiles / now: 64 -> 64 at 224 x 224 208 (implicit GEMM) / 148 us, 64 -> 128 at 112 x 112 84 / 72, 128 -> 128 147 / 125, 128 -> 256 at
+// 56 x 56 81 / 67, 256 -> 256 127 / 120, 256 -> 512 at 28 x 28 66.6 / 60.4, 512 -> 512 126.5 / 109.6; 64 -> 64 at 56 x 56 14.5 / 13.9,
+// 128 -> 128 at 28 x 28 11.3 / 11.1, 512 -> 512 at 7 x 7 14.1 / 13.1.
+int conv_halo_pick(const ConvArgs& a, bool is_i8) {
+  if (a.R != 3 || a.S != 3 || a.C < 64) return -1;
+  const long flat = (long)a.N * (a.H + 1) * (a.W + 1), tiles_n = (a.K + 63) / 64;
+  if (((flat + 63) / 64) * tiles_n < 80 || !conv_halo_shape(a, is_i8)) return -1;
+  const long t128 = ((flat + 127) / 128) * tiles_n;
+  if (!is_i8 && a.C == 64 && a.K <= 64 && t128 > 512 && t128 <= 1700 && halo_fits(a, is_i8, 2, 80 * 1024)) return 2;
+  if (is_i8 && igemm_dma_wide(a)) return -1;
+  const float staged = igemm_dma_estimate(a, is_i8), small = conv_small_estimate(a, is_i8);
+  const int ve = is_i8 ? 16 : 8;
+  const bool whole = conv_halo_keeps_whole(a, is_i8);
+  float best = whole ? staged * (a.C % (2 * BKV * ve) ? 1.f / 0.82f : 1.f / 0.9f) : 0.98f * staged;
+  if (best > 0.98f * small) best = 0.98f * small;
+  int pick = -1;
+  const bool pooled = !is_i8 && igemm_dma_pool_supported(a, false);
+  const int rows = is_i8 ? (int)(sizeof(kCostI8) / sizeof(HaloCost)) : (int)(sizeof(kCostF16) / sizeof(HaloCost));
+  for (int i = 0; i < rows; ++i) {
+    const HaloCost& h = is_i8 ? kCostI8[i] : kCostF16[i];
+    const HaloTile& t = kHalo[h.v];
+    const int chunk = h.kp * BKV * ve;
+    if ((a.C == chunk) != h.one || a.C % chunk != 0 || (!is_i8 && small < staged && h.v != 6) || (pooled && h.v == 6)) continue;
+    const long tm = t.square ? (long)a.N * ((a.H + SQ - 1) / SQ) * ((a.W + SQ - 1) / SQ) : (flat + t.bm() - 1) / t.bm();
+    const long tiles = tm * ((a.K + t.bn() - 1) / t.bn());
+    if ((h.most && tiles > h.most) || ((h.v == 4 || h.v == 5) && tiles <= 256)) continue;
+    const float n = (float)((tiles + 255) / 256), x = (float)tiles * (1.f / 256.f), s = 9.f * (float)(a.C / chunk);
+    const float us = (h.a + n * (h.b + h.c * s) + h.e * x * s) * (whole && h.v == 5 ? (a.C % (2 * BKV * ve) ? 1.f / 0.9f : 1.f / 0.95f) : 1.f);
+    const size_t most_lds = 160 * 1024 / (h.v == 4 ? 2 : is_i8 && h.v == 1 && h.one && a.W > 62 ? (tiles + 255) / 256 : 1);
+    if (us < best && chunk_planes(a, is_i8, h.v) == h.kp && halo_fits(a, is_i8, h.v, most_lds)) {
+      best = us;
+      pick = h.v;
+    }
+  }
+  return pick;
+}
+
+int conv_halo_chunk(const ConvArgs& a, bool is_i8, int v) { return chunk_planes(a, is_i8, v) * BKV * (is_i8 ? 16 : 8); }
 
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {
   const HaloTile& t = kHalo[v];
