@@ -1082,6 +1082,8 @@ static relay_status image_conv_args(const relay_conv2d_desc* d, bool pool, relay
   relay::StemArgs g;
   memset(&g, 0, sizeof(g));
   g.a = make_args(d, ho, wo);   // (the packed filters are those of the padded image's conv)
+  const int small = i8 ? -1 : relay::conv_small_pick(g.a, false);
+  g.runs = small >= 0 ? relay::conv_small_sums(g.a, small) : 1;
   g.a.C = d->c; g.a.S = d->s; g.a.H = d->h; g.a.W = d->w; g.a.ph = d->pad_h; g.a.pw = d->pad_w;
   g.Hp = (ho - 1) / 2 + 1;
   g.Wp = (wo - 1) / 2 + 1;

@@ -532,6 +532,8 @@ float conv_small_estimate(const ConvArgs& a, bool is_i8) {
   return small_considered(a, is_i8) && small_best(a, is_i8, false, &us) >= 0 ? us : INFINITY;
 }
 
+int conv_small_sums(const ConvArgs& a, int v) { return kSmall[v].w * small_runs(a, false, v, false); }
+
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {
   const SmallTile& t = kSmall[v];
   const int u = small_unit(a, is_i8, v);

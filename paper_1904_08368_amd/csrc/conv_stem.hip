@@ -6,8 +6,10 @@
 // output channels.  The filters go straight to LDS; the image patch goes through registers, where the channel planes are
 // interleaved to four channels per pixel, so that a filter row is a run of 16-byte operands along a patch row, as in the pooled
 // tile of the staged kernel.  The finished tile takes the place of both, and leaves it in whole 8-channel vectors.  Sums per
-// output: filter row by filter row, in one accumulator, or (RUNS = 2, the tiles for few outputs) in one for each half of the
-// rows, as the small-tile kernel's two waves do.
+// output: filter row by filter row, in one accumulator, or (MANY, the tiles for few outputs) in runs of per_run rows whose sums are
+// added up in order: two, or as many as the waves of the small-tile kernel where the conv over the padded copy runs there, since
+// a run's rounding error grows with its length (rms of the fp32 errors against 64 bits, 8 x 8 windows of 4 channels: one run 1.48e-7, two
+// 1.14e-7, four 9.9e-8, which is also that of the small-tile kernel's four waves).
 //
 // What bounds it: latency -- the patch, then the stores -- hidden by three or four workgroups per CU.  (Workgroups that walk over
 // several tiles, filters kept and the next patch in registers meanwhile, have room for two: 31.6 us against 25.4 for ResNet-18's
@@ -21,7 +23,7 @@
 namespace relay {
 namespace {
 
-template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, int RUNS, bool POOL, bool PAIRS, int NI>
+template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, bool MANY, bool POOL, bool PAIRS, int NI>
 __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 || NI > 10 ? 3 : 4) void conv_stem_kernel(const StemArgs g) {
   constexpr int NT = 64 * WM * WN, NW = WM * WN, ES = IS_I8 ? 1 : 2, VE = 16 / ES, PXB = 4 * ES;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32, WTM = TM * 32, WTN = TN * 32;
@@ -177,40 +179,48 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 || NI > 10 ? 3 : 4) void 
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = Mma<IS_I8>::mma(wf[b][k][tn], xf[b][k][tm], acc[tn][tm]);
   };
-  auto reduce_rows = [&](int lo, int hi, auto wide_tag) {   // filter rows [lo, hi)
-    if (lo >= hi) return;
-    operands(lo, 0, wide_tag);
-    for (int r = lo; r < hi; r += 2) {
-      if (r + 1 < hi) operands(r + 1, 1, wide_tag);
-      multiply(0);
-      if (r + 2 < hi) operands(r + 2, 0, wide_tag);
-      if (r + 1 < hi) multiply(1);
-    }
-  };
-  acc_t first[RUNS == 2 ? TN : 1][RUNS == 2 ? TM : 1];
-  // (the halves as two turns of one loop: its code is fetched once)
-#pragma unroll 1
-  for (int u = 0; u < RUNS; ++u) {
-    const int half = RUNS == 2 ? (a.R + 1) / 2 : a.R, lo = u ? half : 0, hi = u ? a.R : half;
-    if (wide) reduce_rows(lo, hi, std::integral_constant<bool, !IS_I8>{});
-    else reduce_rows(lo, hi, std::false_type{});
-    if constexpr (RUNS == 2) {
-      if (u == 0) {
+  acc_t sum[MANY ? TN : 1][MANY ? TM : 1];   // ... of the runs behind
+  auto end_run = [&]() {
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-          for (int tm = 0; tm < TM; ++tm) first[tn][tm] = acc[tn][tm];
-        clear();
-      }
-    }
-  }
-  if constexpr (RUNS == 2) {
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
+    for (int tn = 0; tn < (MANY ? TN : 0); ++tn)
 #pragma unroll
       for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[tn][tm][e] = first[tn][tm][e] + acc[tn][tm][e];
+        for (int e = 0; e < 16; ++e) sum[tn][tm][e] += acc[tn][tm][e];
+    clear();
+  };
+  if constexpr (MANY) {
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm) sum[tn][tm] = acc[tn][tm];
+  }
+  auto reduce_rows = [&](auto wide_tag) {
+    operands(0, 0, wide_tag);
+    int left = g.per_run;   // rows until the run ends
+    for (int r = 0; r < a.R; r += 2) {
+      if (r + 1 < a.R) operands(r + 1, 1, wide_tag);
+      multiply(0);
+      if (MANY && --left == 0) {
+        end_run();
+        left = g.per_run;
+      }
+      if (r + 2 < a.R) operands(r + 2, 0, wide_tag);
+      if (r + 1 < a.R) multiply(1);
+      if (MANY && --left == 0) {   // (behind an odd number of rows it ends a run of nothing)
+        end_run();
+        left = g.per_run;
+      }
+    }
+  };
+  if (wide) reduce_rows(std::integral_constant<bool, !IS_I8>{});
+  else reduce_rows(std::false_type{});
+  if constexpr (MANY) {
+    end_run();
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = sum[tn][tm];
   }
 
   meet();   // (the tile takes the place of filters and patch)
@@ -373,9 +383,9 @@ bool stem_geom(StemArgs& g, bool is_i8, int t, size_t& lds_bytes, int& items_per
   return items_per_thread <= (g.pairs ? 10 : 20) && lds_bytes <= 160 * 1024;
 }
 
-template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, int RUNS, bool POOL, bool PAIRS, int NI>
+template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, bool MANY, bool POOL, bool PAIRS, int NI>
 hipError_t launch_stem_items(const StemArgs& g, size_t lds_bytes, hipStream_t st) {
-  auto kern = conv_stem_kernel<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, RUNS, POOL, PAIRS, NI>;
+  auto kern = conv_stem_kernel<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, PAIRS, NI>;
   static std::atomic<bool> raised{false};  // dynamic LDS above the default limit has to be asked for once per kernel
   if (!raised.load(std::memory_order_acquire)) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -387,22 +397,22 @@ hipError_t launch_stem_items(const StemArgs& g, size_t lds_bytes, hipStream_t st
   return hipGetLastError();
 }
 
-template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, int RUNS, bool POOL>
+template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, bool MANY, bool POOL>
 hipError_t launch_stem_one(const StemArgs& g, size_t lds, int items, hipStream_t st) {
   if (g.pairs)
-    return items <= 3 ? launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, RUNS, POOL, true, 3>(g, lds, st)
-                      : launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, RUNS, POOL, true, 10>(g, lds, st);
-  return items <= 6 ? launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, RUNS, POOL, false, 6>(g, lds, st)
-                    : launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, RUNS, POOL, false, 20>(g, lds, st);
+    return items <= 3 ? launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, true, 3>(g, lds, st)
+                      : launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, true, 10>(g, lds, st);
+  return items <= 6 ? launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, false, 6>(g, lds, st)
+                    : launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, false, 20>(g, lds, st);
 }
 
 template <bool IS_I8, int KS>
 hipError_t launch_stem_plain(const StemArgs& g, int t, size_t lds, int items, hipStream_t st) {
-  if (t == 0) return launch_stem_one<IS_I8, 4, 1, 2, 2, 16, 16, KS, 1, false>(g, lds, items, st);
-  if (t == 2) return launch_stem_one<IS_I8, 2, 2, 1, 1, 8, 8, KS, 2, false>(g, lds, items, st);
+  if (t == 0) return launch_stem_one<IS_I8, 4, 1, 2, 2, 16, 16, KS, false, false>(g, lds, items, st);
+  if (t == 2) return launch_stem_one<IS_I8, 2, 2, 1, 1, 8, 8, KS, true, false>(g, lds, items, st);
   if constexpr (!IS_I8) {
-    if (t == 1) return launch_stem_one<false, 4, 1, 2, 1, 16, 16, KS, 1, false>(g, lds, items, st);
-    if (t == 3) return launch_stem_one<false, 2, 1, 1, 1, 8, 8, KS, 2, false>(g, lds, items, st);
+    if (t == 1) return launch_stem_one<false, 4, 1, 2, 1, 16, 16, KS, false, false>(g, lds, items, st);
+    if (t == 3) return launch_stem_one<false, 2, 1, 1, 1, 8, 8, KS, true, false>(g, lds, items, st);
   }
   return hipErrorInvalidValue;
 }
@@ -414,8 +424,14 @@ int stem_pick(StemArgs& g, bool is_i8, bool pool, size_t& lds, int& items) {
   // Small tiles until the large ones occupy half the chip.  In networks, the copy, the conv (and the pool) apart / this launch: 7x7 / 2 with
   // pool, batch 1 fp16 9.6 / 7.6 us, int8 8.5 / 5.2, int8 batch 16 18.7 / 13.8, fp16 batch 7 of 197 x 251 18.9 / 12.6, batch 32 28.5 /
   // 25.4; 3x3 / 2 of 163 x 206, batch 11 11.2 / 7.1; 3x3 of 224 x 224, batch 32 71.1 / 57.0; 8x8 / 4 of one frame 5.7 / 5.7 and a launch less.
-  if (stem_geom(g, is_i8, large, lds, items) && g.tiles * tn >= 128) return large;
-  if (stem_geom(g, is_i8, small, lds, items)) return small;
+  // Also where the conv over the padded copy sums in several runs, whatever their number.
+  const bool fits = stem_geom(g, is_i8, large, lds, items);
+  if (fits && g.runs <= 1 && g.tiles * tn >= 128) return large;
+  if (stem_geom(g, is_i8, small, lds, items)) {
+    const int runs = g.runs > 2 ? g.runs : 2;
+    g.per_run = (g.a.R + runs - 1) / runs;
+    return small;
+  }
   return -1;
 }
 
@@ -436,8 +452,8 @@ hipError_t launch_conv_stem(const StemArgs& s, bool is_i8, bool pool, hipStream_
   size_t lds;
   int items;
   const int t = stem_pick(g, is_i8, pool, lds, items);
-  if (t == 4) return is_i8 ? launch_stem_one<true, 4, 1, 2, 2, 15, 17, 1, 1, true>(g, lds, items, st) : launch_stem_one<false, 4, 1, 2, 2, 15, 17, 2, 1, true>(g, lds, items, st);
-  if (t == 5) return is_i8 ? launch_stem_one<true, 2, 2, 1, 1, 7, 9, 1, 2, true>(g, lds, items, st) : launch_stem_one<false, 2, 2, 1, 1, 7, 9, 2, 2, true>(g, lds, items, st);
+  if (t == 4) return is_i8 ? launch_stem_one<true, 4, 1, 2, 2, 15, 17, 1, false, true>(g, lds, items, st) : launch_stem_one<false, 4, 1, 2, 2, 15, 17, 2, false, true>(g, lds, items, st);
+  if (t == 5) return is_i8 ? launch_stem_one<true, 2, 2, 1, 1, 7, 9, 1, true, true>(g, lds, items, st) : launch_stem_one<false, 2, 2, 1, 1, 7, 9, 2, true, true>(g, lds, items, st);
   if (t < 0) return hipErrorInvalidValue;
   if (is_i8) return launch_stem_plain<true, 1>(g, t, lds, items, st);
   return ksteps(g.a, false) == 1 ? launch_stem_plain<false, 1>(g, t, lds, items, st) : launch_stem_plain<false, 2>(g, t, lds, items, st);

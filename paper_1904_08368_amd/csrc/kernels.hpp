@@ -155,6 +155,7 @@ int conv_small_variant_count();
 hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStream_t st, bool dense = false);
 bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, int own_of_b);
 hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, hipStream_t st);
+int conv_small_sums(const ConvArgs& a, int variant);   // in how many runs it sums an fp16 conv
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
 // A first-layer conv on the NCHW image (conv_stem.hip): `a` describes the conv over the image itself (x: the image, H and W its
 // extents, C its channels, Kp the packed filters' pitch; y: the conv outputs or NULL); the rest is set by the launcher.
@@ -162,6 +163,8 @@ struct StemArgs {
   ConvArgs a;
   void* y_pooled;
   int Hp, Wp;                         // extents of the pooled outputs
+  int runs;                           // in how many runs the conv over the padded copy sums (fp16; int8 sums are exact): never fewer here
+  int per_run;                        // filter rows of a run (tiles for few outputs)
   int tiles, tiles_img, tiles_row;
   int pitch, patch_bytes, cst_at;     // pixels of a patch row, bytes of the patch, where the constants stand in LDS
   int pairs, per_row, items;          // loads of the patch: pixel pairs or pixels, per row, in all

@@ -96,3 +96,37 @@ def test_image_conv_argument_checks():
                          ((x, w + 8, y, None), 5), ((x, w, y + 8, None), 5)):
         got = B.lib().relay_fused_image_conv2d(C.byref(desc()), args[0], args[1], None, None, None, args[2], args[3], None)
         assert got == status, (status, got, B.lib().relay_last_error())
+
+
+# deep Q-network, ResNet's and VGG's first layers at sizes where the conv over the padded copy splits its sums over four waves (and
+# one where it does not): the fp32 sums against 64 bits, seen through a scale and shift that leave little but their error
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,c,h,w,k,r,st,pad,pooled", [(11, 4, 84, 84, 32, 8, 4, 0, False), (32, 4, 84, 84, 32, 8, 4, 0, False), (8, 3, 64, 64, 64, 7, 2, 3, True),
+                                                       (2, 3, 128, 128, 64, 7, 2, 3, True), (1, 3, 64, 64, 64, 3, 1, 1, False), (2, 3, 224, 224, 64, 7, 2, 3, True)])
+def test_sums_are_no_less_exact_than_those_of_the_separate_calls(n, c, h, w, k, r, st, pad, pooled):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1904_08368_amd import binding as B
+    from tests import gpu_util as G
+    d = B.conv_desc(n, c, h, w, k, r, r, st, pad, B.RELAY_F16, B.RELAY_NHWC4_PADDED, B.HAS_BN | B.RELU)
+    ho, wo = B.relay_conv2d_out_shape(d)
+    oy, ox = ho // 2, wo // 2
+    errors = ([], [])
+    for seed in range(40):
+        g = np.random.default_rng(seed)
+        x = np.broadcast_to(g.standard_normal((1, c, h, w)).astype(np.float16), (n, c, h, w))
+        wt = (g.standard_normal((k, c, r, r)) * np.sqrt(2.0 / (c * r * r))).astype(np.float16)
+        y0, x0 = oy * st - pad, ox * st - pad
+        e = 2.0 ** 20 * np.einsum("kcrs,crs->k", wt.astype(np.float64), x[0, :, y0:y0 + r, x0:x0 + r].astype(np.float64))
+        # 2^20 acc + 8 - round(e): a whole number below 2^24 is taken from a sum beside it, exact in fp32, and 2^-7 is fp16's step at 8
+        p = dict(b=None, sc=torch.full((k,), 2.0 ** 20, device=G.DEV), sf=G.up((8.0 - np.round(e)).astype(np.float32)))
+        xd, wp, y, yp = _calls(G, B, False, x, wt, p, d, ho, wo, pooled)
+        z, zp = torch.empty_like(y), torch.empty_like(yp)
+        B.relay_fused_image_conv2d(d, xd, wp, None, p["sc"], p["sf"], z, zp if pooled else None)
+        torch.cuda.synchronize()
+        for out, t in zip(errors, (y, z)):
+            out.append(t[n - 1, oy, ox].double().cpu().numpy() - 8.0 + np.round(e) - e)
+    two, one = (np.sqrt(np.mean(np.concatenate(v) ** 2)) * 2.0 ** -20 for v in errors)
+    print(f"[observed] rms of the sums' errors, {n} x {h} x {w}, {r} x {r}: separate calls {two:.2e}, one launch {one:.2e}")
+    # (the same sums in as many runs: only how a matrix instruction adds up its 16 or 32 products differs; half the runs are 1.08 to 1.5 times)
+    assert one <= 1.03 * two
