@@ -1161,6 +1161,15 @@ bool narrow_better(const ConvArgs& a, bool is_i8) {
   return a.C % 128 == 0 || (a.C % 64 == 0 && a.Kred / 64 >= 8);
 }
 
+// The same of two convs in one launch.  Together they may give a CU two tiles where one kind is short: it then runs beside the
+// other's, whose own loads leave it room (graph-timed pairs, 64 x 64 tiles / these: 3x3 / 2 and 1x1 / 2, 448 tiles of 512 -> 512 15.97 / 12.0
+// us, 304 of 128 -> 128 7.08 / 5.41, 512 of 256 -> 512 10.2 / 8.8; two 1x1 / 2, 256 of 512 -> 512 5.18 / 4.29, but 272 of 128 -> 256 4.11 /
+// 5.24, 352 of 512 -> 512 5.22 / 6.33).
+bool narrow_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8) {
+  if (!narrow_better(a, is_i8) || !narrow_fits(b, is_i8) || narrow_tiles(b) > 256 || narrow_planes(a) != narrow_planes(b)) return false;
+  return narrow_tiles(a) + narrow_tiles(b) <= 256 || a.Kred >= 4 * b.Kred || b.Kred >= 4 * a.Kred;
+}
+
 int resolve_tile(const ConvArgs& a, bool is_i8, int tile) {
   if (tile_fits(a, is_i8, tile)) return tile;
   return narrow_better(a, is_i8) ? kNarrow : pick_tile(a, is_i8);
@@ -1193,8 +1202,8 @@ int igemm_dma_pair_tile(const ConvArgs& a, const ConvArgs& b, bool is_i8) {
 }
 
 hipError_t launch_conv_igemm_dma_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int tile, hipStream_t st) {
-  // (same sums, whatever the tile; ResNet-18's first convs and shortcuts of a stage, 64 x 64 tiles / 32 x 32: see narrow_better)
-  if (narrow_better(a, is_i8) && narrow_fits(b, is_i8) && narrow_tiles(b) <= 256 && narrow_planes(a) == narrow_planes(b)) return launch_narrow(a, &b, st);
+  // (same sums, whatever the tile)
+  if (narrow_pair(a, b, is_i8)) return launch_narrow(a, &b, st);
   return is_i8 ? launch_pair_typed<true>(a, b, tile, st) : launch_pair_typed<false>(a, b, tile, st);
 }
 

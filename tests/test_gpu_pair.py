@@ -14,7 +14,10 @@ SHAPES = [(1, 128, 28, 28, (256, 256), (3, 1), 2, True, True), (1, 256, 14, 14, 
           (1, 32, 5, 3, (8, 24), (1, 3), 1, False, True), (3, 192, 28, 28, (256, 64), (3, 1), 2, True, True),
           (1, 128, 28, 28, (64, 64), (1, 1), 1, True, True), (2, 256, 28, 28, (256, 256), (1, 1), 1, True, True),
           (1, 64, 15, 13, (72, 136), (3, 3), 1, True, True), (1, 128, 14, 14, (128, 64), (3, 3), 1, True, True),
-          (2, 96, 9, 11, (40, 40), (1, 1), 1, True, False)]
+          (2, 96, 9, 11, (40, 40), (1, 1), 1, True, False),
+          # 32 x 32 tiles for a pair: 256 of equal reductions, 272 (which is too many), 304 of unequal ones
+          (2, 512, 12, 19, (1024, 1024), (1, 1), 2, True, True), (1, 128, 48, 44, (256, 256), (1, 1), 2, True, True),
+          (7, 128, 18, 37, (128, 128), (3, 1), 2, True, True)]
 
 def _member(B, G, g, i8, n, c, h, w, k, r, st, relu, res):
     pad = r // 2
