@@ -361,7 +361,7 @@ relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* 
 
 /* relay_global_avgpool and relay_fused_dense_bias_act on its result as one launch (one fused function of paper Section 4.1), both
  * results written: pooled [n, c] as by the first (up to the grouping of its fp32 sums), y [n, units] from those fp16 values.  F16;
- * x [n, hw, c], w [units, c]; c % 8 == 0, c <= 2048; x, w and pooled 16-byte aligned.  relay_avgpool_dense_pays writes 1 where
+ * x [n, hw, c], w [units, c]; c % 8 == 0, c <= 2048, n * ceil(units / 8) < 2^23; x, w and pooled 16-byte aligned.  relay_avgpool_dense_pays writes 1 where
  * that is faster than the two launches. */
 relay_status relay_avgpool_dense_pays(int32_t dtype, int32_t n, int32_t c, int32_t hw, int32_t units, int32_t* pays);
 relay_status relay_fused_avgpool_dense(int32_t dtype, int32_t n, int32_t c, int32_t hw, int32_t units, const void* x, const void* w,
@@ -376,7 +376,8 @@ relay_status relay_fused_avgpool_dense(int32_t dtype, int32_t n, int32_t c, int3
  *   x_nchw    the image [n, c, h, w], aligned to two elements
  *   y         the conv outputs NHWC, or NULL if only the pooled ones are wanted
  *   y_pooled  [n, (ho - 1) / 2 + 1, (wo - 1) / 2 + 1, k] NHWC, or NULL: no pool.  F16 16-byte, I8 8-byte aligned
- * relay_image_conv2d_supported writes 1 if these calls take the descriptor (with a pool if `pooled`), else 0; the calls
+ * relay_image_conv2d_supported writes 1 if these calls take the descriptor (with a pool if `pooled`; n below 2^24 to 2^25
+ * workgroups of outputs), else 0; the calls
  * themselves then return an error and launch nothing. */
 relay_status relay_image_conv2d_supported(const relay_conv2d_desc* d, int32_t pooled, int32_t* supported);
 relay_status relay_fused_image_conv2d(const relay_conv2d_desc* d, const void* x_nchw, const void* w_packed, const float* bias,

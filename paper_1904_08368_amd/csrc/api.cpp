@@ -1336,6 +1336,7 @@ static relay_status check_avgpool_dense(int32_t dtype, int32_t n, int32_t c, int
   if (!relay::avgpool_dense_supported(n, c, hw, units)) return fail(RELAY_ERR_UNSUPPORTED, "average pool with dense takes c %% 8 == 0, c <= 2048 (c=%d)", c);
   if ((long)n * hw > kMaxElems || (long)n * hw * c > kMaxElems || (long)units * c > kMaxElems || (long)n * units > kMaxElems)
     return fail(RELAY_ERR_SHAPE, "tensor exceeds 2^31-1 elements");
+  if (!relay::avgpool_dense_fits(n, units)) return fail(RELAY_ERR_SHAPE, "average pool with dense: n=%d units=%d exceed one launch", n, units);
   return RELAY_OK;
 }
 

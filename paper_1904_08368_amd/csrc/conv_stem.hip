@@ -372,7 +372,8 @@ bool stem_geom(StemArgs& g, bool is_i8, int t, size_t& lds_bytes, int& items_per
   const int cy = pool ? s.tyc - 1 : s.tyc, cx = pool ? s.txc - 1 : s.txc;
   g.tiles_row = (a.Wo + cx - 1) / cx;
   g.tiles_img = ((a.Ho + cy - 1) / cy) * g.tiles_row;
-  if ((long)a.N * g.tiles_img >= (1L << 30)) return false;
+  // (a launch holds fewer than 2^32 threads, and 65535 tiles of channels)
+  if ((long)a.N * g.tiles_img * s.threads() >= (1L << 32) || (a.K + s.bn() - 1) / s.bn() > 65535) return false;
   g.tiles = a.N * g.tiles_img;
   g.fd_img = make_fastdiv((uint32_t)g.tiles_img);
   g.fd_row = make_fastdiv((uint32_t)g.tiles_row);

@@ -93,6 +93,9 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t st) {
 
 bool avgpool_dense_supported(int n, int c, int hw, int units) { return c % 8 == 0 && c <= 2048; }
 
+// (a launch holds fewer than 2^32 threads)
+bool avgpool_dense_fits(int n, int units) { return (long)n * ((units + kWaves - 1) / kWaves) * kThreads < (1L << 32); }
+
 // While its workgroups fit the CUs at once and an image is quickly read by each of them.  Two launches / this one, us, one behind the
 // other: one image and 1000 units, 49 positions of 512 channels 5.6 / 4.0, 100 of 512 5.9 / 4.8, 144 of 512 5.5 / 6.0, 49 of 1024 5.7 /
 // 5.2, 16 of 2048 6.1 / 4.8, 49 of 2048 6.4 / 7.2; two images of 49 x 512 5.6 / 4.2; 100 units, 784 x 64, 16 images 6.5 / 5.5.

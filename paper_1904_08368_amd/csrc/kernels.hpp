@@ -216,6 +216,7 @@ hipError_t launch_fold_bias(int K, const float* bias, const float* scale, const 
                             hipStream_t st);
 // global average pool + dense, fp16, one launch (head.hip)
 bool avgpool_dense_supported(int n, int c, int hw, int units);
+bool avgpool_dense_fits(int n, int units);
 bool avgpool_dense_pays(int n, int c, int hw, int units);
 hipError_t launch_avgpool_dense(int n, int c, int hw, int units, const void* x, const void* w, const float* bias, int act, void* pooled,
                                 void* y, hipStream_t st);

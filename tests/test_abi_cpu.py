@@ -541,3 +541,9 @@ def test_scheme_entry_points_validate_on_the_host():
         with pytest.raises(B.RelayError) as e:
             B.relay_quantize_multiplier(bad)
         assert e.value.status == 2
+
+
+def test_average_pool_with_dense_is_held_to_one_launch():
+    call = lambda n, units: _status("relay_fused_avgpool_dense", B.RELAY_F16, n, 8, 1, units, FAKE, FAKE + 4096, None, 0, FAKE + 8192, None, None)
+    assert call(1 << 23, 8) == 2 and call(1 << 20, 64) == 2 and call(10, 1 << 27) == 2
+    assert call((1 << 23) - 1, 8) == 1      # (y is NULL: past the check of the shape)

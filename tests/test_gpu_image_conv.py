@@ -91,6 +91,12 @@ def test_image_conv_argument_checks():
         assert not B.relay_image_conv2d_supported(bad, False)
     assert not B.relay_image_conv2d_supported(desc(flags=0), True)      # a float pool without relu
 
+    # more workgroups than one launch holds; the most of which the smaller ones still fit
+    assert not B.relay_image_conv2d_supported(desc(n=20000000, c=1, h=1, w=2, k=64, r=1, st=1, pad=0), False)
+    assert B.relay_image_conv2d_supported(desc(n=16000000, c=1, h=1, w=2, k=64, r=1, st=1, pad=0), False)
+    assert B.relay_image_conv2d_supported(desc(n=20000000, c=1, h=1, w=2, k=8, r=1, st=1, pad=0), False)
+    assert not B.relay_image_conv2d_supported(desc(c=1, h=1, w=2, k=5000000, r=1, st=1, pad=0), False)
+
     x, w, y = 0x7F0000000000, 0x7F0000100000, 0x7F0000200000     # (never dereferenced: every call is refused)
     for args, status in (((None, w, y, None), 1), ((x, w, None, None), 1), ((x, w, x, None), 4), ((x, w, y, y), 4), ((x + 2, w, y, None), 5),
                          ((x, w + 8, y, None), 5), ((x, w, y + 8, None), 5)):
