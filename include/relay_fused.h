@@ -352,9 +352,11 @@ relay_status relay_qconv2d_requant_maxpool(const relay_conv2d_desc* d, const int
                                            void* hip_stream);
 
 /* relay_fused_conv2d_bias_bn_relu with the 2x2 / stride 2 / pad 0 max pool behind it in the same launch (the fused functions
- * of paper Section 4.1), both results written: those of the two separate calls bit for bit.  F16 NHWC, 3x3 / stride 1 / pad 1 with RELU, no residual, c % 32 == 0, k % 8 == 0,
+ * of paper Section 4.1), both results written: bit for bit those of the two separate calls where relay_conv2d_pool2x2_pays writes 1, else
+ * up to the grouping of the fp32 sums.  F16 NHWC, 3x3 / stride 1 / pad 1 with RELU, no residual, c % 32 == 0, k % 8 == 0,
  * h and w even; y [n, h, w, k], y_pooled [n, h/2, w/2, k], 16-byte aligned.  relay_conv2d_pool2x2_pays writes 1 where the
- * separate conv would take the kernel that this call runs (else the two launches may be the faster ones, or the call is refused). */
+ * separate conv would take the kernel that this call runs (else the two launches may be the faster ones, or the call is refused).
+ * Under a forced tile or split (relay_set_conv_tile, relay_set_conv_split) that gives the conv another kernel it runs as the two launches. */
 relay_status relay_conv2d_pool2x2_pays(const relay_conv2d_desc* d, int32_t* pays);
 relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* x, const void* w_packed, const float* bias,
                                         const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream);
@@ -574,6 +576,11 @@ relay_status relay_set_conv_tile(int32_t tile);
  * all compute units stays whole at any setting (relay_workspace_bytes writes 0).  relay_workspace_bytes
  * called from the same thread follows the setting. */
 relay_status relay_set_conv_split(int32_t split);
+/* Whether one of the two settings above is in force in the calling thread (paper Section 4.1, "Lowering", as above): forced = 1, else 0.
+ * Dedicated entry points that run a conv as part of a larger launch (with a max pool, behind a depthwise conv, on the image) have
+ * kernels of their own and pass the settings by; a caller that wants them obeyed makes the separate calls then, as FusedNet
+ * does for a first layer on the image.  relay_conv2d_pair and relay_fused_conv2d_pool2x2 make them by themselves. */
+relay_status relay_conv_forced(int32_t* forced);
 /* Tuning aid (paper Section 4.1, "Lowering", as above), thread-local: upper bound on the number of
  * workgroups in the grid of the persistent 3x3 stride-1 kernel, whose workgroups each walk a list
  * of output tiles (0 = one per workgroup slot of the chip, the default).  A smaller grid leaves

@@ -105,6 +105,7 @@ SIGNATURES = {
     "relay_probe_grid_barrier": [_I, _I, C.c_uint32, _P, _P, _P],
     "relay_set_conv_tile": [_I],
     "relay_set_conv_split": [_I],
+    "relay_conv_forced": [C.POINTER(_I)],
     "relay_set_conv_workgroups": [_I],
     "relay_conv2d_kernel_name": [_DP, C.c_char_p, _SZ],
     "relay_dwconv_pwconv_kernel_name": [_DP, C.c_int32, C.c_char_p, _SZ],
@@ -532,3 +533,9 @@ def relay_set_conv_workgroups(workgroups: int) -> None:
 
 def relay_set_conv_split(split: int) -> None:
     _check(lib().relay_set_conv_split(split))
+
+
+def relay_conv_forced() -> bool:
+    out = C.c_int32(0)
+    _check(lib().relay_conv_forced(C.byref(out)))
+    return bool(out.value)

@@ -349,6 +349,12 @@ relay_status relay_set_conv_split(int32_t split) {
   return RELAY_OK;
 }
 
+relay_status relay_conv_forced(int32_t* forced) {
+  if (!forced) return fail(RELAY_ERR_NULL, "forced is NULL");
+  *forced = g_force_tile != -1 || g_force_split != 0 ? 1 : 0;
+  return RELAY_OK;
+}
+
 // Takes the caller's workspace into the arguments if this layer splits its reduction.
 static relay_status use_workspace(relay::ConvArgs& a, bool is_i8, void* workspace, size_t workspace_bytes) {
   a.split = 1;
@@ -1038,6 +1044,10 @@ relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* 
   if (y == x || y_pooled == x || y == y_pooled) return fail(RELAY_ERR_UNSUPPORTED, "an output must not alias the input or the other output");
   if (!aligned(x, 16) || !aligned(w_packed, 16) || !aligned(y, 16) || !aligned(y_pooled, 16))
     return fail(RELAY_ERR_ALIGN, "fp16 tensors must be 16-byte aligned");
+  if ((g_force_tile != -1 || g_force_split != 0) && (small_choice(a, false) >= 0 || halo_choice(a, false) != 5)) {
+    st = relay_fused_conv2d_bias_bn_relu(d, x, w_packed, bias, bn_scale, bn_shift, nullptr, y, nullptr, 0, hip_stream);
+    return st != RELAY_OK ? st : relay_maxpool2d(RELAY_F16, d->n, d->k, d->h, d->w, 2, 2, 0, y, y_pooled, hip_stream);
+  }
   a.x = x; a.w = w_packed; a.y = y; a.bias = bias; a.scale = bn_scale; a.shift = bn_shift;
   finish_args(a);
   return device_status(relay::launch_conv_halo_pool2(a, y_pooled, static_cast<hipStream_t>(hip_stream)), "conv2d with a 2x2 pool launch");

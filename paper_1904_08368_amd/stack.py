@@ -520,45 +520,18 @@ class FusedNet:
         first conv: both read the block input, neither reads the other.  The fork event is
         recorded BEFORE that first conv is enqueued, so the side stream waits only for the
         producer of the block input."""
-        if not self.side_calls and not self.pairs and not self.stem and not self.merged:
-            for fn, args in self.calls:
-                fn(*args)
-            return
-        done = 0
-        if self.stem and len(self.calls) >= len(self.stem[0]) and all(a is b for a, b in zip(self.stem[0], self.calls)) and \
-                not any(i <= len(self.stem[0]) for i in self.side_calls):
-            self.stem[1](*self.stem[2])
-            done = len(self.stem[0])
-        # (calls share a launch only while all entries are those it was made for: `calls` may be edited, entries wrapped or cut off)
-        merged_at = lambda i: (m := self.merged.get(i)) and len(self.calls) >= i + len(m[0]) and \
-            all(a is b for a, b in zip(m[0], self.calls[i:])) and m
         if not self.side_calls:
-            i = done
-            while i < len(self.calls):
-                pair, merged = self.pairs.get(i), merged_at(i)
-                if merged:
-                    merged[1](*merged[2])
-                    i += len(merged[0])
-                elif pair and len(self.calls) > i + 1 and self.calls[i] is pair[0] and self.calls[i + 1] is pair[1]:
-                    B.relay_conv2d_pair(pair[0][1], pair[1][1])
-                    i += 2
-                else:
-                    fn, args = self.calls[i]
+            if not self.pairs and not self.stem and not self.merged:
+                for fn, args in self.calls:
                     fn(*args)
-                    i += 1
+                return
+            for _, _, fn, args in self._steps():
+                fn(*args)
             return
         main = torch.cuda.current_stream()
         pending = fork = None
-        for i, (fn, args) in enumerate(self.calls):
-            if i < done:
-                continue
-            merged = merged_at(i)
-            if merged:      # (only where no fork or join falls between its calls, or behind the last of them)
-                last = i + len(merged[0]) - 1
-                if not any(j in self.side_calls for j in range(i, last + 2)) and not any(j in self.join_before for j in range(i + 1, last + 1)):
-                    fn, args = merged[1:]
-                    done = last + 1
-            if i + 1 in self.side_calls:      # the next call runs beside this one
+        for i, n, fn, args in self._steps():
+            if i + n in self.side_calls:      # the next call runs beside this one
                 fork = torch.cuda.Event()
                 fork.record(main)
             if i in self.side_calls:
@@ -574,6 +547,35 @@ class FusedNet:
             fn(*args)
         if pending is not None:
             main.wait_event(pending)
+
+    def _steps(self):
+        """(first call, number of calls, function, arguments) of every launch a run makes.  Calls share one only while all entries
+        are those it was made for: `calls` may be edited, entries wrapped or cut off."""
+        calls, steps, i = self.calls, [], 0
+        same = lambda at, entries: len(calls) >= at + len(entries) and all(a is b for a, b in zip(entries, calls[at:]))
+        # (a forced tile or split of the calling thread is for the conv of the list, which the image's launch would pass by)
+        if self.stem and same(0, self.stem[0]) and not any(j <= len(self.stem[0]) for j in self.side_calls) and not B.relay_conv_forced():
+            i = len(self.stem[0])
+            steps.append((0, i) + tuple(self.stem[1:]))
+        while i < len(calls):
+            merged, pair = self.merged.get(i), self.pairs.get(i)
+            if merged and same(i, merged[0]) and not self._crosses_streams(i, len(merged[0])):
+                steps.append((i, len(merged[0])) + tuple(merged[1:]))
+            elif pair and same(i, pair):
+                steps.append((i, 2, B.relay_conv2d_pair, (pair[0][1], pair[1][1])))
+            else:
+                steps.append((i, 1) + tuple(calls[i]))
+            i += steps[-1][1]
+        return steps
+
+    def _crosses_streams(self, i, n):
+        """Does a fork or join fall between calls i .. i + n - 1, or a fork behind the last of them?"""
+        return bool(self.side_calls) and (any(j in self.side_calls for j in range(i, i + n + 1)) or
+                                          any(j in self.join_before for j in range(i + 1, i + n)))
+
+    def launches(self):
+        """(names of the calls joined by +, function, arguments) of what run() enqueues, in order."""
+        return [("+".join(self.call_names[i:i + n]), fn, args) for i, n, fn, args in self._steps()]
 
     def capture(self) -> None:
         """Record run() into a HIP graph (kernel launches only; nothing in it clears memory)."""

@@ -40,6 +40,33 @@ def test_equals_conv_then_pool(G, shape, bias, bn):
     assert torch.equal(y, z) and torch.equal(yp, zp)
 
 
+def test_a_forced_tile_gets_the_two_launches(G):
+    """128 channels, which the 16 x 16 tiles add up in another order than the implicit GEMM that is asked for."""
+    from paper_1904_08368_amd import binding as B
+    n, c, h, w, k = 3, 128, 34, 30, 72
+    g = torch.Generator(device=G.DEV)
+    g.manual_seed(7)
+    x, wt = torch.randn((n, h, w, c), device=G.DEV, generator=g).half(), (torch.randn((k, c, 3, 3), device=G.DEV, generator=g) * 0.04).half()
+    d = B.conv_desc(n, c, h, w, k, 3, 3, 1, 1, B.RELAY_F16, B.RELAY_NHWC, B.RELU)
+    wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device=G.DEV)
+    B.relay_prepack_conv2d_weights(d, wt, c, wp)
+    outs = {}
+    for tile in (-2, 105):
+        y, yp = (torch.full((n, h // s, w // s, k), -7.0, dtype=torch.float16, device=G.DEV) for s in (1, 2))
+        z, zp = torch.empty_like(y), torch.empty_like(yp)
+        B.relay_set_conv_tile(tile)
+        try:
+            B.relay_fused_conv2d_pool2x2(d, x, wp, None, None, None, y, yp)
+            B.relay_fused_conv2d_bias_bn_relu(d, x, wp, None, None, None, None, z, None)
+        finally:
+            B.relay_set_conv_tile(-1)
+        B.relay_maxpool2d(B.RELAY_F16, n, k, h, w, 2, 2, 0, z, zp)
+        torch.cuda.synchronize()
+        assert torch.equal(y, z) and torch.equal(yp, zp)
+        outs[tile] = y
+    assert not torch.equal(outs[-2], outs[105])
+
+
 def test_what_is_refused(G):
     from paper_1904_08368_amd import binding as B
     t = torch.zeros(1 << 16, dtype=torch.float16, device=G.DEV)

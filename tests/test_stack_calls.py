@@ -68,3 +68,31 @@ def test_calls_with_a_launch_of_their_own_unless_edited(net):
     net.calls[3] = (lambda *a: done.append("edited"), ())
     net.run()
     assert done == [0, 1, 2, "edited"]
+
+
+def test_a_forced_tile_or_split_reaches_the_first_conv(net):
+    net, done = net
+    net.stem = (net.calls[:1], lambda *a: done.append("stem"), ())
+    for set_, off, on in ((B.relay_set_conv_tile, -1, -2), (B.relay_set_conv_tile, -1, 5), (B.relay_set_conv_split, 0, 1)):
+        set_(on)
+        try:
+            net.run()
+        finally:
+            set_(off)
+        assert done == [0, (1, 2), 3]
+        done.clear()
+    net.run()
+    assert done == ["stem", (1, 2), 3]
+
+
+def test_launches_are_what_a_run_makes(net):
+    net, done = net
+    net.call_names = list("abcd")
+    net.stem, net.merged = (net.calls[:1], lambda *a: done.append("stem"), ()), {}
+    assert [n for n, _, _ in net.launches()] == ["a", "b+c", "d"]
+    for _, fn, args in net.launches():
+        fn(*args)
+    assert done == ["stem", (1, 2), 3]
+    net.side_calls, net.join_before, net.pairs = {2}, {3}, {}
+    net.merged = {1: (net.calls[1:3], None, ()), 2: (net.calls[2:4], None, ())}     # across a fork, across a join
+    assert [n for n, _, _ in net.launches()] == ["a", "b", "c", "d"]
