@@ -280,6 +280,8 @@ class FusedNet:
         self.pairs = {} if self.side_calls else self._independent_pairs()
         # the first calls as one launch on the image itself: its padded copy (not written then), the conv and the pool behind it
         self.stem = self._image_stem()
+        if self.stem:
+            self.bufs["x"] = self.x_nchw   # (as the launch reads it: the copy would be what an earlier run left there)
         # further calls that one launch stands for, writing the same tensors
         self.merged = self._merged_calls()
         torch.cuda.synchronize(self.dev)

@@ -463,3 +463,17 @@ def test_dqn_fp16_chain_and_layers(G, batch):
     for name in ("h", "q"):
         assert O.max_rel_err(net.tensor(name).reshape(ref[name].shape), ref[name]) <= TOL_F16_CHAIN, name
     assert net.tensor("h").min() >= 0 and net.tensor("q").min() < 0
+
+
+def test_the_image_in_the_buffers_is_the_one_that_was_run(G):
+    """A first layer that reads the image itself leaves no padded copy behind: the buffer named x is the image."""
+    from paper_1904_08368_amd.fusion import FusedOp
+    from paper_1904_08368_amd.stack import FusedNet
+    ops = [FusedOp("conv", "c", "x", "y", 3, 64, 7, 2, 3, relu=True)]
+    x = inputs.image(8, 1, 3, 32, 32, "f16")
+    net = FusedNet(ops, [inputs.layer_params(ops[0], 8, 0, "f16")], 1, 32, 32, "f16")
+    assert net.stem
+    net.load_input(x)
+    net.run()
+    torch.cuda.synchronize()
+    assert np.array_equal(net.bufs["x"].cpu().numpy(), x)
