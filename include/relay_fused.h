@@ -380,8 +380,9 @@ relay_status relay_fused_avgpool_dense(int32_t dtype, int32_t n, int32_t c, int3
  *   y_pooled  [n, (ho - 1) / 2 + 1, (wo - 1) / 2 + 1, k] NHWC, or NULL: no pool.  F16 16-byte, I8 8-byte aligned
  * relay_image_conv2d_supported writes 1 if these calls take the descriptor (with a pool if `pooled`; n below 2^24 to 2^25
  * workgroups of outputs), else 0; the calls
- * themselves then return an error and launch nothing. */
+ * themselves then return an error and launch nothing.  relay_image_conv2d_pays writes 1 where that is also faster than the separate calls. */
 relay_status relay_image_conv2d_supported(const relay_conv2d_desc* d, int32_t pooled, int32_t* supported);
+relay_status relay_image_conv2d_pays(const relay_conv2d_desc* d, int32_t pooled, int32_t* pays);
 relay_status relay_fused_image_conv2d(const relay_conv2d_desc* d, const void* x_nchw, const void* w_packed, const float* bias,
                                       const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream);
 relay_status relay_qimage_conv2d(const relay_conv2d_desc* d, const int8_t* x_nchw, const int8_t* w_packed, const int32_t* bias,

@@ -93,6 +93,7 @@ SIGNATURES = {
     "relay_conv2d_pool2x2_pays": [_DP, C.POINTER(_I)],
     "relay_fused_conv2d_pool2x2": [_DP, _P, _P, _P, _P, _P, _P, _P, _P],
     "relay_image_conv2d_supported": [_DP, _I, C.POINTER(_I)],
+    "relay_image_conv2d_pays": [_DP, _I, C.POINTER(_I)],
     "relay_fused_image_conv2d": [_DP, _P, _P, _P, _P, _P, _P, _P, _P],
     "relay_qimage_conv2d": [_DP, _P, _P, _P, _I, _P, _P, _P],
     "relay_conv2d_maxpool_kernel_name": [_DP, C.c_char_p, _SZ],
@@ -265,6 +266,12 @@ def relay_fused_conv2d_pool2x2(d: ConvDesc, x, w_packed, bias, bn_scale, bn_shif
 def relay_image_conv2d_supported(d: ConvDesc, pooled: bool) -> bool:
     ok = C.c_int32(0)
     _check(lib().relay_image_conv2d_supported(C.byref(d), 1 if pooled else 0, C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_image_conv2d_pays(d: ConvDesc, pooled: bool) -> bool:
+    ok = C.c_int32(0)
+    _check(lib().relay_image_conv2d_pays(C.byref(d), 1 if pooled else 0, C.byref(ok)))
     return bool(ok.value)
 
 

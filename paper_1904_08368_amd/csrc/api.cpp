@@ -1113,6 +1113,13 @@ relay_status relay_image_conv2d_supported(const relay_conv2d_desc* d, int32_t po
   return RELAY_OK;
 }
 
+relay_status relay_image_conv2d_pays(const relay_conv2d_desc* d, int32_t pooled, int32_t* pays) {
+  if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
+  relay::StemArgs g;
+  *pays = image_conv_args(d, pooled != 0, &g) == RELAY_OK && relay::conv_stem_pays(g, d->dtype == RELAY_I8, pooled != 0) ? 1 : 0;
+  return RELAY_OK;
+}
+
 static relay_status check_image_operands(const relay_conv2d_desc* d, const void* x, const void* w, const void* y, const void* yp) {
   const int es = esize_of(d->dtype), out = es == 2 ? 16 : 8;
   if (!x || !w || (!y && !yp)) return fail(RELAY_ERR_NULL, "x_nchw, w_packed and y or y_pooled are required");

@@ -448,6 +448,21 @@ bool conv_stem_supported(const StemArgs& s, bool is_i8, bool pool) {
   return stem_pick(g, is_i8, pool, lds, items) >= 0;
 }
 
+// One launch, or the padded copy, the conv (and the pool) apart?  Apart where every channel tile reads a large patch anew (a stride of
+// four, more than 16 loads of four channels for each thread between them: 3 x 3 / 4 of 20 images 198 x 31 to 128 channels 11.4 us, apart
+// 8.9; 8 x 8 / 4 of 40 71 x 202 with pool 20.7, 17.4), and where the two waves of the smallest tile read a large patch pixel by
+// pixel (an odd width: 8 x 8 / 4 of 7 115 x 35 to 32 channels 7.3, 6.0).  Of 419 random first layers one launch was slower by 3 % or
+// more on 18; with this rule 7 are, by 3 to 8 % and one by 12 %, and all together take 0.80 of the time.
+bool conv_stem_pays(const StemArgs& s, bool is_i8, bool pool) {
+  StemArgs g = s;
+  size_t lds;
+  int items;
+  const int t = conv_stem_supported(s, is_i8, pool) ? stem_pick(g, is_i8, pool, lds, items) : -1;
+  if (t < 0) return false;
+  const int tn = (g.a.K + kStem[t].bn() - 1) / kStem[t].bn();
+  return !(tn > 1 && items * tn > 16) && !(t == 3 && !g.pairs && items >= 8);
+}
+
 hipError_t launch_conv_stem(const StemArgs& s, bool is_i8, bool pool, hipStream_t st) {
   StemArgs g = s;
   size_t lds;

@@ -171,6 +171,7 @@ struct StemArgs {
   FastDiv fd_img, fd_row, fd_items;
 };
 bool conv_stem_supported(const StemArgs& g, bool is_i8, bool pool);
+bool conv_stem_pays(const StemArgs& g, bool is_i8, bool pool);
 hipError_t launch_conv_stem(const StemArgs& g, bool is_i8, bool pool, hipStream_t st);
 // The persistent 3x3 / stride 1 / pad 1 kernel whose workgroups stream tile after tile (conv_stream.hip).
 bool conv_stream_supported(const ConvArgs& a, bool is_i8, int variant);

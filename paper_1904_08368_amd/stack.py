@@ -307,7 +307,7 @@ class FusedNet:
 
     def _image_stem(self):
         """(calls, function, arguments) of the launch that stands for the first two or three calls -- the padded copy of the image,
-        the conv on it, its 3x3 / stride 2 / pad 1 max pool -- where the library takes them together, else None."""
+        the conv on it, its 3x3 / stride 2 / pad 1 max pool -- where the library takes them together and that pays, else None."""
         if len(self.calls) < 2 or self.calls[0][0] is not B.relay_pack_input_nhwc4:
             return None
         (_, a0), (f1, a1) = self.calls[:2]
@@ -326,12 +326,12 @@ class FusedNet:
         else:
             return None
         if pooled_only:
-            return (self.calls[:2], fn, args + (None, a1[-1])) if B.relay_image_conv2d_supported(d, True) else None
+            return (self.calls[:2], fn, args + (None, a1[-1])) if B.relay_image_conv2d_pays(d, True) else None
         if len(self.calls) > 2 and self.calls[2][0] is B.relay_maxpool2d:
             a2 = self.calls[2][1]
-            if a2[5:8] == (3, 2, 1) and a2[8] is y and B.relay_image_conv2d_supported(d, True):
+            if a2[5:8] == (3, 2, 1) and a2[8] is y and B.relay_image_conv2d_pays(d, True):
                 return self.calls[:3], fn, args + (y, a2[9])
-        return (self.calls[:2], fn, args + (y, None)) if B.relay_image_conv2d_supported(d, False) else None
+        return (self.calls[:2], fn, args + (y, None)) if B.relay_image_conv2d_pays(d, False) else None
 
     def _independent_pairs(self):
         """{i: (call i, call i + 1)} of calls that share a launch: plain convs over the same tensor, neither reading what the

@@ -91,6 +91,12 @@ def test_image_conv_argument_checks():
         assert not B.relay_image_conv2d_supported(bad, False)
     assert not B.relay_image_conv2d_supported(desc(flags=0), True)      # a float pool without relu
 
+    # taken, and slower than the separate calls: large patches read for several channel tiles, or pixel by pixel
+    dqn = dict(c=4, h=84, w=84, k=32, r=8, st=4, pad=0)
+    for d, pooled, pays in ((desc(), True, True), (desc(**dqn), False, True), (desc(**dict(dqn, w=83)), False, False),
+                            (desc(n=20, h=198, w=31, k=128, r=3, st=4, pad=1), False, False), (desc(n=40, h=71, w=202, k=128, r=8, st=4, pad=3), True, False),
+                            (desc(n=40, h=71, w=202, k=64, r=8, st=4, pad=3), True, True), (desc(k=60), False, False)):
+        assert B.relay_image_conv2d_pays(d, pooled) == pays
     # more workgroups than one launch holds; the most of which the smaller ones still fit
     assert not B.relay_image_conv2d_supported(desc(n=20000000, c=1, h=1, w=2, k=64, r=1, st=1, pad=0), False)
     assert B.relay_image_conv2d_supported(desc(n=16000000, c=1, h=1, w=2, k=64, r=1, st=1, pad=0), False)
