@@ -29,13 +29,14 @@ HBM_PEAK_GBS = 8000.0
 
 
 def _layer_table(net, ops, batch, reps, trials):
-    """Per-launch duration of every call of the network: `reps` back-to-back launches (one
+    """Duration of every launch of the network: `reps` of it back to back (one
     graph replay) between two events on the launch stream, median of `trials`."""
     import torch
     from paper_1904_08368_amd import binding as B
     rows = []
-    shp_in = {}
-    for (fn, args), name in zip(net.calls, net.call_names):
+    op_of = lambda name: next(o for o in ops if o.name == name)
+    PLAIN_CONVS = (B.relay_fused_conv2d_bias_bn_relu, B.relay_qconv2d_requant)
+    for name, fn, args in net.launches():
         for _ in range(3):
             fn(*args)
         torch.cuda.synchronize()
@@ -57,25 +58,33 @@ def _layer_table(net, ops, batch, reps, trials):
         del g
         row = {"name": name, "us": statistics.median(ts)}
         d = args[0]
-        if fn in (B.relay_fused_conv2d_bias_bn_relu, B.relay_qconv2d_requant, B.relay_fused_dwconv_bias_relu):
+        if fn in PLAIN_CONVS or fn is B.relay_conv2d_pair:
+            # (logical reduction lengths: padded input channels of the stem carry zeros)
+            members = args if fn is B.relay_conv2d_pair else (args,)
+            row["gflop"], row["mbytes"] = (sum(v) for v in zip(*(_conv_work(m[0], op_of(n)) for m, n in zip(members, name.split("+")))))
+            d = members[0][0]
+            row["kernel"] = B.relay_conv2d_kernel_name(d)
+            if len(members) > 1:   # (named after what runs the first alone: the launch is that kernel's form for two)
+                row["kernel"] = "igemm pair: " + row["kernel"]
+            _rates(row)
+            _bounds(row, d.dtype == B.RELAY_I8, False)
+        elif fn in (B.relay_fused_image_conv2d, B.relay_qimage_conv2d, B.relay_fused_conv2d_pool2x2):
+            # the first layer on the image, or a conv with the 2x2 pool behind it: the conv's FLOP, image + what is written + filters
             ho, wo = B.relay_conv2d_out_shape(d)
-            es = 2 if d.dtype == B.RELAY_F16 else 1
-            if fn is not B.relay_fused_dwconv_bias_relu:
-                # logical reduction length: padded input channels of the stem carry zeros
-                op = next(o for o in ops if o.name == name)
-                macs = d.n * ho * wo * d.k * op.cin * d.r * d.s
-                row["gflop"] = 2 * macs / 1e9
-                row["kernel"] = B.relay_conv2d_kernel_name(d)
-                byts = (d.n * d.h * d.w * op.cin + d.n * ho * wo * d.k * (2 if (d.flags & B.HAS_RESIDUAL) else 1)
-                        + d.k * op.cin * d.r * d.s) * es
-                row["mbytes"] = byts / 1e6
-            else:   # depthwise: input + output + filters
-                row["gflop"] = 2 * d.n * ho * wo * d.c * 9 / 1e9
-                row["kernel"] = "dwconv3x3_f16_kernel"
-                row["mbytes"] = (d.n * d.h * d.w * d.c + d.n * ho * wo * d.c + 9 * d.c) * es / 1e6
-            row["tflops"] = row["gflop"] / row["us"] * 1e3           # GFLOP/us = 1000 TFLOP/s
-            row["gbs"] = row["mbytes"] / row["us"] * 1e3              # MB/us = 1000 GB/s
-            _bounds(row, d.dtype == B.RELAY_I8, fn is B.relay_fused_dwconv_bias_relu)
+            es, image = (2 if d.dtype == B.RELAY_F16 else 1), fn is not B.relay_fused_conv2d_pool2x2
+            op = op_of(name.split("+")[1 if image else 0])
+            row["gflop"] = 2 * d.n * ho * wo * d.k * op.cin * d.r * d.s / 1e9
+            row["kernel"] = "conv_stem_kernel" if image else B.relay_conv2d_kernel_name(d)
+            row["mbytes"] = (d.n * d.h * d.w * op.cin + sum(t.numel() for t in args[-2:] if t is not None) + d.k * op.cin * d.r * d.s) * es / 1e6
+            _rates(row)
+            _bounds(row, d.dtype == B.RELAY_I8, False)
+        elif fn is B.relay_fused_dwconv_bias_relu:   # depthwise: input + output + filters
+            ho, wo = B.relay_conv2d_out_shape(d)
+            row["gflop"] = 2 * d.n * ho * wo * d.c * 9 / 1e9
+            row["kernel"] = "dwconv3x3_f16_kernel"
+            row["mbytes"] = (d.n * d.h * d.w * d.c + d.n * ho * wo * d.c + 9 * d.c) * 2 / 1e6
+            _rates(row)
+            _bounds(row, False, True)
         elif fn is B.relay_fused_dwconv_pwconv:
             # a depthwise conv and its 1x1 conv in one launch: both convs' FLOP; input + output + both filter sets
             ho, wo = B.relay_conv2d_out_shape(d)
@@ -83,8 +92,7 @@ def _layer_table(net, ops, batch, reps, trials):
             row["gflop"] = 2 * d.n * ho * wo * d.c * (9 + k) / 1e9
             row["kernel"] = B.relay_dwconv_pwconv_kernel_name(d, k)
             row["mbytes"] = (d.n * d.h * d.w * d.c + d.n * ho * wo * k + 9 * d.c + k * d.c) * 2 / 1e6
-            row["tflops"] = row["gflop"] / row["us"] * 1e3
-            row["gbs"] = row["mbytes"] / row["us"] * 1e3
+            _rates(row)
             _bounds(row, False, False)
             row["frac_hbm"] = row["gbs"] / HBM_PEAK_GBS
         elif fn is B.relay_fused_conv2d_first_layer:
@@ -93,22 +101,34 @@ def _layer_table(net, ops, batch, reps, trials):
             row["gflop"] = 2 * d.n * ho * wo * d.k * d.c * 9 / 1e9
             row["kernel"] = "conv_first_kernel"
             row["mbytes"] = (d.n * d.h * d.w * d.c + d.n * ho * wo * d.k + d.k * d.c * 9) * 2 / 1e6
-            row["tflops"] = row["gflop"] / row["us"] * 1e3
-            row["gbs"] = row["mbytes"] / row["us"] * 1e3
+            _rates(row)
             _bounds(row, False, True)
         elif fn in (B.relay_fused_conv2d_bn_relu_maxpool, B.relay_qconv2d_requant_maxpool):
             # the conv with its max pool in the same launch: the conv's FLOP, input + pooled output + filters
             ho, wo = B.relay_conv2d_out_shape(d)
             es = 2 if d.dtype == B.RELAY_F16 else 1
-            op = next(o for o in ops if o.name == name.split("+")[0])
+            op = op_of(name.split("+")[0])
             row["gflop"] = 2 * d.n * ho * wo * d.k * op.cin * d.r * d.s / 1e9
             row["kernel"] = B.relay_conv2d_maxpool_kernel_name(d)
             row["mbytes"] = (d.n * d.h * d.w * op.cin + d.n * (ho // 2) * (wo // 2) * d.k + d.k * op.cin * d.r * d.s) * es / 1e6
-            row["tflops"] = row["gflop"] / row["us"] * 1e3
-            row["gbs"] = row["mbytes"] / row["us"] * 1e3
+            _rates(row)
             _bounds(row, d.dtype == B.RELAY_I8, False)
         rows.append(row)
     return rows
+
+
+def _conv_work(d, op):
+    """(GFLOP, MB) of a plain conv: every tensor once."""
+    from paper_1904_08368_amd import binding as B
+    ho, wo = B.relay_conv2d_out_shape(d)
+    outs = d.n * ho * wo * d.k
+    byts = (d.n * d.h * d.w * op.cin + outs * (2 if (d.flags & B.HAS_RESIDUAL) else 1) + d.k * op.cin * d.r * d.s) * (2 if d.dtype == B.RELAY_F16 else 1)
+    return 2 * outs * op.cin * d.r * d.s / 1e9, byts / 1e6
+
+
+def _rates(row):
+    row["tflops"] = row["gflop"] / row["us"] * 1e3           # GFLOP/us = 1000 TFLOP/s
+    row["gbs"] = row["mbytes"] / row["us"] * 1e3              # MB/us = 1000 GB/s
 
 
 def _bounds(row, is_i8, is_dw):
@@ -213,7 +233,7 @@ KERNEL_SOURCES = ("conv_igemm_dma.hip", "conv_halo.hip", "dma_common.hpp", "igem
                   "kernels.hpp", "fastdiv.hpp")
 
 
-CONV_KERNELS = ("igemm", "conv3x3_halo", "conv3x3_stream")      # name prefixes of the MFMA conv kernels in the per-layer table
+CONV_KERNELS = ("igemm", "conv3x3_halo", "conv3x3_stream", "conv_stem")      # name prefixes of the MFMA conv kernels in the per-layer table
 
 
 def _kernel_source_digest():
@@ -343,7 +363,7 @@ def main() -> int:
             un.capture()
         usec = _time_steps(un, max(10, a.steps // 2), a.warmup, use_graph)
         extra["fusion_ablation"] = {"unfused_ms_per_step": round(usec * 1e3, 4), "fused_ms_per_step": round(sec * 1e3, 4),
-                                    "launches_unfused": len(un.calls), "launches_fused": len(net.calls),
+                                    "launches_unfused": len(un.launches()), "launches_fused": len(net.launches()),
                                     "speedup_from_fusion": round(usec / sec, 3)}
         del un
         # ---- batch 1 latency of the same stack
@@ -444,7 +464,7 @@ def main() -> int:
             dsec = _time_steps(dn, a.steps, a.warmup, use_graph)
             dres[f"batch{b}_us_per_step"] = round(dsec * 1e6, 2)
             dres[f"batch{b}_tflops"] = round(2.0 * nets.macs_per_image(dops, 84, 84, 4) * b / dsec / 1e12, 3)
-            dres["launches"] = len(dn.calls)
+            dres["launches"] = len(dn.launches())
             del dn
         extra["dqn_fp16"] = dres
         # ---- parallel convolution combination (paper Section 4.4) on an Inception-shaped block, batch 32:
@@ -459,7 +479,7 @@ def main() -> int:
             if use_graph:
                 inet.capture()
             res[tag + "_ms"] = round(_time_steps(inet, a.steps, a.warmup, use_graph) * 1e3, 4)
-            res[tag + "_launches"] = len(inet.calls)
+            res[tag + "_launches"] = len(inet.launches())
             del inet
         res["speedup_from_combination"] = round(res["separate_ms"] / res["combined_ms"], 3)
         extra["parallel_conv_combination_inception_block_b32"] = res
@@ -471,8 +491,8 @@ def main() -> int:
             mnet.capture()
         msec = _time_steps(mnet, a.steps, a.warmup, use_graph)
         extra["parallel_conv_combination_resnet18_shortcuts"] = {
-            "separate_ms": round(sec * 1e3, 4), "separate_launches": len(net.calls),
-            "merged_ms": round(msec * 1e3, 4), "merged_launches": len(mnet.calls)}
+            "separate_ms": round(sec * 1e3, 4), "separate_launches": len(net.launches()),
+            "merged_ms": round(msec * 1e3, 4), "merged_launches": len(mnet.launches())}
         del mnet
 
     if not a.no_cpu:
