@@ -47,6 +47,10 @@ struct ConvArgs {
   int round_add;           // what the deterministic rules add before the shift (0 when rshift == 0)
   int qmode;               // QMODE_* of the quantized epilogue
   int clip_lo, clip_hi;    // bounds of the code type: -127 .. 127 (signed), 0 .. 255 (unsigned)
+  // Pooled tiles (see pool below): channels that one filter tap takes before the next one, block after block, which is the order in which
+  // the kernel of the conv alone adds up its sums (the 3x3 kernel's chunk, else C), so that both give the same bits.  (Here, where the
+  // alignment of the pointers leaves room: a longer argument block costs MobileNet at batch 1 2.5 %.)
+  int pool_block;
   const int32_t* qmult;    // QMODE_SCALED: per-channel multiplier [K] and shift [K]
   const int32_t* qshift;
   unsigned seed_lo, seed_hi;  // key of the stochastic rounding draws
@@ -59,9 +63,6 @@ struct ConvArgs {
   // tiles): a workgroup computes the 15 x 17 conv outputs under a 7 x 8 block of pooled outputs
   // and writes only those.  pool != 0: y is the pooled tensor [N][Ho/2][Wo/2][K].
   int pool;
-  // channels that one filter tap takes before the next one, block after block: the order in which the kernel of the conv alone adds
-  // up its sums (the 3x3 kernel's chunk, else C), so that both give the same bits
-  int pool_block;
   int pool_tiles_img, pool_tiles_row;   // 7 x 8 blocks per image and per row of blocks
   FastDiv fd_pool_img, fd_pool_row;
   // Reduction split over workgroups (direct-to-LDS implicit GEMM only): `split` workgroups share one
