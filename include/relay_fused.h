@@ -564,7 +564,7 @@ relay_status relay_nchw_to_nhwc(int32_t dtype, int32_t n, int32_t c, int32_t h, 
 /* Tuning aid (the library's stand-in for the schedule search of paper Section 4.1, "Lowering":
  * which schedule a fused operator gets is a choice made per shape and platform): force the
  * implicit-GEMM workgroup tile of later fp16 / int8 conv calls made BY THE CALLING THREAD
- * (0 .. count-1, largest first; 100 + v: variant v of the 3x3 stride-1 kernel, 200 + v of its persistent form,
+ * (0 .. count-1, largest first; 100 + v: variant v of the 3x3 stride-1 kernel -- fp16 0 to 6, int8 0, 1 and 6 --, 200 + v of its persistent form,
  * 400 + v of the kernel for few output tiles; 300 + v and 500 + v: see relay_fused_dwconv_pwconv; -1 = choose by
  * layer shape, the default; -2 = by layer shape without the 3x3 stride-1 kernels and the one for few tiles).  The setting is
  * thread-local: other threads' calls are unaffected and nothing is shared between threads.

@@ -110,6 +110,55 @@ def test_image_conv_argument_checks():
         assert got == status, (status, got, B.lib().relay_last_error())
 
 
+# infinities and a NaN in some pixels of the first image: they reach the outputs whose window they lie in, and those whose filter row,
+# filled up with zeros to 4 or 8 columns, ends on them; all others are what they would be
+@pytest.mark.gpu
+@pytest.mark.parametrize("finite", [True, False])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_image_conv_against_64_bits(shape, finite):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import torch.nn.functional as F
+    from paper_1904_08368_amd import binding as B
+    from tests import gpu_util as G
+    n, c, h, w, k, r, st, pad, pooled = shape
+    g = np.random.default_rng(inputs.BASE_SEED + 99500 + h + k)
+    x = torch.from_numpy(g.standard_normal((n, c, h, w)).astype(np.float16))
+    wt = torch.from_numpy((g.standard_normal((k, c, r, r)) * np.sqrt(2.0 / (c * r * r))).astype(np.float16))
+    b, sc, sf = (torch.from_numpy((m + 0.1 * g.standard_normal(k)).astype(np.float32)) for m in (0, 1, 0))
+    bad = torch.zeros((n, 1, h, w))
+    xb = x.clone()
+    if not finite:
+        for v in (np.inf, -np.inf, np.nan):
+            i, j = int(g.integers(h)), int(g.integers(w))
+            xb[0, int(g.integers(c)), i, j] = v
+            bad[0, 0, i, j] = 1
+    d = B.conv_desc(n, c, h, w, k, r, r, st, pad, B.RELAY_F16, B.RELAY_NHWC4_PADDED, B.HAS_BIAS | B.HAS_BN | B.RELU)
+    ho, wo = B.relay_conv2d_out_shape(d)
+    wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device=G.DEV)
+    B.relay_prepack_conv2d_weights(d, wt.to(G.DEV), c, wp)
+    y = torch.full((n, ho, wo, k), -7.0, dtype=torch.float16, device=G.DEV)
+    yp = torch.full((n, (ho - 1) // 2 + 1, (wo - 1) // 2 + 1, k), -7.0, dtype=torch.float16, device=G.DEV)
+    B.relay_fused_image_conv2d(d, xb.to(G.DEV), wp, b.to(G.DEV), sc.to(G.DEV), sf.to(G.DEV), y, yp if pooled else None)
+    torch.cuda.synchronize()
+    col = lambda v: v.double().reshape(1, k, 1, 1)
+    conv = lambda a, f: F.conv2d(a.double(), f.double(), stride=st, padding=pad)
+    ref = (conv(x, wt) + col(b)) * col(sc) + col(sf)
+    # half a unit of the fp16 result, and the fp32 sums: at most c r r + 4 roundings of partial sums below that of the magnitudes
+    tol = 2.0 ** -11 * ref.abs() + 2.0 ** -24 + (c * r * r + 4) * 2.0 ** -24 * ((conv(x.abs(), wt.abs()) + col(b).abs()) * col(sc).abs() + col(sf).abs())
+    cols = 4 if r <= 4 else 8
+    reach = F.conv2d(F.pad(bad, (pad, pad + cols - r, pad, pad)), torch.ones(1, 1, r, cols), stride=st)[..., :wo] > 0
+    assert finite or int(reach.sum()) < reach.numel() or h * w < 30
+    got = y.cpu().double().permute(0, 3, 1, 2)
+    off = ((got - ref.clamp(min=0)).abs() <= tol) | reach
+    assert bool(off.all())
+    if pooled:
+        pool = lambda a: F.max_pool2d(a, 3, 2, 1)
+        got = yp.cpu().double().permute(0, 3, 1, 2)
+        lo, hi = pool((ref - tol).clamp(min=0)), pool((ref + tol).clamp(min=0))
+        assert bool((((got >= lo) & (got <= hi)) | (pool(reach.double()) > 0)).all())
+
+
 # deep Q-network, ResNet's and VGG's first layers at sizes where the conv over the padded copy splits its sums over four waves (and
 # one where it does not): the fp32 sums against 64 bits, seen through a scale and shift that leave little but their error
 @pytest.mark.gpu
