@@ -614,7 +614,8 @@ relay_status relay_probe_mfma(int32_t dtype, int32_t iters, int32_t workgroups, 
 relay_status relay_probe_copy(const void* src, void* dst, int64_t bytes, void* hip_stream);
 
 /* Profiling aid (lowered code is specific to shape and platform, paper Section 4.1 "Lowering": this
- * tells which specialisation a shape gets): the name, as a kernel trace prints it, of the
+ * tells which specialisation a shape gets): the name, as a kernel trace prints it (3x3 stride-1 kernel: without trailing
+ * template arguments that are "false" or "1"), of the
  * implicit-GEMM kernel variant a fp16 / int8 descriptor runs on (template arguments give the workgroup's wave grid and
  * per-wave MFMA tile).  buf receives a NUL-terminated string of at most len bytes. */
 relay_status relay_conv2d_kernel_name(const relay_conv2d_desc* d, char* buf, size_t len);

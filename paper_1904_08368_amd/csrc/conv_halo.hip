@@ -14,7 +14,8 @@
 // needs the BM + 2P + 2 input positions from its first one on -- the halo -- which it loads once
 // into LDS with global->LDS loads (zero fill by out-of-range offset, as in the other kernel);
 // the nine taps then read the same buffer at row offsets r*P + s.  The LDS swizzle is keyed on
-// row >> 2 and any 16 consecutive rows cover all banks, so the shifted reads stay conflict-free.
+// row >> 2 and any 16 consecutive rows cover all banks, so the shifted reads stay conflict-free.  (16 x 16 tiles read two runs of
+// 16 rows that start 18 apart: 30 % of their LDS clocks are conflicts, 7 % of the flat 256 x 64 tile's.)
 // Filters go through a 3-stage ring, one tap x chunk per stage, exactly as before.
 //
 // Pipeline: a "step" is one (chunk, tap).  Step i multiplies operands that step i-1 read from LDS and reads those of step
@@ -22,8 +23,9 @@
 // loads of step i+3 and its share of the NEXT chunk's halo (spread over the first 7 taps).  Nine steps per chunk and three
 // ring stages make the stage of a step, and how many loads may be pending at its barrier, compile-time constants.
 // What bounds it: layers of one or two tiles per CU spend about 5 us on launch, first loads and stores (256 -> 256 at 14 x 14, batch
-// 32: 11.1 us of which the MFMAs take 4.2); large ones the L2-to-LDS loads and the power limit of the matrix cores (512 -> 512
-// at 28 x 28, batch 32: 1081 TFLOP/s, where a library's 8192^3 product reaches 1515 on the same random data).
+// 32: 11.1 us of which the MFMAs take 4.2); large ones the L2-to-LDS loads and the clock that the card holds under the matrix
+// cores' load (512 -> 512 at 28 x 28, batch 32, over four seconds: 1030 to 1080 TFLOP/s at 1.73 to 1.77 GHz on random data, 1523 at 2.40
+// GHz on zeros; a library's best 8192^3 product 1550 at 1.70 GHz on random data).
 #include <cstdio>
 
 #include <atomic>
@@ -129,10 +131,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   const int rem_0 = (SQUARE ? tile_m : o0) - n_0 * g.F;
 
   // ---- first loads out as early as possible: the epilogue constants (oldest, so that nothing ever waits for
-  //      them longer than for a ring load), then the filters of step 0, which need no decoding.  Every issue
-  //      slot, here and in the loop, holds L loads (a dump load stands in where there is none), and
-  //      the order of the slots is what the waits count on: filters of step 0, the halo of chunk 0,
-  //      filters of step 1.
+  //      them longer than for a ring load), then the filters of step 0, which need no decoding.  What the waits count on is
+  //      this order: constants, filters of step 0 (LW loads), the halo of chunk 0 (XN; a dump load stands in for a block that is
+  //      none), the filters of steps 1 and 2, up to four touches; from then on, behind step t of a chunk, the filters of step
+  //      t + 3 and that step's share of the next chunk's halo (loads_behind), in the last chunk only what filters are left.
   const int srow = lane >> 2, sphys = lane & 3;
   constexpr int CG = TN_E * 4;  // lanes per pixel row in the epilogue
   const int tm_lo = SK == 1 ? 0 : (SK == 2 ? wk : wk >> 1), tn_lo = SK == 4 ? wk & 1 : 0;   // the first block this wave finishes
@@ -727,7 +729,8 @@ int conv_halo_chunk(const ConvArgs& a, bool is_i8, int v) { return chunk_planes(
 
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {
   const HaloTile& t = kHalo[v];
-  char tail[40] = "";   // the arguments that differ from their defaults, and those in front of them
+  // (trailing template arguments at their defaults are left out, though a trace prints all eleven)
+  char tail[40] = "";
   if (a.nseg) snprintf(tail, sizeof(tail), ", %s, %d, true", t.square ? "true" : "false", t.sk);
   else if (t.sk > 1) snprintf(tail, sizeof(tail), ", %s, %d", t.square ? "true" : "false", t.sk);
   else if (t.square) snprintf(tail, sizeof(tail), ", true");
@@ -737,8 +740,8 @@ void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size
 
 // 2x2 / stride 2 max pool behind the conv, on 16 x 16 tiles: fp16, whole vectors of channels, whole windows, and a relu (no NaN left
 // to order).  The pool's read of the conv outputs and its launch go: of 64 -> 64 at batch 32 of 224 x 224 155 + 42 us as two launches,
-// of 128 -> 128 at 112 x 112 120 + 21 us; 168 and 127 as one each.  (The card is at its power limit there: the whole network
-// gains 24 of 1170 us, the convs behind take 5 % longer than with the pools between them.)
+// of 128 -> 128 at 112 x 112 120 + 21 us; 168 and 127 as one each.  (The whole network
+// gains 24 of 1170 us: the convs behind take 5 % longer than with the pools between them, the card's clock being what its load allows.)
 bool conv_halo_pool2_supported(const ConvArgs& a) {
   return conv_halo_supported(a, false, 5) && !a.nseg && (a.flags & F_RELU) && !(a.flags & F_RES) && !((a.H | a.W) & 1) && !(a.K & 7) &&
          (long)a.M * 2 <= 0x7fffffffL;

@@ -492,8 +492,8 @@ int small_best(const ConvArgs& a, bool is_i8, bool regroup, float* us_out) {
   // fp16: splitting a reduction groups its sums anew.  The convs that other entry points run as part of a larger
   // launch with a promise of the same bits keep the staged kernels' order: a 1x1 conv (behind a depthwise conv),
   // a conv with a max pool behind it, and a strided conv whose window is centred on a 1x1 shortcut conv's (merged with it:
-  // such a launch is always the staged kernel's).  At batch 1 that costs 128 -> 256 at 28 x 28 / 2 5.8 us instead
-  // of 3.5 and 256 -> 512 at 14 x 14 / 2 8.4 instead of 4.0.
+  // such a launch is always the staged kernel's).  At batch 1 that costs 128 -> 256 at 28 x 28 / 2 4.4 us instead
+  // of 3.5 and 256 -> 512 at 14 x 14 / 2 5.7 instead of 4.0 (on that kernel's 32 x 32 tiles; 5.8 and 8.4 on its others).
   const bool centred = (a.sh > 1 || a.sw > 1) && (a.R & 1) && (a.S & 1) && a.ph == a.R / 2 && a.pw == a.S / 2;
   if (!is_i8 && !regroup && (a.R * a.S == 1 || centred || igemm_dma_pool_supported(a, false))) return -1;
   const int chunk = staged_chunk(a, is_i8);

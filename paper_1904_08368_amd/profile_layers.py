@@ -83,6 +83,8 @@ def main() -> int:
     conv_case("halo_f16_c256_14", 32, 256, 14, 256, 3, 1, 1, False, True)
     conv_case("halo_f16_c64_56_tile_128x64", 32, 64, 56, 64, 3, 1, 1, False, True, tile=100)   # (the default there is the 256 x 64 tile)
     conv_case("halo_f16_c256_56", 32, 256, 56, 256, 3, 1, 1, False, False)                      # (VGG-16's third stage: the 256 x 128 tile)
+    conv_case("halo_f16_c64_224", 32, 64, 224, 64, 3, 1, 1, False, False)                       # (VGG-16's first stage: 16 x 16 tiles)
+    conv_case("halo_f16_c512_28", 32, 512, 28, 512, 3, 1, 1, False, False)
     conv_case("halo_i8_c64_56", 16, 64, 56, 64, 3, 1, 1, True, True)
     conv_case("halo_i8_c128_28", 16, 128, 28, 128, 3, 1, 1, True, False)
     # ---- the implicit-GEMM kernel: 64 x 64 tile with 256-byte chunks (stage 4), the stride-2 layers, 1x1 layers
@@ -93,6 +95,10 @@ def main() -> int:
     conv_case("igemm_f16_s2_c64_56", 32, 64, 56, 128, 3, 2, 1, False, False)
     conv_case("pointwise_f16_c256_28", 32, 256, 28, 256, 1, 1, 0, False, False)
     conv_case("pointwise_f16_c512_14", 32, 512, 14, 512, 1, 1, 0, False, False)
+    # ---- its 32 x 32 tiles, batch 1: a strided conv, its shortcut, a pointwise conv
+    conv_case("narrow_f16_s2_c256_14", 1, 256, 14, 512, 3, 2, 1, False, False)
+    conv_case("narrow_f16_s2_1x1_c256_14", 1, 256, 14, 512, 1, 2, 0, False, False)
+    conv_case("narrow_f16_1x1_c1024_7", 1, 1024, 7, 1024, 1, 1, 0, False, False)
     # ---- the persistent 3x3 kernel, forced (it is not chosen by default)
     conv_case("stream_f16_c64_56_v0", 32, 64, 56, 64, 3, 1, 1, False, True, tile=200)
     conv_case("stream_f16_c128_28_v0", 32, 128, 28, 128, 3, 1, 1, False, False, tile=200)
@@ -113,6 +119,34 @@ def main() -> int:
         es = 1 if i8 else 2
         run("stem_pool_" + ("i8" if i8 else "f16"), B.relay_conv2d_maxpool_kernel_name(d), fn,
             2.0 * n * 112 * 112 * 64 * 147 / 1e9, (n * 224 * 224 * 3 + n * 56 * 56 * 64 + 64 * 147) * es / 1e6)
+
+    # ---- first layers on the NCHW image: ResNet-18's with its max pool (conv outputs not kept), the deep Q-network's
+    for name, n, c, hw, k, r, st, pad, pooled, i8 in (("image_f16_b32", 32, 3, 224, 64, 7, 2, 3, True, False), ("image_f16_b1", 1, 3, 224, 64, 7, 2, 3, True, False),
+                                                      ("image_i8_b16", 16, 3, 224, 64, 7, 2, 3, True, True), ("image_dqn_f16_b1", 1, 4, 84, 32, 8, 4, 0, False, False)):
+        d = B.conv_desc(n, c, hw, hw, k, r, r, st, pad, B.RELAY_I8 if i8 else B.RELAY_F16, B.RELAY_NHWC4_PADDED, B.flags_of(None, None if i8 else 1, None, True))
+        ho, wo = B.relay_conv2d_out_shape(d)
+        x = tensor((n, c, hw, hw), i8)
+        w = tensor((k, c, r, r), i8) if i8 else (tensor((k, c, r, r), False) * 0.1).to(torch.float16)
+        wpk = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device=dev)
+        B.relay_prepack_conv2d_weights(d, w, c, wpk)
+        y = torch.empty((n, ho // 2 if pooled else ho, wo // 2 if pooled else wo, k), dtype=x.dtype, device=dev)
+        outs = (None, y) if pooled else (y, None)
+        sc, sf = torch.ones(k, device=dev), torch.zeros(k, device=dev)
+        fn = (lambda d=d, x=x, wpk=wpk, outs=outs: B.relay_qimage_conv2d(d, x, wpk, None, 10, *outs)) if i8 else \
+            (lambda d=d, x=x, wpk=wpk, outs=outs, sc=sc, sf=sf: B.relay_fused_image_conv2d(d, x, wpk, None, sc, sf, *outs))
+        run(name, "conv_stem_kernel<", fn, 2.0 * n * ho * wo * k * c * r * r / 1e9, (x.numel() + y.numel() + w.numel()) * (1 if i8 else 2) / 1e6)
+
+    # ---- a 3x3 conv with the 2x2 pool behind it (VGG-16's first stage)
+    d = B.conv_desc(32, 64, 224, 224, 64, 3, 3, 1, 1, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(None, 1, None, True))
+    x, w = tensor((32, 224, 224, 64), False), (tensor((64, 64, 3, 3), False) * 0.05).to(torch.float16)
+    wpk = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device=dev)
+    B.relay_prepack_conv2d_weights(d, w, 64, wpk)
+    y, yp = (torch.empty((32, 224 // e, 224 // e, 64), dtype=torch.float16, device=dev) for e in (1, 2))
+    sc, sf = torch.ones(64, device=dev), torch.zeros(64, device=dev)
+    run("halo_f16_c64_224_pool", "conv3x3_halo_kernel<false, 4, 1, 2, 2, 2, 2, true, 1, false, true>",
+        lambda d=d, x=x, wpk=wpk, sc=sc, sf=sf, y=y, yp=yp: B.relay_fused_conv2d_pool2x2(d, x, wpk, None, sc, sf, y, yp),
+        2.0 * 32 * 224 * 224 * 64 * 576 / 1e9, (x.numel() + y.numel() + yp.numel() + w.numel()) * 2 / 1e6)
+    del x, y, yp
 
     # ---- MobileNet-v1's first layer read from the NCHW image
     d = B.conv_desc(32, 3, 224, 224, 32, 3, 3, 2, 1, B.RELAY_F16, B.RELAY_NCHW, B.flags_of(None, 1, None, True))
