@@ -11,6 +11,9 @@
 // a run's rounding error grows with its length (rms of the fp32 errors against 64 bits, 8 x 8 windows of 4 channels: one run 1.48e-7, two
 // 1.14e-7, four 9.9e-8, which is also that of the small-tile kernel's four waves).
 //
+// Of the small tiles for few outputs one or two waves' worth of matrix work stand beside a patch of several hundred pixels, whose loads and
+// deposits were half of the launch: HW more waves of the workgroup take their share of those and of the stores, and idle in between.
+//
 // What bounds it: latency -- the patch, then the stores -- hidden by three or four workgroups per CU.  (Workgroups that walk over
 // several tiles, filters kept and the next patch in registers meanwhile, have room for two: 31.6 us against 25.4 for ResNet-18's
 // first layer at batch 32; the padded copy, conv and pool apart take 6.2 + 22.3.)
@@ -23,9 +26,9 @@
 namespace relay {
 namespace {
 
-template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, bool MANY, bool POOL, bool PAIRS, int NI>
-__global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 || NI > 10 ? 3 : 4) void conv_stem_kernel(const StemArgs g) {
-  constexpr int NT = 64 * WM * WN, NW = WM * WN, ES = IS_I8 ? 1 : 2, VE = 16 / ES, PXB = 4 * ES;
+template <bool IS_I8, int WM, int WN, int TM, int TN, int HW, int TYC, int TXC, int KS, bool MANY, bool POOL, bool PAIRS, int NI>
+__global__ __launch_bounds__(64 * (WM * WN + HW), TM * TN > 1 || NI > 10 ? 3 : 4) void conv_stem_kernel(const StemArgs g) {
+  constexpr int MW = WM * WN, NW = MW + HW, NT = 64 * NW, ES = IS_I8 ? 1 : 2, VE = 16 / ES, PXB = 4 * ES;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32, WTM = TM * 32, WTN = TN * 32;
   constexpr int OPITCH = BN * ES + 8;   // (8 bytes spread the accumulator layout's writes over the banks)
   constexpr int FB = BN / 16;           // 1 KiB filter blocks of a filter row
@@ -161,6 +164,7 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 || NI > 10 ? 3 : 4) void 
   };
   wait_loads<0>();   // the filters
   meet();
+  const bool multiplies = HW == 0 || wave < MW;   // (uniform; the others have brought their share and store theirs)
   acc_t acc[TN][TM];
   auto clear = [&]() {
 #pragma unroll
@@ -213,8 +217,10 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 || NI > 10 ? 3 : 4) void 
       }
     }
   };
-  if (wide) reduce_rows(std::integral_constant<bool, !IS_I8>{});
-  else reduce_rows(std::false_type{});
+  if (multiplies) {
+    if (wide) reduce_rows(std::integral_constant<bool, !IS_I8>{});
+    else reduce_rows(std::false_type{});
+  }
   if constexpr (MANY) {
     end_run();
 #pragma unroll
@@ -264,8 +270,10 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 || NI > 10 ? 3 : 4) void 
         }
       }
   };
-  if (!IS_I8 || qb.sat_ok) narrow(std::true_type{});
-  else narrow(std::false_type{});
+  if (multiplies) {
+    if (!IS_I8 || qb.sat_ok) narrow(std::true_type{});
+    else narrow(std::false_type{});
+  }
   meet();
 
   // ---- whole 8-channel vectors to memory
@@ -343,14 +351,16 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 || NI > 10 ? 3 : 4) void 
 }
 
 struct StemTile {
-  int wm, wn, tm, tn, tyc, txc;
-  constexpr int threads() const { return 64 * wm * wn; }
+  int wm, wn, tm, tn, hw, tyc, txc;
+  constexpr int threads() const { return 64 * (wm * wn + hw); }
+  constexpr int multiplying() const { return 64 * wm * wn; }
   constexpr int bm() const { return wm * tm * 32; }
   constexpr int bn() const { return wn * tn * 32; }
 };
-// large and small, 64 and 32 channels, without and with a pool (must match launch_stem)
+// large and small, 64 and 32 channels, without and with a pool; the small ones without a pool once more with helpers (must match launch_stem)
 constexpr StemTile kStem[] = {
-    {4, 1, 2, 2, 16, 16}, {4, 1, 2, 1, 16, 16}, {2, 2, 1, 1, 8, 8}, {2, 1, 1, 1, 8, 8}, {4, 1, 2, 2, 15, 17}, {2, 2, 1, 1, 7, 9},
+    {4, 1, 2, 2, 0, 16, 16}, {4, 1, 2, 1, 0, 16, 16}, {2, 2, 1, 1, 0, 8, 8}, {2, 1, 1, 1, 0, 8, 8}, {4, 1, 2, 2, 0, 15, 17}, {2, 2, 1, 1, 0, 7, 9},
+    {2, 2, 1, 1, 4, 8, 8}, {2, 1, 1, 1, 6, 8, 8},
 };
 
 int ksteps(const ConvArgs& a, bool is_i8) { return is_i8 ? (a.S <= 8 ? 1 : 0) : (a.S <= 4 ? 1 : a.S <= 8 ? 2 : 0); }
@@ -360,8 +370,8 @@ bool stem_geom(StemArgs& g, bool is_i8, int t, size_t& lds_bytes, int& items_per
   const StemTile& s = kStem[t];
   const ConvArgs& a = g.a;
   const int es = is_i8 ? 1 : 2, ks = ksteps(a, is_i8);
-  const bool pool = t >= 4;
-  if (ks == 0 || (pool && !is_i8 && ks != 2) || (is_i8 && (t == 1 || t == 3))) return false;
+  const bool pool = t == 4 || t == 5;
+  if (ks == 0 || (pool && !is_i8 && ks != 2) || (is_i8 && (t == 1 || t == 3 || t == 7))) return false;
   g.pitch = ((s.txc - 1) * a.sw + (is_i8 ? 8 : 4) * ks + 1) / 2 * 2;
   const int rows = (s.tyc - 1) * a.sh + a.R;
   g.patch_bytes = (rows * g.pitch * 4 * es + 15) / 16 * 16;
@@ -384,9 +394,9 @@ bool stem_geom(StemArgs& g, bool is_i8, int t, size_t& lds_bytes, int& items_per
   return items_per_thread <= (g.pairs ? 10 : 20) && lds_bytes <= 160 * 1024;
 }
 
-template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, bool MANY, bool POOL, bool PAIRS, int NI>
+template <bool IS_I8, int WM, int WN, int TM, int TN, int HW, int TYC, int TXC, int KS, bool MANY, bool POOL, bool PAIRS, int NI>
 hipError_t launch_stem_items(const StemArgs& g, size_t lds_bytes, hipStream_t st) {
-  auto kern = conv_stem_kernel<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, PAIRS, NI>;
+  auto kern = conv_stem_kernel<IS_I8, WM, WN, TM, TN, HW, TYC, TXC, KS, MANY, POOL, PAIRS, NI>;
   static std::atomic<bool> raised{false};  // dynamic LDS above the default limit has to be asked for once per kernel
   if (!raised.load(std::memory_order_acquire)) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -394,26 +404,28 @@ hipError_t launch_stem_items(const StemArgs& g, size_t lds_bytes, hipStream_t st
     raised.store(true, std::memory_order_release);
   }
   constexpr int BN = WN * TN * 32;
-  hipLaunchKernelGGL(kern, dim3(g.tiles, (g.a.K + BN - 1) / BN), dim3(64 * WM * WN), lds_bytes, st, g);
+  hipLaunchKernelGGL(kern, dim3(g.tiles, (g.a.K + BN - 1) / BN), dim3(64 * (WM * WN + HW)), lds_bytes, st, g);
   return hipGetLastError();
 }
 
-template <bool IS_I8, int WM, int WN, int TM, int TN, int TYC, int TXC, int KS, bool MANY, bool POOL>
+template <bool IS_I8, int WM, int WN, int TM, int TN, int HW, int TYC, int TXC, int KS, bool MANY, bool POOL>
 hipError_t launch_stem_one(const StemArgs& g, size_t lds, int items, hipStream_t st) {
   if (g.pairs)
-    return items <= 3 ? launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, true, 3>(g, lds, st)
-                      : launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, true, 10>(g, lds, st);
-  return items <= 6 ? launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, false, 6>(g, lds, st)
-                    : launch_stem_items<IS_I8, WM, WN, TM, TN, TYC, TXC, KS, MANY, POOL, false, 20>(g, lds, st);
+    return items <= 3 ? launch_stem_items<IS_I8, WM, WN, TM, TN, HW, TYC, TXC, KS, MANY, POOL, true, 3>(g, lds, st)
+                      : launch_stem_items<IS_I8, WM, WN, TM, TN, HW, TYC, TXC, KS, MANY, POOL, true, 10>(g, lds, st);
+  return items <= 6 ? launch_stem_items<IS_I8, WM, WN, TM, TN, HW, TYC, TXC, KS, MANY, POOL, false, 6>(g, lds, st)
+                    : launch_stem_items<IS_I8, WM, WN, TM, TN, HW, TYC, TXC, KS, MANY, POOL, false, 20>(g, lds, st);
 }
 
 template <bool IS_I8, int KS>
 hipError_t launch_stem_plain(const StemArgs& g, int t, size_t lds, int items, hipStream_t st) {
-  if (t == 0) return launch_stem_one<IS_I8, 4, 1, 2, 2, 16, 16, KS, false, false>(g, lds, items, st);
-  if (t == 2) return launch_stem_one<IS_I8, 2, 2, 1, 1, 8, 8, KS, true, false>(g, lds, items, st);
+  if (t == 0) return launch_stem_one<IS_I8, 4, 1, 2, 2, 0, 16, 16, KS, false, false>(g, lds, items, st);
+  if (t == 2) return launch_stem_one<IS_I8, 2, 2, 1, 1, 0, 8, 8, KS, true, false>(g, lds, items, st);
+  if (t == 6) return launch_stem_one<IS_I8, 2, 2, 1, 1, 4, 8, 8, KS, true, false>(g, lds, items, st);
   if constexpr (!IS_I8) {
-    if (t == 1) return launch_stem_one<false, 4, 1, 2, 1, 16, 16, KS, false, false>(g, lds, items, st);
-    if (t == 3) return launch_stem_one<false, 2, 1, 1, 1, 8, 8, KS, true, false>(g, lds, items, st);
+    if (t == 1) return launch_stem_one<false, 4, 1, 2, 1, 0, 16, 16, KS, false, false>(g, lds, items, st);
+    if (t == 3) return launch_stem_one<false, 2, 1, 1, 1, 0, 8, 8, KS, true, false>(g, lds, items, st);
+    if (t == 7) return launch_stem_one<false, 2, 1, 1, 1, 6, 8, 8, KS, true, false>(g, lds, items, st);
   }
   return hipErrorInvalidValue;
 }
@@ -428,12 +440,15 @@ int stem_pick(StemArgs& g, bool is_i8, bool pool, size_t& lds, int& items) {
   // Also where the conv over the padded copy sums in several runs, whatever their number.
   const bool fits = stem_geom(g, is_i8, large, lds, items);
   if (fits && g.runs <= 1 && g.tiles * tn >= 128) return large;
-  if (stem_geom(g, is_i8, small, lds, items)) {
-    const int runs = g.runs > 2 ? g.runs : 2;
-    g.per_run = (g.a.R + runs - 1) / runs;
-    return small;
-  }
-  return -1;
+  if (!stem_geom(g, is_i8, small, lds, items)) return -1;
+  const int runs = g.runs > 2 ? g.runs : 2;
+  g.per_run = (g.a.R + runs - 1) / runs;
+  // With helpers where the chip holds all workgroups at once anyway, two to a CU: 8x8 / 4 of one frame 6.2 -> 4.7 us, of 32 7.2 -> 5.6; 7x7 / 2 of
+  // 120 x 84 to 64 channels 5.4 -> 5.0, 3x3 of 4 60 x 84 5.1 either way.  The pooled tile gains 7 % up to one workgroup per CU and loses
+  // 3 to 13 % beyond (its patch is two loads a thread as it is).
+  const int helped = small == 2 ? 6 : 7;
+  const long tiles = (long)g.tiles * ((g.a.K + kStem[small].bn() - 1) / kStem[small].bn());
+  return !pool && tiles <= 512 && stem_geom(g, is_i8, helped, lds, items) ? helped : small;
 }
 
 }  // namespace
@@ -452,7 +467,8 @@ bool conv_stem_supported(const StemArgs& s, bool is_i8, bool pool) {
 // four, more than 16 loads of four channels for each thread between them: 3 x 3 / 4 of 20 images 198 x 31 to 128 channels 11.4 us, apart
 // 8.9; 8 x 8 / 4 of 40 71 x 202 with pool 20.7, 17.4), and where the two waves of the smallest tile read a large patch pixel by
 // pixel (an odd width: 8 x 8 / 4 of 7 115 x 35 to 32 channels 7.3, 6.0).  Of 419 random first layers one launch was slower by 3 % or
-// more on 18; with this rule 7 are, by 3 to 8 % and one by 12 %, and all together take 0.80 of the time.
+// more on 18; with this rule 7 were, by 3 to 8 % and one by 12 %, and all together take 0.80 of the time.  With helpers none of 215 others
+// that the rule takes is slower, and one of the 5 that it refuses would be faster (by 3 %).
 bool conv_stem_pays(const StemArgs& s, bool is_i8, bool pool) {
   StemArgs g = s;
   size_t lds;
@@ -460,7 +476,8 @@ bool conv_stem_pays(const StemArgs& s, bool is_i8, bool pool) {
   const int t = conv_stem_supported(s, is_i8, pool) ? stem_pick(g, is_i8, pool, lds, items) : -1;
   if (t < 0) return false;
   const int tn = (g.a.K + kStem[t].bn() - 1) / kStem[t].bn();
-  return !(tn > 1 && items * tn > 16) && !(t == 3 && !g.pairs && items >= 8);
+  items = (g.items + kStem[t].multiplying() - 1) / kStem[t].multiplying();   // (as without helpers)
+  return !(tn > 1 && items * tn > 16) && !((t == 3 || t == 7) && !g.pairs && items >= 8);
 }
 
 hipError_t launch_conv_stem(const StemArgs& s, bool is_i8, bool pool, hipStream_t st) {
@@ -468,8 +485,8 @@ hipError_t launch_conv_stem(const StemArgs& s, bool is_i8, bool pool, hipStream_
   size_t lds;
   int items;
   const int t = stem_pick(g, is_i8, pool, lds, items);
-  if (t == 4) return is_i8 ? launch_stem_one<true, 4, 1, 2, 2, 15, 17, 1, false, true>(g, lds, items, st) : launch_stem_one<false, 4, 1, 2, 2, 15, 17, 2, false, true>(g, lds, items, st);
-  if (t == 5) return is_i8 ? launch_stem_one<true, 2, 2, 1, 1, 7, 9, 1, true, true>(g, lds, items, st) : launch_stem_one<false, 2, 2, 1, 1, 7, 9, 2, true, true>(g, lds, items, st);
+  if (t == 4) return is_i8 ? launch_stem_one<true, 4, 1, 2, 2, 0, 15, 17, 1, false, true>(g, lds, items, st) : launch_stem_one<false, 4, 1, 2, 2, 0, 15, 17, 2, false, true>(g, lds, items, st);
+  if (t == 5) return is_i8 ? launch_stem_one<true, 2, 2, 1, 1, 0, 7, 9, 1, true, true>(g, lds, items, st) : launch_stem_one<false, 2, 2, 1, 1, 0, 7, 9, 2, true, true>(g, lds, items, st);
   if (t < 0) return hipErrorInvalidValue;
   if (is_i8) return launch_stem_plain<true, 1>(g, t, lds, items, st);
   return ksteps(g.a, false) == 1 ? launch_stem_plain<false, 1>(g, t, lds, items, st) : launch_stem_plain<false, 2>(g, t, lds, items, st);

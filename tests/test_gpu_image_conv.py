@@ -191,3 +191,14 @@ def test_sums_are_no_less_exact_than_those_of_the_separate_calls(n, c, h, w, k, 
     print(f"[observed] rms of the sums' errors, {n} x {h} x {w}, {r} x {r}: separate calls {two:.2e}, one launch {one:.2e}")
     # (the same sums in as many runs: only how a matrix instruction adds up its 16 or 32 products differs; half the runs are 1.08 to 1.5 times)
     assert one <= 1.03 * two
+
+
+# Small tiles with helper waves (at most 512 workgroups) and without, at 32 and at 64 channels, pixel pairs and single pixels: a patch of
+# more pixels than threads and of fewer, channels past the tile's, workgroups of more than one channel tile.
+@pytest.mark.gpu
+@pytest.mark.parametrize("i8", [False, True])
+@pytest.mark.parametrize("shape", [(1, 4, 84, 84, 32, 8, 4, 0, False), (2, 4, 61, 85, 24, 8, 4, 3, False), (1, 3, 9, 8, 8, 3, 1, 1, False),
+                                   (1, 3, 61, 62, 64, 5, 2, 2, False), (1, 4, 40, 71, 72, 8, 4, 0, False),
+                                   (129, 4, 84, 84, 32, 8, 5, 0, False), (65, 4, 84, 84, 96, 8, 6, 4, False)])
+def test_small_tiles_with_and_without_helper_waves(shape, i8):
+    test_image_conv_gives_the_results_of_the_separate_calls(shape, i8)
