@@ -16,7 +16,10 @@
 // exact in any order), then the fused tail runs as in the other kernels.
 //
 // Bound: the launch with its chain of argument fetch, first loads and store (2.6 us), then the bytes a CU
-// draws for its tile (about 125 KB/us).  Graph-timed at batch 1, staged kernels -> this one: fp16 64 -> 64 at
+// draws for its tile (about 125 KB/us): each goes into LDS and out again once, which keeps LDS as busy as the one wave a SIMD has
+// issues instructions (a 16 x 16 tile of 512 channels: 1.9 K clocks to the last of the first requests, 4.5 K in nine units, 1.4 K for the tail).
+// An input patch shared by the waves (fewer bytes, but a barrier and a wait in front of the loop; 512 channels, seven images 8.3 -> 8.0 us, one image
+// 5.5 -> 5.9), eight waves (5.5 -> 5.9) and deeper rings (1 to 4 % slower with operands from beyond the L2) were no better.  Graph-timed at batch 1, staged kernels -> this one: fp16 64 -> 64 at
 // 56 x 56 5.1 -> 3.8 us, 128 at 28 x 28 5.9 -> 3.7, 256 at 14 x 14 8.2 -> 3.9, 512 at 7 x 7 9.5 -> 4.7; int8 5.0 -> 3.5,
 // 5.3 -> 3.5, 5.8 -> 3.3, 9.0 -> 3.9.
 #include <cmath>
@@ -134,20 +137,28 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
   };
   if (left > 0) request_filters(0);
   int x_off[TM];        // byte offset of tap (0, 0) of the lane's pixel
-  unsigned x_taps[TM];  // bit t: tap t lies inside the image
+  // Is a tap inside the image?  One pixel block: a bit of a mask worked out once (two instructions fewer in a loop that issues one every five
+  // clocks: 512 channels at 7 x 7 5.4 us, 5.7 with comparisons).  Two: two comparisons, which start the first loads earlier (at 7 x 8, seven
+  // images, 8.6 -> 8.1 us together with the early operands below, 16 images 11.6 -> 10.5, int8 7.7 -> 7.3).
+  constexpr bool MASKS = TM == 1;
+  unsigned x_taps[TM];         // MASKS: bit t: tap t lies inside the image
+  int x_row[TM], x_col[TM];    // else: input row and column of tap (0, 0)
 #pragma unroll
   for (int t = 0; t < TM; ++t) {
     const int m = m0 + t * 16 + lr;
     const int n = (int)div_by((uint32_t)m, a.fd_howo), rem = m - n * (a.Ho * a.Wo);
     const int p = (int)div_by((uint32_t)rem, a.fd_wo), q = rem - p * a.Wo;
     const int ih0 = p * a.sh - a.ph, iw0 = q * a.sw - a.pw;
+    x_off[t] = (n * a.xs_n + ih0 * a.xs_h + iw0 * a.xs_w + lk * VE) * ES;
+    x_row[t] = m < a.M ? ih0 : -0x10000000;   // (rows past the end lie in no image)
+    x_col[t] = iw0;
+    if constexpr (!MASKS) continue;
     // the run of valid filter columns, replicated at every valid filter row
     const int rlo = max(0, -ih0), rhi = min(a.R, a.H - ih0);
     const int clo = max(0, -iw0), chi = min(a.S, a.W - iw0);
     const unsigned colbits = (unsigned)((1ull << max(chi, 0)) - 1ull) & ~(unsigned)((1ull << clo) - 1ull);
     const unsigned rows = a.tap_spread & (unsigned)((1ull << (max(rhi, 0) * a.S)) - 1ull) & ~(unsigned)((1ull << (rlo * a.S)) - 1ull);
     x_taps[t] = (m < a.M && rhi > rlo && chi > clo) ? colbits * rows : 0u;
-    x_off[t] = (n * a.xs_n + ih0 * a.xs_h + iw0 * a.xs_w + lk * VE) * ES;
   }
 
   auto request_pixels = [&](int st) {
@@ -156,7 +167,8 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
     const unsigned dst = my_base + (unsigned)(st * LPU + TN * U) * 1024u;
 #pragma unroll
     for (int t = 0; t < TM; ++t) {
-      const unsigned off = (x_taps[t] & tapbit) ? (unsigned)x_off[t] + dx : kOob;
+      const bool in = MASKS ? (x_taps[t] & tapbit) != 0u : (unsigned)(x_row[t] + is_r) < (unsigned)a.H && (unsigned)(x_col[t] + is_s) < (unsigned)a.W;
+      const unsigned off = in ? (unsigned)x_off[t] + dx : kOob;
 #pragma unroll
       for (int u = 0; u < U; ++u) lds_dma16(rs_x, dst + (unsigned)(t * U + u) * 1024u, off + u * 64);
     }
@@ -207,19 +219,28 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
         }
   };
 
-  auto constants = [&]() {  // of the tile's channels, to LDS
-    if (tid < BN) {
-      const int c = n0 + tid < a.K ? n0 + tid : a.K - 1;
-      if constexpr (IS_I8) {
-        cst[tid] = __builtin_bit_cast(float, (a.flags & F_BIAS) ? a.qbias[c] : 0);
-      } else {
-        const float sc = (a.flags & F_BN) ? a.scale[c] : 1.f, sf = (a.flags & F_BN) ? a.shift[c] : 0.f;
-        const float b = (a.flags & F_BIAS) ? a.bias[c] : 0.f;
-        cst[tid] = sc;
-        cst[BN + tid] = b * sc + sf;  // (acc + b)*sc + sf
-      }
+  // The constants of the tile's channels and the residual operand are asked for here, behind the first operands: neither latency then
+  // stands behind the reduction.
+  float k0 = 1.f, k1 = 0.f, k2 = 0.f;
+  if (tid < BN) {
+    const int c = n0 + tid < a.K ? n0 + tid : a.K - 1;
+    if constexpr (IS_I8) {
+      k0 = __builtin_bit_cast(float, (a.flags & F_BIAS) ? a.qbias[c] : 0);
+    } else {
+      if (a.flags & F_BN) k0 = a.scale[c], k1 = a.shift[c];
+      if (a.flags & F_BIAS) k2 = a.bias[c];
     }
-  };
+  }
+  const bool vec_ok = (a.K & 7) == 0;
+  const bool pre_res = (a.flags & F_RES) && vec_ok;
+  uint4 resv[IPT];
+#pragma unroll
+  for (int it = 0; it < IPT; ++it) {
+    const int item = it * (64 * W) + tid, m_out = m0 + item / (TN * 2), ech = n0 + item % (TN * 2) * 8;
+    resv[it] = make_uint4(0u, 0u, 0u, 0u);
+    if (pre_res && item < ITEMS && m_out < a.M && ech < a.K) resv[it] = load_residual8<IS_I8>(a, m_out, ech);
+  }
+
   // NS units are in flight.  The ring is the wave's own: no barrier, only its own loads are waited for.
   int st = 0;
   auto step = [&](auto phase) {  // one unit multiplied, another requested in its place
@@ -278,7 +299,10 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
       for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) acc[i][tn][tm] += acc[i + n][tn][tm];
-  constants();
+  if (tid < BN) {
+    cst[tid] = k0;
+    if constexpr (!IS_I8) cst[BN + tid] = k2 * k0 + k1;  // (acc + b)*sc + sf
+  }
 
   // ---- partial tiles to LDS.  Lane l of a block holds channels 4 (l / 16) .. + 3 of pixel l % 16.
 #pragma unroll
@@ -288,7 +312,6 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
       my[(tm * TN + tn) * 64 + lane] =
           make_uint4(as_u32(acc[0][tn][tm][0]), as_u32(acc[0][tn][tm][1]), as_u32(acc[0][tn][tm][2]), as_u32(acc[0][tn][tm][3]));
   __syncthreads();
-  const bool vec_ok = (a.K & 7) == 0;
   typedef typename std::conditional<IS_I8, int, float>::type sum_t;
 #pragma unroll
   for (int it = 0; it < IPT; ++it) {
@@ -297,9 +320,6 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
     const int it_c = item % (TN * 2), it_p = item / (TN * 2);
     const int m_out = m0 + it_p, ech = n0 + it_c * 8;
     if (item >= ITEMS || m_out >= a.M || ech >= a.K) continue;
-    const bool pre_res = (a.flags & F_RES) && vec_ok;
-    uint4 resv = make_uint4(0u, 0u, 0u, 0u);
-    if (pre_res) resv = load_residual8<IS_I8>(a, m_out, ech);
     // block (it_p / 16, it_c / 2), pixel it_p % 16, channels 8 (it_c % 2) .. + 7
     const uint4* src = ring + ((it_p >> 4) * TN + (it_c >> 1)) * 64 + (it_p & 15) + 32 * (it_c & 1);
     sum_t sum[8];
@@ -326,7 +346,7 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
       }
     }
     const OutLoc ol = EXT ? locate_output(a, ech) : OutLoc{nullptr, 0, 0, 0};
-    finish_store8<IS_I8, false, EXT>(a, raw, m_out, ech, lp, ol, vec_ok, pre_res, resv);
+    finish_store8<IS_I8, false, EXT>(a, raw, m_out, ech, lp, ol, vec_ok, pre_res, resv[it]);
   }
 }
 
