@@ -53,6 +53,7 @@ struct HaloGeom {
 
 constexpr int NSW = 3;         // filter ring stages (9 taps per chunk keep step % NSW compile-time)
 constexpr int XPW = 8;         // halo blocks a wave loads per chunk, times HB
+constexpr unsigned kNoBlock = ~0u;
 
 // The loads behind step t of a chunk that has a successor: lw filter loads, then a wave's share of the xn halo blocks of
 // the next chunk, spread over the first seven steps.  (It is read from the end of the ninth on.)
@@ -79,7 +80,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   constexpr int WB = BN / 16;            // filter staging blocks of a plane: 16 rows x 64 B
   static_assert(KP * WB % NW == 0, "filter staging blocks must divide over the waves");
   constexpr int LW = KP * WB / NW;       // filter loads per step per wave: blocks i * NW + wave, plane by plane
-  constexpr int XN = XPW * HB;           // halo blocks per wave
+  constexpr int XN = XPW * HB;           // halo blocks (of 16 positions x 64 bytes) per wave,
+  constexpr int XJ = XN / KP;            // ... of a plane
+  static_assert(XN % KP == 0, "whole blocks of all planes");
   constexpr int KSTEPS = KP * (BKV / 2);
   constexpr int KSW = KSTEPS / SK;       // ... of which this wave runs KSW
   constexpr int NM = KSW * TN * TM;      // MFMAs of a step
@@ -183,27 +186,32 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
 
-  // ---- this lane's part of a halo: block (t * NW + wave) of the KP * xblk blocks, for t < XN; the load of
-  //      chunk 0's block goes out as soon as its address is known
-  unsigned x_off[XN];    // byte offset of the 16 bytes this lane fetches (chunk 0), or out of range
-  unsigned x_px[XN];     // (all table reads first: one wait for all of them)
-  const int xblocks = KP * g.xblk;
+  // ---- this lane's part of a halo: of each plane the blocks j * NW + wave, j < XJ, so that a position is looked up once for all
+  //      planes.  Branch-free: the loads of a wave are XN whatever the halo's size (a dump load for a block that is none), and few
+  //      instructions, because a wave that has its SIMD to itself issues one every four to five clocks.  (Counted block by block over all
+  //      planes, with a division, two branches and a look-up each, this stretch was 1.75 K of a 64 x 64 tile's 12 K clocks: 128 -> 128 at
+  //      25 x 25, 12 images 7.0 -> 6.7 us, 64 -> 64 at 56 x 56, 32 images 16.6 -> 15.9, operands from beyond the L2.)
+  unsigned x_off[XJ];    // byte offset of the 16 bytes this lane fetches (chunk 0, plane 0), or out of range
+  unsigned x_dst[XJ];    // (uniform) where their plane 0 goes in a halo buffer; the dump's place for a block that is none
+  unsigned x_px[XJ];     // (all table reads first: one wait for all of them)
+  const int kvl_x = sphys ^ lds_swizzle(srow);   // (the swizzle repeats every 16 rows)
 #pragma unroll
-  for (int t = 0; t < XN; ++t) {
-    const int b = t * NW + wave;
-    const int plane = (int)fast_div((uint32_t)b, g.fd_xblk), blk = b - plane * g.xblk;
-    x_px[t] = ptab[plane < KP ? blk * 16 + srow : 0];
-  }
+  for (int j = 0; j < XJ; ++j) x_px[j] = ptab[min(j * NW + wave, g.xblk - 1) * 16 + srow];
 #pragma unroll
-  for (int t = 0; t < XN; ++t) {
-    const int b = t * NW + wave;
-    const int plane = (int)fast_div((uint32_t)b, g.fd_xblk), blk = b - plane * g.xblk;
-    const int row = blk * 16 + srow;
-    const int kvl = sphys ^ lds_swizzle(row);
-    const unsigned px = x_px[t];
-    x_off[t] = (b < xblocks && px != ~0u) ? (unsigned)((px * a.C + plane * (BKV * VE) + kvl * VE) * ES) : kOob;
-    lds_dma16(rs_x, b < xblocks ? lds_base + (unsigned)b * 1024u : dump_base, x_off[t]);
+  for (int j = 0; j < XJ; ++j) {
+    const bool some = j * NW + wave < g.xblk;   // (uniform)
+    unsigned off = x_px[j] * (unsigned)(a.C * ES) + (unsigned)(kvl_x * VE * ES);
+    asm volatile("" : "+v"(off));
+    x_off[j] = some && x_px[j] != ~0u ? off : kOob;
+    x_dst[j] = some ? (unsigned)(j * NW + wave) * 1024u : kNoBlock;
   }
+  // load xt of a wave's XN: plane xt % KP of its block xt / KP, of the chunk `at` bytes into a pixel, to the halo buffer at `buf`
+  auto issue_halo = [&](int xt, unsigned buf, unsigned at) {
+    const unsigned dst = x_dst[xt / KP];
+    lds_dma16(rs_x, dst != kNoBlock ? buf + dst + (unsigned)(xt % KP * xplane) * 16u : dump_base, x_off[xt / KP] + (unsigned)(xt % KP * 64) + at);
+  };
+#pragma unroll
+  for (int t = 0; t < XN; ++t) issue_halo(t, lds_base, 0u);
 #pragma unroll
   for (int s = 1; s < NSW; ++s) issue_filters(s);
 
@@ -231,9 +239,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
       lds_dma16(rs_w, wring_base + (unsigned)((tw % NSW) * WSTAGE + (i * NW + wave) * 64) * 16u,
                 w_off[i] + (unsigned)((tw * a.C + ccw * CK) * ES));   // (kOob + a filter's length stays out of range)
     } else {
-      const int xt = min(halo_first(t, XN) + (i - LW), XN - 1), b = xt * NW + wave;   // which of this wave's halo blocks
-      lds_dma16(rs_x, b < xblocks ? lds_base + (unsigned)(((cc + 1) & 1) * xbuf_slots) * 16u + (unsigned)b * 1024u : dump_base,
-                x_off[xt] + (unsigned)((cc + 1) * CK * ES));
+      const int xt = min(halo_first(t, XN) + (i - LW), XN - 1);   // which of this wave's halo loads
+      issue_halo(xt, lds_base + (unsigned)(((cc + 1) & 1) * xbuf_slots) * 16u, (unsigned)((cc + 1) * CK * ES));
     }
   };
 
@@ -272,6 +279,41 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
     if (e < TN) wf[buf][k][e] = wring[(t % NSW) * WSTAGE + (ks >> 1) * WPLANE + e * 32 * BKV + (wlane ^ kx)];
     else xf[buf][k][e - TN] = lds[(ks >> 1) * xplane + (xslot[e - TN] ^ kx)];
   };
+  // ---- what the epilogue reads: the output pixels of this lane (the output pixel of a flat position o is the table's entry for o + P + 1) and
+  //      its residual vectors, asked for behind step RES_AT of the last chunk, the last one that loads filters, so that they arrive under
+  //      the steps behind it and no wait for filters is one for them.  (Layers with a residual 1 to 3 % faster than when asked for in the
+  //      epilogue; two steps earlier less.  int8: asked for behind the last step, 1 to 3 % better than earlier.)
+  constexpr int PPI = 64 / CG, ITS = 32 / PPI, NRES = TM_E * ITS, RES_AT = IS_I8 ? 8 : 5;
+  const int epix = lane / CG, ecg = lane % CG;
+  const bool vec_ok = (a.K & 7) == 0;
+  const bool pre_res = (a.flags & F_RES) && vec_ok;
+  unsigned mpix[TM_E][ITS];
+  uint4 resv[TM_E][ITS];
+  auto request_residual = [&]() {
+#pragma unroll
+    for (int tm = 0; tm < TM_E; ++tm)
+#pragma unroll
+      for (int it = 0; it < ITS; ++it) {
+        const int pix = it * PPI + epix;
+        mpix[tm][it] = ptab[(SQUARE ? ((wm * TM + tm_lo + tm) * 2 + (pix >> 4)) * SQP + (pix & 15) : wm * WTM + (tm_lo + tm) * 32 + pix) + P + 1];
+      }
+    if (pre_res) {
+      const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.res), 0, (int)((unsigned)a.M * a.K * ES), 0x00020000);
+#pragma unroll
+      for (int tm = 0; tm < TM_E; ++tm)
+#pragma unroll
+        for (int it = 0; it < ITS; ++it) {
+          const unsigned at = mpix[tm][it] != ~0u && ech < a.K ? (mpix[tm][it] * (unsigned)a.K + (unsigned)ech) * ES : kOob;
+          if constexpr (IS_I8) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs_r, (int)at, 0, 0);
+            resv[tm][it] = make_uint4(v[0], v[1], 0u, 0u);
+          } else {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs_r, (int)at, 0, 0);
+            resv[tm][it] = make_uint4(v[0], v[1], v[2], v[3]);
+          }
+        }
+    }
+  };
   // Step t multiplies the operands that step t - 1 read and reads those of step t + 1, so that LDS and matrix cores
   // work at the same time.  A step's loads were issued two steps before they are read.  LAST: the last chunk, behind
   // which nothing is left to load.
@@ -283,6 +325,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
     constexpr int nread = LAST && t == 8 ? 0 : NR;
     if constexpr (nread > 0) {  // the operands this step reads have landed once only the loads behind step t - 1 are pending
       if (t == 0 && touched == 4) wait_loads<LW + 4>();
+      else if (LAST && (t == RES_AT + 1 || t == RES_AT + 2) && pre_res) wait_loads<(t - 1 < FT ? LW : 0) + NRES>();   // (the residual's too)
       else wait_loads<t == 0 ? LW : (LAST ? (t - 1 < FT ? LW : 0) : loads_behind(t == 0 ? 8 : t - 1, LW, XN))>();
       __builtin_amdgcn_s_barrier();
     }
@@ -297,6 +340,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
       for (int i = 2 * m; i < nread && (i < 2 * m + 2 || m == NM - 1); ++i) read_one((t + 1) % 9, i, cur ^ 1);
       // where the next step reads, worked out while the last MFMAs run
       if (m == (2 * (NM - 2) >= NR ? NM - 2 : NM - 1)) locate_tap(cc + (t + 2) / 9, (t + 2) % 9);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (LAST && t == RES_AT) {
+      request_residual();
       __builtin_amdgcn_sched_barrier(0);
     }
     // (the compiler may not sink a step's MFMAs to where the sums are used)
@@ -341,7 +388,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   chunk(g.ncc - 1, std::true_type{});
 
   // ---- epilogue: as in the implicit-GEMM kernel, with the flat position decoded back to a pixel
-  wait_loads<0>();
+  wait_loads<NRES>();   // (nothing but the residual is in flight any more)
   __builtin_amdgcn_s_barrier();  // every wave is done reading
   constexpr int XCH = SK > 1 ? (TM * TN - TM_E * TN_E) * 4 * 64 : 0;  // slots a wave hands to the others of its tile
   acc_t fin[TN_E][TM_E];
@@ -393,31 +440,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
     }
   }
   uint4* stg = lds + NW * XCH + wave * (32 * EP);
-  constexpr int PPI = 64 / CG;
-  const int epix = lane / CG, ecg = lane % CG;
-  const bool vec_ok = (a.K & 7) == 0;
   const OutLoc ol = EXT ? locate_output(a, ech) : OutLoc{nullptr, 0, 0, 0};
-  // the output pixels of this lane (the output pixel of a flat position o is the table's entry for o + P + 1),
-  // read together, and all its residual vectors: in flight together, behind the transpositions below
-  constexpr int ITS = 32 / PPI;
-  const bool pre_res = (a.flags & F_RES) && vec_ok;
-  unsigned mpix[TM_E][ITS];
-  uint4 resv[TM_E][ITS];
-#pragma unroll
-  for (int tm = 0; tm < TM_E; ++tm)
-#pragma unroll
-    for (int it = 0; it < ITS; ++it) {
-      const int pix = it * PPI + epix;
-      mpix[tm][it] = ptab[(SQUARE ? ((wm * TM + tm_lo + tm) * 2 + (pix >> 4)) * SQP + (pix & 15) : wm * WTM + (tm_lo + tm) * 32 + pix) + P + 1];
-    }
-  if (pre_res) {
-#pragma unroll
-    for (int tm = 0; tm < TM_E; ++tm)
-#pragma unroll
-      for (int it = 0; it < ITS; ++it)
-        resv[tm][it] = (mpix[tm][it] != ~0u && ech < a.K) ? load_residual8<IS_I8>(a, (int)mpix[tm][it], ech)
-                                                           : make_uint4(0u, 0u, 0u, 0u);
-  }
 #pragma unroll
   for (int tm = 0; tm < TM_E; ++tm) {
 #pragma unroll

@@ -32,7 +32,7 @@ inline FastDiv make_fastdiv(uint32_t d) {
 }
 
 RELAY_HD inline uint32_t fast_div(uint32_t n, FastDiv f) {
-  return f.mul ? (uint32_t)(((uint64_t)n * f.mul) >> 32) >> f.shift : n;
+  return ((uint32_t)(((uint64_t)n * f.mul) >> 32) >> f.shift) | (f.mul ? 0u : n);   // (no branch: without a multiplier the product is 0)
 }
 
 }  // namespace relay
