@@ -589,6 +589,20 @@ relay_status relay_conv_forced(int32_t* forced);
  * on it. */
 relay_status relay_set_conv_workgroups(int32_t workgroups);
 
+/* The launches of a captured pass, enqueued again by one call (paper Section 5.2, launch overhead at small batch; Section 3.3,
+ * operator invocations as calls on preallocated buffers).  For a HIP graph that is a chain of at most 64 launches of
+ * this library's kernels; RELAY_ERR_UNSUPPORTED and *list = NULL for any other, which is launched as the graph it is.
+ *   create   reads the graph (a hipGraph_t passed as void*; not instantiated).  The list refers to the argument blocks of
+ *            its nodes: the graph has to outlive the list and stay as it is.  Host memory only, no launch.
+ *   run      enqueues every launch on hip_stream, in order, before it returns, with the arguments they were captured with.
+ *            Threads that share a list enqueue one pass after the other.  RELAY_ERR_UNSUPPORTED, nothing enqueued:
+ *            hip_stream is being captured.
+ *   destroy  frees the list (launches already enqueued are not affected). */
+typedef struct relay_launch_list relay_launch_list;
+relay_status relay_launch_list_create(void* hip_graph, relay_launch_list** list);
+relay_status relay_launch_list_run(relay_launch_list* list, void* hip_stream);
+relay_status relay_launch_list_destroy(relay_launch_list* list);
+
 /* Measurement aids for the roofline figures (paper Section 5.1 states how its measurements are
  * taken; these give the chip's measured ceilings to set beside the nominal ones):
  *   relay_probe_mfma  every wave of `workgroups` workgroups of 256 threads runs `iters` rounds of four

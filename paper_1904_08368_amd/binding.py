@@ -104,6 +104,9 @@ SIGNATURES = {
     "relay_probe_mfma": [_I, _I, _I, _P, _P],
     "relay_probe_copy": [_P, _P, C.c_int64, _P],
     "relay_probe_grid_barrier": [_I, _I, C.c_uint32, _P, _P, _P],
+    "relay_launch_list_create": [_P, C.POINTER(_P)],
+    "relay_launch_list_run": [_P, _P],
+    "relay_launch_list_destroy": [_P],
     "relay_set_conv_tile": [_I],
     "relay_set_conv_split": [_I],
     "relay_conv_forced": [C.POINTER(_I)],
@@ -516,6 +519,45 @@ def relay_conv2d_maxpool_kernel_name(d: ConvDesc) -> str:
     buf = C.create_string_buffer(128)
     _check(lib().relay_conv2d_maxpool_kernel_name(C.byref(d), buf, 128))
     return buf.value.decode()
+
+
+def relay_launch_list_create(hip_graph: int) -> int:
+    out = _P(None)
+    _check(lib().relay_launch_list_create(hip_graph, C.byref(out)))
+    return out.value
+
+
+def relay_launch_list_run(handle: int, stream: Optional[int]) -> None:
+    _check(lib().relay_launch_list_run(handle, stream))
+
+
+def relay_launch_list_destroy(handle: int) -> None:
+    _check(lib().relay_launch_list_destroy(handle))
+
+
+class LaunchList:
+    """The launches of a captured torch.cuda.CUDAGraph(keep_graph=True), which it keeps alive."""
+
+    def __init__(self, graph):
+        import torch
+        self.handle = None
+        self.graph = graph
+        self.device = torch.cuda.current_device()
+        self.stream = torch._C._cuda_getCurrentRawStream
+        self.handle = relay_launch_list_create(graph.raw_cuda_graph())
+
+    def run(self) -> bool:
+        """Enqueues them on torch's current stream of the device of the capture; False (and nothing enqueued) while that stream
+        is being captured."""
+        status = _lib.relay_launch_list_run(self.handle, self.stream(self.device) or None)
+        if status == 4:
+            return False
+        _check(status)
+        return True
+
+    def __del__(self):
+        if self.handle is not None and _lib is not None:
+            _lib.relay_launch_list_destroy(self.handle)
 
 
 def relay_probe_mfma(dtype: int, iters: int, workgroups: int, out) -> None:

@@ -257,4 +257,11 @@ hipError_t launch_probe_copy(const void* src, void* dst, long bytes, hipStream_t
 hipError_t launch_pack_filters_rows(const void* w_oihw, void* w_packed, int K, int Csrc, int R, int S, int ck,
                                     int Kp, int esize, hipStream_t st);
 
+// the kernel launches of a captured graph that is a chain of at most `most` of this library's kernels (launch_list.cpp);
+// *out = nullptr for any other
+struct LaunchList;
+hipError_t make_launch_list(hipGraph_t graph, size_t most, LaunchList** out);
+hipError_t run_launch_list(LaunchList* l, hipStream_t st);
+void free_launch_list(LaunchList* l);
+
 }  // namespace relay

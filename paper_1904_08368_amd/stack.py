@@ -580,16 +580,28 @@ class FusedNet:
         return [("+".join(self.call_names[i:i + n]), fn, args) for i, n, fn, args in self._steps()]
 
     def capture(self) -> None:
-        """Record run() into a HIP graph (kernel launches only; nothing in it clears memory)."""
+        """Record run() into a HIP graph (kernel launches only; nothing in it clears memory).  replay() enqueues the recorded
+        launches one by one from native code where they are a chain of the library's kernels, which saves the idle time
+        between two replays of a graph (5 us, of 21 to 257 us a pass at 5 to 20 launches); any other graph is replayed as
+        one.  The graph is instantiated when it is first replayed as one."""
         self.run()
         torch.cuda.synchronize(self.dev)
-        g = torch.cuda.CUDAGraph()
+        g = torch.cuda.CUDAGraph(keep_graph=True)
         with torch.cuda.graph(g):
             self.run()
+        try:
+            self.launch_list = B.LaunchList(g)
+        except B.RelayError:
+            self.launch_list = None
+            g.instantiate()
         self.graph = g
 
+    launch_list = None
+
     def replay(self) -> None:
-        self.graph.replay()
+        recorded = self.launch_list
+        if recorded is None or recorded.graph is not self.graph or not recorded.run():
+            self.graph.replay()
 
     def tensor(self, name: str) -> np.ndarray:
         """Download a named tensor as NCHW with the logical channel count."""
