@@ -4,7 +4,7 @@
 // memory latency where there are many pixels, but a layer of few pixels is one long serial chain: 512 -> 512 at
 // 14 x 14, batch 32 took 15.2 us there for 3.3 GFLOP and 13 MB, and at batch 1 two launches (4.8 + 4.6 us) beat it.
 // Here a workgroup has a single barrier:
-//   1. every thread computes depthwise outputs of 8 channels of two pixels (one above the other) at a time straight
+//   1. every thread computes depthwise outputs of 8 channels of two or four pixels (one above the other) at a time straight
 //      from memory -- channels lie along the lanes, so a wave's load is a run of whole lines, taps in the
 //      padding read zeros -- with the loads of its next pixels under way, and writes them, narrowed to fp16, into an
 //      LDS tile that holds ALL channels of the rectangle;
@@ -43,7 +43,7 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t rsrc, unsi
 
 // What the host works out for a launch.
 struct DirectGeom {
-  int th, tw;                      // rectangle of output pixels, th even, th * tw <= BM
+  int th, tw;                      // rectangle of output pixels, th a multiple of MR, th * tw <= BM
   int tiles_x, tiles_y, tiles_n;   // rectangles of an image, channel tiles
   int n_major;                     // consecutive workgroups share a channel tile (else a rectangle)
   int log_cv;                      // log2(C / 8)
@@ -52,15 +52,19 @@ struct DirectGeom {
 };
 
 // BM: rows of the tile (16: the matrix instruction's other 16 rows repeat them); WN: waves with 32 output channels each,
-// of NW that share the depthwise work; NS: ring stages of 32 channels; CP: most channels / 32.
-template <int STRIDE, int BM, int WN, int NW, int NS, int CP>
-__global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwArgs a, const DirectGeom g) {
+// of NW that share the depthwise work; NS: ring stages of 32 channels; CP: most channels / 32.  OCC: 0, a thread has the
+// inputs of two items in registers, or the waves per SIMD for which it has those of one.  MR: output rows of an item.
+// Four rows take 18 loads at stride 1 where twice two take 24, and one memory latency instead of two: with 256 or 128 channels
+// and 64 x 128 tiles, a thread's whole share (128 -> 128 at 56 x 56, batch 32 21.4 -> 20.0 us; 512 -> 512 at 14 x 14 as 64 x 256
+// 13.9 -> 13.2, as 32 x 256 9.5 -> 8.9 at batch 16 of 13 x 12).  Where fewer items than threads are left the two rows win.
+template <int STRIDE, int BM, int WN, int NW, int NS, int CP, int OCC, int MR>
+__global__ __launch_bounds__(64 * NW, OCC ? OCC : 1) void dwpw_fused_direct_kernel(const DwPwArgs a, const DirectGeom g) {
   constexpr int NT = 64 * NW, BN = 32 * WN;
   constexpr int TM = BM >= 32 ? BM / 32 : 1;
   constexpr int APL = BM * BKV + BKV;       // slots of a 32-channel plane of the tile (padded: the planes start on other banks)
   constexpr int FPL = 32 * BKV;             // slots of a ring stage: 32 filters x 64 bytes
   constexpr int EP = 9;                     // epilogue staging pitch
-  constexpr int IH = STRIDE + 3;            // input rows under an item's two pixels
+  constexpr int IH = (MR - 1) * STRIDE + 3; // input rows under an item's MR pixels
   static_assert(NS * FPL >= 32 * EP, "the staging block reuses the ring");
   static_assert(NS % 2 == 0 && NS >= 4, "whole groups of planes");
   static_assert(NW % WN == 0, "the waves share the first fill of the rings evenly");
@@ -89,7 +93,7 @@ __global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwAr
   const int ty = (int)t2 - n * g.tiles_y;
   const int oy0 = ty * g.th, ox0 = tx * g.tw, n0 = tile_n * BN;
 
-  // ---- depthwise work: item = (two pixels, one above the other; channel vector); a thread keeps its channel vector
+  // ---- depthwise work: item = (MR pixels, one above the other; channel vector); a thread keeps its channel vector
   const int cvecs = 1 << g.log_cv;
   const int cv = tid & (cvecs - 1);
   const int groups = NT >> g.log_cv;              // items of a channel vector that the workgroup takes at a time
@@ -100,8 +104,8 @@ __global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwAr
   auto load_item = [&](int it, uint4(&xv)[IH][3]) {
     const int item = it * groups + (tid >> g.log_cv);
     const int py = (int)fast_div((unsigned)item, g.fd_tw), px = item - py * g.tw;
-    const int iy = (oy0 + 2 * py) * STRIDE - 1, ix = (ox0 + px) * STRIDE - 1;
-    const bool live = 2 * py < g.th;
+    const int iy = (oy0 + MR * py) * STRIDE - 1, ix = (ox0 + px) * STRIDE - 1;
+    const bool live = MR * py < g.th;
     const unsigned base = (unsigned)(((n * a.H + iy) * a.W + ix) * pix_bytes + cv * 16);
 #pragma unroll
     for (int r = 0; r < IH; ++r) {
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwAr
   // requested in the order of need: the first two items, the depthwise filters and constants, the 1x1 filters
   uint4 xa[IH][3], xb[IH][3];
   load_item(0, xa);
-  if (nit > 1) load_item(1, xb);
+  if (!OCC && nit > 1) load_item(1, xb);
   uint4 wv[9];
   {
     const uint4* w = static_cast<const uint4*>(a.dw_w) + cv;   // [tap][C/8]
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwAr
     const int item = it * groups + (tid >> g.log_cv);
     const int py = (int)fast_div((unsigned)item, g.fd_tw), px = item - py * g.tw;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < MR; ++i) {
       float dacc[8];
 #pragma unroll
       for (int fr = 0; fr < 3; ++fr)
@@ -185,11 +189,16 @@ __global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwAr
             }
           }
         }
-      const int row = (2 * py + i) * g.tw + px;
-      if (2 * py < g.th) act[(cv >> 2) * APL + lds_slot(row, cv & 3)] = scale_shift_narrow8(dacc, mul, add, relu_lo);
+      const int row = (MR * py + i) * g.tw + px;
+      if (MR * py < g.th) act[(cv >> 2) * APL + lds_slot(row, cv & 3)] = scale_shift_narrow8(dacc, mul, add, relu_lo);
     }
   };
-  for (int it = 0; it < nit; it += 2) {
+  if constexpr (OCC) {
+    for (int it = 0; it < nit; ++it) {
+      compute_item(it, xa);
+      if (it + 1 < nit) load_item(it + 1, xa);
+    }
+  } else for (int it = 0; it < nit; it += 2) {
     compute_item(it, xa);
     if (it + 2 < nit) load_item(it + 2, xa);
     if (it + 1 < nit) {
@@ -210,7 +219,8 @@ __global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwAr
     for (int v = 0; v < 16; ++v) acc[tm][v] = 0;
   const int lrow = lane & 31, lhalf = lane >> 5;
   // a group of UP planes is multiplied while the fragments of the next are on their way from LDS
-  constexpr int UP = TM == 1 && NS % 4 == 0 ? 4 : 2;
+  // (three waves per SIMD cover each other's reads, and the registers of a second plane would spill: 128 -> 128 at 56 x 56 36 us)
+  constexpr int UP = OCC >= 3 ? 1 : TM == 1 && NS % 8 == 0 ? 4 : 2;
   struct Frags {
     uint4 w[UP][2], x[UP][2][TM];
   };
@@ -296,23 +306,26 @@ __global__ __launch_bounds__(64 * NW) void dwpw_fused_direct_kernel(const DwPwAr
 }
 
 struct DirectTile {
-  int bm, wn, nw, ns, cp;
+  int bm, wn, nw, ns, cp, mr;
 };
-// (index, rows, waves with filters, waves, ring stages, most channels / 32)
+// (at stride 2 four output rows would need nine input rows in registers)
+constexpr int rows_of(int stride, int mr) { return stride == 1 ? mr : 2; }
+// (index, rows, waves with filters, waves, ring stages, most channels / 32, OCC, MR at stride 1)
 #define RELAY_DWPW_DIRECT(X) \
-  X(0, 16, 2, 4, 8, 8) X(1, 32, 4, 4, 8, 8) X(2, 32, 8, 8, 8, 8) X(3, 16, 1, 8, 32, 32) X(4, 16, 2, 8, 16, 16) \
-  X(5, 32, 2, 8, 16, 16) X(6, 32, 4, 8, 8, 16) X(7, 32, 8, 8, 6, 16) X(8, 64, 8, 8, 4, 16)
-#define RELAY_DWPW_DIRECT_ENTRY(i, bm, wn, nw, ns, cp) {bm, wn, nw, ns, cp},
+  X(0, 16, 2, 4, 8, 8, 0, 2) X(1, 32, 4, 4, 8, 8, 0, 2) X(2, 32, 8, 8, 8, 8, 0, 2) X(3, 16, 1, 8, 32, 32, 0, 2) X(4, 16, 2, 8, 16, 16, 0, 2) \
+  X(5, 32, 2, 8, 16, 16, 0, 2) X(6, 32, 4, 8, 8, 16, 0, 2) X(7, 32, 8, 8, 6, 16, 0, 2) X(8, 64, 8, 8, 4, 16, 0, 2) X(9, 32, 8, 8, 6, 16, 2, 4) \
+  X(10, 64, 8, 8, 4, 16, 2, 4) X(11, 64, 4, 4, 4, 4, 3, 4) X(12, 64, 4, 4, 4, 4, 3, 2)
+#define RELAY_DWPW_DIRECT_ENTRY(i, bm, wn, nw, ns, cp, occ, mr) {bm, wn, nw, ns, cp, mr},
 constexpr DirectTile kDirect[] = {RELAY_DWPW_DIRECT(RELAY_DWPW_DIRECT_ENTRY)};
 constexpr int kNumDirect = sizeof(kDirect) / sizeof(kDirect[0]);
 
-// The rectangle of at most bm pixels, an even number of rows high, that covers an image with the fewest tiles; of those
+// The rectangle of at most bm pixels, a multiple of mr rows high, that covers an image with the fewest tiles; of those
 // the one with the smallest input patch.
-void pick_rectangle(const DwPwArgs& a, int bm, int* th, int* tw) {
+void pick_rectangle(const DwPwArgs& a, int bm, int mr, int* th, int* tw) {
   long best_tiles = -1, best_patch = 0;
-  for (int h = 2; h <= bm; h += 2) {
+  for (int h = mr; h <= bm; h += mr) {
     const int w = bm / h < a.Wo ? bm / h : a.Wo;
-    if (w < 1 || (h > 2 && h > a.Ho + 1)) break;
+    if (w < 1 || (h > mr && h > a.Ho + mr - 1)) break;
     const int nx = (a.Wo + w - 1) / w, wb = (a.Wo + nx - 1) / nx;   // (as narrow as the same number of tiles allows)
     const long tiles = (long)((a.Ho + h - 1) / h) * nx;
     const long patch = (long)((h - 1) * a.stride + 3) * ((wb - 1) * a.stride + 3);
@@ -327,7 +340,8 @@ void pick_rectangle(const DwPwArgs& a, int bm, int* th, int* tw) {
 
 DirectGeom make_geom(const DwPwArgs& a, const DirectTile& t) {
   DirectGeom g;
-  pick_rectangle(a, t.bm, &g.th, &g.tw);
+  const int mr = rows_of(a.stride, t.mr);
+  pick_rectangle(a, t.bm, mr, &g.th, &g.tw);
   g.tiles_x = (a.Wo + g.tw - 1) / g.tw;
   g.tiles_y = (a.Ho + g.th - 1) / g.th;
   g.tiles_n = (a.pw.K + t.wn * 32 - 1) / (t.wn * 32);
@@ -341,15 +355,15 @@ DirectGeom make_geom(const DwPwArgs& a, const DirectTile& t) {
   g.fd_p = make_fastdiv((uint32_t)(a.N * g.tiles_y * g.tiles_x));
   g.fd_tw = make_fastdiv((uint32_t)g.tw);
   const int groups = (t.nw * 64) >> g.log_cv;
-  g.nit = (g.th / 2 * g.tw + groups - 1) / groups;
+  g.nit = (g.th / mr * g.tw + groups - 1) / groups;
   return g;
 }
 
-template <int STRIDE, int BM, int WN, int NW, int NS, int CP>
+template <int STRIDE, int BM, int WN, int NW, int NS, int CP, int OCC, int MR>
 hipError_t launch_direct_one(const DwPwArgs& a, hipStream_t st) {
-  const DirectGeom g = make_geom(a, DirectTile{BM, WN, NW, NS, CP});
+  const DirectGeom g = make_geom(a, DirectTile{BM, WN, NW, NS, CP, MR});
   const long wgs = (long)a.N * g.tiles_y * g.tiles_x * g.tiles_n;
-  hipLaunchKernelGGL((dwpw_fused_direct_kernel<STRIDE, BM, WN, NW, NS, CP>), dim3((unsigned)wgs), dim3(64 * NW), 0, st, a, g);
+  hipLaunchKernelGGL((dwpw_fused_direct_kernel<STRIDE, BM, WN, NW, NS, CP, OCC, MR>), dim3((unsigned)wgs), dim3(64 * NW), 0, st, a, g);
   return hipGetLastError();
 }
 
@@ -366,35 +380,54 @@ bool dwpw_direct_supported(const DwPwArgs& a, int v) {
          (size_t)a.N * a.H * a.W * a.C * 2 <= lim && (size_t)a.pw.K * a.pw.Kp * 2 <= lim;
 }
 
-// The smallest tile whose workgroups fit the chip at once, from 64 channels on; -1 where none does: a second round
-// of workgroups repeats the whole chain, and the chunked kernel or two launches are then as fast.  (Graph-timed; two
+// From 64 channels on, the smallest tile whose workgroups fit the chip at once: a second round of such
+// workgroups repeats the whole chain, and the chunked kernel or two launches are then as fast.  (Graph-timed; two
 // launches or, with a star, the chunked kernel -> this one.)  One image: 64 -> 128 at 112 x 112 / 2 6.2 -> 4.4 us, 128 at 56 x 56
 // 7.4 -> 4.5, 256 at 28 x 28 7.7 -> 4.4, 512 at 14 x 14 8.7 -> 5.5, 1024 at 7 x 7 9.8 -> 7.6.  4 images: 6.8* -> 5.7, 8.4* -> 5.9,
 // 8.1 -> 5.8, 8.7 -> 7.3.  32 images: 256 -> 512 at 28 x 28 / 2 12.7* -> 9.8, 512 at 14 x 14 13.7* -> 13.0, 512 -> 1024 / 2 12.1 -> 9.7.
-// Two rounds: 64 -> 128 at 82 x 103 / 2, 11 images 9.1* against 10.0; 1024 at 7 x 7, 4 images 10.5 against 14.3.
+// Two rounds: 1024 at 7 x 7, 4 images 10.5 against 14.3.
 // (A tile of up to 256 channels takes 3 us behind the launch with 16 pixels x 64 channels, 5 with 32 x 256, 7 with 64 x 256;
 // with 512 channels 4.1 with 16 x 32, 5.5 with 32 x 64, 7.1 with 32 x 256, 10 with 64 x 256.)
+// The tiles of four-row items come before those of two where every thread has one (512 channels in 32 rows, 256 in 64), and are passed by
+// where their rectangles are too many (9 rows as 4 + 4 + 1).
+// Up to 128 channels on both sides, beyond one round: 64 x 128 tiles, three workgroups to a CU (41 to 49 KB of LDS, 150 registers), which
+// cover each other's latencies where the chunked kernel waits at its barriers.  Operands from beyond the L2, chunked* or two launches -> this:
+// 64 -> 128 / 2 at 82 x 103, 11 images 11.5 -> 8.2, at 100 x 90, 16 images 15.8 -> 10.2, at 112 x 112, 32 images 24.2* -> 23.0; 128 -> 128 at
+// 50 x 45, 16 images 13.7* -> 11.1, at 56 x 56, 32 images 24.0* -> 20.0, at 112 x 112 79* -> 69; 128 -> 128 / 2 at 112 x 112 47.9 -> 34.0; 64 -> 64 at
+// 56 x 56 17.7* -> 14.4, at 112 x 112 47.4 -> 48.2.  64 channels take them also within one round of 64 x 256 (3 images at 56 x 56
+// 5.15 -> 4.82), 128 do not (128 -> 128 / 2 at 90 x 70, 7 images 7.3 against 7.8).
 int dwpw_direct_pick(const DwPwArgs& a) {
   if (a.C < 64) return -1;
-  for (int v = 0; v < kNumDirect; ++v) {
-    const bool wide_c = kDirect[v].cp > 8;   // (up to 256 channels: the variants whose LDS is sized for them, then the largest tile)
-    if ((a.C > 256) != wide_c && v != kNumDirect - 1) continue;
-    if (!dwpw_direct_supported(a, v)) continue;
+  auto one_round = [&](int v) {
+    if (!dwpw_direct_supported(a, v)) return false;
     const DirectGeom g = make_geom(a, kDirect[v]);
-    if ((long)a.N * g.tiles_y * g.tiles_x * g.tiles_n <= 256) return v;
+    return (long)a.N * g.tiles_y * g.tiles_x * g.tiles_n <= 256;
+  };
+  const bool thin = a.C <= 128 && a.pw.K <= 128;
+  const int streams = a.C > 64 ? 11 : 12;   // (four-row items where every thread has one)
+  if (a.C > 256) {
+    for (int v : {3, 4, 5, 6, 9, 7, 10})
+      if (one_round(v)) return v;
+  } else {
+    for (int v : {0, 1, 2})
+      if (one_round(v)) return v;
+    if (thin && a.C <= 64 && dwpw_direct_supported(a, streams)) return streams;
+    if (a.C == 256 && one_round(10)) return 10;
   }
-  return -1;
+  if (one_round(8)) return 8;
+  return thin && dwpw_direct_supported(a, streams) ? streams : -1;
 }
 
 hipError_t launch_dwpw_direct(const DwPwArgs& a, int v, hipStream_t st) {
   switch (v) {
-#define RELAY_DWPW_DIRECT_CASE(i, bm, wn, nw, ns, cp) \
-  case i: return a.stride == 1 ? launch_direct_one<1, bm, wn, nw, ns, cp>(a, st) : launch_direct_one<2, bm, wn, nw, ns, cp>(a, st);
+#define RELAY_DWPW_DIRECT_CASE(i, bm, wn, nw, ns, cp, occ, mr) \
+  case i: return a.stride == 1 ? launch_direct_one<1, bm, wn, nw, ns, cp, occ, mr>(a, st) : launch_direct_one<2, bm, wn, nw, ns, cp, occ, 2>(a, st);
     RELAY_DWPW_DIRECT(RELAY_DWPW_DIRECT_CASE)
     default: return hipErrorInvalidValue;
   }
 }
 
+// (without the last two template arguments)
 void dwpw_direct_kernel_name(const DwPwArgs& a, int v, char* buf, size_t len) {
   const DirectTile& t = kDirect[v];
   snprintf(buf, len, "dwpw_fused_direct_kernel<%d, %d, %d, %d, %d, %d>", a.stride, t.bm, t.wn, t.nw, t.ns, t.cp);

@@ -62,3 +62,24 @@ def test_rule(G, n, c, h, w, k, stride, name):
     got = B.relay_dwconv_pwconv_kernel_name(d, k)
     assert (f"dwpw_fused_direct_kernel<{stride}, {name}>" == got) if name else ("direct" not in got)
     assert B.relay_dwconv_pwconv_few_pixels(d, k) == (name is not None)
+
+
+# most channels of the variants with items of four rows (9 to 11) or three workgroups to a CU (11, 12)
+@pytest.mark.gpu
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("variant,most", [(9, 512), (10, 512), (11, 128), (12, 128)])
+def test_variants_of_one_item_in_registers_at_the_edges(G, variant, most, stride):
+    """Heights of every remainder of four, images lower than an item, rectangles that end past the image, channel tiles that
+    end within a wave's 32 channels, threads without an item, several rounds of workgroups."""
+    for i, (n, c, h, w, k) in enumerate([(1, 32, 1, 1, 8), (2, 64, 5, 3, 40), (1, most, 7, 7, 136), (3, 64, 9, 33, 72), (1, 128, 2, 70, 136),
+                                         (1, most // 2, 14, 15, 64), (2, most, 11, 13, 128), (1, most, 10, 6, 8), (5, 128, 60, 61, 128)]):
+        _case(G, 9900 + 100 * variant + 10 * stride + i, n, c, h, w, k, stride, variant=200 + variant, plain_tail=i % 2 == 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,c,h,w,k,stride,name", [
+    (32, 64, 56, 56, 64, 1, "64, 4, 4, 4, 4"), (32, 64, 56, 56, 136, 1, None), (32, 128, 56, 56, 128, 1, "64, 4, 4, 4, 4"),
+    (32, 128, 56, 56, 128, 2, "64, 4, 4, 4, 4"), (7, 128, 90, 70, 128, 2, "64, 8, 8, 4, 16"), (32, 512, 10, 9, 512, 1, "32, 8, 8, 6, 16"),
+    (32, 256, 18, 18, 256, 1, "64, 8, 8, 4, 16"), (32, 256, 56, 56, 256, 1, None)])
+def test_rule_beyond_one_round(G, n, c, h, w, k, stride, name):
+    test_rule(G, n, c, h, w, k, stride, name)
