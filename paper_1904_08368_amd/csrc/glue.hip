@@ -56,7 +56,7 @@ template <typename T>
 __global__ __launch_bounds__(64) void nchw_to_nhwc_vec_kernel(const T* x, T* y, int C, int HW, int Cpad, int pgroups, int cgroups) {
   constexpr int VE = 16 / (int)sizeof(T), PX = sizeof(T) == 2 ? 8 : 4;
   constexpr int NV = PX * (int)sizeof(T) / 4;  // words of a channel's piece
-  const int tile = blockIdx.x;                 // (image, pixel block, channel block)
+  const int tile = xcd_remap((int)blockIdx.x, (int)gridDim.x);   // (image, pixel block, channel block); the XCD of the conv that reads it
   const int per_n = pgroups * cgroups;
   const int n = tile / per_n, rem = tile - n * per_n;
   const int pb = rem / cgroups, cb = rem - pb * cgroups;
