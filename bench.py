@@ -285,7 +285,7 @@ def main() -> int:
     ap.add_argument("--steps", type=int, default=100)
     ap.add_argument("--warmup", type=int, default=10)
     ap.add_argument("--batch", type=int, default=32)
-    ap.add_argument("--no-graph", action="store_true", help="launch eagerly instead of replaying a HIP graph")
+    ap.add_argument("--no-graph", action="store_true", help="launch eagerly instead of replaying the captured pass")
     ap.add_argument("--no-extra", action="store_true", help="skip the int8 / MobileNet / batch-1 sections")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--layer-reps", type=int, default=20)
@@ -342,7 +342,8 @@ def main() -> int:
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f16", "data": "synthetic",
         "config": {"workload": "configs[2]: full ResNet-18 stack (20 fused convs + pools + dense 512->1000), "
                                f"fp16 / fp32 accumulate, batch {a.batch}, 3x224x224, NHWC",
-                   "batch": a.batch, "hip_graph": use_graph},
+                   "batch": a.batch, "hip_graph": use_graph and net.launch_list is None,
+                   "recorded_launches": use_graph and net.launch_list is not None},
         "ms_per_img": round(sec * 1e3 / a.batch, 5),
         "roofline": roofline,
     }

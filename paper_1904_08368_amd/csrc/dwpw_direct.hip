@@ -1,4 +1,5 @@
-// Depthwise 3x3 conv2d and the 1x1 conv2d behind it as one kernel, for layers of few pixels (small batches, deep layers).
+// Depthwise 3x3 conv2d and the 1x1 conv2d behind it as one kernel, for layers of few pixels (small batches, deep layers) and for blocks
+// of at most 128 channels.
 //
 // The patch kernel (dwpw.hip) cuts the channels into chunks and walks them behind a barrier per chunk.  That hides
 // memory latency where there are many pixels, but a layer of few pixels is one long serial chain: 512 -> 512 at

@@ -193,7 +193,7 @@ int dwpw_pick(const DwPwArgs& a);   // variant expected to beat the two separate
 int dwpw_any(const DwPwArgs& a);    // dwpw_pick, else any variant that takes the shape, or -1
 hipError_t launch_dwpw(const DwPwArgs& a, int variant, hipStream_t st);
 void dwpw_kernel_name(int variant, char* buf, size_t len);
-// ... and for layers of few pixels, without chunks (dwpw_direct.hip).
+// ... and for layers of few pixels and blocks of at most 128 channels, without chunks (dwpw_direct.hip).
 int dwpw_direct_variant_count();
 bool dwpw_direct_supported(const DwPwArgs& a, int variant);
 int dwpw_direct_pick(const DwPwArgs& a);   // variant expected to beat the two separate launches and the chunked kernel, or -1
