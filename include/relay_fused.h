@@ -592,8 +592,8 @@ relay_status relay_set_conv_workgroups(int32_t workgroups);
 /* The launches of a captured pass, enqueued again by one call (paper Section 5.2, launch overhead at small batch; Section 3.3,
  * operator invocations as calls on preallocated buffers).  For a HIP graph that is a chain of at most 64 launches of
  * this library's kernels; RELAY_ERR_UNSUPPORTED and *list = NULL for any other, which is launched as the graph it is.
- *   create   reads the graph (a hipGraph_t passed as void*; not instantiated).  The list refers to the argument blocks of
- *            its nodes: the graph has to outlive the list and stay as it is.  Host memory only, no launch.
+ *   create   reads the graph (a hipGraph_t passed as void*; not instantiated) and keeps a copy of it: what becomes of the graph
+ *            later does not reach the list.  The buffers that its launches name are the caller's to keep.  Host memory only, no launch.
  *   run      enqueues every launch on hip_stream, in order, before it returns, with the arguments they were captured with.
  *            Threads that share a list enqueue one pass after the other.  RELAY_ERR_UNSUPPORTED, nothing enqueued:
  *            hip_stream is being captured.

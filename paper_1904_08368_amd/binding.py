@@ -536,15 +536,21 @@ def relay_launch_list_destroy(handle: int) -> None:
 
 
 class LaunchList:
-    """The launches of a captured torch.cuda.CUDAGraph(keep_graph=True), which it keeps alive."""
+    """The launches that a captured torch.cuda.CUDAGraph(keep_graph=True) holds now, in a copy of their own.  The graph is kept alive
+    for the memory that belongs to it; `held`, where it has one, counts how often what it holds was replaced."""
 
     def __init__(self, graph):
         import torch
         self.handle = None
         self.graph = graph
+        self.held = getattr(graph, "held", 0)
         self.device = torch.cuda.current_device()
         self.stream = torch._C._cuda_getCurrentRawStream
         self.handle = relay_launch_list_create(graph.raw_cuda_graph())
+
+    def is_of(self, graph) -> bool:
+        """Are these the launches that the graph holds?  Not after its reset() or another capture into it."""
+        return self.graph is graph and self.held == getattr(graph, "held", 0)
 
     def run(self) -> bool:
         """Enqueues them on torch's current stream of the device of the capture; False (and nothing enqueued) while that stream

@@ -7,8 +7,8 @@
 // deep Q-network at batch 1 22.9 -> 17.8 us, ResNet-18 at batch 1 89.6 -> 81.9 (int8 72.5 -> 66.8), at batch 32 260 -> 248,
 // MobileNet-v1 at batch 32 255.4 -> 250.5; the first pass on a new network of five launches 60 -> 33 us.  The host spends 12 us on
 // five launches and 35 to 46 on 16 to 20, the graph's replay 18 and 25: it stays ahead of the GPU in both.
+#include <memory>
 #include <mutex>
-#include <new>
 #include <vector>
 
 #include <dlfcn.h>
@@ -19,9 +19,13 @@
 namespace relay {
 
 struct LaunchList {
-  std::vector<hipKernelNodeParams> launches;   // (their argument blocks are owned by the graph's nodes)
+  hipGraph_t copy = nullptr;                   // owns the argument blocks: the captured graph may go before the list
+  std::vector<hipKernelNodeParams> launches;
   int device = 0;
   std::mutex issue;   // a pass is enqueued whole, also when threads share the list and the stream
+  ~LaunchList() {
+    if (copy) (void)hipGraphDestroy(copy);
+  }
 };
 
 namespace {
@@ -39,12 +43,15 @@ hipError_t make_launch_list(hipGraph_t graph, size_t most, LaunchList** out) {
   hipError_t e = hipGraphGetNodes(graph, nullptr, &n);
   if (e != hipSuccess) return e;
   if (n == 0 || n > most) return hipSuccess;
+  auto l = std::make_unique<LaunchList>();
+  if ((e = hipGetDevice(&l->device)) != hipSuccess) return e;
+  if ((e = hipGraphClone(&l->copy, graph)) != hipSuccess) return e;
   std::vector<hipGraphNode_t> nodes(n);
-  if ((e = hipGraphGetNodes(graph, nodes.data(), &n)) != hipSuccess) return e;
-  if ((e = hipGraphGetEdges(graph, nullptr, nullptr, &edges)) != hipSuccess) return e;
+  if ((e = hipGraphGetNodes(l->copy, nodes.data(), &n)) != hipSuccess) return e;
+  if ((e = hipGraphGetEdges(l->copy, nullptr, nullptr, &edges)) != hipSuccess) return e;
   if (edges != n - 1) return hipSuccess;
   std::vector<hipGraphNode_t> from(n), to(n);
-  if (edges && (e = hipGraphGetEdges(graph, from.data(), to.data(), &edges)) != hipSuccess) return e;
+  if (edges && (e = hipGraphGetEdges(l->copy, from.data(), to.data(), &edges)) != hipSuccess) return e;
   // the first node is the one that nothing leads to; from it every node leads to one other
   hipGraphNode_t at = nullptr;
   for (hipGraphNode_t v : nodes) {
@@ -55,26 +62,22 @@ hipError_t make_launch_list(hipGraph_t graph, size_t most, LaunchList** out) {
       at = v;
     }
   }
-  LaunchList* l = new LaunchList;
-  if ((e = hipGetDevice(&l->device)) != hipSuccess) at = nullptr;
   while (at && l->launches.size() < n) {
     hipGraphNodeType type;
     hipKernelNodeParams p{};
     if (hipGraphNodeGetType(at, &type) != hipSuccess || type != hipGraphNodeTypeKernel || hipGraphKernelNodeGetParams(at, &p) != hipSuccess ||
-        !p.kernelParams || p.extra || !own_kernel(p.func)) break;
+        !p.kernelParams || p.extra || !own_kernel(p.func)) return hipSuccess;
     l->launches.push_back(p);
     hipGraphNode_t next = nullptr;
     for (size_t i = 0; i < edges; ++i)
       if (from[i] == at) {
-        if (next) l->launches.clear(), i = edges;   // two successors: not a chain
-        else next = to[i];
+        if (next) return hipSuccess;   // two successors: not a chain
+        next = to[i];
       }
-    if (l->launches.empty()) break;
     at = next;
   }
-  if (l->launches.size() == n) *out = l;
-  else delete l;
-  return e;
+  if (l->launches.size() == n) *out = l.release();
+  return hipSuccess;
 }
 
 hipError_t run_launch_list(LaunchList* l, hipStream_t st) {

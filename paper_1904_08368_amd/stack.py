@@ -20,6 +20,20 @@ def _round_up(a: int, b: int) -> int:
     return (a + b - 1) // b * b
 
 
+class PassGraph(torch.cuda.CUDAGraph):
+    """A captured pass, which counts what ends a copy of it."""
+
+    held = 0
+
+    def capture_begin(self, *args, **kwargs) -> None:
+        self.held += 1
+        super().capture_begin(*args, **kwargs)
+
+    def reset(self) -> None:
+        self.held += 1
+        super().reset()
+
+
 class FusedNet:
     """mode 'f16': fp16 NHWC, fp32 accumulation.  mode 'i8': int8 NHWC, int32 accumulation,
     ``shifts[i] = {'s': out_rshift, 'l': residual_lshift}`` per conv."""
@@ -586,7 +600,7 @@ class FusedNet:
         one.  The graph is instantiated when it is first replayed as one."""
         self.run()
         torch.cuda.synchronize(self.dev)
-        g = torch.cuda.CUDAGraph(keep_graph=True)
+        g = PassGraph(keep_graph=True)
         with torch.cuda.graph(g):
             self.run()
         try:
@@ -600,7 +614,7 @@ class FusedNet:
 
     def replay(self) -> None:
         recorded = self.launch_list
-        if recorded is None or recorded.graph is not self.graph or not recorded.run():
+        if recorded is None or not recorded.is_of(self.graph) or not recorded.run():
             self.graph.replay()
 
     def tensor(self, name: str) -> np.ndarray:

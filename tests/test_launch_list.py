@@ -90,3 +90,31 @@ def test_other_graphs_are_replayed_as_graphs():
     net.replay()
     torch.cuda.synchronize()
     assert extra[0].item() == before + 1
+
+
+@pytest.mark.gpu
+def test_a_graph_that_was_reset_is_refused_and_its_list_keeps_its_arguments():
+    net, out = _net("dqn", 3, 84)
+    net.load_input(_inputs("dqn", 3, 84)[0])
+    net.run()
+    want = net.tensor(out).copy()
+    net.capture()
+    recorded = net.launch_list
+    net.graph.reset()
+    net.bufs[out].zero_()
+    with pytest.raises(RuntimeError):
+        net.replay()
+    torch.cuda.synchronize()
+    assert not net.tensor(out).any()
+    assert recorded.run()                # (the network's buffers are there; the graph's nodes are not)
+    torch.cuda.synchronize()
+    assert np.array_equal(net.tensor(out), want)
+    with torch.cuda.graph(net.graph):    # another capture into the same object
+        net.bufs[out].fill_(3)
+    net.replay()
+    torch.cuda.synchronize()
+    assert (net.tensor(out) == 3).all()
+    net.capture()
+    net.replay()
+    torch.cuda.synchronize()
+    assert np.array_equal(net.tensor(out), want)
