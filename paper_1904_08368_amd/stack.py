@@ -613,9 +613,13 @@ class FusedNet:
     launch_list = None
 
     def replay(self) -> None:
+        """Enqueue the captured pass on the current stream; refused (nothing enqueued, the capture stays usable) where that stream is
+        being captured: run() is what a program records into a graph of its own."""
         recorded = self.launch_list
-        if recorded is None or not recorded.is_of(self.graph) or not recorded.run():
+        if recorded is None or not recorded.is_of(self.graph):
             self.graph.replay()
+        elif not recorded.run():
+            raise B.RelayError(4, "a captured pass is not replayed into a stream that is being captured")
 
     def tensor(self, name: str) -> np.ndarray:
         """Download a named tensor as NCHW with the logical channel count."""

@@ -118,3 +118,29 @@ def test_a_graph_that_was_reset_is_refused_and_its_list_keeps_its_arguments():
     net.replay()
     torch.cuda.synchronize()
     assert np.array_equal(net.tensor(out), want)
+
+
+@pytest.mark.gpu
+def test_a_replay_into_a_capture_is_refused_and_the_capture_stays_usable():
+    net, out = _net("dqn", 1, 84)
+    net.load_input(_inputs("dqn", 1, 84)[0])
+    net.capture()
+    net.replay()
+    torch.cuda.synchronize()
+    want, mark = net.tensor(out).copy(), torch.zeros(8, device=net.dev)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        mark.add_(1)
+        with pytest.raises(RuntimeError):
+            net.replay()
+        net.run()
+        mark.add_(1)
+    for rep in (1, 2):
+        net.bufs[out].zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert mark[0].item() == 2 * rep and np.array_equal(net.tensor(out), want)
+    net.bufs[out].zero_()
+    net.replay()
+    torch.cuda.synchronize()
+    assert np.array_equal(net.tensor(out), want)

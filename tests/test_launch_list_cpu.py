@@ -76,3 +76,12 @@ def test_a_graph_that_was_reset_is_not_replayed():
     net.graph = _Graph()            # another graph in its place
     net.replay()
     assert (recorded.runs, net.graph.replays) == (1, 1)
+
+
+def test_a_replay_into_a_capture_is_refused_without_touching_the_graph():
+    """(the graph is not instantiated while there is a list, and its first replay would do that inside the caller's capture)"""
+    net, recorded = _net()
+    recorded.run = lambda: False
+    with pytest.raises(RuntimeError):
+        net.replay()
+    assert net.graph.replays == 0
