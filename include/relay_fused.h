@@ -595,8 +595,9 @@ relay_status relay_set_conv_workgroups(int32_t workgroups);
  *   create   reads the graph (a hipGraph_t passed as void*; not instantiated) and keeps a copy of it: what becomes of the graph
  *            later does not reach the list.  The buffers that its launches name are the caller's to keep.  Host memory only, no launch.
  *   run      enqueues every launch on hip_stream, in order, before it returns, with the arguments they were captured with.
- *            Threads that share a list enqueue one pass after the other.  RELAY_ERR_UNSUPPORTED, nothing enqueued:
- *            hip_stream is being captured.
+ *            Threads that share a list enqueue one pass after the other; a pass is not one item of its stream, as a graph is:
+ *            what another thread enqueues there by other means may land between two launches.  RELAY_ERR_UNSUPPORTED, nothing
+ *            enqueued: hip_stream is being captured.
  *   destroy  frees the list (launches already enqueued are not affected). */
 typedef struct relay_launch_list relay_launch_list;
 relay_status relay_launch_list_create(void* hip_graph, relay_launch_list** list);

@@ -1572,9 +1572,8 @@ relay_status relay_nchw_to_nhwc(int32_t dtype, int32_t n, int32_t c, int32_t h, 
                        "layout conversion launch");
 }
 
-// At most 64 launches: measured from 3 to 20, where a pass gains 3.8 to 7 us however long it is (the host issues a launch in 2.1 to 2.4 us
-// and the smallest kernels of these networks take 2.8).  Past 64 the gain is small against the pass, and a program's other work on
-// the host would feel the loop.
+// At most 64 launches: measured from 3 to 20, where a queued pass gains 2 to 6 us over its graph however long it is.  Past 64 that is small
+// against the pass, and a program's other work on the host would feel the loop.
 relay_status relay_launch_list_create(void* hip_graph, relay_launch_list** list) {
   if (!hip_graph || !list) return fail(RELAY_ERR_NULL, "hip_graph and list are required");
   *list = nullptr;

@@ -3,10 +3,12 @@
 // Replaying a HIP graph leaves the GPU idle for about 5 us between one replay and the next (measured as the difference between
 // a graph that holds a network once and one that holds it two and four times: 5.0 to 5.7 us from 5 launches to 20), whatever the network;
 // launches enqueued one by one leave no gap, as long as the host keeps ahead of the GPU.  From Python it does not at small
-// batches (4.9 us a call); this loop over the launches of the captured graph does (2.1 to 2.4 us each).  One after another, graph -> list:
-// deep Q-network at batch 1 22.9 -> 17.8 us, ResNet-18 at batch 1 89.6 -> 81.9 (int8 72.5 -> 66.8), at batch 32 260 -> 248,
-// MobileNet-v1 at batch 32 255.4 -> 250.5; the first pass on a new network of five launches 60 -> 33 us.  The host spends 12 us on
-// five launches and 35 to 46 on 16 to 20, the graph's replay 18 and 25: it stays ahead of the GPU in both.
+// batches (4.5 us a call); this loop over the launches of the captured graph does (2.1 to 2.6 us each) where passes are queued.  One after another,
+// graph -> list: deep Q-network at batch 1 21.6 -> 18.1 us, ResNet-18 at batch 1 88.0 -> 83.7, at batch 32 231 -> 227, an Inception block of 32
+// images 65.6 -> 60.5; int8 ResNet-18 at batch 1, whose 17 launches take the GPU 3.6 us each, 67 -> 69.
+// The price is the host's time: 12 us for five launches and 36 to 49 for 16 to 20, where the graph's replay takes 18 and 13 to 30.  A GPU that
+// idles when the pass comes waits for each launch in turn: waited for, the Q-network 38 -> 28 us, but ResNet-18 at batch 1 101 -> 94 to 107, int8
+// 79 -> 80 to 109, MobileNet-v1 98 -> 95 to 121.  Which of the two a pass takes is the caller's choice (FusedNet.replay).
 #include <memory>
 #include <mutex>
 #include <vector>
@@ -22,7 +24,7 @@ struct LaunchList {
   hipGraph_t copy = nullptr;                   // owns the argument blocks: the captured graph may go before the list
   std::vector<hipKernelNodeParams> launches;
   int device = 0;
-  std::mutex issue;   // a pass is enqueued whole, also when threads share the list and the stream
+  std::mutex issue;   // passes of threads that share the list follow one another whole
   ~LaunchList() {
     if (copy) (void)hipGraphDestroy(copy);
   }

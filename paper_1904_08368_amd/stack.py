@@ -8,6 +8,8 @@ on torch's current stream, so it can also be captured into a HIP graph.
 """
 from __future__ import annotations
 
+import threading
+import time
 from typing import Dict, List, Optional
 
 import numpy as np
@@ -594,10 +596,17 @@ class FusedNet:
         return [("+".join(self.call_names[i:i + n]), fn, args) for i, n, fn, args in self._steps()]
 
     def capture(self) -> None:
-        """Record run() into a HIP graph (kernel launches only; nothing in it clears memory).  replay() enqueues the recorded
-        launches one by one from native code where they are a chain of the library's kernels, which saves the idle time
-        between two replays of a graph (5 us, of 21 to 257 us a pass at 5 to 20 launches); any other graph is replayed as
-        one.  The graph is instantiated when it is first replayed as one."""
+        """Record run() into a HIP graph (kernel launches only; nothing in it clears memory).  Where that is a chain of the library's
+        kernels, replay() can also enqueue the recorded launches one by one from native code.
+
+        The list saves the idle time between two replays of a graph (4 to 6 us a pass) and costs the host 2.5 us a launch, the
+        graph's replay 13 to 30 us whatever its length.  So the list runs passes of at most 6 launches (deep Q-network 21.6 -> 18.1 us one after
+        another, 38 -> 28 waited for) and passes with work for the whole chip in a launch, which keep the GPU busy longer than the host
+        (an average of 400 K outputs: ResNet-18 of 7 images 136 -> 132 and 149 -> 144 us, of 3 images 113 -> 108 and 126 -> 124).  In between
+        (one image: 16 to 18 launches of 4 to 5 us) the list wins where the GPU has passes queued (ResNet-18 88 -> 84 us, MobileNet-v1 88 -> 84)
+        and loses where it idles until the first launch (waited for, int8 ResNet-18 79 -> 92, MobileNet-v1 98 -> 107; with 80 us of a program's own
+        work between passes 112 -> 125): see replay().  Such a graph is instantiated and launched once here, because its first launch takes 10 us
+        more than a later one; any other that has a list is instantiated when it is first launched itself."""
         self.run()
         torch.cuda.synchronize(self.dev)
         g = PassGraph(keep_graph=True)
@@ -605,21 +614,34 @@ class FusedNet:
             self.run()
         try:
             self.launch_list = B.LaunchList(g)
+            launches = len(self.launches())
+            outputs = self.batch * sum(c * h * w for c, h, w in self.shape.values())
+            self.list_always = launches <= 6 or outputs >= 400_000 * launches
         except B.RelayError:
             self.launch_list = None
+        if self.launch_list is None:
             g.instantiate()
+        elif not self.list_always:
+            g.replay()
         self.graph = g
 
     launch_list = None
+    list_always = True
+    _enqueued = threading.local()   # .at: when this thread last enqueued a captured pass, of any network
 
     def replay(self) -> None:
         """Enqueue the captured pass on the current stream; refused (nothing enqueued, the capture stays usable) where that stream is
-        being captured: run() is what a program records into a graph of its own."""
+        being captured: run() is what a program records into a graph of its own.
+
+        Between list and graph (capture()) a pass of many short launches goes by whether the GPU has work queued, for which the
+        10 us since the calling thread's last pass stand: asking the stream takes 20 us.  Both enqueue the same launches."""
         recorded = self.launch_list
-        if recorded is None or not recorded.is_of(self.graph):
+        if recorded is None or not recorded.is_of(self.graph) or \
+                not (self.list_always or time.perf_counter_ns() - getattr(self._enqueued, "at", 0) < 10_000):
             self.graph.replay()
         elif not recorded.run():
             raise B.RelayError(4, "a captured pass is not replayed into a stream that is being captured")
+        self._enqueued.at = time.perf_counter_ns()
 
     def tensor(self, name: str) -> np.ndarray:
         """Download a named tensor as NCHW with the logical channel count."""

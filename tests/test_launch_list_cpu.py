@@ -3,6 +3,7 @@ which of list and graph FusedNet.replay() takes."""
 import os
 import shutil
 import subprocess
+import threading
 
 import pytest
 
@@ -85,3 +86,22 @@ def test_a_replay_into_a_capture_is_refused_without_touching_the_graph():
     with pytest.raises(RuntimeError):
         net.replay()
     assert net.graph.replays == 0
+
+
+def test_passes_of_many_short_launches_take_the_list_only_behind_another_pass(monkeypatch):
+    from paper_1904_08368_amd import stack
+    now = [1_000_000]
+    monkeypatch.setattr(stack.time, "perf_counter_ns", lambda: now[0])
+    net, recorded = _net()
+    net._enqueued = threading.local()
+    net.list_always = False
+    taken = []
+    for gap_us in (1000, 2, 9, 11, 9, 300):
+        now[0] += gap_us * 1000
+        before = recorded.runs
+        net.replay()
+        taken.append(recorded.runs - before)
+    assert taken == [0, 1, 1, 0, 1, 0] and net.graph.replays == 3
+    net.list_always = True
+    net.replay()
+    assert recorded.runs == 4
