@@ -307,7 +307,7 @@ __global__ __launch_bounds__(64 * NW, OCC ? OCC : 1) void dwpw_fused_direct_kern
 }
 
 struct DirectTile {
-  int bm, wn, nw, ns, cp, mr;
+  int bm, wn, nw, ns, cp, occ, mr;
 };
 // (at stride 2 four output rows would need nine input rows in registers)
 constexpr int rows_of(int stride, int mr) { return stride == 1 ? mr : 2; }
@@ -316,7 +316,7 @@ constexpr int rows_of(int stride, int mr) { return stride == 1 ? mr : 2; }
   X(0, 16, 2, 4, 8, 8, 0, 2) X(1, 32, 4, 4, 8, 8, 0, 2) X(2, 32, 8, 8, 8, 8, 0, 2) X(3, 16, 1, 8, 32, 32, 0, 2) X(4, 16, 2, 8, 16, 16, 0, 2) \
   X(5, 32, 2, 8, 16, 16, 0, 2) X(6, 32, 4, 8, 8, 16, 0, 2) X(7, 32, 8, 8, 6, 16, 0, 2) X(8, 64, 8, 8, 4, 16, 0, 2) X(9, 32, 8, 8, 6, 16, 2, 4) \
   X(10, 64, 8, 8, 4, 16, 2, 4) X(11, 64, 4, 4, 4, 4, 3, 4) X(12, 64, 4, 4, 4, 4, 3, 2)
-#define RELAY_DWPW_DIRECT_ENTRY(i, bm, wn, nw, ns, cp, occ, mr) {bm, wn, nw, ns, cp, mr},
+#define RELAY_DWPW_DIRECT_ENTRY(i, bm, wn, nw, ns, cp, occ, mr) {bm, wn, nw, ns, cp, occ, mr},
 constexpr DirectTile kDirect[] = {RELAY_DWPW_DIRECT(RELAY_DWPW_DIRECT_ENTRY)};
 constexpr int kNumDirect = sizeof(kDirect) / sizeof(kDirect[0]);
 
@@ -362,7 +362,7 @@ DirectGeom make_geom(const DwPwArgs& a, const DirectTile& t) {
 
 template <int STRIDE, int BM, int WN, int NW, int NS, int CP, int OCC, int MR>
 hipError_t launch_direct_one(const DwPwArgs& a, hipStream_t st) {
-  const DirectGeom g = make_geom(a, DirectTile{BM, WN, NW, NS, CP, MR});
+  const DirectGeom g = make_geom(a, DirectTile{BM, WN, NW, NS, CP, OCC, MR});
   const long wgs = (long)a.N * g.tiles_y * g.tiles_x * g.tiles_n;
   hipLaunchKernelGGL((dwpw_fused_direct_kernel<STRIDE, BM, WN, NW, NS, CP, OCC, MR>), dim3((unsigned)wgs), dim3(64 * NW), 0, st, a, g);
   return hipGetLastError();
@@ -428,10 +428,10 @@ hipError_t launch_dwpw_direct(const DwPwArgs& a, int v, hipStream_t st) {
   }
 }
 
-// (without the last two template arguments)
 void dwpw_direct_kernel_name(const DwPwArgs& a, int v, char* buf, size_t len) {
   const DirectTile& t = kDirect[v];
-  snprintf(buf, len, "dwpw_fused_direct_kernel<%d, %d, %d, %d, %d, %d>", a.stride, t.bm, t.wn, t.nw, t.ns, t.cp);
+  snprintf(buf, len, "dwpw_fused_direct_kernel<%d, %d, %d, %d, %d, %d, %d, %d>", a.stride, t.bm, t.wn, t.nw, t.ns, t.cp, t.occ,
+           rows_of(a.stride, t.mr));
 }
 
 }  // namespace relay

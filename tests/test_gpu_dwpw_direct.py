@@ -53,8 +53,8 @@ def test_a_forced_variant_that_does_not_take_the_shape_is_an_error():
 # the first and last sizes at which the rule takes a tile (the number of workgroups that fit the chip at once)
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,c,h,w,k,stride,name", [
-    (1, 64, 32, 32, 64, 1, "16, 2, 4, 8, 8"), (8, 64, 28, 28, 64, 1, "32, 4, 4, 8, 8"), (2, 512, 14, 14, 512, 1, "16, 2, 8, 16, 16"), (1, 1024, 7, 7, 1024, 1, "16, 1, 8, 32, 32"),
-    (1, 512, 14, 14, 256, 1, "16, 1, 8, 32, 32"), (4, 512, 14, 14, 512, 1, "32, 2, 8, 16, 16"), (32, 512, 14, 14, 512, 1, "64, 8, 8, 4, 16"),
+    (1, 64, 32, 32, 64, 1, "16, 2, 4, 8, 8, 0, 2"), (8, 64, 28, 28, 64, 1, "32, 4, 4, 8, 8, 0, 2"), (2, 512, 14, 14, 512, 1, "16, 2, 8, 16, 16, 0, 2"), (1, 1024, 7, 7, 1024, 1, "16, 1, 8, 32, 32, 0, 2"),
+    (1, 512, 14, 14, 256, 1, "16, 1, 8, 32, 32, 0, 2"), (4, 512, 14, 14, 512, 1, "32, 2, 8, 16, 16, 0, 2"), (32, 512, 14, 14, 512, 1, "64, 8, 8, 4, 16, 2, 4"),
     (37, 512, 14, 14, 512, 1, None), (3, 1024, 7, 7, 1024, 1, None), (1, 32, 16, 16, 64, 1, None)])
 def test_rule(G, n, c, h, w, k, stride, name):
     from paper_1904_08368_amd import binding as B
@@ -78,8 +78,8 @@ def test_variants_of_one_item_in_registers_at_the_edges(G, variant, most, stride
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,c,h,w,k,stride,name", [
-    (32, 64, 56, 56, 64, 1, "64, 4, 4, 4, 4"), (32, 64, 56, 56, 136, 1, None), (32, 128, 56, 56, 128, 1, "64, 4, 4, 4, 4"),
-    (32, 128, 56, 56, 128, 2, "64, 4, 4, 4, 4"), (7, 128, 90, 70, 128, 2, "64, 8, 8, 4, 16"), (32, 512, 10, 9, 512, 1, "32, 8, 8, 6, 16"),
-    (32, 256, 18, 18, 256, 1, "64, 8, 8, 4, 16"), (32, 256, 56, 56, 256, 1, None)])
+    (32, 64, 56, 56, 64, 1, "64, 4, 4, 4, 4, 3, 2"), (32, 64, 56, 56, 136, 1, None), (32, 128, 56, 56, 128, 1, "64, 4, 4, 4, 4, 3, 4"),
+    (32, 128, 56, 56, 128, 2, "64, 4, 4, 4, 4, 3, 2"), (7, 128, 90, 70, 128, 2, "64, 8, 8, 4, 16, 0, 2"), (32, 512, 10, 9, 512, 1, "32, 8, 8, 6, 16, 0, 2"),
+    (32, 256, 18, 18, 256, 1, "64, 8, 8, 4, 16, 2, 4"), (32, 256, 56, 56, 256, 1, None)])
 def test_rule_beyond_one_round(G, n, c, h, w, k, stride, name):
     test_rule(G, n, c, h, w, k, stride, name)
