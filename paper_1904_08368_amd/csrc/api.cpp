@@ -1259,7 +1259,7 @@ relay_status relay_dwconv_pwconv_few_pixels(const relay_conv2d_desc* dw, int32_t
   relay::DwPwArgs a;
   const relay_status st = dwpw_args(dw, k, 0, &a);
   if (st != RELAY_OK) return st;
-  *few = relay::dwpw_direct_pick(a) >= 0 ? 1 : 0;
+  *few = relay::dwpw_direct_pays(a) ? 1 : 0;
   return RELAY_OK;
 }
 

@@ -419,6 +419,21 @@ int dwpw_direct_pick(const DwPwArgs& a) {
   return thin && dwpw_direct_supported(a, streams) ? streams : -1;
 }
 
+// Is the block faster as this launch than as two?  Not where most of the 64 rows of many workgroups are empty (images far smaller than a
+// tile; the work of a workgroup is that of a full one).  917 random blocks of up to 128 channels, images of 1 to 40 a side, that two launches
+// were chosen for before: up to 512 workgroups, two to a CU, one launch took 0.54 to 0.98 of the time whatever the filling; beyond, with 1 row
+// filled up to 3.9 times (4096 images of 1 x 1 7.5 -> 28.2 us), 4 rows 2.2 (2048 of 2 x 2 6.6 -> 12.1), 9 rows 2.0 (1024 of 3 x 3 6.9 -> 8.4).  From 13 rows
+// on at 128 channels, from 16 or, beyond one round of three to a CU, 24 at 64, whose two launches are the cheaper ones, one of 535
+// was slower by more than 2 % (6 %).
+bool dwpw_direct_pays(const DwPwArgs& a) {
+  const int v = dwpw_direct_pick(a);
+  if (v < 0 || kDirect[v].occ != 3) return v >= 0;
+  const DirectGeom g = make_geom(a, kDirect[v]);
+  const long tiles = (long)a.N * g.tiles_y * g.tiles_x;
+  const int rows = a.C > 64 ? 13 : tiles <= 768 ? 16 : 24;
+  return tiles <= 512 || (long)a.N * a.Ho * a.Wo >= rows * tiles;
+}
+
 hipError_t launch_dwpw_direct(const DwPwArgs& a, int v, hipStream_t st) {
   switch (v) {
 #define RELAY_DWPW_DIRECT_CASE(i, bm, wn, nw, ns, cp, occ, mr) \

@@ -196,7 +196,8 @@ void dwpw_kernel_name(int variant, char* buf, size_t len);
 // ... and for layers of few pixels and blocks of at most 128 channels, without chunks (dwpw_direct.hip).
 int dwpw_direct_variant_count();
 bool dwpw_direct_supported(const DwPwArgs& a, int variant);
-int dwpw_direct_pick(const DwPwArgs& a);   // variant expected to beat the two separate launches and the chunked kernel, or -1
+int dwpw_direct_pick(const DwPwArgs& a);   // variant expected to beat the chunked kernel, or -1
+bool dwpw_direct_pays(const DwPwArgs& a);  // ... and the two separate launches
 hipError_t launch_dwpw_direct(const DwPwArgs& a, int variant, hipStream_t st);
 void dwpw_direct_kernel_name(const DwPwArgs& a, int variant, char* buf, size_t len);
 bool dense_splits_units(int m, int n, int k);  // fp16: launch_dense is the faster kernel for these extents

@@ -42,3 +42,20 @@ def test_every_variant_has_the_name_of_its_kernel(stride):
     (32, 64, 112, 112, 128, 2, "64, 4, 4, 4, 4, 3, 2")])
 def test_the_rule_names_one_variant(n, c, h, w, k, stride, tail):
     assert B.relay_dwconv_pwconv_kernel_name(_desc(n, c, h, w, stride), k) == f"dwpw_fused_direct_kernel<{stride}, {tail}>"
+
+
+@pytest.mark.parametrize("n,c,h,w,k,stride,pays", [
+    (4096, 128, 1, 1, 128, 1, False), (1024, 64, 1, 1, 8, 2, False), (2048, 64, 2, 2, 64, 1, False), (2048, 128, 2, 2, 128, 2, False),
+    (1024, 64, 3, 3, 128, 1, False), (1024, 128, 3, 3, 64, 1, False), (2048, 64, 9, 9, 32, 2, True), (2420, 64, 7, 7, 96, 2, False),
+    # up to two workgroups to a CU, however empty
+    (512, 64, 3, 3, 64, 1, True), (513, 64, 3, 3, 64, 1, False), (300, 128, 5, 5, 8, 2, True),
+    # just enough rows: 13 of 128 channels (12, 13), 16 of 64 channels within one round of three to a CU, 24 beyond
+    (1024, 128, 3, 4, 32, 1, False), (1024, 128, 1, 13, 32, 1, True), (768, 64, 4, 4, 32, 1, True), (769, 64, 4, 4, 32, 1, False),
+    (681, 64, 4, 6, 32, 1, True), (1024, 64, 1, 15, 32, 1, False),
+    # the blocks of a network, small outputs
+    (32, 64, 56, 56, 64, 1, True), (32, 128, 56, 56, 128, 1, True), (32, 64, 112, 112, 128, 2, True), (32, 64, 56, 56, 8, 1, True),
+    (16, 128, 33, 47, 16, 1, True)])
+def test_one_launch_is_offered_only_where_its_rows_are_filled(n, c, h, w, k, stride, pays):
+    d = _desc(n, c, h, w, stride)
+    assert B.relay_dwconv_pwconv_few_pixels(d, k) == pays
+    assert "direct_kernel" in B.relay_dwconv_pwconv_kernel_name(d, k)      # the entry point itself takes this kernel either way
