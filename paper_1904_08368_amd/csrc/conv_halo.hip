@@ -44,7 +44,7 @@ struct HaloGeom {
   int nxbuf;          // halo buffers: 2 when there are several channel chunks, else 1
   int ncc;            // channel chunks, C / CK
   int tab_slot;       // 16-byte slot of LDS where the pixel table starts (behind the ring and the epilogue staging)
-  FastDiv fd_f, fd_xblk, fd_row;    // division by F, by xblk and (square tiles) by the tiles of a row
+  FastDiv fd_f, fd_row;             // division by F and (square tiles) by the tiles of a row
   FastDiv fd_tiles_m, fd_tiles_n;   // ... by the tile counts of the launched variant
   // the 2x2 / stride 2 maxima of the outputs [N][H/2][W/2][K], and division by W (square tiles with POOL)
   void* y_pooled;
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
     asm volatile("" ::"s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult),
                  "s"(a.qshift));
   asm volatile("" ::"s"(g.P), "s"(g.F), "s"(g.Mflat), "s"(g.rcp_p), "s"(g.rcp_f), "s"(g.xblk), "s"(g.nxbuf), "s"(g.ncc),
-               "s"(g.tab_slot), "s"(g.fd_f.mul), "s"(g.fd_f.shift), "s"(g.fd_xblk.mul), "s"(g.fd_xblk.shift),
+               "s"(g.tab_slot), "s"(g.fd_f.mul), "s"(g.fd_f.shift),
                "s"(g.fd_tiles_m.mul), "s"(g.fd_tiles_m.shift), "s"(g.fd_tiles_n.mul), "s"(g.fd_tiles_n.shift));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -545,7 +545,6 @@ bool make_geom(const ConvArgs& a, bool is_i8, int v, HaloGeom& g, size_t& lds_by
   g.ncc = a.C / (kp * BKV * ve);
   g.nxbuf = g.ncc > 1 ? 2 : 1;
   g.fd_f = make_fastdiv((uint32_t)g.F);
-  g.fd_xblk = make_fastdiv((uint32_t)g.xblk);
   if (kp * g.xblk > XPW * kHalo[v].hb * kHalo[v].waves()) return false;  // a halo must fit the waves' load slots
   const size_t ring = (size_t)g.nxbuf * kp * g.xblk * 64 + (size_t)NSW * kp * kHalo[v].bn() * BKV + 64;
   const HaloTile& t = kHalo[v];
