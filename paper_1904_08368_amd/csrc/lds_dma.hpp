@@ -8,7 +8,10 @@ namespace relay {
 
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
-constexpr unsigned kOob = 0x80000000u;  // a buffer offset beyond any num_records this library accepts: reads zeros
+// A buffer offset beyond the num_records of every input and filter buffer (the kernels take at most 2^31 - 1 bytes of them): reads
+// zeros.  The residual buffer of conv3x3_halo_kernel alone may be larger (up to 2^32 - 2 bytes).  There an out-of-range lane reads what lies at
+// 2^31, inside the tensor, and stores nothing.
+constexpr unsigned kOob = 0x80000000u;
 
 // The statement overwrites M0 and says so in its clobber list.  The compiler treats M0 as a reserved
 // register (it sets M0 itself right before each of its own instructions that read it and keeps no
