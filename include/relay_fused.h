@@ -297,8 +297,8 @@ relay_status relay_fused_dwconv_pwconv(const relay_conv2d_desc* dw, const void* 
 relay_status relay_dwconv_pwconv_fusion_pays(const relay_conv2d_desc* dw, int32_t k, int32_t* pays);
 /* The same question for the other kernel behind relay_fused_dwconv_pwconv, the one made for layers of few pixels (paper Section
  * 4.1, as above): *few = 1 where that kernel was measured faster than two launches and than the kernel the query above is
- * about: 64 channels or more, and one round of its workgroups fits the chip, or 64 or 128 channels and at most 128 output channels
- * on images that are not far smaller than its tiles of 64 pixels.  One launch pays where either query says 1; relay_fused_dwconv_pwconv
+ * about (than two launches at least within 3 %): 64 channels or more, and one round of its workgroups fits the chip, or 64 or 128 channels and
+ * at most 128 output channels on images that are not far smaller than its tiles of 64 pixels.  One launch pays where either query says 1; relay_fused_dwconv_pwconv
  * takes the faster of its kernels whatever they say.  Host-only; same errors. */
 relay_status relay_dwconv_pwconv_few_pixels(const relay_conv2d_desc* dw, int32_t k, int32_t* few);
 /* Profiling aid (paper Section 4.1 "Lowering": the lowered code is specific to the shape): the name, as a

@@ -390,12 +390,14 @@ bool dwpw_direct_supported(const DwPwArgs& a, int v) {
 // (A tile of up to 256 channels takes 3 us behind the launch with 16 pixels x 64 channels, 5 with 32 x 256, 7 with 64 x 256;
 // with 512 channels 4.1 with 16 x 32, 5.5 with 32 x 64, 7.1 with 32 x 256, 10 with 64 x 256.)
 // The tiles of four-row items come before those of two where every thread has one (512 channels in 32 rows, 256 in 64), and are passed by
-// where their rectangles are too many (9 rows as 4 + 4 + 1).
-// Up to 128 channels on both sides, beyond one round: 64 x 128 tiles, three workgroups to a CU (41 to 49 KB of LDS, 150 registers), which
+// where their rectangles are too many (9 rows as 4 + 4 + 1).  At stride 2, where both have items of two rows, one item's inputs in registers
+// instead of two is no slower: 19 blocks 0.99 to 1.01 of the time in 32 rows (512 at 28 x 28 / 2, 16 images 10.7 and 10.6 us), 0.96 to 0.99 in 64
+// (32 images 15.4 and 14.8, 256 -> 512 11.1 and 10.8).
+// Up to 128 channels on both sides, beyond one round: 64 x 128 tiles, three workgroups to a CU (49 KB of LDS, 150 registers), which
 // cover each other's latencies where the chunked kernel waits at its barriers.  Operands from beyond the L2, chunked* or two launches -> this:
 // 64 -> 128 / 2 at 82 x 103, 11 images 11.5 -> 8.2, at 100 x 90, 16 images 15.8 -> 10.2, at 112 x 112, 32 images 24.2* -> 23.0; 128 -> 128 at
 // 50 x 45, 16 images 13.7* -> 11.1, at 56 x 56, 32 images 24.0* -> 20.0, at 112 x 112 79* -> 69; 128 -> 128 / 2 at 112 x 112 47.9 -> 34.0; 64 -> 64 at
-// 56 x 56 17.7* -> 14.4, at 112 x 112 47.4 -> 48.2.  64 channels take them also within one round of 64 x 256 (3 images at 56 x 56
+// 56 x 56 17.7* -> 14.4, at 112 x 112, 32 images 51.8* -> 48.2 (the one size of these where two launches, 47.4, are faster).  64 channels take them also within one round of 64 x 256 (3 images at 56 x 56
 // 5.15 -> 4.82), 128 do not (128 -> 128 / 2 at 90 x 70, 7 images 7.3 against 7.8).
 int dwpw_direct_pick(const DwPwArgs& a) {
   if (a.C < 64) return -1;

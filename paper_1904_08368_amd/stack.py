@@ -627,21 +627,22 @@ class FusedNet:
 
     launch_list = None
     list_always = True
-    _enqueued = threading.local()   # .at: when this thread last enqueued a captured pass, of any network
+    _enqueued = threading.local()   # .at: when this thread last enqueued a pass of many short launches, of any network
 
     def replay(self) -> None:
         """Enqueue the captured pass on the current stream; refused (nothing enqueued, the capture stays usable) where that stream is
         being captured: run() is what a program records into a graph of its own.
 
         Between list and graph (capture()) a pass of many short launches goes by whether the GPU has work queued, for which the
-        10 us since the calling thread's last pass stand: asking the stream takes 20 us.  Both enqueue the same launches."""
+        10 us since the calling thread's last such pass stand: asking the stream takes 20 us.  Both enqueue the same launches."""
         recorded = self.launch_list
         if recorded is None or not recorded.is_of(self.graph) or \
                 not (self.list_always or time.perf_counter_ns() - getattr(self._enqueued, "at", 0) < 10_000):
             self.graph.replay()
         elif not recorded.run():
             raise B.RelayError(4, "a captured pass is not replayed into a stream that is being captured")
-        self._enqueued.at = time.perf_counter_ns()
+        if not self.list_always:
+            self._enqueued.at = time.perf_counter_ns()
 
     def tensor(self, name: str) -> np.ndarray:
         """Download a named tensor as NCHW with the logical channel count."""

@@ -55,7 +55,16 @@ def test_replays_equal_eager_passes(name, batch, hw):
                     net.replay()
             torch.cuda.synchronize()
             assert np.array_equal(net.tensor(out), w)
-    threads = [threading.Thread(target=lambda: [net.replay() for _ in range(20)]) for _ in range(4)]
+    raised = []
+
+    def passes():
+        try:
+            for _ in range(20):
+                net.replay()
+        except Exception as e:      # (a thread's own exception would end the thread and be lost)
+            raised.append(e)
+    # (that passes do not mix shows in tests/test_launch_list_cpu.py: here they would give the same bits)
+    threads = [threading.Thread(target=passes) for _ in range(4)]
     net.bufs[out].zero_()
     torch.cuda.synchronize()
     for t in threads:
@@ -63,6 +72,7 @@ def test_replays_equal_eager_passes(name, batch, hw):
     for t in threads:
         t.join()
     torch.cuda.synchronize()
+    assert not raised
     assert np.array_equal(net.tensor(out), want[-1])
     net.graph.replay()      # the graph itself stays usable
     torch.cuda.synchronize()
