@@ -3,6 +3,7 @@ on every replay, with new inputs and eager work in between, on other streams and
 deterministic and the launches and their arguments are the same, so the bound is equality.)"""
 import ctypes as C
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -131,18 +132,22 @@ def test_a_graph_that_was_reset_is_refused_and_its_list_keeps_its_arguments():
 
 
 @pytest.mark.gpu
-def test_a_replay_into_a_capture_is_refused_and_the_capture_stays_usable():
-    net, out = _net("dqn", 1, 84)
-    net.load_input(_inputs("dqn", 1, 84)[0])
+@pytest.mark.parametrize("name,batch,hw,always", [("dqn", 1, 84, True), ("resnet18", 1, 96, False)])
+def test_a_replay_into_a_capture_is_refused_and_the_capture_stays_usable(name, batch, hw, always):
+    net, out = _net(name, batch, hw)
+    net.load_input(_inputs(name, batch, hw)[0])
     net.capture()
+    assert net.list_always == always
     net.replay()
     torch.cuda.synchronize()
     want, mark = net.tensor(out).copy(), torch.zeros(8, device=net.dev)
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         mark.add_(1)
-        with pytest.raises(RuntimeError):
-            net.replay()
+        for wait in (0.0, 0.001):       # (right behind another pass and later: list and graph)
+            time.sleep(wait)
+            with pytest.raises(RuntimeError):
+                net.replay()
         net.run()
         mark.add_(1)
     for rep in (1, 2):
