@@ -38,6 +38,9 @@ __device__ __forceinline__ float dot2(unsigned x, unsigned w, float acc) {
 // PASS: output channels per pass.  SPLIT: a workgroup takes one pass only, of PASS channels from blockIdx.y * PASS on.
 template <int PASS, bool SPLIT>
 __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
+  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
+  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K),
+               "s"(a.Ho), "s"(a.Wo), "s"(a.flags), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift));
   extern __shared__ uint4 lds[];
   const int k0 = SPLIT ? (int)blockIdx.y * PASS : 0, kn = SPLIT ? PASS : a.K;   // this workgroup's output channels
   float* cmul = reinterpret_cast<float*>(lds);                              // [kn]
@@ -48,7 +51,7 @@ __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
   const int tid = threadIdx.x;
   // ---- this thread's kPix pixels: (n, p, q0 .. q0 + kPix - 1)
   const int wq = a.Wo / kPix;                                // threads per output row
-  const unsigned t_raw = blockIdx.x * blockDim.x + tid, t_end = (unsigned)(a.N * a.Ho * wq);
+  const unsigned t_raw = (unsigned)bid * 128u + tid, t_end = (unsigned)(a.N * a.Ho * wq);
   const bool live = t_raw < t_end;                           // (threads past the end load the last pixels again and store nothing)
   const unsigned t = live ? t_raw : t_end - 1;
   const unsigned row = fast_div(t, a.fd_howo);               // n * Ho + p  (the launch sets this divisor to wq,
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
       xl[c * 3 + r] = l;
     }
   // ---- the constants of the tail into LDS (behind the image loads above, so that both memory latencies pass together)
-  for (int k = tid; k < kn; k += blockDim.x) {
+  for (int k = tid; k < kn; k += 128) {
     const float sc = a.scale ? a.scale[k0 + k] : 1.f, sf = a.shift ? a.shift[k0 + k] : 0.f, bb = a.bias ? a.bias[k0 + k] : 0.f;
     cmul[k] = sc;
     cadd[k] = bb * sc + sf;   // (acc + b) * sc + sf

@@ -108,23 +108,27 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
 
   // Every argument the kernel uses is asked for here, so that their scalar loads leave as one batch with one
   // wait; left to itself the compiler loads them where they are first used, and the prologue then waits
-  // for five scalar-load round trips one after another.
-  asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias));
-  asm volatile("" ::"s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K), "s"(a.Kp), "s"(a.flags), "s"(a.param_vec),
-               "s"(a.n_major), "s"(a.xs_n));
+  // for five scalar-load round trips one after another.  (The workgroup's number passes through the same statement: arithmetic on it that
+  // needs only some of them would otherwise be placed ahead of the others' loads.)
+  int bid = (int)blockIdx.x;
+#define RELAY_ASKED                                                                                                                     \
+  "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), \
+      "s"(a.K), "s"(a.Kp), "s"(a.flags), "s"(a.param_vec), "s"(a.n_major), "s"(a.xs_n), "s"(g.P), "s"(g.F), "s"(g.Mflat), "s"(g.rcp_p),  \
+      "s"(g.rcp_f), "s"(g.xblk), "s"(g.nxbuf), "s"(g.ncc), "s"(g.tab_slot), "s"(g.fd_f.mul), "s"(g.fd_f.shift), "s"(g.fd_tiles_m.mul),   \
+      "s"(g.fd_tiles_m.shift), "s"(g.fd_tiles_n.mul), "s"(g.fd_tiles_n.shift)
   if constexpr (IS_I8)   // (the quantized tail's own arguments too)
-    asm volatile("" ::"s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult),
-                 "s"(a.qshift));
-  asm volatile("" ::"s"(g.P), "s"(g.F), "s"(g.Mflat), "s"(g.rcp_p), "s"(g.rcp_f), "s"(g.xblk), "s"(g.nxbuf), "s"(g.ncc),
-               "s"(g.tab_slot), "s"(g.fd_f.mul), "s"(g.fd_f.shift),
-               "s"(g.fd_tiles_m.mul), "s"(g.fd_tiles_m.shift), "s"(g.fd_tiles_n.mul), "s"(g.fd_tiles_n.shift));
+    asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi),
+                 "s"(a.qmult), "s"(a.qshift));
+  else
+    asm volatile("" : "+s"(bid) : RELAY_ASKED);
+#undef RELAY_ASKED
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave / (WAVES_M * WAVES_N), wsub = wave % (WAVES_M * WAVES_N);
   const int wm = wsub % WAVES_M, wn = wsub / WAVES_M;
   const int tiles_m = (g.Mflat + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
-  const int tile = xcd_remap(blockIdx.x, tiles_m * tiles_n);
+  const int tile = xcd_remap(bid, tiles_m * tiles_n);
   const int tile_q = (int)fast_div((uint32_t)tile, a.n_major ? g.fd_tiles_m : g.fd_tiles_n);
   const int tile_n = a.n_major ? tile_q : tile - tile_q * tiles_n;
   const int tile_m = a.n_major ? tile - tile_q * tiles_m : tile_q;
@@ -219,7 +223,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   //      its run of tiles, else all of them.  (These loads are younger than those the first two steps wait for, and
   //      older than all others.)  Only in short launches (measured up to 912 tiles x chunks): in longer ones the first
   //      use of the filters is a small part of the time and the extra wait costs as much (VGG-16 0.7 %).
-  const int nb = tiles_m * tiles_n, xcd_idx = blockIdx.x >> 3;
+  const int nb = tiles_m * tiles_n, xcd_idx = bid >> 3;
   int touched = 0;
   if (nb * g.ncc <= 1024 && xcd_idx < 64) {
     const int per = nb >> 3, wgs = min(per + 1, 64);  // (two workgroups on each of the XCD's 32 CUs)

@@ -58,7 +58,7 @@ using acc_t_scalar = typename std::conditional<IS_I8, int, float>::type;
 // outputs (255 of 256 rows); the finished patch goes to LDS and only the pooled block is stored.
 // bid: the workgroup's number among those of this conv
 template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP, int SK, bool STOCH, bool EXT, bool POOL>
-__device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid) {
+__device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, int bid) {
   constexpr int NW = WAVES_M * WAVES_N * SK;
   static_assert(SK == 1 || (SK == 2 && KP == 2 && TM % 2 == 0), "k-split pairs take one 64-byte plane each");
   constexpr int VE = IS_I8 ? 16 : 8;
@@ -102,18 +102,22 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, const int bid)
   __shared__ uint4 ring[RING];
   __shared__ float pool_cst[POOL ? 2 * BN : 1];  // pooled tiles: the epilogue constants of the tile's channels
 
-  // The arguments of the prologue are asked for here, so that their scalar loads leave as one batch with
-  // one wait; left to itself the compiler loads them where they are first used and the prologue waits
-  // for several scalar-load round trips one after another.
-  asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias));
-  asm volatile("" ::"s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw), "s"(a.ph),
-               "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.xs_n), "s"(a.xs_h), "s"(a.xs_w), "s"(a.rcp_wo), "s"(a.rcp_ho),
-               "s"(a.tap_spread), "s"(a.param_vec), "s"(a.n_major), "s"(a.M), "s"(a.Kred), "s"(a.Kp), "s"(a.flags));
-  asm volatile("" ::"s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul),
-               "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul), "s"(a.fd_tiles_n.shift));
-  if constexpr (IS_I8)   // (the quantized tail's own arguments too: asked for at its first use they cost it a scalar-load round trip per branch)
-    asm volatile("" ::"s"(a.res), "s"(a.y), "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi),
-                 "s"(a.qmult), "s"(a.qshift));
+  // The arguments of the prologue are asked for here, so that their scalar loads leave as one batch with one wait; left to itself the
+  // compiler loads them where they are first used and the prologue waits for several scalar-load round trips one after another.  The
+  // workgroup's number passes through the same statement: arithmetic on it that needs only some of them is otherwise moved ahead of the
+  // others' loads, and the prologue waits twice (480 to 1100 clocks each, from memory the host has just written; see igemm_small_kernel).
+  // (The quantized tail's own arguments too: asked for at its first use they cost it a round trip per branch.)
+#define RELAY_ASKED                                                                                                                          \
+  "s"(a.x), "s"(a.w), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K), "s"(a.R), "s"(a.S),          \
+      "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.xs_n), "s"(a.xs_h), "s"(a.xs_w), "s"(a.rcp_wo), "s"(a.rcp_ho), \
+      "s"(a.tap_spread), "s"(a.param_vec), "s"(a.n_major), "s"(a.M), "s"(a.Kred), "s"(a.Kp), "s"(a.flags), "s"(a.fd_wo.mul),              \
+      "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul), "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul), \
+      "s"(a.fd_tiles_n.shift)
+  if constexpr (IS_I8)
+    asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.qbias), "s"(a.res), "s"(a.y), "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode),
+                 "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult), "s"(a.qshift));
+  else
+    asm volatile("" : "+s"(bid) : RELAY_ASKED);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -794,17 +798,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
 // fifth multiplies.  The fifth reads chunk kc from LDS while it multiplies chunk kc - 1, so a chunk takes the longest of its
 // loads (KP KB per wave), its LDS reads and its MFMAs (64 KP clocks) instead of their sum behind a barrier.
 template <int KP>
-__device__ __forceinline__ void igemm_dma_narrow_tile(const ConvArgs& a, const int bid) {
+__device__ __forceinline__ void igemm_dma_narrow_tile(const ConvArgs& a, int bid) {
   constexpr int VE = 8, ES = 2, CK = KP * BKV * VE, BM = 32, BN = 32, NS = KP == 4 ? 4 : (KP == 2 ? 6 : 8);
   constexpr int PLANE = (BM + BN) * BKV, STAGE = KP * PLANE, KSTEPS = KP * 2;
   constexpr int EP = BN / 4 + 1;
   __shared__ uint4 ring[NS * STAGE + 32 * EP];
-  asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.res), "s"(a.y));
-  asm volatile("" ::"s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw), "s"(a.ph),
-               "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.xs_n), "s"(a.xs_h), "s"(a.xs_w), "s"(a.rcp_wo), "s"(a.rcp_ho),
-               "s"(a.tap_spread), "s"(a.param_vec), "s"(a.n_major), "s"(a.M), "s"(a.Kred), "s"(a.Kp), "s"(a.flags));
-  asm volatile("" ::"s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul),
-               "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul), "s"(a.fd_tiles_n.shift));
+  asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.res), "s"(a.y));
+#undef RELAY_ASKED
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
@@ -952,19 +952,20 @@ __global__ __launch_bounds__(320) void igemm_dma_kernel_narrow(const ConvArgs a)
 // second (see igemm_small_pair_kernel).
 struct DmaPair {
   ConvArgs a[2];
-  int tiles;
 };
 template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (NS * KP * (WAVES_M * TM + WAVES_N * TN) * 32 * 64 <= 80 * 1024 ? 2 : 1))
-    void igemm_dma_pair_kernel(const DmaPair p) {
-  const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
-  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, 1, false, false, false>(p.a[second], (int)blockIdx.x - (second ? p.tiles : 0));
+    void igemm_dma_pair_kernel(const int tiles, const DmaPair p) {
+  const int second = (int)blockIdx.x >= tiles ? 1 : 0;
+  const ConvArgs a = p.a[second];
+  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, 1, false, false, false>(a, (int)blockIdx.x - (second ? tiles : 0));
 }
 
 template <int KP>
-__global__ __launch_bounds__(320) void igemm_dma_pair_kernel_narrow(const DmaPair p) {
-  const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
-  igemm_dma_narrow_tile<KP>(p.a[second], (int)blockIdx.x - (second ? p.tiles : 0));
+__global__ __launch_bounds__(320) void igemm_dma_pair_kernel_narrow(const int tiles, const DmaPair p) {
+  const int second = (int)blockIdx.x >= tiles ? 1 : 0;
+  const ConvArgs a = p.a[second];
+  igemm_dma_narrow_tile<KP>(a, (int)blockIdx.x - (second ? tiles : 0));
 }
 
 struct DmaTile {
@@ -1032,8 +1033,7 @@ hipError_t launch_narrow_one(const ConvArgs& a, const ConvArgs* second, hipStrea
     p.a[i].fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
     p.a[i].fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
   }
-  p.tiles = tiles[0];
-  if (second) hipLaunchKernelGGL(igemm_dma_pair_kernel_narrow<KP>, dim3(tiles[0] + tiles[1]), dim3(320), 0, st, p);
+  if (second) hipLaunchKernelGGL(igemm_dma_pair_kernel_narrow<KP>, dim3(tiles[0] + tiles[1]), dim3(320), 0, st, tiles[0], p);
   else hipLaunchKernelGGL(igemm_dma_kernel_narrow<KP>, dim3(tiles[0]), dim3(320), 0, st, p.a[0]);
   return hipGetLastError();
 }
@@ -1059,8 +1059,7 @@ hipError_t launch_pair_one(const ConvArgs& a, const ConvArgs& b, hipStream_t st)
     p.a[i].fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
     p.a[i].fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
   }
-  p.tiles = tiles[0];
-  hipLaunchKernelGGL((igemm_dma_pair_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP>), dim3(tiles[0] + tiles[1]), dim3(64 * WAVES_M * WAVES_N), 0, st, p);
+  hipLaunchKernelGGL((igemm_dma_pair_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP>), dim3(tiles[0] + tiles[1]), dim3(64 * WAVES_M * WAVES_N), 0, st, tiles[0], p);
   return hipGetLastError();
 }
 

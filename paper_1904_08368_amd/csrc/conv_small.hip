@@ -68,7 +68,7 @@ struct SmallGeom {
 // EXT: the instantiation that stores output channel segments.  NA: accumulators per block of a tile, used in turn (see small_runs).
 // bid: the workgroup's number among the tiles of this conv.
 template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT, int NA>
-__device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g, const int bid) {
+__device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g, int bid) {
   constexpr int VE = IS_I8 ? 16 : 8;
   constexpr int ES = IS_I8 ? 1 : 2;
   constexpr int CU = U * BKV * VE;  // channels per unit: U steps of 64 bytes
@@ -84,18 +84,24 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
   __shared__ uint4 ring[W * RING];
   __shared__ float cst[2 * BN];
 
-  // (every argument is asked for at the top, so that the scalar loads leave as one batch)
-  asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias));
-  asm volatile("" ::"s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw), "s"(a.ph),
-               "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.xs_n), "s"(a.xs_h), "s"(a.xs_w), "s"(a.tap_spread), "s"(a.n_major), "s"(a.M),
-               "s"(a.Kred), "s"(a.Kp), "s"(a.flags));
-  asm volatile("" ::"s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul),
-               "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul), "s"(a.fd_tiles_n.shift));
-  asm volatile("" ::"s"(g.tiles_m), "s"(g.tiles_n), "s"(g.xcd_per), "s"(g.xcd_rem), "s"(g.per_tap), "s"(g.per_wave), "s"(g.units),
-               "s"(g.fd_per_tap.mul), "s"(g.fd_per_tap.shift), "s"(g.fd_s.mul), "s"(g.fd_s.shift));
+  // Every argument is asked for at the top, so that the scalar loads leave as one batch with one wait.  The workgroup's number passes through
+  // the same statement: arithmetic on it that needs only some of the arguments was moved ahead of the others' loads, and two batches one
+  // behind the other are two latencies of 480 to 1100 clocks (the host has just written that memory, no cache has it yet).  With the
+  // other kernels', whose prologues had two or three batches, and the copied blocks of the pairs: ResNet-18 at batch 1 81.9 -> 75.5 us, int8 66.8
+  // -> 61.4, at batch 7 131.8 -> 126.2, at batch 32 264.2 -> 260.9, deep Q-network 18.0 -> 17.3, MobileNet-v1 of 11 images 130.9 -> 129.4.
+#define RELAY_ASKED                                                                                                                      \
+  "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), \
+      "s"(a.K), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.xs_n), "s"(a.xs_h),           \
+      "s"(a.xs_w), "s"(a.tap_spread), "s"(a.n_major), "s"(a.M), "s"(a.Kred), "s"(a.Kp), "s"(a.flags), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift), \
+      "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul), "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul),                    \
+      "s"(a.fd_tiles_n.shift), "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.xcd_per), "s"(g.xcd_rem), "s"(g.per_tap), "s"(g.per_wave), "s"(g.units), \
+      "s"(g.fd_per_tap.mul), "s"(g.fd_per_tap.shift), "s"(g.fd_s.mul), "s"(g.fd_s.shift)
   if constexpr (IS_I8)
-    asm volatile("" ::"s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult),
+    asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult),
                  "s"(a.qshift));
+  else
+    asm volatile("" : "+s"(bid) : RELAY_ASKED);
+#undef RELAY_ASKED
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -356,16 +362,20 @@ __global__ __launch_bounds__(64 * W) void igemm_small_kernel(const ConvArgs a, c
 }
 
 // Two convs that do not read each other's output, in one launch: the first `tiles` workgroups run the first, the others the
-// second.  (The argument block is addressed by a uniform index: the same scalar loads as with one conv.)
+// second.  The argument block is picked by a uniform index and copied whole: read field by field through that index its loads were 40 to
+// 57 of one word each, and the arguments there after 2600 to 3200 clocks where a single conv's are after 700.
+struct SmallArgs {
+  ConvArgs a;
+  SmallGeom g;
+};
 struct SmallPair {
-  ConvArgs a[2];
-  SmallGeom g[2];
-  int tiles;
+  SmallArgs c[2];
 };
 template <bool IS_I8, int TM, int TN, int W, int U, int NS>
-__global__ __launch_bounds__(64 * W) void igemm_small_pair_kernel(const SmallPair p) {
-  const int second = (int)blockIdx.x >= p.tiles ? 1 : 0;
-  small_tile<IS_I8, TM, TN, W, U, NS, false, 1>(p.a[second], p.g[second], (int)blockIdx.x - (second ? p.tiles : 0));
+__global__ __launch_bounds__(64 * W) void igemm_small_pair_kernel(const int tiles, const SmallPair p) {
+  const int second = (int)blockIdx.x >= tiles ? 1 : 0;
+  const SmallArgs c = p.c[second];
+  small_tile<IS_I8, TM, TN, W, U, NS, false, 1>(c.a, c.g, (int)blockIdx.x - (second ? tiles : 0));
 }
 
 struct SmallTile {
@@ -453,10 +463,10 @@ hipError_t launch_small_one(const ConvArgs& a, const ConvArgs* second, int runs,
   constexpr int NS = stages(U, TM, TN, W);
   if (second) {
     SmallPair p;
-    p.g[0] = small_geom<IS_I8, TM, TN, W, U>(a, p.a[0]);
-    p.g[1] = small_geom<IS_I8, TM, TN, W, U>(*second, p.a[1]);
-    p.tiles = p.g[0].tiles_m * p.g[0].tiles_n;
-    hipLaunchKernelGGL((igemm_small_pair_kernel<IS_I8, TM, TN, W, U, NS>), dim3(p.tiles + p.g[1].tiles_m * p.g[1].tiles_n), dim3(64 * W), 0, st, p);
+    p.c[0].g = small_geom<IS_I8, TM, TN, W, U>(a, p.c[0].a);
+    p.c[1].g = small_geom<IS_I8, TM, TN, W, U>(*second, p.c[1].a);
+    const int tiles = p.c[0].g.tiles_m * p.c[0].g.tiles_n;
+    hipLaunchKernelGGL((igemm_small_pair_kernel<IS_I8, TM, TN, W, U, NS>), dim3(tiles + p.c[1].g.tiles_m * p.c[1].g.tiles_n), dim3(64 * W), 0, st, tiles, p);
     return hipGetLastError();
   }
   if constexpr (!IS_I8 && TM * TN <= kMostBlocks) {

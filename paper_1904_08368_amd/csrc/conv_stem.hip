@@ -43,6 +43,13 @@ __global__ __launch_bounds__(64 * (WM * WN + HW), TM * TN > 1 || NI > 10 ? 3 : 4
   float* cst = reinterpret_cast<float*>(out + g.cst_at);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave % WM, wn = wave / WM;
+  // (one batch of scalar loads; the workgroup's number passes through, so that arithmetic on it stays behind all of them)
+  int bid = (int)blockIdx.x;
+  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias), "s"(a.N), "s"(a.H), "s"(a.W),
+               "s"(a.C), "s"(a.K), "s"(a.R), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.Kp), "s"(a.flags),
+               "s"(g.y_pooled), "s"(g.Hp), "s"(g.Wp), "s"(g.per_run), "s"(g.tiles), "s"(g.tiles_img), "s"(g.tiles_row), "s"(g.pitch), "s"(g.cst_at),
+               "s"(g.per_row), "s"(g.items), "s"(g.fd_img.mul), "s"(g.fd_img.shift), "s"(g.fd_row.mul), "s"(g.fd_row.shift), "s"(g.fd_items.mul),
+               "s"(g.fd_items.shift));
   const int n0 = blockIdx.y * BN;
 
   // ---- filters and constants, once
@@ -71,7 +78,7 @@ __global__ __launch_bounds__(64 * (WM * WN + HW), TM * TN > 1 || NI > 10 ? 3 : 4
   //  and the layer behind finds these outputs in the L2 of the XCD that reads them.  First layer and the one behind it, ResNet-18 at
   //  batch 32 41.6 -> 38.7 us, int8 at batch 16 19.1 -> 17.9, MobileNet-v1 at batch 11 15.8 -> 14.1.  In a few small tiles the arithmetic
   //  costs what it gives: deep Q-network at batch 1 17.5 against 17.6.)
-  const int tile = TM * TN > 1 ? xcd_remap((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+  const int tile = TM * TN > 1 ? xcd_remap(bid, g.tiles) : bid;
   const int t_n = (int)fast_div((uint32_t)tile, g.fd_img), t_rem = tile - t_n * g.tiles_img;
   const int t_ty = (int)fast_div((uint32_t)t_rem, g.fd_row), t_tx = t_rem - t_ty * g.tiles_row;
   const int c_y = POOL ? t_ty * (TYC - 1) - 1 : t_ty * TYC, c_x = POOL ? t_tx * (TXC - 1) - 1 : t_tx * TXC;

@@ -30,8 +30,9 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t rsrc, unsi
 
 template <int STRIDE, int TH, int TW>
 __global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const ConvArgs a) {
+  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
   // all arguments as one batch of scalar loads with one wait (the compiler would load them where first used)
-  asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
+  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
                "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.sh), "s"(a.ph), "s"(a.pw), "s"(a.flags), "s"(a.fd_tiles_n.mul),
                "s"(a.fd_tiles_n.shift), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift));
   constexpr int IH = (TH - 1) * STRIDE + 3, IW = (TW - 1) * STRIDE + 3;
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const ConvArgs a) {
   const int cvecs = a.C >> 3;
   const int tiles_w = (a.Wo + TW - 1) / TW, tiles_h = (a.Ho + TH - 1) / TH;
   const unsigned total = (unsigned)(a.N * tiles_h * tiles_w * cvecs);  // < 2^31: checked by the launcher
-  unsigned idx = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  unsigned idx = (unsigned)xcd_remap(bid, (int)((total + 255u) / 256u)) * 256u + threadIdx.x;
   if (idx >= total) return;
   // (divisions by multiply-high with the launcher's constants -- fd_tiles_n: cvecs, fd_wo: tiles_w, fd_howo:
   // tiles_h --: three software divisions per thread sat in front of the first load)
@@ -141,9 +142,11 @@ __global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const ConvArgs a) {
 // element that the vector ALUs must issue are what is left of the gap to the HBM rate.
 template <int CBV, int MTH, int NT>
 __global__ __launch_bounds__(NT) void dwconv3x3_s1_lds_kernel(const ConvArgs a) {
+  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
   // all arguments as one batch of scalar loads with one wait (the compiler would load them where first used)
-  asm volatile("" ::"s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
-               "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.sh), "s"(a.ph), "s"(a.pw), "s"(a.flags));
+  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
+               "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.sh), "s"(a.ph), "s"(a.pw), "s"(a.flags), "s"(a.fd_tiles_n.mul),
+               "s"(a.fd_tiles_n.shift), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift));
   constexpr int MTW = 7;                       // micro-tiles (2 x 4 outputs) across the workgroup tile
   constexpr int TH = 2 * MTH, TW = 4 * MTW;    // output tile
   constexpr int PH = TH + 2, PW = TW + 2;      // input patch
@@ -159,7 +162,7 @@ __global__ __launch_bounds__(NT) void dwconv3x3_s1_lds_kernel(const ConvArgs a) 
   const int tiles_w = (a.Wo + TW - 1) / TW, tiles_h = (a.Ho + TH - 1) / TH;
   // (n, tile row, tile column, channel block), channel block fastest; divisions by multiply-high with the
   // launcher's constants (fd_tiles_n: cblocks, fd_wo: tiles_w, fd_howo: tiles_h)
-  const unsigned t0 = (unsigned)xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned t0 = (unsigned)xcd_remap(bid, a.N * tiles_h * tiles_w * cblocks);
   const unsigned t1 = fast_div(t0, a.fd_tiles_n), t2 = fast_div(t1, a.fd_wo);
   const int cb = (int)(t0 - t1 * (unsigned)cblocks);
   const int tx = (int)(t1 - t2 * (unsigned)tiles_w);

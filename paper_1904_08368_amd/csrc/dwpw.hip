@@ -106,18 +106,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void dwpw_fused_kernel
   uint4* const filt = lds + O_FILT;
 
   const ConvArgs& pw = a.pw;
-  asm volatile("" ::"s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
+  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
+  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
                "s"(a.W), "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.tiles_x), "s"(a.tiles_y), "s"(a.tiles_n), "s"(a.fd_x.mul), "s"(a.fd_x.shift),
-               "s"(a.fd_y.mul), "s"(a.fd_y.shift), "s"(a.fd_n.mul), "s"(a.fd_n.shift));
-  asm volatile("" ::"s"(pw.w), "s"(pw.y), "s"(pw.bias), "s"(pw.scale), "s"(pw.shift), "s"(pw.K), "s"(pw.Kp), "s"(pw.flags),
-               "s"(pw.param_vec));
+               "s"(a.fd_y.mul), "s"(a.fd_y.shift), "s"(a.fd_n.mul), "s"(a.fd_n.shift), "s"(pw.w), "s"(pw.y), "s"(pw.bias), "s"(pw.scale),
+               "s"(pw.shift), "s"(pw.K), "s"(pw.Kp), "s"(pw.flags), "s"(pw.param_vec));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WAVES_M, wn = wave / WAVES_M;
   // (image, tile row, tile column, channel tile), channel tile fastest: the workgroups that share a patch are neighbours
   // (divisions by multiply-high with host-computed constants: three software divisions would be a fifth of the
   // vector instructions of a single-chunk tile)
-  const unsigned t0 = (unsigned)xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned t0 = (unsigned)xcd_remap(bid, a.N * a.tiles_y * a.tiles_x * a.tiles_n);
   const unsigned t1 = fast_div(t0, a.fd_n), t2 = fast_div(t1, a.fd_x);
   const int tile_n = (int)(t0 - t1 * (unsigned)a.tiles_n);
   const int tx = (int)(t1 - t2 * (unsigned)a.tiles_x);

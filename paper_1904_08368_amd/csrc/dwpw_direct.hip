@@ -75,15 +75,15 @@ __global__ __launch_bounds__(64 * NW, OCC ? OCC : 1) void dwpw_fused_direct_kern
   __shared__ uint4 ring[WN * NS * FPL];
 
   const ConvArgs& pw = a.pw;
-  asm volatile("" ::"s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
-               "s"(a.W), "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(g.th), "s"(g.tw), "s"(g.tiles_x), "s"(g.tiles_y), "s"(g.tiles_n), "s"(g.n_major),
-               "s"(g.log_cv), "s"(g.nit));
-  asm volatile("" ::"s"(g.fd_x.mul), "s"(g.fd_x.shift), "s"(g.fd_y.mul), "s"(g.fd_y.shift), "s"(g.fd_n.mul), "s"(g.fd_n.shift),
-               "s"(g.fd_p.mul), "s"(g.fd_p.shift), "s"(g.fd_tw.mul), "s"(g.fd_tw.shift), "s"(pw.w), "s"(pw.y), "s"(pw.bias), "s"(pw.scale),
-               "s"(pw.shift), "s"(pw.K), "s"(pw.Kp), "s"(pw.flags), "s"(pw.param_vec));
+  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
+  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
+               "s"(a.W), "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.stride), "s"(g.th), "s"(g.tw), "s"(g.tiles_x), "s"(g.tiles_y), "s"(g.tiles_n), "s"(g.n_major),
+               "s"(g.log_cv), "s"(g.nit), "s"(g.fd_x.mul), "s"(g.fd_x.shift), "s"(g.fd_y.mul), "s"(g.fd_y.shift), "s"(g.fd_n.mul),
+               "s"(g.fd_n.shift), "s"(g.fd_p.mul), "s"(g.fd_p.shift), "s"(g.fd_tw.mul), "s"(g.fd_tw.shift), "s"(pw.w), "s"(pw.y), "s"(pw.bias),
+               "s"(pw.scale), "s"(pw.shift), "s"(pw.K), "s"(pw.Kp), "s"(pw.flags), "s"(pw.param_vec));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const unsigned t0 = (unsigned)xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned t0 = (unsigned)xcd_remap(bid, a.N * g.tiles_y * g.tiles_x * g.tiles_n);
   const unsigned tq = fast_div(t0, g.n_major ? g.fd_p : g.fd_n);
   const unsigned rects = (unsigned)(g.tiles_x * g.tiles_y * a.N);
   const int tile_n = (int)(g.n_major ? tq : t0 - tq * (unsigned)g.tiles_n);

@@ -53,10 +53,10 @@ __global__ __launch_bounds__(256) void nchw_to_nhwc_kernel(const T* x, T* y, int
 // the pixels first (4 lanes: 64 bytes of a channel row), then along the channels.  Bound by memory: 256 channels at
 // 28 x 28, batch 32: 32.0 -> 5.9 us for 25.7 MB (one element per thread read 2 bytes of a line each).
 template <typename T>
-__global__ __launch_bounds__(64) void nchw_to_nhwc_vec_kernel(const T* x, T* y, int C, int HW, int Cpad, int pgroups, int cgroups) {
+__global__ __launch_bounds__(64) void nchw_to_nhwc_vec_kernel(const T* x, T* y, int C, int HW, int Cpad, int pgroups, int cgroups, int tiles) {
   constexpr int VE = 16 / (int)sizeof(T), PX = sizeof(T) == 2 ? 8 : 4;
   constexpr int NV = PX * (int)sizeof(T) / 4;  // words of a channel's piece
-  const int tile = xcd_remap((int)blockIdx.x, (int)gridDim.x);   // (image, pixel block, channel block); the XCD of the conv that reads it
+  const int tile = xcd_remap((int)blockIdx.x, tiles);   // (image, pixel block, channel block); the XCD of the conv that reads it
   const int per_n = pgroups * cgroups;
   const int n = tile / per_n, rem = tile - n * per_n;
   const int pb = rem / cgroups, cb = rem - pb * cgroups;
@@ -215,7 +215,10 @@ __device__ __forceinline__ void keep_first(half8& best, const half8& first) { be
 template <typename V, int VE, int R, int STRIDE, int OUT>
 __global__ __launch_bounds__(256) void maxpool_fixed_kernel(const V* x, V* y, const PoolGeom g) {
   static_assert(OUT == 1 || STRIDE == 1, "outputs below each other share rows at stride 1");
-  const unsigned idx = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
+  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
+  asm volatile("" : "+s"(bid) : "s"(g.CV), "s"(g.H), "s"(g.W), "s"(g.stride), "s"(g.pad), "s"(g.Ho), "s"(g.Wo), "s"(g.rows), "s"(g.total),
+               "s"(g.fd_cv.mul), "s"(g.fd_cv.shift), "s"(g.fd_wo.mul), "s"(g.fd_wo.shift), "s"(g.fd_rows.mul), "s"(g.fd_rows.shift));
+  const unsigned idx = (unsigned)xcd_remap(bid, (int)((g.total + 255u) / 256u)) * 256u + threadIdx.x;
   if (idx >= g.total) return;
   const unsigned t1 = fast_div(idx, g.fd_cv), t2 = fast_div(t1, g.fd_wo);
   const int cv = (int)(idx - t1 * (unsigned)g.CV), q = (int)(t1 - t2 * (unsigned)g.Wo);
@@ -497,10 +500,10 @@ hipError_t launch_nchw_to_nhwc(int esize, int N, int C, int H, int W, int Cpad, 
     if ((long)N * pg * cg <= 0x7fffffffL) {
       const dim3 tiles((unsigned)(N * pg * cg)), wave(64);
       if (esize == 1)
-        hipLaunchKernelGGL((nchw_to_nhwc_vec_kernel<int8_t>), tiles, wave, 0, st, (const int8_t*)x, (int8_t*)y, C, H * W, Cpad, pg, cg);
+        hipLaunchKernelGGL((nchw_to_nhwc_vec_kernel<int8_t>), tiles, wave, 0, st, (const int8_t*)x, (int8_t*)y, C, H * W, Cpad, pg, cg, N * pg * cg);
       else
         hipLaunchKernelGGL((nchw_to_nhwc_vec_kernel<uint16_t>), tiles, wave, 0, st, (const uint16_t*)x, (uint16_t*)y, C, H * W, Cpad,
-                           pg, cg);
+                           pg, cg, N * pg * cg);
       return hipGetLastError();
     }
   }

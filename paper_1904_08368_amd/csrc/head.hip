@@ -25,10 +25,13 @@ constexpr int kThreads = 512, kWaves = kThreads / 64;
 // A wave makes one output.  KI: reduction vectors of a lane, C <= 512 KI.  DEPTH: positions a thread has in flight.
 template <int KI, int DEPTH>
 __global__ __launch_bounds__(kThreads) void avgpool_dense_kernel(const HeadArgs a) {
+  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
+  asm volatile("" : "+s"(bid) : "s"(a.N), "s"(a.C), "s"(a.HW), "s"(a.units), "s"(a.act), "s"(a.cvt_log2), "s"(a.x), "s"(a.w), "s"(a.bias),
+               "s"(a.pooled), "s"(a.y));
   __shared__ float part[kThreads * 8];
   __shared__ half8 pl[KI * 64];
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n = (int)blockIdx.x % a.N, ug = (int)blockIdx.x / a.N;
+  const int n = bid % a.N, ug = bid / a.N;
   const int CV = a.C >> 3, CVT = 1 << a.cvt_log2, parts = kThreads >> a.cvt_log2;
   const int j = ug * kWaves + wave;
   half8 w[KI];
