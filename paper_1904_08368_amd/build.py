@@ -11,6 +11,8 @@ LIB = os.path.join(HERE, "librelayfused.so")
 SOURCES = ["api.cpp", "fusion.cpp", "launch_list.cpp", "conv_igemm.hip", "conv_igemm_dma.hip", "conv_halo.hip", "conv_small.hip", "conv_stream.hip", "conv_direct_f32.hip", "conv_first.hip", "conv_stem.hip", "head.hip", "dwconv.hip", "dwpw.hip", "dwpw_direct.hip", "dense.hip", "glue.hip", "quant.hip", "realize.hip", "probe.hip", "qschemes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # a kernel's leading scalar parameters are in registers when a wave starts (see xcd_remap)
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-command-line-argument"]
 
 

@@ -37,7 +37,7 @@ __device__ __forceinline__ float dot2(unsigned x, unsigned w, float acc) {
 
 // PASS: output channels per pass.  SPLIT: a workgroup takes one pass only, of PASS channels from blockIdx.y * PASS on.
 template <int PASS, bool SPLIT>
-__global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
+__global__ __launch_bounds__(128) void conv_first_kernel(const int threads, const ConvArgs a) {
   int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
   asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.K),
                "s"(a.Ho), "s"(a.Wo), "s"(a.flags), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift));
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(128) void conv_first_kernel(const ConvArgs a) {
   const int tid = threadIdx.x;
   // ---- this thread's kPix pixels: (n, p, q0 .. q0 + kPix - 1)
   const int wq = a.Wo / kPix;                                // threads per output row
-  const unsigned t_raw = (unsigned)bid * 128u + tid, t_end = (unsigned)(a.N * a.Ho * wq);
+  const unsigned t_raw = (unsigned)bid * 128u + tid, t_end = (unsigned)threads;
   const bool live = t_raw < t_end;                           // (threads past the end load the last pixels again and store nothing)
   const unsigned t = live ? t_raw : t_end - 1;
   const unsigned row = fast_div(t, a.fd_howo);               // n * Ho + p  (the launch sets this divisor to wq,
@@ -200,11 +200,11 @@ hipError_t launch_conv_first(const ConvArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)((threads + 127) / 128));
   const long waves = (threads + 63) / 64;
   if (waves * (a.K / 16) <= 256)
-    hipLaunchKernelGGL((conv_first_kernel<kPass / 2, true>), dim3(grid.x, a.K / (kPass / 2)), dim3(128), kPass / 2 * 8, st, b);
+    hipLaunchKernelGGL((conv_first_kernel<kPass / 2, true>), dim3(grid.x, a.K / (kPass / 2)), dim3(128), kPass / 2 * 8, st, (int)threads, b);
   else if (waves <= 1600 && a.K > kPass)
-    hipLaunchKernelGGL((conv_first_kernel<kPass, true>), dim3(grid.x, a.K / kPass), dim3(128), kPass * 8, st, b);
+    hipLaunchKernelGGL((conv_first_kernel<kPass, true>), dim3(grid.x, a.K / kPass), dim3(128), kPass * 8, st, (int)threads, b);
   else
-    hipLaunchKernelGGL((conv_first_kernel<kPass, false>), grid, dim3(128), (size_t)a.K * 8, st, b);
+    hipLaunchKernelGGL((conv_first_kernel<kPass, false>), grid, dim3(128), (size_t)a.K * 8, st, (int)threads, b);
   return hipGetLastError();
 }
 

@@ -51,6 +51,11 @@ struct HaloGeom {
   FastDiv fd_w;
 };
 
+struct HaloArgs {
+  HaloGeom g;
+  ConvArgs a;
+};
+
 constexpr int NSW = 3;         // filter ring stages (9 taps per chunk keep step % NSW compile-time)
 constexpr int XPW = 8;         // halo blocks a wave loads per chunk, times HB
 constexpr unsigned kNoBlock = ~0u;
@@ -70,7 +75,9 @@ constexpr int SQ = 16, SQP = SQ + 2;   // square tiles: 16 x 16 outputs, 18 x 18
 // tile, so each matrix instruction needs fewer operand reads -- what the small tiles are bound by.
 template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int KP, int HB = 1, bool SQUARE = false, int SK = 1, bool EXT = false,
           bool POOL = false>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_kernel(const ConvArgs a, const HaloGeom g) {
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_kernel(const int workgroups, const HaloArgs block) {
+  const HaloGeom& g = block.g;
+  const ConvArgs& a = block.a;
   constexpr int NW = WAVES_M * WAVES_N * SK;
   constexpr int VE = IS_I8 ? 16 : 8;
   constexpr int ES = IS_I8 ? 1 : 2;
@@ -110,17 +117,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   // wait; left to itself the compiler loads them where they are first used, and the prologue then waits
   // for five scalar-load round trips one after another.  (The workgroup's number passes through the same statement: arithmetic on it that
   // needs only some of them would otherwise be placed ahead of the others' loads.)
-  int bid = (int)blockIdx.x;
+  int tile = xcd_remap((int)blockIdx.x, workgroups);
+  const void* ptr_x = a.x;   // (through it too, like the operands' addresses: their copies into a descriptor wait for nothing ahead of it)
+  const void* ptr_w = a.w;
 #define RELAY_ASKED                                                                                                                     \
-  "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), \
+  "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.C), \
       "s"(a.K), "s"(a.Kp), "s"(a.flags), "s"(a.param_vec), "s"(a.n_major), "s"(a.xs_n), "s"(g.P), "s"(g.F), "s"(g.Mflat), "s"(g.rcp_p),  \
       "s"(g.rcp_f), "s"(g.xblk), "s"(g.nxbuf), "s"(g.ncc), "s"(g.tab_slot), "s"(g.fd_f.mul), "s"(g.fd_f.shift), "s"(g.fd_tiles_m.mul),   \
       "s"(g.fd_tiles_m.shift), "s"(g.fd_tiles_n.mul), "s"(g.fd_tiles_n.shift)
   if constexpr (IS_I8)   // (the quantized tail's own arguments too)
-    asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi),
+    asm volatile("" : "+s"(tile), "+s"(ptr_x), "+s"(ptr_w) : RELAY_ASKED, "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi),
                  "s"(a.qmult), "s"(a.qshift));
   else
-    asm volatile("" : "+s"(bid) : RELAY_ASKED);
+    asm volatile("" : "+s"(tile), "+s"(ptr_x), "+s"(ptr_w) : RELAY_ASKED);
 #undef RELAY_ASKED
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -128,7 +137,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   const int wk = wave / (WAVES_M * WAVES_N), wsub = wave % (WAVES_M * WAVES_N);
   const int wm = wsub % WAVES_M, wn = wsub / WAVES_M;
   const int tiles_m = (g.Mflat + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
-  const int tile = xcd_remap(bid, tiles_m * tiles_n);
   const int tile_q = (int)fast_div((uint32_t)tile, a.n_major ? g.fd_tiles_m : g.fd_tiles_n);
   const int tile_n = a.n_major ? tile_q : tile - tile_q * tiles_n;
   const int tile_m = a.n_major ? tile - tile_q * tiles_m : tile_q;
@@ -156,8 +164,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
     const int ch = n0 + row;
     w_off[i] = ch < a.K ? (unsigned)((ch * a.Kp + (b / WB) * (BKV * VE) + kvl * VE) * ES) : kOob;
   }
-  const intx4 rs_x = make_rsrc(a.x, (unsigned)((size_t)a.N * a.xs_n * ES));
-  const intx4 rs_w = make_rsrc(a.w, (unsigned)((size_t)a.K * a.Kp * ES));
+  const intx4 rs_x = make_rsrc(ptr_x, (unsigned)((size_t)a.N * a.xs_n * ES));
+  const intx4 rs_w = make_rsrc(ptr_w, (unsigned)((size_t)a.K * a.Kp * ES));
   auto issue_filters = [&](int s) {  // the filters of step (0, s), s < NSW
 #pragma unroll
     for (int i = 0; i < LW; ++i)
@@ -223,7 +231,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK, 2) void conv3x3_halo_k
   //      its run of tiles, else all of them.  (These loads are younger than those the first two steps wait for, and
   //      older than all others.)  Only in short launches (measured up to 912 tiles x chunks): in longer ones the first
   //      use of the filters is a small part of the time and the extra wait costs as much (VGG-16 0.7 %).
-  const int nb = tiles_m * tiles_n, xcd_idx = bid >> 3;
+  const int nb = workgroups, xcd_idx = (int)blockIdx.x >> 3;
   int touched = 0;
   if (nb * g.ncc <= 1024 && xcd_idx < 64) {
     const int per = nb >> 3, wgs = min(per + 1, 64);  // (two workgroups on each of the XCD's 32 CUs)
@@ -571,10 +579,10 @@ hipError_t launch_halo_store(const ConvArgs& a, const HaloGeom& g, size_t lds_by
   }
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
   const int tiles_m = (g.Mflat + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
-  HaloGeom gl = g;
-  gl.fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
-  gl.fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
-  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(64 * WM * WN * SK), lds_bytes, st, a, gl);
+  HaloArgs block{g, a};
+  block.g.fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
+  block.g.fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
+  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(64 * WM * WN * SK), lds_bytes, st, tiles_m * tiles_n, block);
   return hipGetLastError();
 }
 

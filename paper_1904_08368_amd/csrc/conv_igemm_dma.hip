@@ -56,9 +56,9 @@ using acc_t_scalar = typename std::conditional<IS_I8, int, float>::type;
 // branches they cost it about 1 % each (registers held across the main loop, code size).
 // POOL: the tile is the 15 x 17 patch of conv outputs under a 7 x 8 block of 3x3/s2/p1 max-pool
 // outputs (255 of 256 rows); the finished patch goes to LDS and only the pooled block is stored.
-// bid: the workgroup's number among those of this conv
+// wg: the workgroup's place among those of this conv (xcd_remap)
 template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP, int SK, bool STOCH, bool EXT, bool POOL>
-__device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, int bid) {
+__device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, int wg) {
   constexpr int NW = WAVES_M * WAVES_N * SK;
   static_assert(SK == 1 || (SK == 2 && KP == 2 && TM % 2 == 0), "k-split pairs take one 64-byte plane each");
   constexpr int VE = IS_I8 ? 16 : 8;
@@ -114,10 +114,10 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, int bid) {
       "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul), "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul), \
       "s"(a.fd_tiles_n.shift)
   if constexpr (IS_I8)
-    asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.qbias), "s"(a.res), "s"(a.y), "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode),
+    asm volatile("" : "+s"(wg) : RELAY_ASKED, "s"(a.qbias), "s"(a.res), "s"(a.y), "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode),
                  "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult), "s"(a.qshift));
   else
-    asm volatile("" : "+s"(bid) : RELAY_ASKED);
+    asm volatile("" : "+s"(wg) : RELAY_ASKED);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -126,7 +126,6 @@ __device__ __forceinline__ void igemm_dma_tile(const ConvArgs& a, int bid) {
   const int tiles_m = POOL ? a.N * a.pool_tiles_img : (a.M + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
   // with a split reduction consecutive workgroups (same XCD) share a tile
   const int nsplit = (EXT && a.split > 1) ? a.split : 1;
-  const int wg = xcd_remap(bid, tiles_m * tiles_n * nsplit);
   const int tile = wg / nsplit, ks = wg - tile * nsplit;
   const int tile_q = (int)fast_div((uint32_t)tile, a.n_major ? a.fd_tiles_m : a.fd_tiles_n);
   const int tile_n = a.n_major ? tile_q : tile - tile_q * tiles_n;
@@ -788,8 +787,8 @@ template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP, 
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
                              // two workgroups per CU where their LDS rings fit side by side
                              (NS * KP * (WAVES_M * TM + WAVES_N * TN) * 32 * 64 <= 80 * 1024 ? 2 : 1))
-    void igemm_dma_kernel(const ConvArgs a) {
-  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, STOCH, EXT, POOL>(a, (int)blockIdx.x);
+    void igemm_dma_kernel(const int workgroups, const ConvArgs a) {
+  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, STOCH, EXT, POOL>(a, xcd_remap((int)blockIdx.x, workgroups));
 }
 
 // The tile for fp16 layers of few pixels whose sums other launches promise to the bit (strided convs centred on a shortcut's,
@@ -798,17 +797,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * SK,
 // fifth multiplies.  The fifth reads chunk kc from LDS while it multiplies chunk kc - 1, so a chunk takes the longest of its
 // loads (KP KB per wave), its LDS reads and its MFMAs (64 KP clocks) instead of their sum behind a barrier.
 template <int KP>
-__device__ __forceinline__ void igemm_dma_narrow_tile(const ConvArgs& a, int bid) {
+__device__ __forceinline__ void igemm_dma_narrow_tile(const ConvArgs& a, int wg) {
   constexpr int VE = 8, ES = 2, CK = KP * BKV * VE, BM = 32, BN = 32, NS = KP == 4 ? 4 : (KP == 2 ? 6 : 8);
   constexpr int PLANE = (BM + BN) * BKV, STAGE = KP * PLANE, KSTEPS = KP * 2;
   constexpr int EP = BN / 4 + 1;
   __shared__ uint4 ring[NS * STAGE + 32 * EP];
-  asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.res), "s"(a.y));
+  asm volatile("" : "+s"(wg) : RELAY_ASKED, "s"(a.res), "s"(a.y));
 #undef RELAY_ASKED
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.K + BN - 1) / BN;
-  const int tile = xcd_remap(bid, tiles_m * tiles_n);
+  const int tile = wg;
   const int tile_q = (int)fast_div((uint32_t)tile, a.n_major ? a.fd_tiles_m : a.fd_tiles_n);
   const int tile_n = a.n_major ? tile_q : tile - tile_q * tiles_n;
   const int tile_m = a.n_major ? tile - tile_q * tiles_m : tile_q;
@@ -944,8 +943,8 @@ __device__ __forceinline__ void igemm_dma_narrow_tile(const ConvArgs& a, int bid
 }
 
 template <int KP>
-__global__ __launch_bounds__(320) void igemm_dma_kernel_narrow(const ConvArgs a) {
-  igemm_dma_narrow_tile<KP>(a, (int)blockIdx.x);
+__global__ __launch_bounds__(320) void igemm_dma_kernel_narrow(const int workgroups, const ConvArgs a) {
+  igemm_dma_narrow_tile<KP>(a, xcd_remap((int)blockIdx.x, workgroups));
 }
 
 // Two convs that do not read each other's output, in one launch: the first `tiles` workgroups run the first, the others the
@@ -955,17 +954,17 @@ struct DmaPair {
 };
 template <bool IS_I8, int WAVES_M, int WAVES_N, int TM, int TN, int NS, int KP>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (NS * KP * (WAVES_M * TM + WAVES_N * TN) * 32 * 64 <= 80 * 1024 ? 2 : 1))
-    void igemm_dma_pair_kernel(const int tiles, const DmaPair p) {
+    void igemm_dma_pair_kernel(const int tiles, const int others, const DmaPair p) {
   const int second = (int)blockIdx.x >= tiles ? 1 : 0;
   const ConvArgs a = p.a[second];
-  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, 1, false, false, false>(a, (int)blockIdx.x - (second ? tiles : 0));
+  igemm_dma_tile<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, 1, false, false, false>(a, xcd_remap((int)blockIdx.x - (second ? tiles : 0), second ? others : tiles));
 }
 
 template <int KP>
-__global__ __launch_bounds__(320) void igemm_dma_pair_kernel_narrow(const int tiles, const DmaPair p) {
+__global__ __launch_bounds__(320) void igemm_dma_pair_kernel_narrow(const int tiles, const int others, const DmaPair p) {
   const int second = (int)blockIdx.x >= tiles ? 1 : 0;
   const ConvArgs a = p.a[second];
-  igemm_dma_narrow_tile<KP>(a, (int)blockIdx.x - (second ? tiles : 0));
+  igemm_dma_narrow_tile<KP>(a, xcd_remap((int)blockIdx.x - (second ? tiles : 0), second ? others : tiles));
 }
 
 struct DmaTile {
@@ -1013,10 +1012,10 @@ hipError_t launch_one(const ConvArgs& a, hipStream_t st) {
   b.fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
   if (STOCH || a.nseg || a.split > 1)
     hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, STOCH, true>), dim3(tiles),
-                       dim3(64 * WAVES_M * WAVES_N * SK), 0, st, b);
+                       dim3(64 * WAVES_M * WAVES_N * SK), 0, st, tiles, b);
   else
     hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP, SK, false, false>), dim3(tiles),
-                       dim3(64 * WAVES_M * WAVES_N * SK), 0, st, b);
+                       dim3(64 * WAVES_M * WAVES_N * SK), 0, st, tiles, b);
   return hipGetLastError();
 }
 
@@ -1033,8 +1032,8 @@ hipError_t launch_narrow_one(const ConvArgs& a, const ConvArgs* second, hipStrea
     p.a[i].fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
     p.a[i].fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
   }
-  if (second) hipLaunchKernelGGL(igemm_dma_pair_kernel_narrow<KP>, dim3(tiles[0] + tiles[1]), dim3(320), 0, st, tiles[0], p);
-  else hipLaunchKernelGGL(igemm_dma_kernel_narrow<KP>, dim3(tiles[0]), dim3(320), 0, st, p.a[0]);
+  if (second) hipLaunchKernelGGL(igemm_dma_pair_kernel_narrow<KP>, dim3(tiles[0] + tiles[1]), dim3(320), 0, st, tiles[0], tiles[1], p);
+  else hipLaunchKernelGGL(igemm_dma_kernel_narrow<KP>, dim3(tiles[0]), dim3(320), 0, st, tiles[0], p.a[0]);
   return hipGetLastError();
 }
 
@@ -1059,7 +1058,7 @@ hipError_t launch_pair_one(const ConvArgs& a, const ConvArgs& b, hipStream_t st)
     p.a[i].fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
     p.a[i].fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
   }
-  hipLaunchKernelGGL((igemm_dma_pair_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP>), dim3(tiles[0] + tiles[1]), dim3(64 * WAVES_M * WAVES_N), 0, st, tiles[0], p);
+  hipLaunchKernelGGL((igemm_dma_pair_kernel<IS_I8, WAVES_M, WAVES_N, TM, TN, NS, KP>), dim3(tiles[0] + tiles[1]), dim3(64 * WAVES_M * WAVES_N), 0, st, tiles[0], tiles[1], p);
   return hipGetLastError();
 }
 
@@ -1236,9 +1235,9 @@ bool pool_stem(const ConvArgs& a, bool is_i8) {
 template <bool IS_I8>
 hipError_t launch_pool_one(const ConvArgs& a, int tiles, hipStream_t st) {
   if (pool_stem(a, IS_I8))
-    hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, 4, 1, 2, 2, 1, 1, 1, false, false, true>), dim3(tiles), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, 4, 1, 2, 2, 1, 1, 1, false, false, true>), dim3(tiles), dim3(256), 0, st, tiles, a);
   else
-    hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, 4, 1, 2, 2, 2, 1, 1, false, false, true>), dim3(tiles), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((igemm_dma_kernel<IS_I8, 4, 1, 2, 2, 2, 1, 1, false, false, true>), dim3(tiles), dim3(256), 0, st, tiles, a);
   return hipGetLastError();
 }
 }  // namespace

@@ -60,15 +60,14 @@ __device__ __forceinline__ uint32_t div_by(uint32_t n, FastDiv f) { return (__um
 // What the host works out for a launch, so that no wave divides or multiplies for it.
 struct SmallGeom {
   int tiles_m, tiles_n;
-  int xcd_per, xcd_rem;          // tiles per XCD and the XCDs that take one more
   int per_tap, per_wave, units;  // units of a filter tap, of a wave's run, of the reduction
   FastDiv fd_per_tap, fd_s;      // division by per_tap and by S
 };
 
 // EXT: the instantiation that stores output channel segments.  NA: accumulators per block of a tile, used in turn (see small_runs).
-// bid: the workgroup's number among the tiles of this conv.
+// tile: the workgroup's place among the tiles of this conv (xcd_remap).
 template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT, int NA>
-__device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g, int bid) {
+__device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g, int tile) {
   constexpr int VE = IS_I8 ? 16 : 8;
   constexpr int ES = IS_I8 ? 1 : 2;
   constexpr int CU = U * BKV * VE;  // channels per unit: U steps of 64 bytes
@@ -94,20 +93,17 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
       "s"(a.K), "s"(a.R), "s"(a.S), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.xs_n), "s"(a.xs_h),           \
       "s"(a.xs_w), "s"(a.tap_spread), "s"(a.n_major), "s"(a.M), "s"(a.Kred), "s"(a.Kp), "s"(a.flags), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift), \
       "s"(a.fd_howo.mul), "s"(a.fd_howo.shift), "s"(a.fd_tiles_m.mul), "s"(a.fd_tiles_m.shift), "s"(a.fd_tiles_n.mul),                    \
-      "s"(a.fd_tiles_n.shift), "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.xcd_per), "s"(g.xcd_rem), "s"(g.per_tap), "s"(g.per_wave), "s"(g.units), \
+      "s"(a.fd_tiles_n.shift), "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.per_tap), "s"(g.per_wave), "s"(g.units), \
       "s"(g.fd_per_tap.mul), "s"(g.fd_per_tap.shift), "s"(g.fd_s.mul), "s"(g.fd_s.shift)
   if constexpr (IS_I8)
-    asm volatile("" : "+s"(bid) : RELAY_ASKED, "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult),
+    asm volatile("" : "+s"(tile) : RELAY_ASKED, "s"(a.lshift), "s"(a.rshift), "s"(a.round_add), "s"(a.qmode), "s"(a.clip_lo), "s"(a.clip_hi), "s"(a.qmult),
                  "s"(a.qshift));
   else
-    asm volatile("" : "+s"(bid) : RELAY_ASKED);
+    asm volatile("" : "+s"(tile) : RELAY_ASKED);
 #undef RELAY_ASKED
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // (xcd_remap with the host's divisions)
-  const int xcd = bid & 7;
-  const int tile = xcd * g.xcd_per + min(xcd, g.xcd_rem) + (bid >> 3);
   const int tile_q = (int)div_by((uint32_t)tile, a.n_major ? a.fd_tiles_m : a.fd_tiles_n);
   const int tile_n = a.n_major ? tile_q : tile - tile_q * g.tiles_n;
   const int tile_m = a.n_major ? tile - tile_q * g.tiles_m : tile_q;
@@ -356,26 +352,26 @@ __device__ __forceinline__ void small_tile(const ConvArgs& a, const SmallGeom& g
   }
 }
 
+struct SmallArgs {
+  SmallGeom g;
+  ConvArgs a;
+};
 template <bool IS_I8, int TM, int TN, int W, int U, int NS, bool EXT, int NA>
-__global__ __launch_bounds__(64 * W) void igemm_small_kernel(const ConvArgs a, const SmallGeom g) {
-  small_tile<IS_I8, TM, TN, W, U, NS, EXT, NA>(a, g, (int)blockIdx.x);
+__global__ __launch_bounds__(64 * W) void igemm_small_kernel(const int tiles, const SmallArgs c) {
+  small_tile<IS_I8, TM, TN, W, U, NS, EXT, NA>(c.a, c.g, xcd_remap((int)blockIdx.x, tiles));
 }
 
 // Two convs that do not read each other's output, in one launch: the first `tiles` workgroups run the first, the others the
 // second.  The argument block is picked by a uniform index and copied whole: read field by field through that index its loads were 40 to
 // 57 of one word each, and the arguments there after 2600 to 3200 clocks where a single conv's are after 700.
-struct SmallArgs {
-  ConvArgs a;
-  SmallGeom g;
-};
 struct SmallPair {
   SmallArgs c[2];
 };
 template <bool IS_I8, int TM, int TN, int W, int U, int NS>
-__global__ __launch_bounds__(64 * W) void igemm_small_pair_kernel(const int tiles, const SmallPair p) {
+__global__ __launch_bounds__(64 * W) void igemm_small_pair_kernel(const int tiles, const int others, const SmallPair p) {
   const int second = (int)blockIdx.x >= tiles ? 1 : 0;
   const SmallArgs c = p.c[second];
-  small_tile<IS_I8, TM, TN, W, U, NS, false, 1>(c.a, c.g, (int)blockIdx.x - (second ? tiles : 0));
+  small_tile<IS_I8, TM, TN, W, U, NS, false, 1>(c.a, c.g, xcd_remap((int)blockIdx.x - (second ? tiles : 0), second ? others : tiles));
 }
 
 struct SmallTile {
@@ -430,9 +426,6 @@ SmallGeom small_geom(const ConvArgs& a, ConvArgs& b) {
   SmallGeom g;
   g.tiles_m = (a.M + TM * 16 - 1) / (TM * 16);
   g.tiles_n = (a.K + TN * 16 - 1) / (TN * 16);
-  const int tiles = g.tiles_m * g.tiles_n;
-  g.xcd_per = tiles >> 3;
-  g.xcd_rem = tiles & 7;
   g.per_tap = a.C / (U * BKV * (IS_I8 ? 16 : 8));
   g.units = a.R * a.S * g.per_tap;
   g.per_wave = (g.units + W - 1) / W;
@@ -447,13 +440,13 @@ SmallGeom small_geom(const ConvArgs& a, ConvArgs& b) {
 template <bool IS_I8, int TM, int TN, int W, int U, int NA>
 hipError_t launch_small_alone(const ConvArgs& a, hipStream_t st) {
   constexpr int NS = stages(U, TM, TN, W);
-  ConvArgs b;
-  const SmallGeom g = small_geom<IS_I8, TM, TN, W, U>(a, b);
-  const int tiles = g.tiles_m * g.tiles_n;
+  SmallArgs c;
+  c.g = small_geom<IS_I8, TM, TN, W, U>(a, c.a);
+  const int tiles = c.g.tiles_m * c.g.tiles_n;
   if (a.nseg)
-    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, true, NA>), dim3(tiles), dim3(64 * W), 0, st, b, g);
+    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, true, NA>), dim3(tiles), dim3(64 * W), 0, st, tiles, c);
   else
-    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, false, NA>), dim3(tiles), dim3(64 * W), 0, st, b, g);
+    hipLaunchKernelGGL((igemm_small_kernel<IS_I8, TM, TN, W, U, NS, false, NA>), dim3(tiles), dim3(64 * W), 0, st, tiles, c);
   return hipGetLastError();
 }
 
@@ -466,7 +459,8 @@ hipError_t launch_small_one(const ConvArgs& a, const ConvArgs* second, int runs,
     p.c[0].g = small_geom<IS_I8, TM, TN, W, U>(a, p.c[0].a);
     p.c[1].g = small_geom<IS_I8, TM, TN, W, U>(*second, p.c[1].a);
     const int tiles = p.c[0].g.tiles_m * p.c[0].g.tiles_n;
-    hipLaunchKernelGGL((igemm_small_pair_kernel<IS_I8, TM, TN, W, U, NS>), dim3(tiles + p.c[1].g.tiles_m * p.c[1].g.tiles_n), dim3(64 * W), 0, st, tiles, p);
+    const int others = p.c[1].g.tiles_m * p.c[1].g.tiles_n;
+    hipLaunchKernelGGL((igemm_small_pair_kernel<IS_I8, TM, TN, W, U, NS>), dim3(tiles + others), dim3(64 * W), 0, st, tiles, others, p);
     return hipGetLastError();
   }
   if constexpr (!IS_I8 && TM * TN <= kMostBlocks) {

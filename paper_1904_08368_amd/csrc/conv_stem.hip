@@ -27,7 +27,7 @@ namespace relay {
 namespace {
 
 template <bool IS_I8, int WM, int WN, int TM, int TN, int HW, int TYC, int TXC, int KS, bool MANY, bool POOL, bool PAIRS, int NI>
-__global__ __launch_bounds__(64 * (WM * WN + HW), TM * TN > 1 || NI > 10 ? 3 : 4) void conv_stem_kernel(const StemArgs g) {
+__global__ __launch_bounds__(64 * (WM * WN + HW), TM * TN > 1 || NI > 10 ? 3 : 4) void conv_stem_kernel(const int tiles, const StemArgs g) {
   constexpr int MW = WM * WN, NW = MW + HW, NT = 64 * NW, ES = IS_I8 ? 1 : 2, VE = 16 / ES, PXB = 4 * ES;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32, WTM = TM * 32, WTN = TN * 32;
   constexpr int OPITCH = BN * ES + 8;   // (8 bytes spread the accumulator layout's writes over the banks)
@@ -44,17 +44,18 @@ __global__ __launch_bounds__(64 * (WM * WN + HW), TM * TN > 1 || NI > 10 ? 3 : 4
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave % WM, wn = wave / WM;
   // (one batch of scalar loads; the workgroup's number passes through, so that arithmetic on it stays behind all of them)
-  int bid = (int)blockIdx.x;
-  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias), "s"(a.N), "s"(a.H), "s"(a.W),
+  int tile = TM * TN > 1 ? xcd_remap((int)blockIdx.x, tiles) : (int)blockIdx.x;
+  const void* ptr_w = a.w;
+  asm volatile("" : "+s"(tile), "+s"(ptr_w) : "s"(a.x), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.qbias), "s"(a.N), "s"(a.H), "s"(a.W),
                "s"(a.C), "s"(a.K), "s"(a.R), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(a.Ho), "s"(a.Wo), "s"(a.Kp), "s"(a.flags),
-               "s"(g.y_pooled), "s"(g.Hp), "s"(g.Wp), "s"(g.per_run), "s"(g.tiles), "s"(g.tiles_img), "s"(g.tiles_row), "s"(g.pitch), "s"(g.cst_at),
+               "s"(g.y_pooled), "s"(g.Hp), "s"(g.Wp), "s"(g.per_run), "s"(g.tiles_img), "s"(g.tiles_row), "s"(g.pitch), "s"(g.cst_at),
                "s"(g.per_row), "s"(g.items), "s"(g.fd_img.mul), "s"(g.fd_img.shift), "s"(g.fd_row.mul), "s"(g.fd_row.shift), "s"(g.fd_items.mul),
                "s"(g.fd_items.shift));
   const int n0 = blockIdx.y * BN;
 
   // ---- filters and constants, once
   {
-    const intx4 rs_w = make_rsrc(a.w, (unsigned)((size_t)a.K * a.Kp * ES));
+    const intx4 rs_w = make_rsrc(ptr_w, (unsigned)((size_t)a.K * a.Kp * ES));
     const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) uint4*)(&lds[0]);
     const int srow = lane >> 2, sphys = lane & 3;
     for (int b = wave; b < a.R * FB; b += NW) {
@@ -78,7 +79,6 @@ __global__ __launch_bounds__(64 * (WM * WN + HW), TM * TN > 1 || NI > 10 ? 3 : 4
   //  and the layer behind finds these outputs in the L2 of the XCD that reads them.  First layer and the one behind it, ResNet-18 at
   //  batch 32 41.6 -> 38.7 us, int8 at batch 16 19.1 -> 17.9, MobileNet-v1 at batch 11 15.8 -> 14.1.  In a few small tiles the arithmetic
   //  costs what it gives: deep Q-network at batch 1 17.5 against 17.6.)
-  const int tile = TM * TN > 1 ? xcd_remap(bid, g.tiles) : bid;
   const int t_n = (int)fast_div((uint32_t)tile, g.fd_img), t_rem = tile - t_n * g.tiles_img;
   const int t_ty = (int)fast_div((uint32_t)t_rem, g.fd_row), t_tx = t_rem - t_ty * g.tiles_row;
   const int c_y = POOL ? t_ty * (TYC - 1) - 1 : t_ty * TYC, c_x = POOL ? t_tx * (TXC - 1) - 1 : t_tx * TXC;
@@ -416,7 +416,7 @@ hipError_t launch_stem_items(const StemArgs& g, size_t lds_bytes, hipStream_t st
     raised.store(true, std::memory_order_release);
   }
   constexpr int BN = WN * TN * 32;
-  hipLaunchKernelGGL(kern, dim3(g.tiles, (g.a.K + BN - 1) / BN), dim3(64 * (WM * WN + HW)), lds_bytes, st, g);
+  hipLaunchKernelGGL(kern, dim3(g.tiles, (g.a.K + BN - 1) / BN), dim3(64 * (WM * WN + HW)), lds_bytes, st, g.tiles, g);
   return hipGetLastError();
 }
 

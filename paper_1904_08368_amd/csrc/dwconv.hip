@@ -29,10 +29,11 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t rsrc, unsi
 }
 
 template <int STRIDE, int TH, int TW>
-__global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const ConvArgs a) {
-  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
+__global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const int workgroups, const ConvArgs a) {
+  int place = xcd_remap((int)blockIdx.x, workgroups);   // (passes through: arithmetic on it stays behind the loads of all arguments)
   // all arguments as one batch of scalar loads with one wait (the compiler would load them where first used)
-  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
+  const void* ptr_x = a.x;
+  asm volatile("" : "+s"(place), "+s"(ptr_x) : "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
                "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.sh), "s"(a.ph), "s"(a.pw), "s"(a.flags), "s"(a.fd_tiles_n.mul),
                "s"(a.fd_tiles_n.shift), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift));
   constexpr int IH = (TH - 1) * STRIDE + 3, IW = (TW - 1) * STRIDE + 3;
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const ConvArgs a) {
   const int cvecs = a.C >> 3;
   const int tiles_w = (a.Wo + TW - 1) / TW, tiles_h = (a.Ho + TH - 1) / TH;
   const unsigned total = (unsigned)(a.N * tiles_h * tiles_w * cvecs);  // < 2^31: checked by the launcher
-  unsigned idx = (unsigned)xcd_remap(bid, (int)((total + 255u) / 256u)) * 256u + threadIdx.x;
+  const unsigned idx = (unsigned)place * 256u + threadIdx.x;
   if (idx >= total) return;
   // (divisions by multiply-high with the launcher's constants -- fd_tiles_n: cvecs, fd_wo: tiles_w, fd_howo:
   // tiles_h --: three software divisions per thread sat in front of the first load)
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const ConvArgs a) {
   const int ih0 = p0 * STRIDE - a.ph, iw0 = q0 * STRIDE - a.pw;
 
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(a.x), 0, (int)((unsigned)a.N * a.H * a.W * a.C * 2u), 0x00020000);
+      const_cast<void*>(ptr_x), 0, (int)((unsigned)a.N * a.H * a.W * a.C * 2u), 0x00020000);
   const int pix_bytes = a.C * 2;
   const unsigned base = (unsigned)(((n * a.H + ih0) * a.W + iw0) * pix_bytes + c0 * 2);  // tap (0,0)
 
@@ -141,10 +142,11 @@ __global__ __launch_bounds__(256) void dwconv3x3_f16_kernel(const ConvArgs a) {
 // same kernel without its multiply-adds streams at 5.2 TB/s; the 9 fp32 FMAs per output
 // element that the vector ALUs must issue are what is left of the gap to the HBM rate.
 template <int CBV, int MTH, int NT>
-__global__ __launch_bounds__(NT) void dwconv3x3_s1_lds_kernel(const ConvArgs a) {
-  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
+__global__ __launch_bounds__(NT) void dwconv3x3_s1_lds_kernel(const int workgroups, const ConvArgs a) {
+  int place = xcd_remap((int)blockIdx.x, workgroups);   // (passes through: arithmetic on it stays behind the loads of all arguments)
   // all arguments as one batch of scalar loads with one wait (the compiler would load them where first used)
-  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
+  const void* ptr_x = a.x;
+  asm volatile("" : "+s"(place), "+s"(ptr_x) : "s"(a.w), "s"(a.y), "s"(a.bias), "s"(a.scale), "s"(a.shift), "s"(a.N), "s"(a.H), "s"(a.W),
                "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.sh), "s"(a.ph), "s"(a.pw), "s"(a.flags), "s"(a.fd_tiles_n.mul),
                "s"(a.fd_tiles_n.shift), "s"(a.fd_wo.mul), "s"(a.fd_wo.shift), "s"(a.fd_howo.mul), "s"(a.fd_howo.shift));
   constexpr int MTW = 7;                       // micro-tiles (2 x 4 outputs) across the workgroup tile
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(NT) void dwconv3x3_s1_lds_kernel(const ConvArgs a) 
   const int tiles_w = (a.Wo + TW - 1) / TW, tiles_h = (a.Ho + TH - 1) / TH;
   // (n, tile row, tile column, channel block), channel block fastest; divisions by multiply-high with the
   // launcher's constants (fd_tiles_n: cblocks, fd_wo: tiles_w, fd_howo: tiles_h)
-  const unsigned t0 = (unsigned)xcd_remap(bid, a.N * tiles_h * tiles_w * cblocks);
+  const unsigned t0 = (unsigned)place;
   const unsigned t1 = fast_div(t0, a.fd_tiles_n), t2 = fast_div(t1, a.fd_wo);
   const int cb = (int)(t0 - t1 * (unsigned)cblocks);
   const int tx = (int)(t1 - t2 * (unsigned)tiles_w);
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(NT) void dwconv3x3_s1_lds_kernel(const ConvArgs a) 
   const int iy0 = oy0 - a.ph, ix0 = ox0 - a.pw;  // input coordinates of patch pixel (0, 0)
   const int c0 = cb * 8 * CBV;
 
-  const intx4 rs = make_rsrc(a.x, (unsigned)a.N * a.H * a.W * a.C * 2u);
+  const intx4 rs = make_rsrc(ptr_x, (unsigned)a.N * a.H * a.W * a.C * 2u);
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) uint4*)(&patch[0]);
 #pragma unroll
   for (int j = 0; j < LOADS; ++j) {
@@ -264,7 +266,7 @@ hipError_t launch_dw_lds(const ConvArgs& a, hipStream_t st) {
   b.fd_tiles_n = make_fastdiv((uint32_t)(a.C / (8 * CBV)));
   b.fd_wo = make_fastdiv((uint32_t)((a.Wo + 27) / 28));
   b.fd_howo = make_fastdiv((uint32_t)((a.Ho + 2 * MTH - 1) / (2 * MTH)));
-  hipLaunchKernelGGL((dwconv3x3_s1_lds_kernel<CBV, MTH, NT>), dim3((unsigned)tiles), dim3(NT), 0, st, b);
+  hipLaunchKernelGGL((dwconv3x3_s1_lds_kernel<CBV, MTH, NT>), dim3((unsigned)tiles), dim3(NT), 0, st, (int)tiles, b);
   return hipGetLastError();
 }
 
@@ -276,7 +278,7 @@ hipError_t launch_dw(const ConvArgs& a, hipStream_t st) {
   b.fd_tiles_n = make_fastdiv((uint32_t)(a.C / 8));
   b.fd_wo = make_fastdiv((uint32_t)((a.Wo + TW - 1) / TW));
   b.fd_howo = make_fastdiv((uint32_t)((a.Ho + TH - 1) / TH));
-  hipLaunchKernelGGL((dwconv3x3_f16_kernel<STRIDE, TH, TW>), grid, block, 0, st, b);
+  hipLaunchKernelGGL((dwconv3x3_f16_kernel<STRIDE, TH, TW>), grid, block, 0, st, (int)grid.x, b);
   return hipGetLastError();
 }
 

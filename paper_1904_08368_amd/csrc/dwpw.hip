@@ -60,7 +60,7 @@ constexpr int ksteps_before(int u, int ksteps, int units) { return (u * ksteps +
 // OCC: waves per SIMD the register allocation is held to (the layers that stream from memory need several
 // workgroups per CU to keep enough loads and stores in flight).
 template <int STRIDE, int TH, int TW, int MH, int MW, int WAVES_M, int WAVES_N, int TM, int TN, int KP, int NP, int NFS, int CMAX, int OCC>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void dwpw_fused_kernel(const DwPwArgs a) {
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void dwpw_fused_kernel(const int workgroups, const DwPwArgs a) {
   constexpr int NW = WAVES_M * WAVES_N, NT = 64 * NW;
   constexpr int BM = WAVES_M * TM * 32, BN = WAVES_N * TN * 32, WTM = TM * 32, WTN = TN * 32;
   static_assert(TH * TW <= BM, "the rectangle must fit the rows of the tile");
@@ -106,8 +106,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void dwpw_fused_kernel
   uint4* const filt = lds + O_FILT;
 
   const ConvArgs& pw = a.pw;
-  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
-  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
+  int place = xcd_remap((int)blockIdx.x, workgroups);   // (passes through: arithmetic on it stays behind the loads of all arguments)
+  asm volatile("" : "+s"(place) : "s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
                "s"(a.W), "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.tiles_x), "s"(a.tiles_y), "s"(a.tiles_n), "s"(a.fd_x.mul), "s"(a.fd_x.shift),
                "s"(a.fd_y.mul), "s"(a.fd_y.shift), "s"(a.fd_n.mul), "s"(a.fd_n.shift), "s"(pw.w), "s"(pw.y), "s"(pw.bias), "s"(pw.scale),
                "s"(pw.shift), "s"(pw.K), "s"(pw.Kp), "s"(pw.flags), "s"(pw.param_vec));
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void dwpw_fused_kernel
   // (image, tile row, tile column, channel tile), channel tile fastest: the workgroups that share a patch are neighbours
   // (divisions by multiply-high with host-computed constants: three software divisions would be a fifth of the
   // vector instructions of a single-chunk tile)
-  const unsigned t0 = (unsigned)xcd_remap(bid, a.N * a.tiles_y * a.tiles_x * a.tiles_n);
+  const unsigned t0 = (unsigned)place;
   const unsigned t1 = fast_div(t0, a.fd_n), t2 = fast_div(t1, a.fd_x);
   const int tile_n = (int)(t0 - t1 * (unsigned)a.tiles_n);
   const int tx = (int)(t1 - t2 * (unsigned)a.tiles_x);
@@ -461,7 +461,7 @@ hipError_t launch_one(const DwPwArgs& a, hipStream_t st) {
   b.fd_n = make_fastdiv((uint32_t)b.tiles_n);
   const long wgs = (long)a.N * b.tiles_y * b.tiles_x * b.tiles_n;
   hipLaunchKernelGGL((dwpw_fused_kernel<STRIDE, TH, TW, MH, MW, WAVES_M, WAVES_N, TM, TN, KP, NP, NFS, CMAX, OCC>), dim3((unsigned)wgs),
-                     dim3(64 * WAVES_M * WAVES_N), 0, st, b);
+                     dim3(64 * WAVES_M * WAVES_N), 0, st, (int)wgs, b);
   return hipGetLastError();
 }
 

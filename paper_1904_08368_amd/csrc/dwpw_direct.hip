@@ -52,6 +52,11 @@ struct DirectGeom {
   FastDiv fd_x, fd_y, fd_n, fd_p, fd_tw;   // division by tiles_x, tiles_y, tiles_n, the rectangles of all images, tw
 };
 
+struct DirectArgs {
+  DirectGeom g;
+  DwPwArgs a;
+};
+
 // BM: rows of the tile (16: the matrix instruction's other 16 rows repeat them); WN: waves with 32 output channels each,
 // of NW that share the depthwise work; NS: ring stages of 32 channels; CP: most channels / 32.  OCC: 0, a thread has the
 // inputs of two items in registers, or the waves per SIMD for which it has those of one.  MR: output rows of an item.
@@ -59,7 +64,9 @@ struct DirectGeom {
 // and 64 x 128 tiles, a thread's whole share (128 -> 128 at 56 x 56, batch 32 21.4 -> 20.0 us; 512 -> 512 at 14 x 14 as 64 x 256
 // 13.9 -> 13.2, as 32 x 256 9.5 -> 8.9 at batch 16 of 13 x 12).  Where fewer items than threads are left the two rows win.
 template <int STRIDE, int BM, int WN, int NW, int NS, int CP, int OCC, int MR>
-__global__ __launch_bounds__(64 * NW, OCC ? OCC : 1) void dwpw_fused_direct_kernel(const DwPwArgs a, const DirectGeom g) {
+__global__ __launch_bounds__(64 * NW, OCC ? OCC : 1) void dwpw_fused_direct_kernel(const int workgroups, const DirectArgs block) {
+  const DirectGeom& g = block.g;
+  const DwPwArgs& a = block.a;
   constexpr int NT = 64 * NW, BN = 32 * WN;
   constexpr int TM = BM >= 32 ? BM / 32 : 1;
   constexpr int APL = BM * BKV + BKV;       // slots of a 32-channel plane of the tile (padded: the planes start on other banks)
@@ -75,15 +82,15 @@ __global__ __launch_bounds__(64 * NW, OCC ? OCC : 1) void dwpw_fused_direct_kern
   __shared__ uint4 ring[WN * NS * FPL];
 
   const ConvArgs& pw = a.pw;
-  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
-  asm volatile("" : "+s"(bid) : "s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
+  int place = xcd_remap((int)blockIdx.x, workgroups);   // (passes through: arithmetic on it stays behind the loads of all arguments)
+  asm volatile("" : "+s"(place) : "s"(a.x), "s"(a.dw_w), "s"(a.dw_bias), "s"(a.dw_scale), "s"(a.dw_shift), "s"(a.dw_flags), "s"(a.N), "s"(a.H),
                "s"(a.W), "s"(a.C), "s"(a.Ho), "s"(a.Wo), "s"(a.stride), "s"(g.th), "s"(g.tw), "s"(g.tiles_x), "s"(g.tiles_y), "s"(g.tiles_n), "s"(g.n_major),
                "s"(g.log_cv), "s"(g.nit), "s"(g.fd_x.mul), "s"(g.fd_x.shift), "s"(g.fd_y.mul), "s"(g.fd_y.shift), "s"(g.fd_n.mul),
                "s"(g.fd_n.shift), "s"(g.fd_p.mul), "s"(g.fd_p.shift), "s"(g.fd_tw.mul), "s"(g.fd_tw.shift), "s"(pw.w), "s"(pw.y), "s"(pw.bias),
                "s"(pw.scale), "s"(pw.shift), "s"(pw.K), "s"(pw.Kp), "s"(pw.flags), "s"(pw.param_vec));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const unsigned t0 = (unsigned)xcd_remap(bid, a.N * g.tiles_y * g.tiles_x * g.tiles_n);
+  const unsigned t0 = (unsigned)place;
   const unsigned tq = fast_div(t0, g.n_major ? g.fd_p : g.fd_n);
   const unsigned rects = (unsigned)(g.tiles_x * g.tiles_y * a.N);
   const int tile_n = (int)(g.n_major ? tq : t0 - tq * (unsigned)g.tiles_n);
@@ -362,9 +369,9 @@ DirectGeom make_geom(const DwPwArgs& a, const DirectTile& t) {
 
 template <int STRIDE, int BM, int WN, int NW, int NS, int CP, int OCC, int MR>
 hipError_t launch_direct_one(const DwPwArgs& a, hipStream_t st) {
-  const DirectGeom g = make_geom(a, DirectTile{BM, WN, NW, NS, CP, OCC, MR});
-  const long wgs = (long)a.N * g.tiles_y * g.tiles_x * g.tiles_n;
-  hipLaunchKernelGGL((dwpw_fused_direct_kernel<STRIDE, BM, WN, NW, NS, CP, OCC, MR>), dim3((unsigned)wgs), dim3(64 * NW), 0, st, a, g);
+  const DirectArgs block{make_geom(a, DirectTile{BM, WN, NW, NS, CP, OCC, MR}), a};
+  const long wgs = (long)a.N * block.g.tiles_y * block.g.tiles_x * block.g.tiles_n;
+  hipLaunchKernelGGL((dwpw_fused_direct_kernel<STRIDE, BM, WN, NW, NS, CP, OCC, MR>), dim3((unsigned)wgs), dim3(64 * NW), 0, st, (int)wgs, block);
   return hipGetLastError();
 }
 

@@ -24,14 +24,14 @@ constexpr int kThreads = 512, kWaves = kThreads / 64;
 
 // A wave makes one output.  KI: reduction vectors of a lane, C <= 512 KI.  DEPTH: positions a thread has in flight.
 template <int KI, int DEPTH>
-__global__ __launch_bounds__(kThreads) void avgpool_dense_kernel(const HeadArgs a) {
-  int bid = (int)blockIdx.x;   // (passes through: arithmetic on it stays behind the loads of all arguments)
-  asm volatile("" : "+s"(bid) : "s"(a.N), "s"(a.C), "s"(a.HW), "s"(a.units), "s"(a.act), "s"(a.cvt_log2), "s"(a.x), "s"(a.w), "s"(a.bias),
-               "s"(a.pooled), "s"(a.y));
+__global__ __launch_bounds__(kThreads) void avgpool_dense_kernel(const int N, const int C, const int HW, const int units, const int cvt_log2_act,
+                                                                  const half8* x, const half8* w_units, _Float16* y, const float* bias,
+                                                                  _Float16* pooled) {
+  const HeadArgs a{N, C, HW, units, cvt_log2_act >> 8, cvt_log2_act & 255, x, w_units, bias, pooled, y};
   __shared__ float part[kThreads * 8];
   __shared__ half8 pl[KI * 64];
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n = bid % a.N, ug = bid / a.N;
+  const int n = (int)blockIdx.x % a.N, ug = (int)blockIdx.x / a.N;
   const int CV = a.C >> 3, CVT = 1 << a.cvt_log2, parts = kThreads >> a.cvt_log2;
   const int j = ug * kWaves + wave;
   half8 w[KI];
@@ -87,8 +87,12 @@ __global__ __launch_bounds__(kThreads) void avgpool_dense_kernel(const HeadArgs 
 template <int KI>
 hipError_t launch_head(const HeadArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)(a.N * ((a.units + kWaves - 1) / kWaves))), block(kThreads);
-  if (a.HW <= 8 * (kThreads >> a.cvt_log2)) hipLaunchKernelGGL((avgpool_dense_kernel<KI, 8>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((avgpool_dense_kernel<KI, 16>), grid, block, 0, st, a);   // (two rounds of 8 behind each other otherwise)
+  // (apart, and in this order, because fourteen words of leading scalars are in registers when a wave starts: all but `pooled`)
+  const int mode = a.act << 8 | a.cvt_log2;
+  if (a.HW <= 8 * (kThreads >> a.cvt_log2))
+    hipLaunchKernelGGL((avgpool_dense_kernel<KI, 8>), grid, block, 0, st, a.N, a.C, a.HW, a.units, mode, a.x, a.w, a.y, a.bias, a.pooled);
+  else
+    hipLaunchKernelGGL((avgpool_dense_kernel<KI, 16>), grid, block, 0, st, a.N, a.C, a.HW, a.units, mode, a.x, a.w, a.y, a.bias, a.pooled);   // (two rounds of 8 behind each other otherwise)
   return hipGetLastError();
 }
 

@@ -27,34 +27,36 @@ struct ConvArgs {
   const float* scale;
   const float* shift;
   const int32_t* qbias;
-  int N, H, W, C, K, R, S, sh, sw, ph, pw, Ho, Wo;
+  // (In the order of use: what every kernel's prologue reads stands first, so that it reads few lines of 64 bytes.  A batch of scalar
+  // loads over one to four lines that the host has just written is back after 480 to 600 clocks, over eight after 1100.)
+  int N, H, W, C, K;
+  int Kp;                 // row pitch of the packed filters, elements
+  unsigned flags;
+  int param_vec;          // per-channel constants are 16-byte aligned and K % 8 == 0: vector loads
+  int n_major;            // tile order: consecutive workgroups share an output-channel tile (else a pixel tile)
   // element strides of x along image, row and pixel (NHWC: H*W*C, W*C, C).  The row-packed
   // stem path views a [.., Wp, 4] tensor as 32- or 64-"channel" pixels that overlap: then
   // xs_w = 4 while C is the chunk length.
   int xs_n, xs_h, xs_w;
-  // host-computed constants of the implicit-GEMM prologue
-  float rcp_wo, rcp_ho;   // 1/Wo, 1/Ho
-  unsigned tap_spread;    // bit r*S set for every filter row r (R*S <= 32)
-  int param_vec;          // per-channel constants are 16-byte aligned and K % 8 == 0: vector loads
-  int n_major;            // tile order: consecutive workgroups share an output-channel tile (else a pixel tile)
+  int R, S, sh, sw, ph, pw, Ho, Wo;
   FastDiv fd_wo, fd_howo;           // division by Wo and by Ho*Wo (tile decoding in the prologue)
   FastDiv fd_tiles_m, fd_tiles_n;   // ... by the tile counts of the launched kernel variant (set by its launcher)
+  // host-computed constants of the implicit-GEMM prologue
+  unsigned tap_spread;    // bit r*S set for every filter row r (R*S <= 32)
   int M;        // N*Ho*Wo  (rows of the implicit GEMM)
   int Kred;     // R*S*C    (reduction length)
-  int Kp;       // row pitch of the packed filters, elements
+  float rcp_wo, rcp_ho;   // 1/Wo, 1/Ho
   int lshift, rshift;
-  int round_mode;          // ROUND_* rule of the requantization acc / 2^rshift
   int round_add;           // what the deterministic rules add before the shift (0 when rshift == 0)
   int qmode;               // QMODE_* of the quantized epilogue
   int clip_lo, clip_hi;    // bounds of the code type: -127 .. 127 (signed), 0 .. 255 (unsigned)
-  // Pooled tiles (see pool below): channels that one filter tap takes before the next one, block after block, which is the order in which
-  // the kernel of the conv alone adds up its sums (the 3x3 kernel's chunk, else C), so that both give the same bits.  (Here, where the
-  // alignment of the pointers leaves room: a longer argument block costs MobileNet at batch 1 2.5 %.)
-  int pool_block;
+  int round_mode;          // ROUND_* rule of the requantization acc / 2^rshift
   const int32_t* qmult;    // QMODE_SCALED: per-channel multiplier [K] and shift [K]
   const int32_t* qshift;
   unsigned seed_lo, seed_hi;  // key of the stochastic rounding draws
-  unsigned flags;
+  // Pooled tiles (see pool below): channels that one filter tap takes before the next one, block after block, which is the order in which
+  // the kernel of the conv alone adds up its sums (the 3x3 kernel's chunk, else C), so that both give the same bits.
+  int pool_block;
   // Output channel segments (parallel convolution combination and concatenation views, paper
   // Section 4.4): channel ch in [seg_end[i-1], seg_end[i]) of output pixel m is stored at
   // seg_y[i] + m*seg_ld[i] + (ch - seg_end[i-1]) elements; boundaries are multiples of 8.
@@ -164,12 +166,14 @@ struct StemArgs {
   ConvArgs a;
   void* y_pooled;
   int Hp, Wp;                         // extents of the pooled outputs
-  int runs;                           // in how many runs the conv over the padded copy sums (fp16; int8 sums are exact): never fewer here
   int per_run;                        // filter rows of a run (tiles for few outputs)
-  int tiles, tiles_img, tiles_row;
-  int pitch, patch_bytes, cst_at;     // pixels of a patch row, bytes of the patch, where the constants stand in LDS
-  int pairs, per_row, items;          // loads of the patch: pixel pairs or pixels, per row, in all
+  int tiles_img, tiles_row;
+  int pitch, cst_at;                  // pixels of a patch row, where the constants stand in LDS
+  int per_row, items;                 // loads of the patch: per row, in all
   FastDiv fd_img, fd_row, fd_items;
+  // (what the host alone uses)
+  int runs;                           // in how many runs the conv over the padded copy sums (fp16; int8 sums are exact): never fewer here
+  int tiles, patch_bytes, pairs;      // tiles of all images, bytes of the patch, its loads are pixel pairs (else pixels)
 };
 bool conv_stem_supported(const StemArgs& g, bool is_i8, bool pool);
 bool conv_stem_pays(const StemArgs& g, bool is_i8, bool pool);
