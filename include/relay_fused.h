@@ -362,6 +362,21 @@ relay_status relay_conv2d_pool2x2_pays(const relay_conv2d_desc* d, int32_t* pays
 relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* x, const void* w_packed, const float* bias,
                                         const float* bn_scale, const float* bn_shift, void* y, void* y_pooled, void* hip_stream);
 
+/* The two convs of a residual block as ONE launch (paper Section 5.2: what each saved launch is worth; the fused functions of Section 4.1):
+ * first reads x and writes t, second reads t and, with HAS_RESIDUAL, adds x, and writes y.  Each is a call of relay_fused_conv2d_bias_bn_relu
+ * (F16) or relay_qconv2d_requant (I8) without a workspace and is checked as by that call; t is written whole.  Where no kernel takes the two together
+ * (relay_conv2d_block_pays writes 0, or a tile or split is forced) they run as two launches.  Results: bit for bit those of the
+ * separate calls.  relay_conv2d_block_pays writes 1 where one launch takes them and is the faster way.
+ * Errors: as the calls above, plus RELAY_ERR_UNSUPPORTED where one conv's output is the other's operand otherwise than said; nothing is
+ * launched on an error. */
+relay_status relay_conv2d_block_pays(const relay_conv2d_desc* first, const relay_conv2d_desc* second, int32_t* pays);
+relay_status relay_fused_conv2d_block(const relay_conv2d_desc* first, const void* x, const void* w1, const float* bias1, const float* scale1,
+                                      const float* shift1, void* t, const relay_conv2d_desc* second, const void* w2, const float* bias2,
+                                      const float* scale2, const float* shift2, void* y, void* hip_stream);
+relay_status relay_qconv2d_block(const relay_conv2d_desc* first, const int8_t* x, const int8_t* w1, const int32_t* bias1, int32_t out_rshift1,
+                                 int8_t* t, const relay_conv2d_desc* second, const int8_t* w2, const int32_t* bias2, int32_t residual_lshift,
+                                 int32_t out_rshift2, int8_t* y, void* hip_stream);
+
 /* relay_global_avgpool and relay_fused_dense_bias_act on its result as one launch (one fused function of paper Section 4.1), both
  * results written: pooled [n, c] as by the first (up to the grouping of its fp32 sums), y [n, units] from those fp16 values.  F16;
  * x [n, hw, c], w [units, c]; c % 8 == 0, c <= 2048, n * ceil(units / 8) < 2^23; x, w and pooled 16-byte aligned.  relay_avgpool_dense_pays writes 1 where

@@ -88,6 +88,9 @@ SIGNATURES = {
     "relay_fold_scale_axis": [_I, _I, _I, _I, _I, _P, _P, _P, _P],
     "relay_fold_bias": [_I, _P, _P, _P, _P, _P],
     "relay_conv2d_maxpool_fusable": [_DP, C.POINTER(_I)],
+    "relay_conv2d_block_pays": [_P, _P, C.POINTER(_I)],
+    "relay_fused_conv2d_block": [_P] * 14,
+    "relay_qconv2d_block": [_P, _P, _P, _P, _I, _P, _P, _P, _P, _I, _I, _P, _P],
     "relay_avgpool_dense_pays": [_I, _I, _I, _I, _I, C.POINTER(_I)],
     "relay_fused_avgpool_dense": [_I, _I, _I, _I, _I, _P, _P, _P, _I, _P, _P, _P],
     "relay_conv2d_pool2x2_pays": [_DP, C.POINTER(_I)],
@@ -243,6 +246,22 @@ def relay_fused_conv2d_bn_relu_maxpool(d: ConvDesc, x, w_packed, bias, bn_scale,
 def relay_qconv2d_requant_maxpool(d: ConvDesc, x, w_packed, bias, out_rshift: int, y_pooled) -> None:
     _check(lib().relay_qconv2d_requant_maxpool(C.byref(d), _ptr(x), _ptr(w_packed), _ptr(bias), out_rshift,
                                                _ptr(y_pooled), _stream()))
+
+
+def relay_conv2d_block_pays(first: ConvDesc, second: ConvDesc) -> bool:
+    ok = C.c_int32(0)
+    _check(lib().relay_conv2d_block_pays(C.byref(first), C.byref(second), C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_fused_conv2d_block(first: ConvDesc, x, w1, bias1, scale1, shift1, t, second: ConvDesc, w2, bias2, scale2, shift2, y) -> None:
+    _check(lib().relay_fused_conv2d_block(C.byref(first), _ptr(x), _ptr(w1), _ptr(bias1), _ptr(scale1), _ptr(shift1), _ptr(t), C.byref(second),
+                                          _ptr(w2), _ptr(bias2), _ptr(scale2), _ptr(shift2), _ptr(y), _stream()))
+
+
+def relay_qconv2d_block(first: ConvDesc, x, w1, bias1, rshift1: int, t, second: ConvDesc, w2, bias2, lshift: int, rshift2: int, y) -> None:
+    _check(lib().relay_qconv2d_block(C.byref(first), _ptr(x), _ptr(w1), _ptr(bias1), rshift1, _ptr(t), C.byref(second), _ptr(w2), _ptr(bias2),
+                                     lshift, rshift2, _ptr(y), _stream()))
 
 
 def relay_avgpool_dense_pays(dtype: int, n: int, c: int, hw: int, units: int) -> bool:

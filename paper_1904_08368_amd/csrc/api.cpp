@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <initializer_list>
 
 #include "../../include/relay_fused.h"
 #include "../../include/relay_fusion.h"
@@ -949,6 +950,92 @@ relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2
   if (p.dma >= 0) return device_status(relay::launch_conv_igemm_dma_pair(m[0], m[1], i8, p.dma, s), "paired conv2d launch");
   const relay_status st = device_status(launch_igemm(m[0], i8, s), "conv2d launch");
   return st != RELAY_OK ? st : device_status(launch_igemm(m[1], i8, s), "conv2d launch");
+}
+
+// ---- the two 3x3 convs of a residual block in one launch -----------------------------------------
+
+// fp16: one round of workgroups (one to a CU), and only where both convs by themselves sum three taps in a run, as the shared launch does.  int8: to where
+// two launches catch up, at a round and a third.  us, two launches / one, graph-timed: fp16 one image of 56 x 56 6.98 / 6.52, two 8.23 / 6.75,
+// eight of 28 x 28 8.22 / 6.79, one of 14 x 14 6.23 / 6.33 (a launch of the host's less all the same); int8 one image of 56 x 56 7.09 / 5.15, two
+// 7.80 / 5.34, five 9.58 / 7.08, seven 11.1 / 10.1, eight 11.3 / 11.7, 16 14.5 / 19.7.
+static bool block_plan(const relay::ConvArgs& a, const relay::ConvArgs& b, bool i8) {
+  if (g_force_tile != -1 || g_force_split != 0 || !relay::conv_block_supported(a, b, i8)) return false;
+  if (relay::conv_block_workgroups(a) > (i8 ? 700 : 256)) return false;
+  if (i8) return true;
+  for (const relay::ConvArgs* c : {&a, &b}) {
+    const int v = small_choice(*c, false);
+    if (v < 0 || !relay::conv_small_sums_by_taps(*c, v)) return false;
+  }
+  return true;
+}
+
+relay_status relay_conv2d_block_pays(const relay_conv2d_desc* first, const relay_conv2d_desc* second, int32_t* pays) {
+  if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
+  const relay_conv2d_desc* ds[2] = {first, second};
+  relay::ConvArgs m[2];
+  bool mfma = true;
+  for (int i = 0; i < 2; ++i) {
+    int ho, wo;
+    const relay_status st = check_geometry(ds[i], &ho, &wo);
+    if (st != RELAY_OK) return st;
+    mfma = mfma && (ds[i]->dtype == RELAY_F16 || ds[i]->dtype == RELAY_I8) && check_igemm_support(ds[i]) == RELAY_OK;
+    m[i] = make_args(ds[i], ho, wo);
+    finish_args(m[i]);
+  }
+  if (first->dtype != second->dtype) return fail(RELAY_ERR_DTYPE, "the two convs have different dtypes");
+  *pays = mfma && block_plan(m[0], m[1], first->dtype == RELAY_I8) ? 1 : 0;
+  return RELAY_OK;
+}
+
+// both members collected: their own checks have passed
+static relay_status launch_block(const relay::ConvArgs (&m)[2], bool i8, hipStream_t s) {
+  if (block_plan(m[0], m[1], i8)) return device_status(relay::launch_conv_block(m[0], m[1], i8, s), "residual block launch");
+  const relay_status st = device_status(launch_igemm(m[0], i8, s), "conv2d launch");
+  return st != RELAY_OK ? st : device_status(launch_igemm(m[1], i8, s), "conv2d launch");
+}
+
+// The second conv may not write what the first reads, nor the first what the second reads beside its result.
+static relay_status check_block_aliases(const void* x, const void* t, const void* y, std::initializer_list<const void*> first,
+                                        std::initializer_list<const void*> second) {
+  if (y && (y == x || y == t)) return fail(RELAY_ERR_UNSUPPORTED, "output must not alias an input");
+  for (const void* p : first)
+    if (p && p == y) return fail(RELAY_ERR_UNSUPPORTED, "the second conv's output is an operand of the first");
+  for (const void* p : second)
+    if (p && p == t) return fail(RELAY_ERR_UNSUPPORTED, "the first conv's output is an operand of the second");
+  return RELAY_OK;
+}
+
+relay_status relay_fused_conv2d_block(const relay_conv2d_desc* first, const void* x, const void* w1, const float* bias1, const float* scale1,
+                                      const float* shift1, void* t, const relay_conv2d_desc* second, const void* w2, const float* bias2,
+                                      const float* scale2, const float* shift2, void* y, void* hip_stream) {
+  if (!first || !second) return fail(RELAY_ERR_NULL, "descriptor is NULL");
+  if (first->dtype != RELAY_F16 || second->dtype != RELAY_F16) return fail(RELAY_ERR_DTYPE, "the float block takes F16");
+  relay::ConvArgs m[2];
+  g_collect = &m[0];
+  relay_status st = relay_fused_conv2d_bias_bn_relu(first, x, w1, bias1, scale1, shift1, nullptr, t, nullptr, 0, hip_stream);
+  g_collect = &m[1];
+  if (st == RELAY_OK)
+    st = relay_fused_conv2d_bias_bn_relu(second, t, w2, bias2, scale2, shift2, (second->flags & RELAY_HAS_RESIDUAL) ? x : nullptr, y, nullptr, 0, hip_stream);
+  g_collect = nullptr;
+  if (st == RELAY_OK) st = check_block_aliases(x, t, y, {w1, bias1, scale1, shift1}, {w2, bias2, scale2, shift2});
+  return st != RELAY_OK ? st : launch_block(m, false, static_cast<hipStream_t>(hip_stream));
+}
+
+relay_status relay_qconv2d_block(const relay_conv2d_desc* first, const int8_t* x, const int8_t* w1, const int32_t* bias1, int32_t out_rshift1,
+                                 int8_t* t, const relay_conv2d_desc* second, const int8_t* w2, const int32_t* bias2, int32_t residual_lshift,
+                                 int32_t out_rshift2, int8_t* y, void* hip_stream) {
+  if (!first || !second) return fail(RELAY_ERR_NULL, "descriptor is NULL");
+  if (first->dtype != RELAY_I8 || second->dtype != RELAY_I8) return fail(RELAY_ERR_DTYPE, "the quantized block takes I8");
+  relay::ConvArgs m[2];
+  g_collect = &m[0];
+  relay_status st = relay_qconv2d_requant(first, x, w1, bias1, nullptr, 0, out_rshift1, t, nullptr, 0, hip_stream);
+  g_collect = &m[1];
+  if (st == RELAY_OK)
+    st = relay_qconv2d_requant(second, t, w2, bias2, (second->flags & RELAY_HAS_RESIDUAL) ? x : nullptr, residual_lshift, out_rshift2, y, nullptr, 0,
+                               hip_stream);
+  g_collect = nullptr;
+  if (st == RELAY_OK) st = check_block_aliases(x, t, y, {w1, bias1}, {w2, bias2});
+  return st != RELAY_OK ? st : launch_block(m, true, static_cast<hipStream_t>(hip_stream));
 }
 
 // ---- conv2d + 3x3 / stride 2 / pad 1 max pool in one launch -------------------------------------

@@ -556,6 +556,10 @@ float conv_small_estimate(const ConvArgs& a, bool is_i8) {
   return small_considered(a, is_i8) && small_best(a, is_i8, false, &us) >= 0 ? us : INFINITY;
 }
 
+bool conv_small_sums_by_taps(const ConvArgs& a, int v) {
+  return a.R * a.S == 9 && a.C == 64 && kSmall[v].w == 4 && small_unit(a, false, v) == 2 && small_runs(a, false, v, false) == 1;
+}
+
 int conv_small_sums(const ConvArgs& a, int v) { return kSmall[v].w * small_runs(a, false, v, false); }
 
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int v, char* buf, size_t len) {

@@ -159,6 +159,11 @@ hipError_t launch_conv_small(const ConvArgs& a, bool is_i8, int variant, hipStre
 bool conv_small_pair_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, int own_of_b);
 hipError_t launch_conv_small_pair(const ConvArgs& a, const ConvArgs& b, bool is_i8, int variant, hipStream_t st);
 int conv_small_sums(const ConvArgs& a, int variant);   // in how many runs it sums an fp16 conv
+bool conv_small_sums_by_taps(const ConvArgs& a, int variant);   // ... whether those are three taps each, in order (64 channels, 3x3)
+// The two 3x3 convs of a residual block of 64 channels in one launch (conv_block.hip): b reads a's outputs, its residual is a's input.
+bool conv_block_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8);
+long conv_block_workgroups(const ConvArgs& a);
+hipError_t launch_conv_block(const ConvArgs& a, const ConvArgs& b, bool is_i8, hipStream_t st);
 void conv_small_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
 // A first-layer conv on the NCHW image (conv_stem.hip): `a` describes the conv over the image itself (x: the image, H and W its
 // extents, C its channels, Kp the packed filters' pitch; y: the conv outputs or NULL); the rest is set by the launcher.

@@ -307,8 +307,8 @@ class FusedNet:
     merged: Dict[int, tuple] = {}
 
     def _merged_calls(self):
-        """{i: (calls, function, arguments)} of a conv and the 2x2 max pool on its outputs, and of the average pool and the dense
-        layer on its result, where the library takes them together and that pays."""
+        """{i: (calls, function, arguments)} of a conv and the 2x2 max pool on its outputs, of the two convs of a residual block, and of the
+        average pool and the dense layer on its result, where the library takes them together and that pays."""
         merged = {}
         for i in range(len(self.calls) - 1):
             (f0, a0), (f1, a1) = self.calls[i], self.calls[i + 1]
@@ -316,6 +316,12 @@ class FusedNet:
             if f0 is B.relay_fused_conv2d_bias_bn_relu and len(a0) == 9 and a0[6] is None and a0[8] is None and \
                     f1 is B.relay_maxpool2d and a1[5:8] == (2, 2, 0) and a1[8] is a0[7] and B.relay_conv2d_pool2x2_pays(a0[0]):
                 merged[i] = (self.calls[i:i + 2], B.relay_fused_conv2d_pool2x2, tuple(a0[:6]) + (a0[7], a1[9]))
+            elif i - 1 not in merged and f0 is f1 is B.relay_fused_conv2d_bias_bn_relu and a1[1] is a0[7] and a0[6] is None and \
+                    (a1[6] is None or a1[6] is a0[1]) and B.relay_conv2d_block_pays(a0[0], a1[0]):
+                merged[i] = (self.calls[i:i + 2], B.relay_fused_conv2d_block, (*a0[:6], a0[7], a1[0], *a1[2:6], a1[7]))
+            elif i - 1 not in merged and f0 is f1 is B.relay_qconv2d_requant and a1[1] is a0[7] and a0[4] is None and \
+                    (a1[4] is None or a1[4] is a0[1]) and B.relay_conv2d_block_pays(a0[0], a1[0]):
+                merged[i] = (self.calls[i:i + 2], B.relay_qconv2d_block, (*a0[:4], a0[6], a0[7], a1[0], a1[2], a1[3], a1[5], a1[6], a1[7]))
             elif f0 is B.relay_global_avgpool and f1 is B.relay_fused_dense_bias_act and a1[4] is a0[5] and a1[2] == a0[2] and \
                     a1[3] == a0[0] and B.relay_avgpool_dense_pays(*a0[:4], a1[1]):
                 merged[i] = (self.calls[i:i + 2], B.relay_fused_avgpool_dense, (*a0[:4], a1[1], a0[4], *a1[5:8], a0[5], a1[8]))
