@@ -229,7 +229,7 @@ def _dominant(rows, peak):
                   "layers": dom["layers"]}
 
 
-KERNEL_SOURCES = ("conv_igemm_dma.hip", "conv_halo.hip", "dma_common.hpp", "igemm_common.hpp", "lds_dma.hpp", "rounding.hpp",
+KERNEL_SOURCES = ("conv_igemm_dma.hip", "igemm_dma_tile.hpp", "conv_halo.hip", "conv_halo_tile.hpp", "dma_common.hpp", "igemm_common.hpp", "lds_dma.hpp", "rounding.hpp",
                   "kernels.hpp", "fastdiv.hpp")
 
 

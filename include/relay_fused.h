@@ -555,6 +555,28 @@ relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2
  * host-only, nothing is launched.  Errors: as relay_workspace_bytes, _DTYPE (two dtypes). */
 relay_status relay_conv2d_pair_fusable(const relay_conv2d_desc* first, const relay_conv2d_desc* second, int32_t* fusable);
 
+/* Two or three convs of different inputs, each into channel segments and none reading what another writes, as ONE launch (paper Section 4.4, for
+ * the members of an Inception block that share no input; Section 5.2).  Each member is a call of relay_fused_conv2d_combined and is checked as by
+ * that call.  Where no kernel takes them together (relay_conv2d_combined_group_pays writes 0; host-only, also 0 while a tile or split is forced)
+ * they run one after another.  Results: bit for bit those of the separate calls.
+ * Errors: as relay_fused_conv2d_combined, plus _SHAPE (n outside 2..3) and _UNSUPPORTED (one conv's output is another's output or operand);
+ * nothing is launched on an error. */
+typedef struct {
+  const relay_conv2d_desc* d;
+  const void* x;
+  int32_t x_ld;
+  const void* w_packed;
+  const float* bias;
+  const float* bn_scale;
+  const float* bn_shift;
+  int32_t nseg;
+  const int32_t* seg_channels;
+  void* const* seg_y;
+  const int32_t* seg_ld;
+} relay_conv2d_views_call;
+relay_status relay_conv2d_combined_group_pays(const relay_conv2d_views_call* calls, int32_t n, int32_t* pays);
+relay_status relay_fused_conv2d_combined_group(const relay_conv2d_views_call* calls, int32_t n, void* hip_stream);
+
 /* For callers that cannot allocate device memory (code under HIP-graph capture, serving loops and
  * harnesses that forbid hipMalloc): relay_fused_conv2d_bias_bn_relu for F16 NHWC / NHWC4_PADDED
  * descriptors with the reduction-split scratch (see relay_workspace_bytes) taken from a static

@@ -88,6 +88,8 @@ SIGNATURES = {
     "relay_fold_scale_axis": [_I, _I, _I, _I, _I, _P, _P, _P, _P],
     "relay_fold_bias": [_I, _P, _P, _P, _P, _P],
     "relay_conv2d_maxpool_fusable": [_DP, C.POINTER(_I)],
+    "relay_conv2d_combined_group_pays": [_P, _I, C.POINTER(_I)],
+    "relay_fused_conv2d_combined_group": [_P, _I, _P],
     "relay_conv2d_block_pays": [_P, _P, C.POINTER(_I)],
     "relay_fused_conv2d_block": [_P] * 14,
     "relay_qconv2d_block": [_P, _P, _P, _P, _I, _P, _P, _P, _P, _I, _I, _P, _P],
@@ -476,6 +478,39 @@ def relay_fused_conv2d_combined(d: ConvDesc, x, x_ld: int, w_packed, bias, bn_sc
     _check(lib().relay_fused_conv2d_combined(C.byref(d), _ptr(x), x_ld, _ptr(w_packed), _ptr(bias), _ptr(bn_scale),
                                              _ptr(bn_shift), n, C.cast(ch, _P), C.cast(ys, _P), C.cast(ld, _P),
                                              _stream()))
+
+
+class ViewsCall(C.Structure):
+    _fields_ = [("d", _P), ("x", _P), ("x_ld", C.c_int32), ("w_packed", _P), ("bias", _P), ("bn_scale", _P), ("bn_shift", _P),
+                ("nseg", C.c_int32), ("seg_channels", _P), ("seg_y", _P), ("seg_ld", _P)]
+
+
+def _views_calls(members):
+    """(the C array, what it points to) of argument tuples of relay_fused_conv2d_combined."""
+    keep = []
+    out = (ViewsCall * max(len(members), 1))()
+    for call, (d, x, x_ld, w_packed, bias, scale, shift, channels, ys, lds) in zip(out, members):
+        n = len(ys)
+        ch, ld = (C.c_int32 * max(n, 1))(*channels), (C.c_int32 * max(n, 1))(*lds)
+        y = (C.c_void_p * max(n, 1))(*[_ptr(t) for t in ys])
+        keep += [d, ch, ld, y]
+        call.d, call.x, call.x_ld, call.w_packed = C.addressof(d), _ptr(x), x_ld, _ptr(w_packed)
+        call.bias, call.bn_scale, call.bn_shift, call.nseg = _ptr(bias), _ptr(scale), _ptr(shift), n
+        call.seg_channels, call.seg_y, call.seg_ld = C.addressof(ch), C.addressof(y), C.addressof(ld)
+    return out, keep
+
+
+def relay_conv2d_combined_group_pays(*members) -> bool:
+    calls, keep = _views_calls(members)
+    ok = C.c_int32(0)
+    _check(lib().relay_conv2d_combined_group_pays(C.addressof(calls), len(members), C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_fused_conv2d_combined_group(*members) -> None:
+    """members: argument tuples of relay_fused_conv2d_combined."""
+    calls, keep = _views_calls(members)
+    _check(lib().relay_fused_conv2d_combined_group(C.addressof(calls), len(members), _stream()))
 
 
 WINDOW_FULL, WINDOW_CENTRE = 0, 1

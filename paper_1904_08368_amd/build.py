@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librelayfused.so")
-SOURCES = ["api.cpp", "fusion.cpp", "launch_list.cpp", "conv_block.hip", "conv_igemm.hip", "conv_igemm_dma.hip", "conv_halo.hip", "conv_small.hip", "conv_stream.hip", "conv_direct_f32.hip", "conv_first.hip", "conv_stem.hip", "head.hip", "dwconv.hip", "dwpw.hip", "dwpw_direct.hip", "dense.hip", "glue.hip", "quant.hip", "realize.hip", "probe.hip", "qschemes.hip"]
+SOURCES = ["api.cpp", "fusion.cpp", "launch_list.cpp", "conv_block.hip", "conv_group.hip", "conv_igemm.hip", "conv_igemm_dma.hip", "conv_halo.hip", "conv_small.hip", "conv_stream.hip", "conv_direct_f32.hip", "conv_first.hip", "conv_stem.hip", "head.hip", "dwconv.hip", "dwpw.hip", "dwpw_direct.hip", "dense.hip", "glue.hip", "quant.hip", "realize.hip", "probe.hip", "qschemes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # a kernel's leading scalar parameters are in registers when a wave starts (see xcd_remap)

@@ -952,6 +952,87 @@ relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2
   return st != RELAY_OK ? st : device_status(launch_igemm(m[1], i8, s), "conv2d launch");
 }
 
+// ---- convs of different inputs into channel segments in one launch --------------------------------------
+
+// The member of each kind that the shared launch has room for, or none where it does not take them: then each runs by itself.  It takes convs that
+// by themselves run on tiles of 128 x 64 or less of the kernels whose tiles it has, so that the sums are in the same order and no wider tile's rate is
+// given up.  us, separate / together, graph-timed, {128 -> 192 3x3, 32 -> 96 5x5, 256 -> 64 1x1}: 32 images of 28 x 28 37.9 / 29.8, 16 25.5 / 16.7, 12 21.2 /
+// 12.4, 20 of 33 x 29 30.1 / 21.8; the first two of 4 x 64 x 64 25.6 / 21.6; the last two of 32 x 40 x 40 31.7 / 25.7, but of 32 x 64 x 64, where
+// the 5x5 one has 256 x 128 tiles by itself, 49.9 / 58.5.
+struct GroupPlan {
+  const relay::ConvArgs* c3 = nullptr;
+  const relay::ConvArgs* c[2] = {nullptr, nullptr};
+  bool together = false;
+};
+static GroupPlan group_plan(const relay::ConvArgs* m, int n) {
+  GroupPlan p;
+  if (g_force_tile != -1 || g_force_split != 0) return p;
+  for (int i = 0; i < n; ++i) {
+    const relay::ConvArgs& a = m[i];
+    if (a.seg_centre || small_choice(a, false) >= 0 || stream_choice(a, false) >= 0) return p;
+    const int v = halo_choice(a, false);
+    if (v >= 0) {
+      if (p.c3 || v > 1 || relay::conv_halo_chunk(a, false, v) != 64 || !relay::conv_group_takes_3x3(a)) return p;
+      p.c3 = &a;
+    } else {
+      const int kind = a.C % 64 == 0 ? 1 : 0;
+      if (p.c[kind] || relay::igemm_dma_wide(a)) return p;
+      p.c[kind] = &a;
+    }
+  }
+  p.together = true;
+  return p;
+}
+
+// The members' arguments, each checked as by its own call, and that none reads or overwrites what another writes.
+static relay_status group_args(const relay_conv2d_views_call* calls, int32_t n, relay::ConvArgs* m) {
+  if (!calls) return fail(RELAY_ERR_NULL, "calls is NULL");
+  if (n < 2 || n > 3) return fail(RELAY_ERR_SHAPE, "n=%d outside 2..3", n);
+  for (int i = 0; i < n; ++i) {
+    const relay_conv2d_views_call& c = calls[i];
+    if (!c.d) return fail(RELAY_ERR_NULL, "descriptor is NULL");
+    g_collect = &m[i];
+    const relay_status st =
+        combined_conv(c.d, c.x, c.x_ld, c.w_packed, c.bias, c.bn_scale, c.bn_shift, c.nseg, c.seg_channels, c.seg_y, c.seg_ld, nullptr, nullptr, nullptr);
+    g_collect = nullptr;
+    if (st != RELAY_OK) return st;
+  }
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j) {
+      if (i == j) continue;
+      const relay_conv2d_views_call& o = calls[j];
+      for (int s = 0; s < calls[i].nseg; ++s) {
+        const void* y = calls[i].seg_y[s];
+        const void* others[] = {o.x, o.w_packed, o.bias, o.bn_scale, o.bn_shift};
+        for (const void* p : others)
+          if (y == p) return fail(RELAY_ERR_UNSUPPORTED, "one conv's output is another's operand");
+        for (int t = 0; t < o.nseg; ++t)
+          if (y == o.seg_y[t]) return fail(RELAY_ERR_UNSUPPORTED, "two convs share an output address");
+      }
+    }
+  return RELAY_OK;
+}
+
+relay_status relay_conv2d_combined_group_pays(const relay_conv2d_views_call* calls, int32_t n, int32_t* pays) {
+  if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
+  relay::ConvArgs m[3];
+  const relay_status st = group_args(calls, n, m);
+  if (st != RELAY_OK) return st;
+  *pays = group_plan(m, n).together ? 1 : 0;
+  return RELAY_OK;
+}
+
+relay_status relay_fused_conv2d_combined_group(const relay_conv2d_views_call* calls, int32_t n, void* hip_stream) {
+  relay::ConvArgs m[3];
+  relay_status st = group_args(calls, n, m);
+  if (st != RELAY_OK) return st;
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  const GroupPlan p = group_plan(m, n);
+  if (p.together) return device_status(relay::launch_conv_group(p.c3, p.c[0], p.c[1], s), "conv group launch");
+  for (int i = 0; i < n && st == RELAY_OK; ++i) st = device_status(launch_igemm(m[i], false, s), "combined conv2d launch");
+  return st;
+}
+
 // ---- the two 3x3 convs of a residual block in one launch -----------------------------------------
 
 // fp16: one round of workgroups (one to a CU), and only where both convs by themselves sum three taps in a run, as the shared launch does.  int8: to where

@@ -1,0 +1,76 @@
+// Convs that read different tensors, none the other's output, as ONE launch: a 3x3 conv on the 3x3 kernel's 128 x 64 tiles and up to
+// two convs on the implicit GEMM's (paper Section 4.4, for the members of an Inception block that cannot share an input).
+//
+// One after the other each of them ends with the chip half empty: the 128 -> 192 3x3 conv of a block of 32 images of 28 x 28 is 633
+// tiles on 512 workgroup slots (19.4 us), the 32 -> 96 5x5 one 392 tiles of 25 short steps in a row, each waiting at a barrier
+// (13.9 us), the 256 -> 64 1x1 one 196 tiles that are mostly first loads and stores (6.6 us).  Sharing a grid, the tiles of one fill
+// the slots and the waits that the others leave.  A workgroup's number says whose tile it runs; each runs the code, and sums in the order, of
+// the conv's own launch.  What a tile needs of LDS and registers is the most of the three: two workgroups fit a CU, as by themselves.
+// The longest tiles come first, the shortest last, so that the last round is short.
+// Measured: the block 64.9 -> 52.0 us (5x5 first, then 3x3, then 1x1; 3x3 first 56.8, 1x1 before 3x3 53.2); the rule that chooses is api.cpp's.
+#include <atomic>
+
+#include "conv_halo_tile.hpp"
+#include "igemm_dma_tile.hpp"
+
+namespace relay {
+namespace {
+
+// The numbers of workgroups come first, in preloaded registers: whose tile it is is known before the first argument is fetched.
+__global__ __launch_bounds__(256, 2) void conv_group_kernel(const int tiles1, const int tiles3, const int tiles2, const ConvArgs a1, const HaloArgs a3,
+                                                            const ConvArgs a2) {
+  extern __shared__ uint4 lds[];
+  const int wg = (int)blockIdx.x, first3 = tiles1, first2 = tiles1 + tiles3;
+  if (wg < first3) igemm_dma_tile<false, 2, 2, 2, 1, 4, 1, 1, false, true, false>(a1, xcd_remap(wg, tiles1), lds);
+  else if (wg < first2) conv3x3_halo_tile<false, 2, 2, 2, 1, 2, 1, false, 1, true, false>(a3, xcd_remap(wg - first3, tiles3), wg - first3, tiles3);
+  else igemm_dma_tile<false, 2, 2, 2, 1, 3, 2, 1, false, true, false>(a2, xcd_remap(wg - first2, tiles2), lds);
+}
+
+constexpr int kBM = 128, kBN = 64;
+
+}  // namespace
+
+// The 3x3 kernel's variant 0 with 128-byte chunks and LDS for two workgroups a CU; its sums are those of every variant with such
+// chunks (a chunk's nine taps one after another) but the one that splits them (6).
+bool conv_group_takes_3x3(const ConvArgs& a) {
+  HaloArgs h;
+  size_t lds_bytes;
+  return a.nseg && conv_halo_group_args(a, h, lds_bytes) && lds_bytes <= 80 * 1024 - 64;
+}
+
+hipError_t launch_conv_group(const ConvArgs* c3, const ConvArgs* c1, const ConvArgs* c2, hipStream_t st) {
+  HaloArgs h{};
+  ConvArgs m[2] = {};
+  int tiles[3] = {0, 0, 0};
+  size_t lds_bytes = 0;
+  if (c3) {
+    if (!conv_group_takes_3x3(*c3) || !conv_halo_group_args(*c3, h, lds_bytes)) return hipErrorInvalidValue;
+    const int tiles_m = (h.g.Mflat + kBM - 1) / kBM, tiles_n = (c3->K + kBN - 1) / kBN;
+    h.g.fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
+    h.g.fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
+    tiles[0] = tiles_m * tiles_n;
+  }
+  const ConvArgs* c[2] = {c1, c2};
+  const size_t ring[2] = {igemm_dma_slots<false, 2, 2, 2, 1, 4, 1, false>() * 16, igemm_dma_slots<false, 2, 2, 2, 1, 3, 2, false>() * 16};
+  for (int i = 0; i < 2; ++i) {
+    if (!c[i]) continue;
+    m[i] = *c[i];
+    if (!igemm_dma_supported(m[i], false) || (i == 1 && m[i].C % (2 * BKV * 8))) return hipErrorInvalidValue;
+    const int tiles_m = (m[i].M + kBM - 1) / kBM, tiles_n = (m[i].K + kBN - 1) / kBN;
+    m[i].split = 1;
+    m[i].fd_tiles_m = make_fastdiv((uint32_t)tiles_m);
+    m[i].fd_tiles_n = make_fastdiv((uint32_t)tiles_n);
+    tiles[1 + i] = tiles_m * tiles_n;
+    lds_bytes = lds_bytes > ring[i] ? lds_bytes : ring[i];
+  }
+  static std::atomic<bool> raised{false};  // dynamic LDS above the default limit has to be asked for once per kernel
+  if (!raised.load(std::memory_order_acquire)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_group_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+    if (e != hipSuccess) return e;
+    raised.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(conv_group_kernel, dim3(tiles[0] + tiles[1] + tiles[2]), dim3(256), lds_bytes, st, tiles[1], tiles[0], tiles[2], m[0], h, m[1]);
+  return hipGetLastError();
+}
+
+}  // namespace relay

@@ -149,6 +149,10 @@ hipError_t launch_conv_halo(const ConvArgs& a, bool is_i8, int variant, hipStrea
 bool conv_halo_pool2_supported(const ConvArgs& a);
 hipError_t launch_conv_halo_pool2(const ConvArgs& a, void* y_pooled, hipStream_t st);
 void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf, size_t len);
+// fp16 convs into channel segments side by side in one launch (conv_group.hip): c3 on the 3x3 kernel's tiles, c1 on the implicit GEMM's with
+// 64-byte chunks, c2 with 128-byte ones; NULL: none of that kind
+bool conv_group_takes_3x3(const ConvArgs& a);
+hipError_t launch_conv_group(const ConvArgs* c3, const ConvArgs* c1, const ConvArgs* c2, hipStream_t st);
 // The kernel for layers of few output tiles: the waves of a workgroup split the reduction (conv_small.hip).
 bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);
 // The variant, or -1: leave the layer to the other kernels.  regroup: nothing else promises the bits of this call, so

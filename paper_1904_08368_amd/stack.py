@@ -113,7 +113,8 @@ class FusedNet:
         absorbed = {j for i, g in group_of.items() for j in g if j != i}
         self._plan_concats(ops, batch, h, w, in_channels, cpad)
 
-        for i, (op, p) in enumerate(zip(ops, params)):
+        for i in self._emission_order(ops) if combine else range(len(ops)):
+            op, p = ops[i], params[i]
             if i in absorbed:
                 continue
             cin_l, hi, wi = self.shape[op.src]
@@ -299,7 +300,7 @@ class FusedNet:
         if self.stem:
             self.bufs["x"] = self.x_nchw   # (as the launch reads it: the copy would be what an earlier run left there)
         # further calls that one launch stands for, writing the same tensors
-        self.merged = self._merged_calls()
+        self.merged = {**self._merged_calls(), **self._combined_groups()}
         torch.cuda.synchronize(self.dev)
         self.graph = None
 
@@ -326,6 +327,24 @@ class FusedNet:
                     a1[3] == a0[0] and B.relay_avgpool_dense_pays(*a0[:4], a1[1]):
                 merged[i] = (self.calls[i:i + 2], B.relay_fused_avgpool_dense, (*a0[:4], a1[1], a0[4], *a1[5:8], a0[5], a1[8]))
         return merged
+
+    def _combined_groups(self):
+        """{i: (calls, function, arguments)} of two or three neighbouring convs into channel segments, none reading what another of them
+        writes, that run as one launch."""
+        groups = {}
+        for i in range(len(self.calls)):
+            for n in (3, 2):
+                part = self.calls[i:i + n]
+                if len(part) < n or any(f is not B.relay_fused_conv2d_combined for f, _ in part) or any(j in groups for j in range(i - n + 1, i)):
+                    continue
+                spans = [[(t.untyped_storage().data_ptr(), t.data_ptr()) for t in a[8]] for _, a in part]
+                reads = [a[1].untyped_storage().data_ptr() for _, a in part]
+                if any(x == y[0] for j, x in enumerate(reads) for k, ys in enumerate(spans) if j != k for y in ys):
+                    continue
+                if B.relay_conv2d_combined_group_pays(*[a for _, a in part]):
+                    groups[i] = (part, B.relay_fused_conv2d_combined_group, tuple(a for _, a in part))
+                    break
+        return groups
 
     def _image_stem(self):
         """(calls, function, arguments) of the launch that stands for the first two or three calls -- the padded copy of the image,
@@ -368,6 +387,16 @@ class FusedNet:
             if a0[1] is a1[1] and not any(t is y0 or t is y1 for t in reads) and B.relay_conv2d_pair_fusable(a0[0], a1[0]):
                 pairs[i] = (self.calls[i], self.calls[i + 1])
         return pairs
+
+    @staticmethod
+    def _emission_order(ops):
+        """Positions of `ops` in the order of their launches: a max pool directly behind the first conv that reads the tensor it reads, ahead of the
+        convs that wait for that one, so that the conv on the pool's result is a neighbour of those."""
+        order = []
+        for i, op in enumerate(ops):
+            at = [k for k, j in enumerate(order) if op.kind == "maxpool" and ops[j].kind == "conv" and ops[j].src == op.src]
+            order.insert(at[0] + 1 if at else len(order), i)
+        return order
 
     def _pointwise_behind(self, ops, i, group_of, absorbed):
         """Index of the plain 1x1 / stride 1 conv that is the only reader of depthwise conv i's output, or None."""

@@ -1,0 +1,128 @@
+"""Convs of different inputs into channel segments as one launch (relay_fused_conv2d_combined_group) against the separate calls, bit for bit; which
+convs take it; what the call refuses; the Inception block that uses it."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1904_08368_amd import binding as B
+from paper_1904_08368_amd.stack import FusedNet
+from workloads import nets
+
+MEMBERS = {"3": (128, 192, 3, 128), "5": (32, 96, 5, 320), "1": (256, 64, 1, 416)}   # channels, filters, window, first channel of 480
+
+
+def _desc(n, h, w, kind, flags):
+    c, k, r, _ = MEMBERS[kind]
+    return B.conv_desc(n, c, h, w, k, r, r, 1, r // 2, B.RELAY_F16, B.RELAY_NHWC, flags)
+
+
+class Address:
+    """What a host-only call takes for a tensor."""
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+
+def _host_members(n, h, w, kinds):
+    f = B.flags_of(None, True, None, True)
+    at = lambda i, j: Address((i + 1 << 36) + (j << 34))
+    return [(_desc(n, h, w, kd, f), at(i, 0), MEMBERS[kd][0], at(i, 1), None, at(i, 2), at(i, 2), [MEMBERS[kd][1]],
+             [Address((1 << 40) + 2 * MEMBERS[kd][3] + 960 * 64 * i)], [480]) for i, kd in enumerate(kinds)]
+
+
+def test_which_convs_share_a_launch():
+    """(host only) Convs that take tiles of 128 x 64 or less of the two staged kernels by themselves, one of each kind."""
+    pays = lambda n, h, w, kinds: B.relay_conv2d_combined_group_pays(*_host_members(n, h, w, kinds))
+    assert all(pays(32, 28, 28, k) for k in ("351", "35", "51", "31", "513", "15")) and pays(12, 28, 28, "351")
+    assert not pays(10, 28, 28, "351")                                # (the 5x5 conv runs on the small-tile kernel)
+    assert not pays(32, 28, 28, "33") and not pays(32, 28, 28, "11")  # (two of a kind)
+    assert not pays(32, 40, 40, "31") and pays(32, 40, 40, "51")      # (a halo too wide for two workgroups a CU)
+    assert not pays(32, 64, 64, "51") and not pays(32, 64, 64, "31")  # (wider tiles)
+    B.relay_set_conv_tile(9)
+    try:
+        assert not pays(32, 28, 28, "351")
+    finally:
+        B.relay_set_conv_tile(-1)
+
+
+def test_refused_calls():
+    """(host only: every check runs before the first launch)"""
+    def status(members, n=None):
+        calls, keep = B._views_calls(members)
+        return B.lib().relay_fused_conv2d_combined_group(C.addressof(calls) if members else None, len(members) if n is None else n, None)
+    good = _host_members(32, 28, 28, "351")
+    swap = lambda i, j, v: [tuple(v if (a, b) == (i, j) else x for b, x in enumerate(m)) for a, m in enumerate(good)]
+    assert status([], 2) == 1 and status(good[:1]) == 2 and status(good, 4) == 2
+    assert status(swap(1, 1, None)) == 1 and status(swap(2, 5, None)) == 1
+    assert status(swap(0, 8, good[1][8])) == 4                        # (one address)
+    assert status(swap(1, 1, good[0][8][0])) == 4 and status(swap(2, 3, good[1][8][0])) == 4
+    assert status(swap(1, 1, Address(good[1][1].at + 2))) == 5
+    assert status(swap(1, 9, [90])) == 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,h,w,kinds", [(32, 28, 28, "351"), (12, 28, 28, "315"), (13, 27, 31, "35"), (20, 33, 29, "51"), (20, 33, 29, "31"), (4, 64, 64, "35"),
+                                         (10, 28, 28, "351"), (2, 9, 11, "513")])
+@pytest.mark.parametrize("tail", ["bn_relu", "bias"])
+def test_group_is_the_separate_calls(n, h, w, kinds, tail):
+    """Tiles with and without a remainder, one kind absent, and shapes that run as separate launches (the last two)."""
+    g = torch.Generator().manual_seed(5)
+    flags = B.flags_of(None, True, None, True) if tail == "bn_relu" else B.flags_of(True, None, None, False)
+    cat = torch.empty((n, h, w, 480), dtype=torch.float16, device="cuda")
+    members = []
+    for kind in kinds:
+        c, k, r, at = MEMBERS[kind]
+        d = _desc(n, h, w, kind, flags)
+        x = torch.randn((n, h, w, c), generator=g).half().cuda()
+        src = (torch.randn((k, c, r, r), generator=g) * (2.0 / (c * r * r)) ** 0.5).half().cuda()
+        wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device="cuda")
+        B.relay_prepack_conv2d_weights(d, src, c, wp)
+        v = [torch.randn(k, generator=g).cuda() for _ in range(3)]
+        members.append((d, x, c, wp) + ((None, v[0], v[1]) if tail == "bn_relu" else (v[2], None, None)) + ([k], [cat[..., at:at + k]], [480]))
+    assert B.relay_conv2d_combined_group_pays(*members) == (n > 2 and (n, h, w) != (10, 28, 28))
+    got = []
+    for call in (lambda: [B.relay_fused_conv2d_combined(*m) for m in members], lambda: B.relay_fused_conv2d_combined_group(*members)):
+        cat.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        got.append(cat.cpu().view(torch.int16))
+    assert torch.equal(got[0], got[1])
+    assert torch.isfinite(cat).all() and not (got[0][..., MEMBERS[kinds[0]][3]] == got[0].new_full((), 0x4700)).all()
+
+
+@pytest.mark.gpu
+def test_inception_block_runs_them_together():
+    """Eager and captured, against the same network with every call by itself, on two inputs."""
+    ops, rng = nets.inception_block(), np.random.default_rng(3)
+    params = []
+    for op in ops:
+        p = {}
+        if op.kind == "conv":
+            p["w"] = (rng.standard_normal((op.cout, op.cin, op.r, op.r)) * np.sqrt(2.0 / (op.cin * op.r * op.r))).astype(np.float16)
+            if op.bias:
+                p["bias"] = rng.standard_normal(op.cout).astype(np.float32)
+            if op.bn:
+                p["scale"], p["shift"] = (rng.standard_normal(op.cout).astype(np.float32) for _ in range(2))
+        params.append(p)
+    net = FusedNet(ops, params, 12, 28, 28, "f16", in_channels=256, combine=True)
+    assert any(fn is B.relay_fused_conv2d_combined_group for _, fn, _ in net.launches())
+    out = ops[-1].dst
+    for seed in range(2):
+        net.load_input(np.random.default_rng(seed).standard_normal((12, 256, 28, 28)).astype(np.float16))
+        merged, net.merged = net.merged, {}
+        net.run()
+        alone = net.tensor(out)
+        net.merged = merged
+        net.bufs[out].fill_(7.0)
+        net.run()
+        assert np.array_equal(alone.view(np.int16), net.tensor(out).view(np.int16))
+        if net.graph is None:
+            net.capture()
+        for _ in range(3):
+            net.bufs[out].fill_(7.0)
+            net.replay()
+            assert np.array_equal(alone.view(np.int16), net.tensor(out).view(np.int16))
