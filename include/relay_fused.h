@@ -576,6 +576,16 @@ typedef struct {
 } relay_conv2d_views_call;
 relay_status relay_conv2d_combined_group_pays(const relay_conv2d_views_call* calls, int32_t n, int32_t* pays);
 relay_status relay_fused_conv2d_combined_group(const relay_conv2d_views_call* calls, int32_t n, void* hip_stream);
+/* The same (paper Section 4.4) for a conv into channel segments and an F16 max pool (relay_maxpool2d), neither reading what the other writes: an Inception block's convs
+ * on its input and its pool.  One launch for 3 x 3 windows beside a conv on tiles that the launch has (relay_conv2d_combined_maxpool_pays, host-only), else
+ * two.  Results: bit for bit those of the separate calls.  Errors: theirs, plus _UNSUPPORTED as above; nothing is launched on an error. */
+typedef struct {
+  int32_t n, c, h, w, r, stride, pad;
+  const void* x;
+  void* y;
+} relay_maxpool2d_call;
+relay_status relay_conv2d_combined_maxpool_pays(const relay_conv2d_views_call* conv, const relay_maxpool2d_call* pool, int32_t* pays);
+relay_status relay_fused_conv2d_combined_maxpool(const relay_conv2d_views_call* conv, const relay_maxpool2d_call* pool, void* hip_stream);
 
 /* For callers that cannot allocate device memory (code under HIP-graph capture, serving loops and
  * harnesses that forbid hipMalloc): relay_fused_conv2d_bias_bn_relu for F16 NHWC / NHWC4_PADDED

@@ -90,6 +90,8 @@ SIGNATURES = {
     "relay_conv2d_maxpool_fusable": [_DP, C.POINTER(_I)],
     "relay_conv2d_combined_group_pays": [_P, _I, C.POINTER(_I)],
     "relay_fused_conv2d_combined_group": [_P, _I, _P],
+    "relay_conv2d_combined_maxpool_pays": [_P, _P, C.POINTER(_I)],
+    "relay_fused_conv2d_combined_maxpool": [_P, _P, _P],
     "relay_conv2d_block_pays": [_P, _P, C.POINTER(_I)],
     "relay_fused_conv2d_block": [_P] * 14,
     "relay_qconv2d_block": [_P, _P, _P, _P, _I, _P, _P, _P, _P, _I, _I, _P, _P],
@@ -511,6 +513,25 @@ def relay_fused_conv2d_combined_group(*members) -> None:
     """members: argument tuples of relay_fused_conv2d_combined."""
     calls, keep = _views_calls(members)
     _check(lib().relay_fused_conv2d_combined_group(C.addressof(calls), len(members), _stream()))
+
+
+class PoolCall(C.Structure):
+    _fields_ = [(k, C.c_int32) for k in ("n", "c", "h", "w", "r", "stride", "pad")] + [("x", _P), ("y", _P)]
+
+
+def relay_conv2d_combined_maxpool_pays(conv, pool) -> bool:
+    calls, keep = _views_calls([conv])
+    p = PoolCall(*pool[1:8], _ptr(pool[8]), _ptr(pool[9]))
+    ok = C.c_int32(0)
+    _check(lib().relay_conv2d_combined_maxpool_pays(C.addressof(calls), C.addressof(p), C.byref(ok)))
+    return bool(ok.value)
+
+
+def relay_fused_conv2d_combined_maxpool(conv, pool) -> None:
+    """Argument tuples of relay_fused_conv2d_combined and of an fp16 relay_maxpool2d."""
+    calls, keep = _views_calls([conv])
+    p = PoolCall(*pool[1:8], _ptr(pool[8]), _ptr(pool[9]))
+    _check(lib().relay_fused_conv2d_combined_maxpool(C.addressof(calls), C.addressof(p), _stream()))
 
 
 WINDOW_FULL, WINDOW_CENTRE = 0, 1

@@ -565,6 +565,8 @@ static relay_status combined_conv(const relay_conv2d_desc* d, const void* x, int
                                   const int32_t* seg_channels, void* const* seg_y, const int32_t* seg_ld,
                                   const int32_t* seg_window, const int32_t* seg_relu, void* hip_stream,
                                   const CombinedQuant* q = nullptr);
+static relay_status check_maxpool(int32_t dtype, int32_t n, int32_t c, int32_t h, int32_t w, int32_t r, int32_t stride, int32_t pad, const void* x,
+                                  const void* y);
 
 relay_status relay_fused_conv2d_combined(const relay_conv2d_desc* d, const void* x, int32_t x_ld,
                                          const void* w_packed, const float* bias, const float* bn_scale,
@@ -1031,6 +1033,55 @@ relay_status relay_fused_conv2d_combined_group(const relay_conv2d_views_call* ca
   if (p.together) return device_status(relay::launch_conv_group(p.c3, p.c[0], p.c[1], s), "conv group launch");
   for (int i = 0; i < n && st == RELAY_OK; ++i) st = device_status(launch_igemm(m[i], false, s), "combined conv2d launch");
   return st;
+}
+
+// ---- a conv into channel segments and a 3x3 max pool in one launch -----------------------------------
+
+// Does one launch take them?  Beside the conv's small-ring tiles, of which a CU holds four (us, separate / together, graph-timed, 256 -> 288 and the 3x3 /
+// stride 1 pool: 32 images of 28 x 28 19.3 / 18.0, 20 14.8 / 13.5, 32 of 40 x 40 31.8 / 28.7, of 64 x 64 66.4 / 60.2, 4 14.8 / 12.9).  Beside
+// those with longer chunks, two to a CU, the pool has too few loads in flight (16 of 28 x 28 11.9 / 14.1, 12 10.6 / 11.6).
+static bool conv_pool_together(const relay::ConvArgs& a, int r) {
+  if (g_force_tile != -1 || g_force_split != 0 || r != 3 || a.seg_centre) return false;
+  if (small_choice(a, false) >= 0 || stream_choice(a, false) >= 0 || halo_choice(a, false) >= 0) return false;
+  return relay::igemm_dma_supported(a, false) && relay::igemm_dma_small_ring(a);
+}
+
+static relay_status conv_pool_args(const relay_conv2d_views_call* conv, const relay_maxpool2d_call* pool, relay::ConvArgs* m) {
+  if (!conv || !pool || !conv->d) return fail(RELAY_ERR_NULL, "a member or its descriptor is NULL");
+  g_collect = m;
+  relay_status st = combined_conv(conv->d, conv->x, conv->x_ld, conv->w_packed, conv->bias, conv->bn_scale, conv->bn_shift, conv->nseg, conv->seg_channels,
+                                  conv->seg_y, conv->seg_ld, nullptr, nullptr, nullptr);
+  g_collect = nullptr;
+  if (st != RELAY_OK) return st;
+  if ((st = check_maxpool(RELAY_F16, pool->n, pool->c, pool->h, pool->w, pool->r, pool->stride, pool->pad, pool->x, pool->y)) != RELAY_OK) return st;
+  const void* reads[] = {conv->x, conv->w_packed, conv->bias, conv->bn_scale, conv->bn_shift, pool->x};
+  for (const void* p : reads)
+    if (pool->y == p) return fail(RELAY_ERR_UNSUPPORTED, "the pool's output is an operand");
+  for (int s = 0; s < conv->nseg; ++s)
+    if (conv->seg_y[s] == pool->x || conv->seg_y[s] == pool->y) return fail(RELAY_ERR_UNSUPPORTED, "the conv's output is the pool's input or output");
+  return RELAY_OK;
+}
+
+relay_status relay_conv2d_combined_maxpool_pays(const relay_conv2d_views_call* conv, const relay_maxpool2d_call* pool, int32_t* pays) {
+  if (!pays) return fail(RELAY_ERR_NULL, "pays is NULL");
+  relay::ConvArgs a;
+  const relay_status st = conv_pool_args(conv, pool, &a);
+  if (st != RELAY_OK) return st;
+  *pays = conv_pool_together(a, pool->r) ? 1 : 0;
+  return RELAY_OK;
+}
+
+relay_status relay_fused_conv2d_combined_maxpool(const relay_conv2d_views_call* conv, const relay_maxpool2d_call* pool, void* hip_stream) {
+  relay::ConvArgs a;
+  relay_status st = conv_pool_args(conv, pool, &a);
+  if (st != RELAY_OK) return st;
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  const relay_maxpool2d_call& p = *pool;
+  const int ho = (p.h + 2 * p.pad - p.r) / p.stride + 1, wo = (p.w + 2 * p.pad - p.r) / p.stride + 1;
+  if (conv_pool_together(a, p.r))
+    return device_status(relay::launch_conv_pool(a, p.n, p.c, p.h, p.w, p.stride, p.pad, ho, wo, p.x, p.y, s), "conv and maxpool launch");
+  if ((st = device_status(launch_igemm(a, false, s), "combined conv2d launch")) != RELAY_OK) return st;
+  return device_status(relay::launch_maxpool(false, p.n, p.c, p.h, p.w, p.r, p.stride, p.pad, ho, wo, p.x, p.y, s), "maxpool launch");
 }
 
 // ---- the two 3x3 convs of a residual block in one launch -----------------------------------------
@@ -1700,8 +1751,8 @@ relay_status relay_fuse_extract(int32_t n_ops, const int32_t* pattern, const int
   return RELAY_OK;
 }
 
-relay_status relay_maxpool2d(int32_t dtype, int32_t n, int32_t c, int32_t h, int32_t w, int32_t r, int32_t stride,
-                             int32_t pad, const void* x, void* y, void* hip_stream) {
+static relay_status check_maxpool(int32_t dtype, int32_t n, int32_t c, int32_t h, int32_t w, int32_t r, int32_t stride, int32_t pad, const void* x,
+                                  const void* y) {
   if (n <= 0 || c <= 0 || h <= 0 || w <= 0 || r <= 0 || stride <= 0 || pad < 0 || pad >= r || h + 2 * pad < r ||
       w + 2 * pad < r)
     return fail(RELAY_ERR_SHAPE, "bad pooling geometry");
@@ -1711,6 +1762,13 @@ relay_status relay_maxpool2d(int32_t dtype, int32_t n, int32_t c, int32_t h, int
   if (!x || !y) return fail(RELAY_ERR_NULL, "x and y are required");
   if (!aligned(x, 16) || !aligned(y, 16)) return fail(RELAY_ERR_ALIGN, "tensors must be 16-byte aligned");
   if ((long)n * c * h * w > kMaxElems) return fail(RELAY_ERR_SHAPE, "tensor exceeds 2^31-1 elements");
+  return RELAY_OK;
+}
+
+relay_status relay_maxpool2d(int32_t dtype, int32_t n, int32_t c, int32_t h, int32_t w, int32_t r, int32_t stride,
+                             int32_t pad, const void* x, void* y, void* hip_stream) {
+  const relay_status st = check_maxpool(dtype, n, c, h, w, r, stride, pad, x, y);
+  if (st != RELAY_OK) return st;
   const int ho = (h + 2 * pad - r) / stride + 1, wo = (w + 2 * pad - r) / stride + 1;
   return device_status(relay::launch_maxpool(dtype == RELAY_I8, n, c, h, w, r, stride, pad, ho, wo, x, y,
                                              static_cast<hipStream_t>(hip_stream)),

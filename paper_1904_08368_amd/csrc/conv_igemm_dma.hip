@@ -528,6 +528,8 @@ float igemm_dma_estimate(const ConvArgs& a, bool is_i8) {
   return 0.f;   // (a tile no 3 x 3 layer of 64 channels takes: nothing is faster)
 }
 
+bool igemm_dma_small_ring(const ConvArgs& a) { return resolve_tile(a, false, -1) == 16; }
+
 int igemm_dma_tile_count() { return kNumTiles + 1; }
 
 int igemm_dma_plan_split(const ConvArgs& a, bool is_i8, int tile, int want, size_t* counter_bytes,

@@ -152,6 +152,9 @@ void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf
 // fp16 convs into channel segments side by side in one launch (conv_group.hip): c3 on the 3x3 kernel's tiles, c1 on the implicit GEMM's with
 // 64-byte chunks, c2 with 128-byte ones; NULL: none of that kind
 bool conv_group_takes_3x3(const ConvArgs& a);
+// ... and an fp16 conv of the implicit GEMM's small-ring 128 x 64 tiles beside a 3x3 max pool of C channels
+bool igemm_dma_small_ring(const ConvArgs& a);
+hipError_t launch_conv_pool(const ConvArgs& conv, int N, int C, int H, int W, int stride, int pad, int Ho, int Wo, const void* x, void* y, hipStream_t st);
 hipError_t launch_conv_group(const ConvArgs* c3, const ConvArgs* c1, const ConvArgs* c2, hipStream_t st);
 // The kernel for layers of few output tiles: the waves of a workgroup split the reduction (conv_small.hip).
 bool conv_small_supported(const ConvArgs& a, bool is_i8, int variant);

@@ -329,17 +329,22 @@ class FusedNet:
         return merged
 
     def _combined_groups(self):
-        """{i: (calls, function, arguments)} of two or three neighbouring convs into channel segments, none reading what another of them
-        writes, that run as one launch."""
+        """{i: (calls, function, arguments)} of two or three neighbouring convs into channel segments, or of one and the max pool of the tensor it
+        reads, none reading what another of them writes, that run as one launch."""
         groups = {}
+        at = lambda t: t.untyped_storage().data_ptr()
         for i in range(len(self.calls)):
+            if i + 1 < len(self.calls) and not any(j + len(g[0]) > i for j, g in groups.items()):   # (a conv and the pool of the same tensor)
+                (f0, a0), (f1, a1) = self.calls[i:i + 2]
+                if f0 is B.relay_fused_conv2d_combined and f1 is B.relay_maxpool2d and a1[0] == B.RELAY_F16 and a1[8] is a0[1] and \
+                        not any(at(t) in (at(a0[1]), at(a1[9])) for t in a0[8]) and B.relay_conv2d_combined_maxpool_pays(a0, a1):
+                    groups[i] = (self.calls[i:i + 2], B.relay_fused_conv2d_combined_maxpool, (a0, a1))
+                    continue
             for n in (3, 2):
                 part = self.calls[i:i + n]
-                if len(part) < n or any(f is not B.relay_fused_conv2d_combined for f, _ in part) or any(j in groups for j in range(i - n + 1, i)):
+                if len(part) < n or any(f is not B.relay_fused_conv2d_combined for f, _ in part) or any(j + len(g[0]) > i for j, g in groups.items()):
                     continue
-                spans = [[(t.untyped_storage().data_ptr(), t.data_ptr()) for t in a[8]] for _, a in part]
-                reads = [a[1].untyped_storage().data_ptr() for _, a in part]
-                if any(x == y[0] for j, x in enumerate(reads) for k, ys in enumerate(spans) if j != k for y in ys):
+                if any(at(a[1]) == at(y) for _, a in part for _, b in part if a is not b for y in b[8]):
                     continue
                 if B.relay_conv2d_combined_group_pays(*[a for _, a in part]):
                     groups[i] = (part, B.relay_fused_conv2d_combined_group, tuple(a for _, a in part))

@@ -1,4 +1,5 @@
-"""Convs of different inputs into channel segments as one launch (relay_fused_conv2d_combined_group) against the separate calls, bit for bit; which
+"""Convs of different inputs into channel segments as one launch (relay_fused_conv2d_combined_group), and one beside a max pool
+(relay_fused_conv2d_combined_maxpool), against the separate calls, bit for bit; which
 convs take it; what the call refuses; the Inception block that uses it."""
 import ctypes as C
 
@@ -94,6 +95,61 @@ def test_group_is_the_separate_calls(n, h, w, kinds, tail):
     assert torch.isfinite(cat).all() and not (got[0][..., MEMBERS[kinds[0]][3]] == got[0].new_full((), 0x4700)).all()
 
 
+def _pool_call(n, h, w, stride, x, y, r=3, c=256):
+    return (B.RELAY_F16, n, c, h, w, r, stride, 1, x, y)
+
+
+def test_which_convs_share_a_launch_with_a_pool():
+    """(host only) Convs on small-ring 128 x 64 tiles by themselves, 3 x 3 windows; what is refused."""
+    def members(n, h, w, k=288, r=3, stride=1):
+        at = lambda i: Address((i + 1) << 36)
+        d = B.conv_desc(n, 256, h, w, k, 1, 1, 1, 0, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(True, None, None, True))
+        return (d, at(0), 256, at(1), at(2), None, None, [k], [at(3)], [k]), _pool_call(n, h, w, stride, at(0), at(4), r)
+    pays = lambda *a, **k: B.relay_conv2d_combined_maxpool_pays(*members(*a, **k))
+    assert pays(32, 28, 28) and pays(17, 28, 28) and pays(32, 28, 28, stride=2) and pays(32, 64, 64)
+    assert not pays(3, 17, 40) and not pays(16, 28, 28) and not pays(32, 28, 28, r=2)
+    B.relay_set_conv_split(2)
+    try:
+        assert not pays(32, 28, 28)
+    finally:
+        B.relay_set_conv_split(0)
+    conv, pool = members(32, 28, 28)
+    for i, bad in ((9, pool[8]), (8, conv[8][0]), (9, conv[8][0]), (9, conv[3])):
+        with pytest.raises(B.RelayError, match="UNSUPPORTED"):
+            B.relay_conv2d_combined_maxpool_pays(conv, tuple(bad if j == i else v for j, v in enumerate(pool)))
+    with pytest.raises(B.RelayError, match="SHAPE"):
+        B.relay_conv2d_combined_maxpool_pays(conv, _pool_call(32, 28, 28, 0, pool[8], pool[9]))
+    with pytest.raises(B.RelayError, match="NULL"):
+        B.relay_conv2d_combined_maxpool_pays(conv, _pool_call(32, 28, 28, 1, None, pool[9]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,h,w,k,stride,c", [(32, 28, 28, 288, 1, 256), (20, 33, 29, 288, 1, 256), (32, 28, 28, 192, 2, 256), (13, 31, 37, 288, 2, 64),
+                                              (9, 50, 23, 448, 1, 8), (34, 17, 11, 704, 1, 264), (3, 17, 40, 288, 1, 256)])
+def test_conv_and_pool_are_the_separate_calls(n, h, w, k, stride, c):
+    """One and two outputs a thread, more workgroups of one and of the other, remainders, a NaN and infinities in the pool's input, a pool of another
+    tensor; the last runs as two launches."""
+    g = torch.Generator().manual_seed(n)
+    x = torch.randn((n, h, w, 256), generator=g).half().cuda()
+    px = x if c == 256 else torch.randn((n, h, w, c), generator=g).half().cuda()
+    if c != 256:
+        px[0, 1, 1, :3] = torch.tensor([float("nan"), float("inf"), float("-inf")])
+    d = B.conv_desc(n, 256, h, w, k, 1, 1, 1, 0, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(True, None, None, True))
+    wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device="cuda")
+    B.relay_prepack_conv2d_weights(d, (torch.randn((k, 256, 1, 1), generator=g) / 16).half().cuda(), 256, wp)
+    y = torch.empty((n, h, w, k), dtype=torch.float16, device="cuda")
+    py = torch.empty((n, (h - 1) // stride + 1, (w - 1) // stride + 1, c), dtype=torch.float16, device="cuda")
+    conv, pool = (d, x, 256, wp, torch.randn(k, generator=g).cuda(), None, None, [k], [y], [k]), _pool_call(n, h, w, stride, px, py, c=c)
+    assert B.relay_conv2d_combined_maxpool_pays(conv, pool) == (n > 3)
+    got = []
+    for call in (lambda: (B.relay_fused_conv2d_combined(*conv), B.relay_maxpool2d(*pool)), lambda: B.relay_fused_conv2d_combined_maxpool(conv, pool)):
+        y.fill_(7.0), py.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        got.append([t.cpu().view(torch.int16) for t in (y, py)])
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 @pytest.mark.gpu
 def test_inception_block_runs_them_together():
     """Eager and captured, against the same network with every call by itself, on two inputs."""
@@ -108,11 +164,11 @@ def test_inception_block_runs_them_together():
             if op.bn:
                 p["scale"], p["shift"] = (rng.standard_normal(op.cout).astype(np.float32) for _ in range(2))
         params.append(p)
-    net = FusedNet(ops, params, 12, 28, 28, "f16", in_channels=256, combine=True)
-    assert any(fn is B.relay_fused_conv2d_combined_group for _, fn, _ in net.launches())
+    net = FusedNet(ops, params, 17, 28, 28, "f16", in_channels=256, combine=True)
+    assert {B.relay_fused_conv2d_combined_group, B.relay_fused_conv2d_combined_maxpool} <= {fn for _, fn, _ in net.launches()}
     out = ops[-1].dst
     for seed in range(2):
-        net.load_input(np.random.default_rng(seed).standard_normal((12, 256, 28, 28)).astype(np.float16))
+        net.load_input(np.random.default_rng(seed).standard_normal((17, 256, 28, 28)).astype(np.float16))
         merged, net.merged = net.merged, {}
         net.run()
         alone = net.tensor(out)
