@@ -254,6 +254,8 @@ bool conv_halo_keeps_whole(const ConvArgs& a, bool is_i8) {
 //    12 x 20 x 18, 512 -> 512 38.6 us against 32.4 as 128 x 64).
 //  * 64 -> 64 channels in fp16, 128-position tiles for between one and about three rounds of the chip's 512 workgroup slots: the
 //    256-position tile halves the rounds (56 x 56 at batch 32: 13.9 against 14.9 us).
+//    But while the implicit GEMM's 128 pixels a tile, without the pad positions, are still one round of those slots, that one is left the layer
+//    (31 x 57 x 37, 511 tiles there and 534 here: 10.0 us against 12.0; 20 x 56 x 59, 517 and 535: 13.9 against 12.1).
 //    Two of its workgroups have to fit a CU's LDS (images up to 86 wide): 34 x 23 x 121, 64 -> 56 13.9 us by the implicit GEMM, 17.0.
 //  * Layers that 128 x 64 tiles suit (conv_halo_keeps_whole) leave them only for a clear gain, since the estimates err by 10 %: for
 //    the implicit GEMM where it is estimated at 0.9 of their time (0.82 with its 64-byte chunks, whose estimates are low), for 16 x 16
@@ -273,7 +275,7 @@ int conv_halo_pick(const ConvArgs& a, bool is_i8) {
   const long flat = (long)a.N * (a.H + 1) * (a.W + 1), tiles_n = (a.K + 63) / 64;
   if (((flat + 63) / 64) * tiles_n < 80 || !conv_halo_shape(a, is_i8)) return -1;
   const long t128 = ((flat + 127) / 128) * tiles_n;
-  if (!is_i8 && a.C == 64 && a.K <= 64 && t128 > 512 && t128 <= 1700 && halo_fits(a, is_i8, 2, 80 * 1024)) return 2;
+  if (!is_i8 && a.C == 64 && a.K <= 64 && t128 > 512 && t128 <= 1700 && halo_fits(a, is_i8, 2, 80 * 1024)) return (a.M + 127) / 128 <= 512 ? -1 : 2;
   if (is_i8 && igemm_dma_wide(a)) return -1;
   const float staged = igemm_dma_estimate(a, is_i8), small = conv_small_estimate(a, is_i8);
   const int ve = is_i8 ? 16 : 8;

@@ -19,3 +19,11 @@ def test_choice(dtype, n, c, h, w, k, kernels):
     d = B.conv_desc(n, c, h, w, k, 3, 3, 1, 1, dtype, B.RELAY_NHWC, 0)
     name = B.relay_conv2d_kernel_name(d)
     assert name.startswith(kernels), name
+
+
+@pytest.mark.parametrize("n,h,w,kernel", [(31, 57, 37, "igemm_dma_kernel"), (20, 56, 59, "conv3x3_halo_kernel<false, 4, 1"), (32, 56, 56, "conv3x3_halo_kernel<false, 4, 1"),
+                                          (18, 57, 59, "conv3x3_halo_kernel<false, 2, 2")])
+def test_64_channels_around_one_round_of_slots(n, h, w, kernel):
+    """Tiles of 128 pixels without and with the pad positions of the 3x3 kernel: 511 / 534, 517 / 535, 784 / 813, 473 / 490."""
+    d = B.conv_desc(n, 64, h, w, 64, 3, 3, 1, 1, B.RELAY_F16, B.RELAY_NHWC, 0)
+    assert B.relay_conv2d_kernel_name(d).startswith(kernel)
