@@ -113,8 +113,7 @@ class FusedNet:
         absorbed = {j for i, g in group_of.items() for j in g if j != i}
         self._plan_concats(ops, batch, h, w, in_channels, cpad)
 
-        for i in self._emission_order(ops) if combine else range(len(ops)):
-            op, p = ops[i], params[i]
+        for i, (op, p) in enumerate(zip(ops, params)):
             if i in absorbed:
                 continue
             cin_l, hi, wi = self.shape[op.src]
@@ -293,19 +292,41 @@ class FusedNet:
                         self.join_before.add(idx_of[users[0].name])
             if self.side_calls:
                 self.side = torch.cuda.Stream(device=self.dev)
-        # two neighbouring calls that run as one launch: a block's first conv and the shortcut conv beside it
-        self.pairs = {} if self.side_calls else self._independent_pairs()
-        # the first calls as one launch on the image itself: its padded copy (not written then), the conv and the pool behind it
-        self.stem = self._image_stem()
+        self._plan_launches()
+        if combine and not self.side_calls:
+            self._move_pools()
         if self.stem:
             self.bufs["x"] = self.x_nchw   # (as the launch reads it: the copy would be what an earlier run left there)
-        # further calls that one launch stands for, writing the same tensors
-        self.merged = {**self._merged_calls(), **self._combined_groups()}
         torch.cuda.synchronize(self.dev)
         self.graph = None
 
     stem = None
     merged: Dict[int, tuple] = {}
+
+    def _plan_launches(self):
+        """Which neighbours in `calls` run as one launch."""
+        # a block's first conv and the shortcut conv beside it
+        self.pairs = {} if self.side_calls else self._independent_pairs()
+        # the first calls on the image itself: its padded copy (not written then), the conv and the pool behind it
+        self.stem = self._image_stem()
+        # further calls that one launch stands for, writing the same tensors
+        self.merged = {**self._merged_calls(), **self._combined_groups()}
+
+    def _move_pools(self):
+        """Puts a max pool right behind a conv on the tensor that it reads where a run then makes fewer launches: the two share one, or the conv on the
+        pool's result shares one with the convs that it now follows.  (Only there: a pool between calls that share a launch parts them.)"""
+        convs = (B.relay_fused_conv2d_combined, B.relay_fused_conv2d_combined_windows, B.relay_fused_conv2d_bias_bn_relu)
+        for pool in [c for c in self.calls if c[0] is B.relay_maxpool2d]:
+            listed = self.calls, self.call_names
+            best, launches = listed, len(self._steps())
+            at = next(i for i, c in enumerate(self.calls) if c is pool)
+            for to in [i + 1 for i, (fn, a) in enumerate(self.calls[:max(at - 1, 0)]) if fn in convs and a[1] is pool[1][8]]:
+                self.calls, self.call_names = ([*v[:to], v[at], *v[to:at], *v[at + 1:]] for v in listed)
+                self._plan_launches()
+                if len(self._steps()) < launches:
+                    best, launches = (self.calls, self.call_names), len(self._steps())
+            self.calls, self.call_names = best
+            self._plan_launches()
 
     def _merged_calls(self):
         """{i: (calls, function, arguments)} of a conv and the 2x2 max pool on its outputs, of the two convs of a residual block, and of the
@@ -392,16 +413,6 @@ class FusedNet:
             if a0[1] is a1[1] and not any(t is y0 or t is y1 for t in reads) and B.relay_conv2d_pair_fusable(a0[0], a1[0]):
                 pairs[i] = (self.calls[i], self.calls[i + 1])
         return pairs
-
-    @staticmethod
-    def _emission_order(ops):
-        """Positions of `ops` in the order of their launches: a max pool directly behind the first conv that reads the tensor it reads, ahead of the
-        convs that wait for that one, so that the conv on the pool's result is a neighbour of those."""
-        order = []
-        for i, op in enumerate(ops):
-            at = [k for k, j in enumerate(order) if op.kind == "maxpool" and ops[j].kind == "conv" and ops[j].src == op.src]
-            order.insert(at[0] + 1 if at else len(order), i)
-        return order
 
     def _pointwise_behind(self, ops, i, group_of, absorbed):
         """Index of the plain 1x1 / stride 1 conv that is the only reader of depthwise conv i's output, or None."""
