@@ -367,8 +367,8 @@ relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* 
  * (F16) or relay_qconv2d_requant (I8) without a workspace and is checked as by that call; t is written whole.  Where no kernel takes the two together
  * (relay_conv2d_block_pays writes 0, or a tile or split is forced) they run as two launches.  Results: bit for bit those of the
  * separate calls.  relay_conv2d_block_pays writes 1 where one launch takes them and is the faster way.
- * Errors: as the calls above, plus RELAY_ERR_UNSUPPORTED where one conv's output is the other's operand otherwise than said; nothing is
- * launched on an error. */
+ * Errors: as the calls above, plus RELAY_ERR_UNSUPPORTED where one conv's output address is the other's operand otherwise than said; nothing is
+ * launched on an error.  Tensors that overlap otherwise: two launches. */
 relay_status relay_conv2d_block_pays(const relay_conv2d_desc* first, const relay_conv2d_desc* second, int32_t* pays);
 relay_status relay_fused_conv2d_block(const relay_conv2d_desc* first, const void* x, const void* w1, const float* bias1, const float* scale1,
                                       const float* shift1, void* t, const relay_conv2d_desc* second, const void* w2, const float* bias2,
@@ -548,8 +548,8 @@ typedef struct relay_conv2d_call {
  * int32, bn_scale and bn_shift NULL) without a workspace, and is checked as by that call; both have one dtype.
  * Where no kernel takes the two together they run as two launches, one after the other.  Results: bit for bit those
  * of the separate calls.
- * Errors: as the calls above, plus RELAY_ERR_DTYPE (two dtypes) and _UNSUPPORTED (a member's output is the other's output or
- * operand); nothing is launched on an error. */
+ * Errors: as the calls above, plus RELAY_ERR_DTYPE (two dtypes) and _UNSUPPORTED (a member's output address is the other's output or
+ * operand); nothing is launched on an error.  Where one's output overlaps the other's tensors otherwise they run one after the other. */
 relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2d_call* second, void* hip_stream);
 /* Whether relay_conv2d_pair runs two convs of these shapes as one launch (paper Section 4.1, a choice per group of operators);
  * host-only, nothing is launched.  Errors: as relay_workspace_bytes, _DTYPE (two dtypes). */
@@ -559,8 +559,9 @@ relay_status relay_conv2d_pair_fusable(const relay_conv2d_desc* first, const rel
  * the members of an Inception block that share no input; Section 5.2).  Each member is a call of relay_fused_conv2d_combined and is checked as by
  * that call.  Where no kernel takes them together (relay_conv2d_combined_group_pays writes 0; host-only, also 0 while a tile or split is forced)
  * they run one after another.  Results: bit for bit those of the separate calls.
- * Errors: as relay_fused_conv2d_combined, plus _SHAPE (n outside 2..3) and _UNSUPPORTED (one conv's output is another's output or operand);
- * nothing is launched on an error. */
+ * Errors: as relay_fused_conv2d_combined, plus _SHAPE (n outside 2..3) and _UNSUPPORTED (one conv's output address is another's output or operand);
+ * nothing is launched on an error.  Where an output overlaps another member's tensors otherwise (channel ranges of one tensor that have no channel in
+ * common do not), _pays writes 0 and they run one after another. */
 typedef struct {
   const relay_conv2d_desc* d;
   const void* x;
@@ -578,7 +579,8 @@ relay_status relay_conv2d_combined_group_pays(const relay_conv2d_views_call* cal
 relay_status relay_fused_conv2d_combined_group(const relay_conv2d_views_call* calls, int32_t n, void* hip_stream);
 /* The same (paper Section 4.4) for a conv into channel segments and an F16 max pool (relay_maxpool2d), neither reading what the other writes: an Inception block's convs
  * on its input and its pool.  One launch for 3 x 3 windows beside a conv on tiles that the launch has (relay_conv2d_combined_maxpool_pays, host-only), else
- * two.  Results: bit for bit those of the separate calls.  Errors: theirs, plus _UNSUPPORTED as above; nothing is launched on an error. */
+ * two, also where they overlap as said above.  Results: bit for bit those of the separate calls.  Errors: theirs, plus _UNSUPPORTED as above; nothing is
+ * launched on an error. */
 typedef struct {
   int32_t n, c, h, w, r, stride, pad;
   const void* x;

@@ -876,6 +876,48 @@ static relay_status qconv_common(const relay_conv2d_desc* d, const int8_t* x, co
   return device_status(launch_igemm(a, true, static_cast<hipStream_t>(hip_stream)), "qconv2d launch");
 }
 
+// ---- which memory the members of a shared launch touch ------------------------------------------------------
+
+// `rows` pieces of `width` bytes, `pitch` bytes apart: a channel range of an NHWC tensor, or one piece.
+struct Span {
+  const void* at;
+  size_t rows, pitch, width;
+};
+// Can the two have a byte in common?  Exact for channel ranges of tensors of one pitch; otherwise ranges of addresses that overlap count as common.
+static bool spans_meet(const Span& a, const Span& b) {
+  if (!a.at || !b.at) return false;
+  const uintptr_t pa = reinterpret_cast<uintptr_t>(a.at), pb = reinterpret_cast<uintptr_t>(b.at);
+  if (pa + (a.rows - 1) * a.pitch + a.width <= pb || pb + (b.rows - 1) * b.pitch + b.width <= pa) return false;
+  if (a.rows == 1 || b.rows == 1 || a.pitch != b.pitch) return true;
+  const size_t off = pb >= pa ? (pb - pa) % a.pitch : (a.pitch - (pa - pb) % a.pitch) % a.pitch;   // of a piece of b in a's row
+  return off < a.width || off + b.width > a.pitch;
+}
+
+// Does conv `a` write what conv `b` reads or writes, or the span `other`?  Then the two keep their order: separate launches.
+static bool conv_writes(const relay::ConvArgs& a, bool i8, const Span& other) {
+  const size_t es = i8 ? 1 : 2;
+  if (!a.nseg) return spans_meet({a.y, 1, 0, (size_t)a.M * a.K * es}, other);
+  for (int i = 0, begin = 0; i < a.nseg; begin = a.seg_end[i], ++i)
+    if (spans_meet({a.seg_y[i], (size_t)a.M, a.seg_ld[i] * es, (a.seg_end[i] - begin) * es}, other)) return true;
+  return false;
+}
+static Span conv_input(const relay::ConvArgs& a, bool i8) {
+  const size_t es = i8 ? 1 : 2;
+  if (a.xs_w < a.C) return {a.x, 1, 0, (size_t)a.N * a.xs_n * es};   // (overlapping rows of a padded image)
+  return {a.x, (size_t)a.N * a.H * a.W, a.xs_w * es, a.C * es};
+}
+static bool conv_writes(const relay::ConvArgs& a, bool i8, const relay::ConvArgs& b) {
+  const size_t es = i8 ? 1 : 2, consts = (size_t)b.K * 4;
+  const Span reads[] = {conv_input(b, i8), {b.w, 1, 0, (size_t)b.K * b.Kp * es}, {b.res, 1, 0, (size_t)b.M * b.K * es}, {b.bias, 1, 0, consts},
+                        {b.scale, 1, 0, consts}, {b.shift, 1, 0, consts}, {b.qbias, 1, 0, consts}};
+  for (const Span& r : reads)
+    if (conv_writes(a, i8, r)) return true;
+  if (!b.nseg) return conv_writes(a, i8, Span{b.y, 1, 0, (size_t)b.M * b.K * es});
+  for (int i = 0, begin = 0; i < b.nseg; begin = b.seg_end[i], ++i)
+    if (conv_writes(a, i8, Span{b.seg_y[i], (size_t)b.M, b.seg_ld[i] * es, (b.seg_end[i] - begin) * es})) return true;
+  return false;
+}
+
 // ---- two independent convs in one launch ----------------------------------------------------------------------
 
 // Which kernel runs the two: variant `small` of the small-tile kernel (the first conv's own choice), or tile `dma` of the
@@ -947,7 +989,7 @@ relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2
     if (st != RELAY_OK) return st;
   }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  const PairPlan p = pair_plan(m[0], m[1], i8);
+  const PairPlan p = conv_writes(m[0], i8, m[1]) || conv_writes(m[1], i8, m[0]) ? PairPlan() : pair_plan(m[0], m[1], i8);
   if (p.small >= 0) return device_status(relay::launch_conv_small_pair(m[0], m[1], i8, p.small, s), "paired conv2d launch");
   if (p.dma >= 0) return device_status(relay::launch_conv_igemm_dma_pair(m[0], m[1], i8, p.dma, s), "paired conv2d launch");
   const relay_status st = device_status(launch_igemm(m[0], i8, s), "conv2d launch");
@@ -969,6 +1011,9 @@ struct GroupPlan {
 static GroupPlan group_plan(const relay::ConvArgs* m, int n) {
   GroupPlan p;
   if (g_force_tile != -1 || g_force_split != 0) return p;
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j)
+      if (i != j && conv_writes(m[i], false, m[j])) return p;
   for (int i = 0; i < n; ++i) {
     const relay::ConvArgs& a = m[i];
     if (a.seg_centre || small_choice(a, false) >= 0 || stream_choice(a, false) >= 0) return p;
@@ -986,7 +1031,7 @@ static GroupPlan group_plan(const relay::ConvArgs* m, int n) {
   return p;
 }
 
-// The members' arguments, each checked as by its own call, and that none reads or overwrites what another writes.
+// The members' arguments, each checked as by its own call, and that no output address is another's output or operand.
 static relay_status group_args(const relay_conv2d_views_call* calls, int32_t n, relay::ConvArgs* m) {
   if (!calls) return fail(RELAY_ERR_NULL, "calls is NULL");
   if (n < 2 || n > 3) return fail(RELAY_ERR_SHAPE, "n=%d outside 2..3", n);
@@ -1040,8 +1085,14 @@ relay_status relay_fused_conv2d_combined_group(const relay_conv2d_views_call* ca
 // Does one launch take them?  Beside the conv's small-ring tiles, of which a CU holds four (us, separate / together, graph-timed, 256 -> 288 and the 3x3 /
 // stride 1 pool: 32 images of 28 x 28 19.3 / 18.0, 20 14.8 / 13.5, 32 of 40 x 40 31.8 / 28.7, of 64 x 64 66.4 / 60.2, 4 14.8 / 12.9).  Beside
 // those with longer chunks, two to a CU, the pool has too few loads in flight (16 of 28 x 28 11.9 / 14.1, 12 10.6 / 11.6).
-static bool conv_pool_together(const relay::ConvArgs& a, int r) {
-  if (g_force_tile != -1 || g_force_split != 0 || r != 3 || a.seg_centre) return false;
+static bool conv_pool_together(const relay::ConvArgs& a, const relay_maxpool2d_call& p) {
+  if (g_force_tile != -1 || g_force_split != 0 || p.r != 3 || a.seg_centre) return false;
+  const int ho = (p.h + 2 * p.pad - p.r) / p.stride + 1, wo = (p.w + 2 * p.pad - p.r) / p.stride + 1;
+  const Span x{p.x, 1, 0, (size_t)p.n * p.h * p.w * p.c * 2}, y{p.y, 1, 0, (size_t)p.n * ho * wo * p.c * 2};
+  const size_t consts = (size_t)a.K * 4;
+  if (conv_writes(a, false, x) || conv_writes(a, false, y) || spans_meet(y, conv_input(a, false)) || spans_meet(y, {a.w, 1, 0, (size_t)a.K * a.Kp * 2}) ||
+      spans_meet(y, {a.bias, 1, 0, consts}) || spans_meet(y, {a.scale, 1, 0, consts}) || spans_meet(y, {a.shift, 1, 0, consts}))
+    return false;
   if (small_choice(a, false) >= 0 || stream_choice(a, false) >= 0 || halo_choice(a, false) >= 0) return false;
   return relay::igemm_dma_supported(a, false) && relay::igemm_dma_small_ring(a);
 }
@@ -1067,7 +1118,7 @@ relay_status relay_conv2d_combined_maxpool_pays(const relay_conv2d_views_call* c
   relay::ConvArgs a;
   const relay_status st = conv_pool_args(conv, pool, &a);
   if (st != RELAY_OK) return st;
-  *pays = conv_pool_together(a, pool->r) ? 1 : 0;
+  *pays = conv_pool_together(a, *pool) ? 1 : 0;
   return RELAY_OK;
 }
 
@@ -1078,7 +1129,7 @@ relay_status relay_fused_conv2d_combined_maxpool(const relay_conv2d_views_call* 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const relay_maxpool2d_call& p = *pool;
   const int ho = (p.h + 2 * p.pad - p.r) / p.stride + 1, wo = (p.w + 2 * p.pad - p.r) / p.stride + 1;
-  if (conv_pool_together(a, p.r))
+  if (conv_pool_together(a, p))
     return device_status(relay::launch_conv_pool(a, p.n, p.c, p.h, p.w, p.stride, p.pad, ho, wo, p.x, p.y, s), "conv and maxpool launch");
   if ((st = device_status(launch_igemm(a, false, s), "combined conv2d launch")) != RELAY_OK) return st;
   return device_status(relay::launch_maxpool(false, p.n, p.c, p.h, p.w, p.r, p.stride, p.pad, ho, wo, p.x, p.y, s), "maxpool launch");
@@ -1121,7 +1172,10 @@ relay_status relay_conv2d_block_pays(const relay_conv2d_desc* first, const relay
 
 // both members collected: their own checks have passed
 static relay_status launch_block(const relay::ConvArgs (&m)[2], bool i8, hipStream_t s) {
-  if (block_plan(m[0], m[1], i8)) return device_status(relay::launch_conv_block(m[0], m[1], i8, s), "residual block launch");
+  relay::ConvArgs beside = m[1];   // what the second conv reads beside the first one's outputs
+  beside.x = nullptr;
+  if (block_plan(m[0], m[1], i8) && !conv_writes(m[1], i8, m[0]) && !conv_writes(m[0], i8, beside))
+    return device_status(relay::launch_conv_block(m[0], m[1], i8, s), "residual block launch");
   const relay_status st = device_status(launch_igemm(m[0], i8, s), "conv2d launch");
   return st != RELAY_OK ? st : device_status(launch_igemm(m[1], i8, s), "conv2d launch");
 }

@@ -117,6 +117,37 @@ def test_infinities_reach_what_they_reach_in_the_two_calls():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("mode", ["f16", "i8"])
+def test_outputs_that_overlap_an_operand_are_those_of_the_calls_in_order(mode):
+    """The second conv's output a few rows into the first one's input (which no residual needs again), and a little ahead of it; for the paired
+    call the second member's output in the first one's input, whose launch is the earlier one."""
+    n, h, w = 1, 24, 24
+    f = RELU
+    a0, a1 = _calls(mode, n, h, w, f, f, 77)
+    a2 = _calls(mode, n, h, w, f, f, 78)[0]
+    row, rows = w * 64, n * h * w * 64
+    for shift in (3 * row, -2 * row):
+        buf = torch.empty(rows + 3 * row, dtype=a0[1].dtype, device="cuda")
+        x0, y0 = max(0, -shift), max(0, shift)
+        x, y = buf[x0:x0 + rows].view_as(a0[1]), buf[y0:y0 + rows].view_as(a0[1])
+        b0, b1, t = (a0[0], x, *a0[2:]), (*a1[:-1], y), torch.empty_like(x)
+        conv, tail = (B.relay_fused_conv2d_bias_bn_relu, 6) if mode == "f16" else (B.relay_qconv2d_requant, 4)
+        assert b1[tail] is None and B.relay_conv2d_block_pays(b0[0], b1[0])
+        pair = (*a2[:-1], y)   # (reads its own tensor)
+        block = (*b0[:6], t, b1[0], *b1[2:6], y) if mode == "f16" else (*b0[:4], b0[6], t, b1[0], b1[2], b1[3], b1[5], b1[6], y)
+        ways = ((lambda: (conv(*b0[:-1], t, None), conv(b1[0], t, *b1[2:], None)), lambda: (B.relay_fused_conv2d_block if mode == "f16" else B.relay_qconv2d_block)(*block)),
+                (lambda: (conv(*b0[:-1], t, None), conv(*pair, None)), lambda: B.relay_conv2d_pair((*b0[:-1], t, None), (*pair, None))))
+        for two, one in ways:
+            got = []
+            for call in (two, one):
+                buf.fill_(1), t.fill_(5), x.copy_(a0[1])
+                call()
+                torch.cuda.synchronize()
+                got.append([v.cpu().view(torch.uint8) for v in (buf, t)])
+            assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", ["f16", "i8"])
 def test_a_network_of_one_block(mode):
     """FusedNet takes it: against the oracle, and the same bits as its calls one by one; an edited list of calls is followed."""
     ops = nets.basic_block(64)

@@ -65,6 +65,44 @@ def test_refused_calls():
     assert status(swap(1, 9, [90])) == 2
 
 
+def _views(n, h, w, cat, spans):
+    """Members 5x5 and 1x1 on channel ranges of one tensor of 1024 channels: (first input channel, first output channel) of each; None: a tensor of its own."""
+    f, out = B.flags_of(None, True, None, True), []
+    for i, (kd, (x0, y0)) in enumerate(zip("51", spans)):
+        (c, k, _, _), own = MEMBERS[kd], lambda j: Address((i + 1 << 36) + (j << 34))
+        x, x_ld = (own(0), c) if x0 is None else (Address(cat + 2 * x0), 1024)
+        y, y_ld = (own(3), k) if y0 is None else (Address(cat + 2 * y0), 1024)
+        out.append((_desc(n, h, w, kd, f), x, x_ld, own(1), None, own(2), own(2), [k], [y], [y_ld]))
+    return out
+
+
+def test_members_that_meet_in_memory_keep_their_order():
+    """(host only) An output that begins inside another member's input or output view is a dependence though no two addresses are equal; ranges of
+    one tensor without a common channel are none, nor are neighbours in one allocation."""
+    cat, n, h, w = 1 << 40, 32, 28, 28
+    pays = lambda *spans: B.relay_conv2d_combined_group_pays(*_views(n, h, w, cat, spans))
+    assert pays((None, None), (None, None)) and pays((None, 0), (None, 96)) and pays((0, 32), (128, 384)) and pays((992, 0), (96, 352))
+    assert not pays((None, 64), (0, None))            # 5x5 -> channels 64 .. 159, the 1x1 conv reads 0 .. 255
+    assert not pays((80, None), (None, 64))           # 1x1 -> channels 64 .. 127, the 5x5 conv reads 80 .. 111
+    assert not pays((None, 0), (None, 88)) and not pays((None, 88), (None, 32))
+    members = _views(n, h, w, cat, ((None, None), (None, None)))
+    spot = lambda i, at: [tuple([Address(at)] if (a, b) == (i, 8) else x for b, x in enumerate(m)) for a, m in enumerate(members)]
+    w1 = members[1][3].at
+    assert not B.relay_conv2d_combined_group_pays(*spot(0, w1 + 32)) and not B.relay_conv2d_combined_group_pays(*spot(0, members[1][5].at - 64))
+    ends = w1 + B.relay_packed_weight_bytes(members[1][0])
+    assert B.relay_conv2d_combined_group_pays(*spot(0, ends)) and not B.relay_conv2d_combined_group_pays(*spot(0, ends - 16))
+    # beside a pool
+    at = lambda i: (i + 1) << 36
+    d, size = B.conv_desc(n, 256, h, w, 288, 1, 1, 1, 0, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(True, None, None, True)), n * h * w * 512
+    conv = lambda x, y, ld=288: (d, Address(x), 256, Address(at(1)), Address(at(2)), None, None, [288], [Address(y)], [ld])
+    pays = lambda c, x, y: B.relay_conv2d_combined_maxpool_pays(c, _pool_call(n, h, w, 1, Address(x), Address(y)))
+    assert pays(conv(at(0), at(3)), at(0), at(4)) and pays(conv(at(0), at(3)), at(0), at(0) + size) and pays(conv(at(0), at(3)), at(0), at(0) - size)
+    assert not pays(conv(at(0), at(5) + 128, 512), at(5), at(4))      # the conv stores into the pool's input,
+    assert not pays(conv(at(0), at(4) + 64, 512), at(0), at(4))       # into its output,
+    assert not pays(conv(at(0), at(3)), at(5), at(0) + 16)            # the pool into the conv's input,
+    assert not pays(conv(at(0), at(3)), at(0), at(2) + 16 - size)     # into its bias
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,h,w,kinds", [(32, 28, 28, "351"), (12, 28, 28, "315"), (13, 27, 31, "35"), (20, 33, 29, "51"), (20, 33, 29, "31"), (4, 64, 64, "35"),
                                          (10, 28, 28, "351"), (2, 9, 11, "513")])
@@ -182,3 +220,32 @@ def test_inception_block_runs_them_together():
             net.bufs[out].fill_(7.0)
             net.replay()
             assert np.array_equal(alone.view(np.int16), net.tensor(out).view(np.int16))
+
+
+@pytest.mark.gpu
+def test_members_that_meet_in_memory_give_what_the_calls_in_order_give():
+    """The second conv, or the pool, reads channels that the first conv writes."""
+    n, h, w, g = 32, 28, 28, torch.Generator().manual_seed(9)
+    wide = torch.randn((n, h, w, 512), generator=g).half().cuda()
+    f = B.flags_of(True, None, None, False)
+
+    def member(c, k, r, x, y):
+        d = B.conv_desc(n, c, h, w, k, r, r, 1, r // 2, B.RELAY_F16, B.RELAY_NHWC, f)
+        wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device="cuda")
+        B.relay_prepack_conv2d_weights(d, (torch.randn((k, c, r, r), generator=g) * (2.0 / (c * r * r)) ** 0.5).half().cuda(), c, wp)
+        return (d, x, x.stride(2), wp, torch.randn(k, generator=g).cuda(), None, None, [k], [y], [y.stride(2)])
+    cat, y1, py = torch.empty_like(wide), torch.empty((n, h, w, 64), dtype=torch.float16, device="cuda"), torch.empty_like(wide)
+    first = member(32, 96, 5, torch.randn((n, h, w, 32), generator=g).half().cuda(), cat[..., 64:160])
+    second = member(256, 64, 1, cat[..., :256], y1)
+    trio = member(256, 288, 1, torch.randn((n, h, w, 256), generator=g).half().cuda(), cat[..., 128:416])
+    pool = _pool_call(n, h, w, 1, cat, py, c=512)
+    for a, b, one in ((lambda: B.relay_fused_conv2d_combined(*first), lambda: B.relay_fused_conv2d_combined(*second),
+                       lambda: B.relay_fused_conv2d_combined_group(first, second)),
+                      (lambda: B.relay_fused_conv2d_combined(*trio), lambda: B.relay_maxpool2d(*pool), lambda: B.relay_fused_conv2d_combined_maxpool(trio, pool))):
+        got = []
+        for call in (lambda: (a(), b()), one):
+            cat.copy_(wide), y1.fill_(7.0), py.fill_(7.0)
+            call()
+            torch.cuda.synchronize()
+            got.append([t.cpu().view(torch.int16) for t in (cat, y1, py)])
+        assert all(torch.equal(p, q) for p, q in zip(*got))
