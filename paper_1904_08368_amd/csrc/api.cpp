@@ -1082,9 +1082,13 @@ relay_status relay_fused_conv2d_combined_group(const relay_conv2d_views_call* ca
 
 // ---- a conv into channel segments and a 3x3 max pool in one launch -----------------------------------
 
-// Does one launch take them?  Beside the conv's small-ring tiles, of which a CU holds four (us, separate / together, graph-timed, 256 -> 288 and the 3x3 /
-// stride 1 pool: 32 images of 28 x 28 19.3 / 18.0, 20 14.8 / 13.5, 32 of 40 x 40 31.8 / 28.7, of 64 x 64 66.4 / 60.2, 4 14.8 / 12.9).  Beside
-// those with longer chunks, two to a CU, the pool has too few loads in flight (16 of 28 x 28 11.9 / 14.1, 12 10.6 / 11.6).
+// Does one launch take them?  Beside the conv's small-ring tiles, of which a CU holds four, and where what they read and write fits the 256 MiB cache behind
+// the L2s with room to spare: beyond, the pool's rows are gone before the next one needs them again.  us, separate / together, graph-timed, the
+// conv and a pool of its input, stride 1 unless said: 32 images of 28 x 28, 256 -> 288 20.7 / 19.4, 256 -> 512 26.3 / 23.2, 192 -> 176 14.5 / 12.5, stride
+// 2 12.0 / 10.8; of 56 x 56, 256 -> 512 (196 MiB) 76.3 / 74.5, 256 -> 64 33.8 / 28.2, 64 -> 64 15.0 / 12.9; 20 of 33 x 29, 256 -> 288 16.6 / 15.8; 16 of 64 x
+// 64, 256 -> 1024 (192 MiB) 88.9 / 89.4, and the one loss below the line, 512 tiles beside a stride 2 pool of 256 channels 14.9 / 15.5.  Above it: 32 of 56
+// x 56, 128 -> 1024 (245 MiB) 81.6 / 86.1, 64 of 56 x 56, 256 -> 288 (306) 112 / 139, 16 of 128 x 128, 256 -> 64 (288) 75.8 / 99.0.  Beside the tiles
+// of longer chunks, two to a CU, the pool has too few loads in flight (16 of 28 x 28, 256 -> 288 11.9 / 14.1, 12 10.6 / 11.6).
 static bool conv_pool_together(const relay::ConvArgs& a, const relay_maxpool2d_call& p) {
   if (g_force_tile != -1 || g_force_split != 0 || p.r != 3 || a.seg_centre) return false;
   const int ho = (p.h + 2 * p.pad - p.r) / p.stride + 1, wo = (p.w + 2 * p.pad - p.r) / p.stride + 1;
@@ -1093,6 +1097,8 @@ static bool conv_pool_together(const relay::ConvArgs& a, const relay_maxpool2d_c
   if (conv_writes(a, false, x) || conv_writes(a, false, y) || spans_meet(y, conv_input(a, false)) || spans_meet(y, {a.w, 1, 0, (size_t)a.K * a.Kp * 2}) ||
       spans_meet(y, {a.bias, 1, 0, consts}) || spans_meet(y, {a.scale, 1, 0, consts}) || spans_meet(y, {a.shift, 1, 0, consts}))
     return false;
+  const size_t bytes = ((size_t)a.N * a.H * a.W * a.C + (size_t)a.M * a.K) * 2 + (a.x == p.x ? 0 : x.width) + y.width;
+  if (bytes > (size_t)200 << 20) return false;
   if (small_choice(a, false) >= 0 || stream_choice(a, false) >= 0 || halo_choice(a, false) >= 0) return false;
   return relay::igemm_dma_supported(a, false) && relay::igemm_dma_small_ring(a);
 }

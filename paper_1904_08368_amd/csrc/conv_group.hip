@@ -34,15 +34,20 @@ constexpr int kBM = 128, kBN = 64;
 // for the other in HBM.  So workgroups of the two alternate, eight at a time (one to an XCD), in the proportion of their numbers: an XCD works
 // through both in the same order, and reads the tensor once for the two.  Measured: 256 -> 288 and the 3 x 3 / stride 1 pool on 32 images of 28 x 28, in a
 // block of three launches instead of four, 51.7 -> 48.0 us; the two alone at the rule that chooses (api.cpp).
-// mul: (groups of eight of the conv << 32) / all groups, rounded up
+// The proportion holds in every fourth of an XCD's workgroups by itself, because its four shader engines take workgroups in turn: with the
+// two alternating one by one, or one to three, the convs were all on two engines, or on one (32 images of 56 x 56, 256 -> 512 92.4 us against
+// 74.3 for two launches, 192 -> 96 38.1 against 31.3; now 74.5 and 28.6).
+// mul: (groups of eight of the conv << 32) / all groups, rounded up; there are four groups or a multiple.
 template <int STRIDE, int OUT>
 __global__ __launch_bounds__(256, 4) void conv_pool_kernel(const unsigned mul, const int tiles, const int pooled, const ConvArgs a, const PoolGeom g, const half8* x,
                                                            half8* y) {
   extern __shared__ uint4 lds[];
-  const unsigned group = blockIdx.x >> 3;
-  const unsigned convs = (unsigned)(((unsigned long long)group * mul) >> 32), next = (unsigned)(((unsigned long long)(group + 1) * mul) >> 32);
-  const bool conv = next > convs;
-  const int place = (int)((conv ? convs : group - convs) * 8 + (blockIdx.x & 7));
+  const unsigned number = blockIdx.x >> 3, round = number >> 2, engine = number & 3;
+  auto convs_of = [&](unsigned e, unsigned rounds) { return (unsigned)(((unsigned long long)rounds * mul + ((unsigned long long)e << 30)) >> 32); };
+  const bool conv = convs_of(engine, round + 1) > convs_of(engine, round);
+  unsigned convs = 0;
+  for (unsigned e = 0; e < 4; ++e) convs += convs_of(e, round + (e < engine));
+  const int place = (int)((conv ? convs : number - convs) * 8 + (blockIdx.x & 7));
   if (place >= (conv ? tiles : pooled)) return;   // (the last eight of either)
   if (conv) igemm_dma_tile<false, 2, 2, 2, 1, 3, 1, 1, false, true, false>(a, xcd_remap(place, tiles), lds);
   else maxpool_fixed_tile<half8, 8, 3, STRIDE, OUT>(x, y, g, place);
@@ -50,7 +55,7 @@ __global__ __launch_bounds__(256, 4) void conv_pool_kernel(const unsigned mul, c
 
 template <int STRIDE, int OUT>
 hipError_t launch_pool_with(const ConvArgs& a, int tiles, const PoolGeom& g, const void* x, void* y, hipStream_t st) {
-  const int pooled = (int)((g.total + 255u) / 256u), groups = (tiles + 7) / 8 + (pooled + 7) / 8;
+  const int pooled = (int)((g.total + 255u) / 256u), groups = ((tiles + 7) / 8 + (pooled + 7) / 8 + 3) & ~3;
   const unsigned mul = (unsigned)((((unsigned long long)((tiles + 7) / 8) << 32) + (unsigned)groups - 1) / (unsigned)groups);
   const size_t lds_bytes = igemm_dma_slots<false, 2, 2, 2, 1, 3, 1, false>() * 16;
   hipLaunchKernelGGL((conv_pool_kernel<STRIDE, OUT>), dim3((unsigned)groups * 8u), dim3(256), lds_bytes, st, mul, tiles, pooled, a, g,

@@ -138,7 +138,7 @@ def _pool_call(n, h, w, stride, x, y, r=3, c=256):
 
 
 def test_which_convs_share_a_launch_with_a_pool():
-    """(host only) Convs on small-ring 128 x 64 tiles by themselves, 3 x 3 windows; what is refused."""
+    """(host only) Convs on small-ring 128 x 64 tiles by themselves, 3 x 3 windows, at most 200 MiB in all; what is refused."""
     def members(n, h, w, k=288, r=3, stride=1):
         at = lambda i: Address((i + 1) << 36)
         d = B.conv_desc(n, 256, h, w, k, 1, 1, 1, 0, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(True, None, None, True))
@@ -146,6 +146,9 @@ def test_which_convs_share_a_launch_with_a_pool():
     pays = lambda *a, **k: B.relay_conv2d_combined_maxpool_pays(*members(*a, **k))
     assert pays(32, 28, 28) and pays(17, 28, 28) and pays(32, 28, 28, stride=2) and pays(32, 64, 64)
     assert not pays(3, 17, 40) and not pays(16, 28, 28) and not pays(32, 28, 28, r=2)
+    assert pays(32, 56, 56, k=512) and not pays(32, 56, 56, k=544) and pays(32, 56, 56, k=640, stride=2)   # 196, 202, 184 MiB
+    conv, pool = members(32, 56, 56, k=448)
+    assert B.relay_conv2d_combined_maxpool_pays(conv, pool) and not B.relay_conv2d_combined_maxpool_pays(conv, (*pool[:8], Address(9 << 36), pool[9]))
     B.relay_set_conv_split(2)
     try:
         assert not pays(32, 28, 28)
@@ -163,9 +166,10 @@ def test_which_convs_share_a_launch_with_a_pool():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,h,w,k,stride,c", [(32, 28, 28, 288, 1, 256), (20, 33, 29, 288, 1, 256), (32, 28, 28, 192, 2, 256), (13, 31, 37, 288, 2, 64),
-                                              (9, 50, 23, 448, 1, 8), (34, 17, 11, 704, 1, 264), (3, 17, 40, 288, 1, 256)])
+                                              (9, 50, 23, 448, 1, 8), (34, 17, 11, 704, 1, 264), (64, 14, 14, 1024, 1, 256), (46, 21, 17, 256, 2, 1016),
+                                              (3, 17, 40, 288, 1, 256)])
 def test_conv_and_pool_are_the_separate_calls(n, h, w, k, stride, c):
-    """One and two outputs a thread, more workgroups of one and of the other, remainders, a NaN and infinities in the pool's input, a pool of another
+    """One and two outputs a thread, more workgroups of one and of the other, as many of both, remainders, a NaN and infinities in the pool's input, a pool of another
     tensor; the last runs as two launches."""
     g = torch.Generator().manual_seed(n)
     x = torch.randn((n, h, w, 256), generator=g).half().cuda()
