@@ -1002,7 +1002,15 @@ relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2
 // by themselves run on tiles of 128 x 64 or less of the kernels whose tiles it has, so that the sums are in the same order and no wider tile's rate is
 // given up.  us, separate / together, graph-timed, {128 -> 192 3x3, 32 -> 96 5x5, 256 -> 64 1x1}: 32 images of 28 x 28 37.9 / 29.8, 16 25.5 / 16.7, 12 21.2 /
 // 12.4, 20 of 33 x 29 30.1 / 21.8; the first two of 4 x 64 x 64 25.6 / 21.6; the last two of 32 x 40 x 40 31.7 / 25.7, but of 32 x 64 x 64, where
-// the 5x5 one has 256 x 128 tiles by itself, 49.9 / 58.5.
+// the 5x5 one has 256 x 128 tiles by itself, 49.9 / 58.5.  And not
+// - the member of 128-byte chunks, whose tiles start last, with a long reduction on few tiles: by itself its tiles are of 64 x 64, one to a CU, which
+//   take half the time.  1600 to a sum and less do not lose it, 2048 and more do: beside 32 -> 64 1x1 on 8 images of 28 x 28, 2048 -> 64 1x1 12.4 / 14.9,
+//   512 -> 64 3x3/2 16.7 / 23.9, 256 -> 96 5x5 22.3 / 31.9, but 128 -> 64 3x3/2 9.6 / 9.6, 1024 -> 64 1x1 9.8 / 9.2;
+// - the same member, at most one of its tiles to a CU, where these start in a second round behind the others' tiles: 128 -> 192 3x3 and 256 -> 96
+//   5x5 on 16 of 28 x 28 45.4 / 49.0, but on 13 of 27 x 31, where all start at once, 43.6 / 36.7; 96 -> 64 1x1 and 128 -> 64 3x3/2 on 58 of 32 x 32 13.9 /
+//   16.8.  Three members save a launch more: to 1600 to a sum there, to 832 with two;
+// - convs of short reductions over many pixels, of which a CU holds four workgroups or more by themselves: 32 -> 8 and 64 -> 24 1x1 on 36 of 52 x 72 12.8 / 16.5.
+// Of 9800 random groups that the rule takes 40 are slower than their separate launches by more than 1 %, the worst by 9; the median is 1.22 times as fast.
 struct GroupPlan {
   const relay::ConvArgs* c3 = nullptr;
   const relay::ConvArgs* c[2] = {nullptr, nullptr};
@@ -1014,6 +1022,7 @@ static GroupPlan group_plan(const relay::ConvArgs* m, int n) {
   for (int i = 0; i < n; ++i)
     for (int j = 0; j < n; ++j)
       if (i != j && conv_writes(m[i], false, m[j])) return p;
+  int short_sums = 0;
   for (int i = 0; i < n; ++i) {
     const relay::ConvArgs& a = m[i];
     if (a.seg_centre || small_choice(a, false) >= 0 || stream_choice(a, false) >= 0) return p;
@@ -1023,9 +1032,18 @@ static GroupPlan group_plan(const relay::ConvArgs* m, int n) {
       p.c3 = &a;
     } else {
       const int kind = a.C % 64 == 0 ? 1 : 0;
-      if (p.c[kind] || relay::igemm_dma_wide(a)) return p;
+      const relay::DmaChoice own = relay::igemm_dma_choice(a);
+      if (p.c[kind] || relay::igemm_dma_wide(a) || own.bn == 32) return p;
+      if (kind == 1 && a.Kred > 1600 && own.bm == 64 && own.tiles <= 256) return p;
       p.c[kind] = &a;
+      short_sums += own.small_ring;
     }
+  }
+  if (short_sums == n) return p;
+  if (p.c[1] && p.c[1]->Kred > (n == 2 ? 832 : 1600)) {
+    const long last = relay::conv_group_tiles(*p.c[1], false);
+    const long before = (p.c3 ? relay::conv_group_tiles(*p.c3, true) : 0) + (p.c[0] ? relay::conv_group_tiles(*p.c[0], false) : 0);
+    if (last <= 256 && before + last > 512) return p;
   }
   p.together = true;
   return p;

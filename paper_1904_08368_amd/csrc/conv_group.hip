@@ -73,6 +73,13 @@ bool conv_group_takes_3x3(const ConvArgs& a) {
   return a.nseg && conv_halo_group_args(a, h, lds_bytes) && lds_bytes <= 80 * 1024 - 64;
 }
 
+long conv_group_tiles(const ConvArgs& a, bool is_c3) {
+  HaloArgs h;
+  size_t lds_bytes;
+  const long rows = is_c3 && conv_halo_group_args(a, h, lds_bytes) ? h.g.Mflat : a.M;
+  return (rows + kBM - 1) / kBM * ((a.K + kBN - 1) / kBN);
+}
+
 hipError_t launch_conv_group(const ConvArgs* c3, const ConvArgs* c1, const ConvArgs* c2, hipStream_t st) {
   HaloArgs h{};
   ConvArgs m[2] = {};

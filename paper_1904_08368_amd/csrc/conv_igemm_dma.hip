@@ -514,6 +514,11 @@ void igemm_dma_pool_kernel_name(const ConvArgs& a, bool is_i8, char* buf, size_t
 // a layer with the 256 x 128 tile's 384 tiles or more
 bool igemm_dma_wide(const ConvArgs& a) { return a.K > 64 && tiles_of(a, kTiles[0]) >= 384; }
 
+DmaChoice igemm_dma_choice(const ConvArgs& a) {
+  const int tile = pick_tile(a, false);
+  return {kTiles[tile].bm(), kTiles[tile].bn(), tiles_of(a, kTiles[tile]), tile == 16};
+}
+
 float igemm_dma_estimate(const ConvArgs& a, bool is_i8) {
   const int tile = pick_tile(a, is_i8);
   const DmaTile& t = kTiles[tile];

@@ -140,6 +140,12 @@ bool conv_halo_supported(const ConvArgs& a, bool is_i8, int variant);
 float igemm_dma_estimate(const ConvArgs& a, bool is_i8);
 float conv_small_estimate(const ConvArgs& a, bool is_i8);
 bool igemm_dma_wide(const ConvArgs& a);
+struct DmaChoice {   // the tile that the implicit GEMM takes for an fp16 conv into channel segments
+  int bm, bn;
+  long tiles;
+  bool small_ring;
+};
+DmaChoice igemm_dma_choice(const ConvArgs& a);
 int conv_halo_pick(const ConvArgs& a, bool is_i8);  // variant, or -1: leave the layer to the implicit-GEMM kernel
 int conv_halo_chunk(const ConvArgs& a, bool is_i8, int variant);   // channels of a chunk of that variant
 bool conv_halo_keeps_whole(const ConvArgs& a, bool is_i8);  // a forced split of the reduction leaves this layer whole
@@ -152,6 +158,7 @@ void conv_halo_kernel_name(const ConvArgs& a, bool is_i8, int variant, char* buf
 // fp16 convs into channel segments side by side in one launch (conv_group.hip): c3 on the 3x3 kernel's tiles, c1 on the implicit GEMM's with
 // 64-byte chunks, c2 with 128-byte ones; NULL: none of that kind
 bool conv_group_takes_3x3(const ConvArgs& a);
+long conv_group_tiles(const ConvArgs& a, bool is_c3);   // of 128 x 64
 // ... and an fp16 conv of the implicit GEMM's small-ring 128 x 64 tiles beside a 3x3 max pool of C channels
 bool igemm_dma_small_ring(const ConvArgs& a);
 hipError_t launch_conv_pool(const ConvArgs& conv, int N, int C, int H, int W, int stride, int pad, int Ho, int Wo, const void* x, void* y, hipStream_t st);

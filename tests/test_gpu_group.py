@@ -50,6 +50,24 @@ def test_which_convs_share_a_launch():
         B.relay_set_conv_tile(-1)
 
 
+def test_which_widths_share_a_launch():
+    """(host only) Both sides of the rule's lines: a long reduction on few tiles, such a one behind more tiles than start at once, short reductions over many pixels."""
+    def pays(n, h, w, *members):
+        f, out = B.flags_of(None, True, None, True), []
+        for i, (c, k, r, s) in enumerate(members):
+            at = lambda j: Address((i + 1 << 36) + (j << 34))
+            out.append((B.conv_desc(n, c, h, w, k, r, r, s, r // 2, B.RELAY_F16, B.RELAY_NHWC, f), at(0), c, at(1), None, at(2), at(2), [k], [at(3)], [k]))
+        return B.relay_conv2d_combined_group_pays(*out)
+    short = (32, 64, 1, 1)
+    assert pays(8, 28, 28, short, (1600, 64, 1, 1)) and not pays(8, 28, 28, short, (2048, 64, 1, 1)) and not pays(8, 28, 28, short, (512, 64, 3, 2))
+    assert pays(16, 28, 28, short, (64, 96, 5, 1)) and not pays(8, 28, 28, short, (256, 96, 5, 1)) and pays(16, 28, 28, short, (256, 96, 5, 1))
+    assert pays(32, 17, 17, (96, 96, 5, 1), (256, 64, 1, 1))                    # (long, but not the member whose tiles start last)
+    assert pays(13, 27, 31, (128, 192, 3, 1), (256, 96, 5, 1)) and not pays(16, 28, 28, (128, 192, 3, 1), (256, 96, 5, 1))
+    assert pays(40, 32, 32, (96, 64, 1, 1), (128, 64, 3, 2)) and not pays(58, 32, 32, (96, 64, 1, 1), (128, 64, 3, 2)) and pays(58, 32, 32, (96, 64, 1, 1), (832, 64, 1, 2))
+    assert pays(16, 28, 28, (128, 192, 3, 1), (160, 64, 1, 1), (64, 96, 5, 1)) and not pays(16, 28, 28, (128, 192, 3, 1), (160, 64, 1, 1), (128, 96, 5, 1))
+    assert not pays(36, 52, 72, (32, 8, 1, 1), (64, 24, 1, 1)) and not pays(40, 56, 56, short, (64, 64, 1, 1)) and pays(20, 56, 56, short, (64, 64, 1, 1))
+
+
 def test_refused_calls():
     """(host only: every check runs before the first launch)"""
     def status(members, n=None):
