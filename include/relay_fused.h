@@ -366,7 +366,8 @@ relay_status relay_fused_conv2d_pool2x2(const relay_conv2d_desc* d, const void* 
  * first reads x and writes t, second reads t and, with HAS_RESIDUAL, adds x, and writes y.  Each is a call of relay_fused_conv2d_bias_bn_relu
  * (F16) or relay_qconv2d_requant (I8) without a workspace and is checked as by that call; t is written whole.  Where no kernel takes the two together
  * (relay_conv2d_block_pays writes 0, or a tile or split is forced) they run as two launches.  Results: bit for bit those of the
- * separate calls.  relay_conv2d_block_pays writes 1 where one launch takes them and is the faster way.
+ * separate calls.  relay_conv2d_block_pays writes 1 where one launch takes them and is the faster way, the launch that the
+ * host saves included (F16 below some 1400 pixels: a few tenths of a microsecond more on the GPU, and a launch less).
  * Errors: as the calls above, plus RELAY_ERR_UNSUPPORTED where one conv's output address is the other's operand otherwise than said; nothing is
  * launched on an error.  Tensors that overlap otherwise: two launches. */
 relay_status relay_conv2d_block_pays(const relay_conv2d_desc* first, const relay_conv2d_desc* second, int32_t* pays);

@@ -1161,14 +1161,20 @@ relay_status relay_fused_conv2d_combined_maxpool(const relay_conv2d_views_call* 
 
 // ---- the two 3x3 convs of a residual block in one launch -----------------------------------------
 
-// fp16: one round of workgroups (one to a CU), and only where both convs by themselves sum three taps in a run, as the shared launch does.  int8: to where
-// two launches catch up, at a round and a third.  us, two launches / one, graph-timed: fp16 one image of 56 x 56 6.98 / 6.52, two 8.23 / 6.75,
-// eight of 28 x 28 8.22 / 6.79, one of 14 x 14 6.23 / 6.33 (a launch of the host's less all the same); int8 one image of 56 x 56 7.09 / 5.15, two
-// 7.80 / 5.34, five 9.58 / 7.08, seven 11.1 / 10.1, eight 11.3 / 11.7, 16 14.5 / 19.7.
+// fp16: one round of workgroups (one to a CU), and only where both convs by themselves sum three taps in a run, as the shared launch does.  us, two
+// launches / one, graph-timed: one image of 56 x 56 6.92 / 6.49, two 8.11 / 6.64, eight of 28 x 28 8.21 / 6.87, 42 of 9 x 9 6.94 / 6.85.  Below some 1400
+// pixels the launch gains nothing on the GPU (one of 28 x 28 6.23 / 6.41, of 14 x 14 6.23 / 6.33, 85 of 4 x 4 6.40 / 6.43, at worst 255 of 1 x 1 6.14 / 6.63) and
+// is taken for the launch of the host's that it saves: behind the NHWC copy, 14 x 14 and 28 x 28 alike, called eagerly 14.1 / 9.8, enqueued from
+// a launch list 8.5 to 10.8 / 8.4 to 9.1.
+// int8: one round (two to a CU), where it wins at every size (one image of 56 x 56 7.09 / 5.15, five 9.75 / 7.23, 64 of 14 x 14 9.18 / 7.13, 116 of 5 x 9,
+// a third of whose rectangles is image, 7.69 / 6.83); a third of a round more only where the convs have outgrown the small-tile kernel,
+// at 16 K pixels (six of 56 x 56 10.8 / 9.8, seven 10.8 / 10.1, 22 of 28 x 28 10.6 / 9.9, but 80 of 14 x 14 9.58 / 9.72, 32 of 13 x 33 9.55 / 9.69, 100 of 9
+// x 9 7.84 / 9.57, 640 of 2 x 2 6.61 / 9.29); eight of 56 x 56 11.3 / 11.7.
 static bool block_plan(const relay::ConvArgs& a, const relay::ConvArgs& b, bool i8) {
   if (g_force_tile != -1 || g_force_split != 0 || !relay::conv_block_supported(a, b, i8)) return false;
-  if (relay::conv_block_workgroups(a) > (i8 ? 700 : 256)) return false;
-  if (i8) return true;
+  const long workgroups = relay::conv_block_workgroups(a);
+  if (i8) return workgroups <= 512 || (workgroups <= 700 && small_choice(a, true) < 0 && small_choice(b, true) < 0);
+  if (workgroups > 256) return false;
   for (const relay::ConvArgs* c : {&a, &b}) {
     const int v = small_choice(*c, false);
     if (v < 0 || !relay::conv_small_sums_by_taps(*c, v)) return false;

@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256, IS_I8 ? 2 : 1) void conv_block_kernel(const in
 
 }  // namespace
 
-// One round of workgroups (fp16: one to a CU, int8: two).
+// Two 3x3 convs of 64 channels with the plain tails, the second on the first's outputs, in a buffer's range (for how many workgroups: api.cpp's block_plan).
 bool conv_block_supported(const ConvArgs& a, const ConvArgs& b, bool is_i8) {
   for (const ConvArgs* c : {&a, &b})
     if (c->C != kChannels || c->K != kChannels || c->R != 3 || c->S != 3 || c->sh != 1 || c->sw != 1 || c->ph != 1 || c->pw != 1 ||

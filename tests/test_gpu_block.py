@@ -22,10 +22,14 @@ BIAS = B.flags_of(True, None, None, False)
 
 
 def test_which_blocks_take_one_launch():
-    """(host only) Up to 256 (int8: 700) workgroups of 4 x 8 outputs, 64 channels, the first conv without a residual."""
+    """(host only) Up to 256 (int8: 512, and 700 where the convs are past the small-tile kernel) workgroups of 4 x 8 outputs, 64 channels, the first conv
+    without a residual."""
     pays = lambda m, n, h, w, f0=BN | RELU, f1=BN | RES | RELU, **k: B.relay_conv2d_block_pays(_desc(m, n, h, w, f0, **k), _desc(m, n, h, w, f1, **k))
     assert pays("f16", 1, 56, 56) and pays("f16", 2, 56, 56) and not pays("f16", 3, 56, 56)
     assert pays("i8", 1, 56, 56, RELU, RES | RELU) and pays("i8", 7, 56, 56, RELU, RES | RELU) and not pays("i8", 8, 56, 56, RELU, RES | RELU)
+    i8 = lambda n, h, w: pays("i8", n, h, w, RELU, RES | RELU)
+    assert i8(64, 14, 14) and i8(116, 5, 9) and i8(512, 1, 1) and i8(87, 14, 14)
+    assert not i8(80, 14, 14) and not i8(32, 13, 33) and not i8(100, 9, 9) and not i8(513, 1, 1)
     assert pays("f16", 1, 7, 64) and pays("f16", 1, 1, 1, BIAS, BIAS)
     assert not pays("f16", 1, 56, 56, RES | RELU) and not pays("f16", 1, 28, 28, c=128, k=128)
     assert not B.relay_conv2d_block_pays(_desc("f16", 1, 56, 56, 0), _desc("f16", 1, 56, 55, 0))
