@@ -151,6 +151,49 @@ def test_group_is_the_separate_calls(n, h, w, kinds, tail):
     assert torch.isfinite(cat).all() and not (got[0][..., MEMBERS[kinds[0]][3]] == got[0].new_full((), 0x4700)).all()
 
 
+# (channels, those of the tensor they are in, filters, window, output segments) of each member
+VIEWS = {"ranges": ((20, 33, 29), [(32, 96, 96, 5, [24, 8, 56, 8]), (256, 480, 64, 1, [8, 56])]),
+         "3x3_of_a_range": ((32, 28, 28), [(128, 192, 192, 3, [72, 104, 16]), (32, 32, 96, 5, [96])]),
+         "all_three": ((13, 27, 31), [(128, 128, 200, 3, [40, 160]), (32, 64, 96, 5, [88, 8]), (256, 320, 72, 1, [8, 8, 8, 48])]),
+         "filters_larger_than_inputs": ((2, 27, 29), [(128, 128, 776, 3, [776]), (32, 32, 1032, 3, [1000, 32]), (128, 136, 2056, 1, [2056])])}
+
+
+def _view_members(case, tensor):
+    """Arguments of the members, the inputs among NaNs, the constants at odd places (not 16-byte aligned) with a NaN on either side.  tensor(shape, scale)."""
+    (n, h, w), members, out, keep = *VIEWS[case], [], []
+    flags = B.flags_of(True, True, None, True)
+    for c, ld, k, r, segments in members:
+        d = B.conv_desc(n, c, h, w, k, r, r, 1, r // 2, B.RELAY_F16, B.RELAY_NHWC, flags)
+        wide, x0 = torch.full((n, h, w, ld), float("nan"), dtype=torch.float16, device="cuda"), (ld - c) // 16 * 8
+        wide[..., x0:x0 + c] = tensor((n, h, w, c), 1).half()
+        wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device="cuda")
+        B.relay_prepack_conv2d_weights(d, tensor((k, c, r, r), (2.0 / (c * r * r)) ** 0.5).half(), c, wp)
+        bias, scale, shift = (torch.nn.functional.pad(tensor((k,), 1), (1, 2), value=float("nan"))[1:k + 1] for _ in range(3))
+        ys = [torch.empty((n, h, w, width + 16 * (i % 2)), dtype=torch.float16, device="cuda") for i, width in enumerate(segments)]
+        keep += ys
+        out.append((d, wide[..., x0:], ld, wp, bias, scale, shift, segments, [y[..., 8 * (i % 2):] for i, y in enumerate(ys)], [y.shape[3] for y in ys]))
+    return out, keep
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", VIEWS)
+def test_group_of_views_is_the_separate_calls(case):
+    """Members that read a channel range of a wider tensor (a 3x3 one then runs on the implicit GEMM's tiles), that store into two to four segments which
+    end inside a tile, with constants that are not 16-byte aligned, and with filters larger than their inputs (the other order of tiles)."""
+    g = torch.Generator().manual_seed(17)
+    members, ys = _view_members(case, lambda shape, scale: (torch.randn(shape, generator=g) * scale).cuda())
+    assert B.relay_conv2d_combined_group_pays(*members)
+    got = []
+    for call in (lambda: [B.relay_fused_conv2d_combined(*m) for m in members], lambda: B.relay_fused_conv2d_combined_group(*members)):
+        for y in ys:
+            y.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        got.append([y.cpu() for y in ys])
+    for alone, together in zip(*got):
+        assert torch.isfinite(alone).all() and torch.equal(alone.view(torch.int16), together.view(torch.int16))
+
+
 def _pool_call(n, h, w, stride, x, y, r=3, c=256):
     return (B.RELAY_F16, n, c, h, w, r, stride, 1, x, y)
 
@@ -208,6 +251,31 @@ def test_conv_and_pool_are_the_separate_calls(n, h, w, k, stride, c):
         torch.cuda.synchronize()
         got.append([t.cpu().view(torch.int16) for t in (y, py)])
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.gpu
+def test_conv_of_a_range_and_pool_are_the_separate_calls():
+    """The conv reads half the channels of the tensor that the pool takes whole, and stores into three segments that end inside a tile; constants not aligned."""
+    n, h, w, segments, g = 16, 29, 31, [96, 8, 184], torch.Generator().manual_seed(23)
+    wide = torch.randn((n, h, w, 512), generator=g).half().cuda()
+    d = B.conv_desc(n, 256, h, w, 288, 1, 1, 1, 0, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(None, True, None, True))
+    wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device="cuda")
+    B.relay_prepack_conv2d_weights(d, (torch.randn((288, 256, 1, 1), generator=g) / 16).half().cuda(), 256, wp)
+    scale, shift = (torch.nn.functional.pad(torch.randn(288, generator=g), (1, 3), value=float("nan")).cuda()[1:289] for _ in range(2))
+    ys = [torch.empty((n, h, w, k + 8), dtype=torch.float16, device="cuda") for k in segments]
+    py = torch.empty_like(wide)
+    conv = (d, wide[..., 128:], 512, wp, None, scale, shift, segments, [y[..., 8:] for y in ys], [y.shape[3] for y in ys])
+    pool = _pool_call(n, h, w, 1, wide, py, c=512)
+    assert B.relay_conv2d_combined_maxpool_pays(conv, pool)
+    got = []
+    for call in (lambda: (B.relay_fused_conv2d_combined(*conv), B.relay_maxpool2d(*pool)), lambda: B.relay_fused_conv2d_combined_maxpool(conv, pool)):
+        for y in (*ys, py):
+            y.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        got.append([y.cpu() for y in (*ys, py)])
+    for alone, together in zip(*got):
+        assert torch.isfinite(alone).all() and torch.equal(alone.view(torch.int16), together.view(torch.int16))
 
 
 @pytest.mark.gpu
