@@ -202,6 +202,33 @@ def main() -> int:
                 B.relay_set_conv_tile(-1)
         run(name, kernel, fn, 2.0 * 32 * ho * wo * c * (9 + k) / 1e9, (32 * hw * hw * c + 32 * ho * wo * k + 9 * c + k * c) * 2 / 1e6)
 
+    # ---- several convs in one launch: a residual block of 64 channels, the members of an Inception block, its 1x1 members beside its max pool
+    for name, n, i8 in (("block_f16_b1", 1, False), ("block_f16_b2", 2, False), ("block_i8_b1", 1, True), ("block_i8_b5", 5, True)):
+        d = [B.conv_desc(n, 64, 56, 56, 64, 3, 3, 1, 1, B.RELAY_I8 if i8 else B.RELAY_F16, B.RELAY_NHWC, B.flags_of(None, None if i8 else 1, r, True)) for r in (None, 1)]
+        x, wpk = tensor((n, 56, 56, 64), i8), [torch.empty(B.relay_packed_weight_bytes(e), dtype=torch.uint8, device=dev) for e in d]
+        for e, wp in zip(d, wpk):
+            B.relay_prepack_conv2d_weights(e, tensor((64, 64, 3, 3), i8) if i8 else (tensor((64, 64, 3, 3), False) * 0.05).to(torch.float16), 64, wp)
+        t, y, sc, sf = torch.empty_like(x), torch.empty_like(x), torch.ones(64, device=dev), torch.zeros(64, device=dev)
+        fn = (lambda d=d, x=x, w=wpk, t=t, y=y: B.relay_qconv2d_block(d[0], x, w[0], None, 10, t, d[1], w[1], None, 10, 10, y)) if i8 else \
+            (lambda d=d, x=x, w=wpk, t=t, y=y, sc=sc, sf=sf: B.relay_fused_conv2d_block(d[0], x, w[0], None, sc, sf, t, d[1], w[1], None, sc, sf, y))
+        run(name, "conv_block_kernel<%s>" % str(i8).lower(), fn, 2.0 * 2 * n * 56 * 56 * 64 * 576 / 1e9, (3 * x.numel() + 2 * 64 * 576) * (1 if i8 else 2) / 1e6)
+
+    def views_call(c, k, r, x=None):
+        d = B.conv_desc(32, c, 28, 28, k, r, r, 1, r // 2, B.RELAY_F16, B.RELAY_NHWC, B.flags_of(None, 1, None, True))
+        x = tensor((32, 28, 28, c), False) if x is None else x
+        wp = torch.empty(B.relay_packed_weight_bytes(d), dtype=torch.uint8, device=dev)
+        B.relay_prepack_conv2d_weights(d, (tensor((k, c, r, r), False) * 0.05).to(torch.float16), c, wp)
+        y = torch.empty((32, 28, 28, k), dtype=torch.float16, device=dev)
+        return (d, x, c, wp, None, torch.ones(k, device=dev), torch.zeros(k, device=dev), [k], [y], [k])
+    shapes = ((32, 96, 5), (128, 192, 3), (256, 64, 1))
+    members, px = [views_call(*s) for s in shapes], 32 * 28 * 28
+    run("group_f16_inception_28", "conv_group_kernel", lambda: B.relay_fused_conv2d_combined_group(*members), sum(2.0 * px * c * k * r * r for c, k, r in shapes) / 1e9,
+        sum((px * (c + k) + c * k * r * r) * 2 for c, k, r in shapes) / 1e6)
+    first = views_call(256, 288, 1)
+    pool = (B.RELAY_F16, 32, 256, 28, 28, 3, 1, 1, first[1], torch.empty_like(first[1]))
+    run("pool_f16_inception_28", "conv_pool_kernel<1, 2>", lambda: B.relay_fused_conv2d_combined_maxpool(first, pool), 2.0 * px * 256 * 288 / 1e9,
+        (px * (256 + 288 + 256) + 256 * 288) * 2 / 1e6)
+
     # ---- measured ceilings
     out = torch.zeros(1, dtype=torch.int32, device=dev)
     iters, wgs = 256, 256 * 8      # ~0.1 ms per launch: long enough to fill the chip, short enough for 32-bit counters
