@@ -1000,8 +1000,8 @@ relay_status relay_conv2d_pair(const relay_conv2d_call* first, const relay_conv2
 
 // The member of each kind that the shared launch has room for, or none where it does not take them: then each runs by itself.  It takes convs that
 // by themselves run on tiles of 128 x 64 or less of the kernels whose tiles it has, so that the sums are in the same order and no wider tile's rate is
-// given up.  us, separate / together, graph-timed, {128 -> 192 3x3, 32 -> 96 5x5, 256 -> 64 1x1}: 32 images of 28 x 28 37.9 / 29.8, 16 25.5 / 16.7, 12 21.2 /
-// 12.4, 20 of 33 x 29 30.1 / 21.8; the first two of 4 x 64 x 64 25.6 / 21.6; the last two of 32 x 40 x 40 31.7 / 25.7, but of 32 x 64 x 64, where
+// given up.  us, separate / together, graph-timed, {128 -> 192 3x3, 32 -> 96 5x5, 256 -> 64 1x1}: 32 images of 28 x 28 37.9 / 27.1, 16 25.0 / 16.6, 12 20.9 /
+// 12.3, 20 of 33 x 29 30.1 / 22.4; the first two of 4 x 64 x 64 24.9 / 21.2; the last two of 32 x 40 x 40 31.0 / 25.6, but of 32 x 64 x 64, where
 // the 5x5 one has 256 x 128 tiles by itself, 49.9 / 58.5.  And not
 // - the member of 128-byte chunks, whose tiles start last, with a long reduction on few tiles: by itself its tiles are of 64 x 64, one to a CU, which
 //   take half the time.  1600 to a sum and less do not lose it, 2048 and more do: beside 32 -> 64 1x1 on 8 images of 28 x 28, 2048 -> 64 1x1 12.4 / 14.9,

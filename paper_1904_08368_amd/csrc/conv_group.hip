@@ -7,7 +7,8 @@
 // the slots and the waits that the others leave.  A workgroup's number says whose tile it runs; each runs the code, and sums in the order, of
 // the conv's own launch.  What a tile needs of LDS and registers is the most of the three: two workgroups fit a CU, as by themselves.
 // The longest tiles come first, the shortest last, so that the last round is short.
-// Measured: the block 64.9 -> 52.0 us (5x5 first, then 3x3, then 1x1; 3x3 first 56.8, 1x1 before 3x3 53.2); the rule that chooses is api.cpp's.
+// Measured, 32 images of 28 x 28: these three 37.9 -> 27.1 us (graph-timed; 36.1 -> 25.4 on another card), the whole block, called one after another, 65.5 ->
+// 53.3; the order 5x5, 3x3, 1x1 takes 12.9 us off a block of 64.9, 3x3 first 8.1, 1x1 before 3x3 11.7.  The rule that chooses is api.cpp's.
 #include <atomic>
 
 #include "conv_halo_tile.hpp"
@@ -33,7 +34,7 @@ constexpr int kBM = 128, kBN = 64;
 // conv's tiles wait for their few loads and the pool for memory; both pass over the same tensor, which one of them by itself leaves behind
 // for the other in HBM.  So workgroups of the two alternate, eight at a time (one to an XCD), in the proportion of their numbers: an XCD works
 // through both in the same order, and reads the tensor once for the two.  Measured: 256 -> 288 and the 3 x 3 / stride 1 pool on 32 images of 28 x 28, in a
-// block of three launches instead of four, 51.7 -> 48.0 us; the two alone at the rule that chooses (api.cpp).
+// block of three launches instead of four, 53.3 -> 48.7 us; the two alone at the rule that chooses (api.cpp).
 // The proportion holds in every fourth of an XCD's workgroups by itself, because its four shader engines take workgroups in turn: with the
 // two alternating one by one, or one to three, the convs were all on two engines, or on one (32 images of 56 x 56, 256 -> 512 92.4 us against
 // 74.3 for two launches, 192 -> 96 38.1 against 31.3; now 74.5 and 28.6).

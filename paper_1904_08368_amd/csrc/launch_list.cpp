@@ -4,11 +4,11 @@
 // a graph that holds a network once and one that holds it two and four times: 5.0 to 5.7 us from 5 launches to 20), whatever the network;
 // launches enqueued one by one leave no gap, as long as the host keeps ahead of the GPU.  From Python it does not at small
 // batches (4.5 us a call); this loop over the launches of the captured graph does (2.1 to 2.6 us each) where passes are queued.  One after another,
-// graph -> list: deep Q-network at batch 1 21.6 -> 18.1 us, ResNet-18 at batch 1 88.0 -> 83.7, at batch 32 231 -> 227, an Inception block of 32
-// images 65.6 -> 60.5; int8 ResNet-18 at batch 1, whose 17 launches take the GPU 3.6 us each, 67 -> 69.
-// The price is the host's time: 12 us for five launches and 36 to 49 for 16 to 20, where the graph's replay takes 18 and 13 to 30.  A GPU that
-// idles when the pass comes waits for each launch in turn: waited for, the Q-network 38 -> 28 us, but ResNet-18 at batch 1 101 -> 94 to 107, int8
-// 79 -> 80 to 109, MobileNet-v1 98 -> 95 to 121.  Which of the two a pass takes is the caller's choice (FusedNet.replay).
+// graph -> list: deep Q-network at batch 1 21.4 -> 16.3 to 18.4 us, ResNet-18 at batch 1 79.9 -> 74.9, at batch 32 224 -> 219, an Inception block of 32
+// images 52.1 -> 46.5; int8 ResNet-18 at batch 1, whose 15 launches take the GPU 3.8 us each, 59.9 -> 57.2 to 58.6.
+// The price is the host's time: 12 us for five launches and 32 to 49 for 15 to 20, where the graph's replay takes 18 and 13 to 30.  A GPU that
+// idles when the pass comes waits for each launch in turn: waited for, the Q-network 38 -> 28 us, but ResNet-18 at batch 1 92 -> 92 to 94, int8
+// 72 -> 69 to 87, MobileNet-v1 97 -> 108.  Which of the two a pass takes is the caller's choice (FusedNet.replay).
 #include <memory>
 #include <mutex>
 #include <vector>

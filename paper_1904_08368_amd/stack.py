@@ -651,12 +651,13 @@ class FusedNet:
         kernels, replay() can also enqueue the recorded launches one by one from native code.
 
         The list saves the idle time between two replays of a graph (4 to 6 us a pass) and costs the host 2.5 us a launch, the
-        graph's replay 13 to 30 us whatever its length.  So the list runs passes of at most 6 launches (deep Q-network 21.6 -> 18.1 us one after
-        another, 38 -> 28 waited for) and passes with work for the whole chip in a launch, which keep the GPU busy longer than the host
-        (an average of 400 K outputs: ResNet-18 of 7 images 136 -> 132 and 149 -> 144 us, of 3 images 113 -> 108 and 126 -> 124).  In between
-        (one image: 16 to 18 launches of 4 to 5 us) the list wins where the GPU has passes queued (ResNet-18 88 -> 84 us, MobileNet-v1 88 -> 84)
-        and loses where it idles until the first launch (waited for, int8 ResNet-18 79 -> 92, MobileNet-v1 98 -> 107; with 80 us of a program's own
-        work between passes 112 -> 125): see replay().  Such a graph is instantiated and launched once here, because its first launch takes 10 us
+        graph's replay 13 to 30 us whatever its length.  So the list runs passes of at most 6 launches (deep Q-network 21.4 -> 18.4 us one after
+        another, 38 -> 28 waited for; the first ten operators of ResNet-18, six launches, 33 -> 30 and 46 -> 40, but waited for twelve, eight launches,
+        53 -> 63) and passes with work for the whole chip in a launch, which keep the GPU busy longer than the host (an average of 400 K outputs:
+        ResNet-18 of 7 images 129 -> 124 and 142 -> 137 us; of 3 images 106 -> 100, but waited for 117 -> 123).  In between (one image: 15 or 16 launches
+        of 4 to 5 us) the list wins where the GPU has passes queued (ResNet-18 80 -> 75 us, int8 60 -> 58, MobileNet-v1 86 -> 83) and loses where it
+        idles until the first launch (waited for, int8 ResNet-18 72 -> 69 to 87, MobileNet-v1 97 -> 108; with 80 us of a program's own work between
+        passes 110 -> 125): see replay().  Such a graph is instantiated and launched once here, because its first launch takes 10 us
         more than a later one; any other that has a list is instantiated when it is first launched itself."""
         self.run()
         torch.cuda.synchronize(self.dev)
